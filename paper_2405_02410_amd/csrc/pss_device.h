@@ -164,6 +164,16 @@ __device__ __forceinline__ void gstore_sel(float2* p, float2 v) {
         *q = __builtin_bit_cast(double, v);
     }
 }
+// p + e of an array below 4 GiB, as a scalar base and a 32-bit byte offset
+// (the load's own addressing mode), or with a 64-bit offset
+__device__ __forceinline__ const float2* elem(const float2* p, uint32_t e) {
+    return reinterpret_cast<const float2*>(reinterpret_cast<const char*>(p) + static_cast<uint32_t>(e * 8u));
+}
+__device__ __forceinline__ float2* elem(float2* p, uint32_t e) {
+    return reinterpret_cast<float2*>(reinterpret_cast<char*>(p) + static_cast<uint32_t>(e * 8u));
+}
+__device__ __forceinline__ const float2* elem(const float2* p, size_t e) { return p + e; }
+__device__ __forceinline__ float2* elem(float2* p, size_t e) { return p + e; }
 // two neighbouring float2 in one 16-byte load (p 16-byte aligned).  Loaded
 // as four floats: the same load typed as two doubles and split by bit casts
 // compiled here to overlapping destination registers for loads in flight,
@@ -176,17 +186,29 @@ __device__ __forceinline__ void gload_pair(const float2* p, float2& a, float2& b
     b = make_float2(v.z, v.w);
 }
 
+// two neighbouring float2 in one 16-byte store (p 16-byte aligned)
+template <bool NT>
+__device__ __forceinline__ void gstore_pair_sel(float2* p, float2 a, float2 b) {
+    pss_gfvec4* q = (pss_gfvec4*)(p);
+    const pss_fvec4 v = {a.x, a.y, b.x, b.y};
+    if constexpr (NT) {
+        __builtin_nontemporal_store(v, q);
+    } else {
+        *q = v;
+    }
+}
+
 // ------------------------------------------------------------ block order
 // The hardware hands out the blocks of a grid round-robin over the 8 XCDs
 // (block b starts on XCD b mod 8), and each XCD has its own L2.  Renumber
 // the blocks so that every XCD works on one contiguous range of logical
 // blocks: neighbouring rows or lines that share cache lines then share an
 // L2.  A bijection on [0, n) for any n.
-__device__ __forceinline__ int xcd_block(int b, int n) {
-    constexpr int X = 8;
+__device__ __forceinline__ int xcd_block(unsigned b, unsigned n) {
+    constexpr unsigned X = 8;
     const int per = n / X, rem = n % X;
     const int x = b % X, k = b / X;
-    return (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + k;
+    return x * per + (x < rem ? x : rem) + k;
 }
 
 // ------------------------------------------------------------------ Philox
@@ -207,7 +229,9 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
         const uint64_t p1 = static_cast<uint64_t>(PSS_PHILOX_M1) * c.z;
         const uint32_t hi0 = static_cast<uint32_t>(p0 >> 32), lo0 = static_cast<uint32_t>(p0);
         const uint32_t hi1 = static_cast<uint32_t>(p1 >> 32), lo1 = static_cast<uint32_t>(p1);
-        c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
+        // three-input xors (0x96: odd parity), one instruction each
+        c = make_uint4(__builtin_amdgcn_bitop3_b32(hi1, c.y, k0, 0x96), lo1,
+                       __builtin_amdgcn_bitop3_b32(hi0, c.w, k1, 0x96), lo0);
     }
     return c;
 }

@@ -120,16 +120,59 @@ struct LineFFT {
         return d;
     }
 
-    template <int DIR>
-    static __device__ __forceinline__ float2 twiddle(const float2* __restrict__ tw, int i) {
-        float2 w = tw[i];
+    // twiddles of the stages before `s`: a stage of radix R on a line held P
+    // points a thread has P/R butterflies of R - 1 twiddles each
+    static constexpr int tw_count(int s) {
+        int n = 0;
+        for (int i = 0; i < s; ++i) n += kSt.Ls[i] > kSt.R[i] ? (P / kSt.R[i]) * (kSt.R[i] - 1) : 0;
+        return n;
+    }
+    static constexpr int kTw = tw_count(kSt.n);
+
+    // The twiddles of this thread in registers.  A thread uses the same ones
+    // in every transform of its line (both directions: the inverse takes the
+    // conjugate), so they are read once, straight from the table in global
+    // memory, instead of through a copy of the table in LDS that every block
+    // writes, waits for and reads again in each transform.
+    struct Regs {
+        float2 w[kTw > 0 ? kTw : 1];
+        __device__ __forceinline__ float2 at(int flat, int) const { return w[flat]; }
+        template <int S>
+        __device__ __forceinline__ void load_stage(const float2* __restrict__ tw_g, int t) {
+            if constexpr (S >= 0) {
+                constexpr int Ls = kSt.Ls[S], G = kSt.G[S], R = kSt.R[S], PR = P / R;
+                if constexpr (Ls > R) {
+                    const int g = t & (G - 1);
+#pragma unroll
+                    for (int h = 0; h < PR; ++h)
+#pragma unroll
+                        for (int k1 = 1; k1 < R; ++k1)
+                            w[tw_count(S) + h * (R - 1) + k1 - 1] = gload(elem(tw_g, static_cast<uint32_t>((g + h * G) * k1 * (L / Ls))));
+                }
+                load_stage<S - 1>(tw_g, t);
+            }
+        }
+        // the stages that a forward (dit) transform runs first are loaded first
+        __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t) { load_stage<kSt.n - 1>(tw_g, t); }
+    };
+    // the same read from a table (in LDS) at each use
+    struct Table {
+        const float2* __restrict__ p;
+        __device__ __forceinline__ float2 at(int, int i) const { return p[i]; }
+    };
+
+    template <int DIR, class TW>
+    static __device__ __forceinline__ float2 twiddle(const TW& tw, int flat, int i) {
+        float2 w = tw.at(flat, i);
         if (DIR > 0) w.y = -w.y;
         return w;
     }
 
-    template <int DIR, int S>
-    static __device__ __forceinline__ void dif_stage(float2 (&v)[P], LdsLine& ld, int t,
-                                                     const float2* __restrict__ tw) {
+    // LDS slots: pad() adds over index parts with disjoint bits, so an
+    // exchange computes one padded base and reaches its P elements at
+    // compile-time offsets
+    template <int DIR, int S, class TW>
+    static __device__ __forceinline__ void dif_stage(float2 (&v)[P], LdsLine& ld, int t, const TW& tw) {
         constexpr int Ls = kSt.Ls[S], G = kSt.G[S], R = kSt.R[S];
         constexpr int PR = P / R;
         const int g = t & (G - 1);
@@ -142,7 +185,8 @@ struct LineFFT {
             if constexpr (Ls > R) {
                 const int n2 = g + h * G;
 #pragma unroll
-                for (int k1 = 1; k1 < R; ++k1) a[k1] = cmul(a[k1], twiddle<DIR>(tw, n2 * k1 * (L / Ls)));
+                for (int k1 = 1; k1 < R; ++k1)
+                    a[k1] = cmul(a[k1], twiddle<DIR>(tw, tw_count(S) + h * (R - 1) + k1 - 1, n2 * k1 * (L / Ls)));
             }
 #pragma unroll
             for (int k1 = 0; k1 < R; ++k1) v[h + k1 * PR] = a[k1];
@@ -154,25 +198,26 @@ struct LineFFT {
             float2* __restrict__ buf = cross ? ld.next_blk() : ld.wl;
             const int gb = (t - g) * P;  // the group's Ls elements
             if constexpr (!cross) wave_lds_sync();
+            float2* const wb = buf + pad(gb + g);
 #pragma unroll
             for (int h = 0; h < PR; ++h)
 #pragma unroll
-                for (int k1 = 0; k1 < R; ++k1) buf[pad(gb + k1 * Lr + g + h * G)] = v[h + k1 * PR];
+                for (int k1 = 0; k1 < R; ++k1) wb[pad(k1 * Lr + h * G)] = v[h + k1 * PR];
             if constexpr (cross) {
                 __syncthreads();
             } else {
                 wave_lds_sync();
             }
             const int k1 = g / Gn, gp = g & (Gn - 1);
+            const float2* const rb = buf + pad(gb + k1 * Lr + gp);
 #pragma unroll
-            for (int j = 0; j < P; ++j) v[j] = buf[pad(gb + k1 * Lr + gp + j * Gn)];
+            for (int j = 0; j < P; ++j) v[j] = rb[pad(j * Gn)];
             dif_stage<DIR, S + 1>(v, ld, t, tw);
         }
     }
 
-    template <int DIR, int S>
-    static __device__ __forceinline__ void dit_stage(float2 (&v)[P], LdsLine& ld, int t,
-                                                     const float2* __restrict__ tw) {
+    template <int DIR, int S, class TW>
+    static __device__ __forceinline__ void dit_stage(float2 (&v)[P], LdsLine& ld, int t, const TW& tw) {
         constexpr int Ls = kSt.Ls[S], G = kSt.G[S], R = kSt.R[S];
         constexpr int PR = P / R;
         const int g = t & (G - 1);
@@ -185,17 +230,19 @@ struct LineFFT {
             const int gb = (t - g) * P;
             const int k1 = g / Gn, gp = g & (Gn - 1);
             if constexpr (!cross) wave_lds_sync();
+            float2* const wb = buf + pad(gb + k1 * Lr + gp);
 #pragma unroll
-            for (int j = 0; j < P; ++j) buf[pad(gb + k1 * Lr + gp + j * Gn)] = v[j];
+            for (int j = 0; j < P; ++j) wb[pad(j * Gn)] = v[j];
             if constexpr (cross) {
                 __syncthreads();
             } else {
                 wave_lds_sync();
             }
+            const float2* const rb = buf + pad(gb + g);
 #pragma unroll
             for (int h = 0; h < PR; ++h)
 #pragma unroll
-                for (int kk = 0; kk < R; ++kk) v[h + kk * PR] = buf[pad(gb + kk * Lr + g + h * G)];
+                for (int kk = 0; kk < R; ++kk) v[h + kk * PR] = rb[pad(kk * Lr + h * G)];
         }
 #pragma unroll
         for (int h = 0; h < PR; ++h) {
@@ -205,7 +252,8 @@ struct LineFFT {
             if constexpr (Ls > R) {
                 const int n2 = g + h * G;
 #pragma unroll
-                for (int k1 = 1; k1 < R; ++k1) a[k1] = cmul(a[k1], twiddle<DIR>(tw, n2 * k1 * (L / Ls)));
+                for (int k1 = 1; k1 < R; ++k1)
+                    a[k1] = cmul(a[k1], twiddle<DIR>(tw, tw_count(S) + h * (R - 1) + k1 - 1, n2 * k1 * (L / Ls)));
             }
             DFT<R, DIR>::run(a);
 #pragma unroll
@@ -214,14 +262,23 @@ struct LineFFT {
     }
 
     // natural order in, X[D(t) + m T] out
-    template <int DIR>
-    static __device__ __forceinline__ void dif(float2 (&v)[P], LdsLine& ld, int t, const float2* __restrict__ tw) {
+    template <int DIR, class TW>
+    static __device__ __forceinline__ void dif(float2 (&v)[P], LdsLine& ld, int t, const TW& tw) {
         dif_stage<DIR, 0>(v, ld, t, tw);
     }
     // X[D(t) + m T] in, natural order out
-    template <int DIR>
-    static __device__ __forceinline__ void dit(float2 (&v)[P], LdsLine& ld, int t, const float2* __restrict__ tw) {
+    template <int DIR, class TW>
+    static __device__ __forceinline__ void dit(float2 (&v)[P], LdsLine& ld, int t, const TW& tw) {
         dit_stage<DIR, 0>(v, ld, t, tw);
+    }
+    // with the table in LDS
+    template <int DIR>
+    static __device__ __forceinline__ void dif(float2 (&v)[P], LdsLine& ld, int t, const float2* tw) {
+        dif_stage<DIR, 0>(v, ld, t, Table{tw});
+    }
+    template <int DIR>
+    static __device__ __forceinline__ void dit(float2 (&v)[P], LdsLine& ld, int t, const float2* tw) {
+        dit_stage<DIR, 0>(v, ld, t, Table{tw});
     }
 };
 

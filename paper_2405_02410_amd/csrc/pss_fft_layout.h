@@ -26,4 +26,11 @@ constexpr int fft_lds_elems(int L, int P, int lines, int pads = kFftPad) {
     return lines * ((L / P > 64) ? 3 : 1) * fft_region(L, pads);
 }
 
+// Where the twiddles of a line held P points a thread live: in registers up
+// to 8 points (at most 21 complex values, read once and used by every
+// transform of the kernel), in an LDS copy of the table for 16 (30 values
+// would halve the waves in flight).
+constexpr bool fft_reg_twiddles(int P) { return P <= 8; }
+constexpr int fft_tw_elems(int L, int P) { return fft_reg_twiddles(P) ? 0 : L; }
+
 }  // namespace pss

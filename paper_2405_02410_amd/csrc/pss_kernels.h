@@ -77,7 +77,10 @@ struct Geo {
     int nublk;    // update-kernel blocks (= ntile * Ny/to in 3D, ntile in 2D)
     int tz;       // y pass: z values per block
     int nyblk;    // y-pass blocks (= ntile * Nz/tz)
+    int nx, ny;   // Nx, Ny
     int nz;       // Nz (1 in 2D)
+    int ncol[PSS_MAXG];  // packed columns that factor slot g keeps (DevMask::ncol)
+    int grp;      // 2D, one-column tiles: exchange arrays in groups of four rows (pss_kernels.hip, Exch)
     int tc_log2;  // log2(tc)
     int rb_log2;  // log2(rb)
     int pu;       // points per thread: update kernel
@@ -303,18 +306,19 @@ inline size_t fft_lds(int L, int P, int lines, int pads = kFftPad) {
     return static_cast<size_t>(fft_lds_elems(L, P, lines, pads));
 }
 // dynamic LDS of the update kernel: TC*TO line transforms, one exchange line
-// and the staged twiddle table (L entries), in that order
+// and the twiddle table where it is staged, in that order
 inline size_t update_lds_bytes(int L, int P, int tc, int to, int pads = kFftPad) {
-    return sizeof(float2) * (fft_lds(L, P, tc * to, pads) + 2 * static_cast<size_t>(L));
+    return sizeof(float2) * (fft_lds(L, P, tc * to, pads) + static_cast<size_t>(L + fft_tw_elems(L, P)));
 }
 // dynamic LDS of the y pass: TC*TZ line transforms, one exchange line per z
-// and the staged twiddle table (L entries), in that order
+// and the twiddle table where it is staged, in that order
 inline size_t ypass_lds_bytes(int L, int P, int tc, int tz) {
-    return sizeof(float2) * (fft_lds(L, P, tc * tz) + static_cast<size_t>(tz + 1) * L);
+    return sizeof(float2) * (fft_lds(L, P, tc * tz) + static_cast<size_t>(tz) * L +
+                             static_cast<size_t>(fft_tw_elems(L, P)));
 }
-// dynamic LDS of the x kernel: RB/2 line transforms + the staged twiddle table
+// dynamic LDS of the x kernel: RB/2 line transforms + the twiddle table where it is staged
 inline size_t xrow_lds_bytes(int L, int P, int rb) {
-    return sizeof(float2) * (fft_lds(L, P, rb / 2) + static_cast<size_t>(L));
+    return sizeof(float2) * (fft_lds(L, P, rb / 2) + static_cast<size_t>(fft_tw_elems(L, P)));
 }
 
 // Allocation-free reductions (pss_noalloc.hip): the device address of the

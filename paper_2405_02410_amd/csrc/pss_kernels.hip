@@ -61,6 +61,31 @@ __device__ __forceinline__ const float2* store_twiddles(float2* dst, const float
     return dst;
 }
 
+// The twiddles of a kernel's line transforms: load() issues the reads next to
+// the kernel's first data loads, ready() ends before the first transform (a
+// block barrier only where the table is staged in LDS), get() goes to
+// dif / dit.
+template <class FFT, int L, int P, bool REG = fft_reg_twiddles(P)>
+struct Twiddles {
+    typename FFT::Regs r;
+    __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t, int, int) { r.load(tw_g, t); }
+    __device__ __forceinline__ void ready(float2*, int, int) {}
+    __device__ __forceinline__ const typename FFT::Regs& get() const { return r; }
+};
+template <class FFT, int L, int P>
+struct Twiddles<FFT, L, P, false> {
+    float2 w[P];
+    typename FFT::Table tab;
+    __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int, int tid, int nthr) {
+        load_twiddles<L, P>(w, tw_g, tid, nthr);
+    }
+    __device__ __forceinline__ void ready(float2* lds, int tid, int nthr) {
+        tab.p = store_twiddles<L, P>(lds, w, tid, nthr);
+        __syncthreads();
+    }
+    __device__ __forceinline__ const typename FFT::Table& get() const { return tab; }
+};
+
 // Sum of NV per-thread FP64 values over the block in a fixed order (a
 // shuffle tree inside each wave, then the waves in index order), added by
 // thread 0 into this block's own slot[0..NV).  Launches with the same grid
@@ -96,6 +121,38 @@ __device__ __forceinline__ void block_sum_to_slot(double (&v)[NV], double* __res
     }
 }
 
+// ---------------------------------------------------------- exchange layout
+// Where the arrays that pass between the column kernels and the x kernel
+// (products N, factors V, the transform modes' in / out, the adjoint's
+// counterparts) hold packed column c at row y of a 2D lattice.  Tiles of
+// several columns (tc > 1): as the state, [ctile][y][TC].  One-column tiles:
+// groups of four rows, [y/4][c][4].  A column is then 32-byte pieces and a
+// row pair half of such pieces side by side: a kernel of either direction
+// uses at least a quarter (columns) or half (rows) of the cache lines that it
+// fetches, where whole columns, [c][y], gave the x kernel 16 bytes of each
+// 128-byte line (1024^2: the gather took 1.4 us of the x launch).
+// Offsets are 32-bit in 2D (a packed plane has at most 2^23 elements), so
+// that they add to a scalar base in the load itself.
+template <class I>
+struct Exch {
+    I c0;       // element of (c, y = 0)
+    I ystride;  // from y to y + 1 (groups: from y to y + 4)
+    bool grp;   // groups of four rows
+    __device__ __forceinline__ I at(int y) const {
+        return grp ? c0 + static_cast<I>(y >> 2) * ystride + static_cast<I>(y & 3) : c0 + static_cast<I>(y) * ystride;
+    }
+    // from y to y + n, n a multiple of four where rows are grouped
+    __device__ __forceinline__ I step(int n) const { return static_cast<I>(grp ? n >> 2 : n) * ystride; }
+};
+// column c = ct * tc + cc of a 2D lattice of L rows
+__device__ __forceinline__ Exch<uint32_t> exch_column(const Geo& geo, int ct, int cc, int L) {
+    Exch<uint32_t> e;
+    e.grp = geo.grp != 0;
+    e.c0 = static_cast<uint32_t>(geo.grp ? ct * 4 : ct * L * geo.tc + cc);
+    e.ystride = static_cast<uint32_t>(geo.grp ? geo.ntile * 4 : geo.tc);
+    return e;
+}
+
 // ----------------------------------------------------------------- modes
 struct ModeQ {
     float q2;
@@ -106,17 +163,20 @@ struct ModeQ {
 // signed index of mode i on an axis of even length n (Nyquist read as -n/2)
 __device__ __forceinline__ int signed_mode(int i, int n) { return i < (n >> 1) ? i : i - n; }
 
-__device__ __forceinline__ ModeQ mode_q(const DevPlan& p, int kx, int ky, int kz) {
+__device__ __forceinline__ ModeQ mode_q(int nx, int ny, int nz, const float (&qs)[3], int kx, int ky, int kz) {
     ModeQ m;
-    const float qx = static_cast<float>(kx) * p.qs[0];
-    const float qy = static_cast<float>(ky) * p.qs[1];
-    const float qz = static_cast<float>(kz) * p.qs[2];
+    const float qx = static_cast<float>(kx) * qs[0];
+    const float qy = static_cast<float>(ky) * qs[1];
+    const float qz = static_cast<float>(kz) * qs[2];
     m.q2 = qx * qx + qy * qy + qz * qz;
-    m.iq[0] = (kx == -(p.n[0] >> 1)) ? 0.f : qx;
-    m.iq[1] = (ky == -(p.n[1] >> 1)) ? 0.f : qy;
-    m.iq[2] = (p.n[2] > 1 && kz == -(p.n[2] >> 1)) ? 0.f : qz;
+    m.iq[0] = (kx == -(nx >> 1)) ? 0.f : qx;
+    m.iq[1] = (ky == -(ny >> 1)) ? 0.f : qy;
+    m.iq[2] = (nz > 1 && kz == -(nz >> 1)) ? 0.f : qz;
     m.invq = m.q2 > 0.f ? 1.f / sqrtf(m.q2) : 0.f;
     return m;
+}
+__device__ __forceinline__ ModeQ mode_q(const DevPlan& p, int kx, int ky, int kz) {
+    return mode_q(p.n[0], p.n[1], p.n[2], p.qs, kx, ky, kz);
 }
 
 // monomials with 1/|q| or i q_i factors, evaluated only by the kernel
@@ -142,33 +202,77 @@ __device__ __forceinline__ float2 eval_general(const DevOp& op, const ModeQ& q) 
     return make_float2(re, im);
 }
 
-// sum_j poly[j] (q^2)^j up to the operator's degree.  The coefficients are
-// read at fixed offsets (no load waits for the degree) and the terms above
-// the degree are skipped by a uniform branch; starting from r = 0 the first
-// kept term gives r = poly[deg] exactly, as a loop from the degree would.
-__device__ __forceinline__ float horner(const DevOp& op, float q2) {
-    const int deg = op.deg;
-    float r = 0.f;
+// The pure q^2 part of an operator, read as one block.  Reading coefficient
+// by coefficient behind a test of the degree makes every coefficient a scalar
+// load of its own that the next one waits for, each about a microsecond on a
+// cold cache: a step's operators were some thirty such waits in a row.
+struct OpPoly {
+    float c[PSS_MAXPOW + 1];
+    int deg;
+};
+__device__ __forceinline__ OpPoly op_poly(const DevOp& op) {
+    OpPoly r;
 #pragma unroll
-    for (int j = PSS_MAXPOW; j >= 0; --j)
-        if (j <= deg) r = fmaf(r, q2, op.poly[j]);
+    for (int j = 0; j <= PSS_MAXPOW; ++j) r.c[j] = op.poly[j];
+    r.deg = op.deg;
     return r;
 }
-// the same for P modes at once
-template <int P>
-__device__ __forceinline__ void horner_p(const DevOp& op, const float (&q2)[P], float (&out)[P]) {
-    const int deg = op.deg;
+// keep a uniform value in scalar registers from here on (the compiler would
+// move its load down to the use, behind a barrier)
+__device__ __forceinline__ void hold(int& x) {
+    x = __builtin_amdgcn_readfirstlane(x);
+    asm volatile("" : "+s"(x));
+}
+__device__ __forceinline__ void hold(uint32_t& x) {
+    int v = static_cast<int>(x);
+    hold(v);
+    x = static_cast<uint32_t>(v);
+}
+__device__ __forceinline__ void hold(float& x) {
+    int v = __float_as_int(x);
+    hold(v);
+    x = __int_as_float(v);
+}
+__device__ __forceinline__ void hold(OpPoly& o) {
 #pragma unroll
-    for (int m = 0; m < P; ++m) out[m] = 0.f;
+    for (int j = 0; j <= 4; ++j) hold(o.c[j]);
+    hold(o.deg);
+}
+
+// sum_j c[j] (q^2)^j for P modes.  The coefficients above the degree are
+// zeros, so starting at a fixed power gives c[deg] exactly when it is reached
+// and the value does not depend on which of the three lengths is taken.
+template <int N, int P>
+__device__ __forceinline__ void horner_n(const OpPoly& op, const float (&q2)[P], float (&out)[P]) {
 #pragma unroll
-    for (int j = PSS_MAXPOW; j >= 0; --j) {
-        if (j <= deg) {
-            const float c = op.poly[j];
+    for (int m = 0; m < P; ++m) out[m] = op.c[N];
 #pragma unroll
-            for (int m = 0; m < P; ++m) out[m] = fmaf(out[m], q2[m], c);
-        }
+    for (int j = N - 1; j >= 0; --j) {
+#pragma unroll
+        for (int m = 0; m < P; ++m) out[m] = fmaf(out[m], q2[m], op.c[j]);
     }
 }
+template <int P>
+__device__ __forceinline__ void horner_p(const OpPoly& op, const float (&q2)[P], float (&out)[P]) {
+    if (op.deg <= 2) {
+        horner_n<2>(op, q2, out);
+    } else if (op.deg <= 4) {
+        horner_n<4>(op, q2, out);
+    } else {
+        horner_n<PSS_MAXPOW>(op, q2, out);
+    }
+}
+template <int P>
+__device__ __forceinline__ void horner_p(const DevOp& op, const float (&q2)[P], float (&out)[P]) {
+    horner_p(op_poly(op), q2, out);
+}
+__device__ __forceinline__ float horner(const OpPoly& op, float q2) {
+    const float q[1] = {q2};
+    float r[1];
+    horner_p(op, q, r);
+    return r[0];
+}
+__device__ __forceinline__ float horner(const DevOp& op, float q2) { return horner(op_poly(op), q2); }
 
 // sum_m coef (q^2)^a |q|^-b (i qx)^cx (i qy)^cy (i qz)^cz: Horner over the
 // pure q^2 part, then the listed general monomials (GEN: the plan has some;
@@ -184,6 +288,56 @@ __device__ __forceinline__ float2 eval_op(const DevOp& op, const ModeQ& q) {
         }
     }
     return make_float2(re, 0.f);
+}
+
+// the same for P modes at once: the monomial list is walked once, so its
+// loads and uniform branches are paid per line and not per mode
+template <int P>
+__device__ __forceinline__ void eval_op_p(const DevOp& op, const float (&q2)[P], const ModeQ (&q)[P],
+                                          float2 (&out)[P]) {
+    float re[P];
+    horner_p(op, q2, re);
+#pragma unroll
+    for (int m = 0; m < P; ++m) out[m] = make_float2(re[m], 0.f);
+    if (op.n == 0) return;
+    float gr[P], gi[P];
+#pragma unroll
+    for (int m = 0; m < P; ++m) gr[m] = gi[m] = 0.f;
+    for (int i = 0; i < op.n; ++i) {
+        const DevMono mo = op.m[i];
+        float s[P];
+#pragma unroll
+        for (int m = 0; m < P; ++m) s[m] = mo.coef;
+        for (int e = 0; e < mo.q2; ++e) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) s[m] *= q[m].q2;
+        }
+        for (int e = 0; e < mo.invq; ++e) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) s[m] *= q[m].invq;
+        }
+        for (int e = 0; e < mo.ix; ++e) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) s[m] *= q[m].iq[0];
+        }
+        for (int e = 0; e < mo.iy; ++e) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) s[m] *= q[m].iq[1];
+        }
+        for (int e = 0; e < mo.iz; ++e) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) s[m] *= q[m].iq[2];
+        }
+        if (mo.ipow & 1) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) gi[m] = mo.ipow == 1 ? gi[m] + s[m] : gi[m] - s[m];
+        } else {
+#pragma unroll
+            for (int m = 0; m < P; ++m) gr[m] = mo.ipow == 0 ? gr[m] + s[m] : gr[m] - s[m];
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < P; ++m) out[m] = make_float2(re[m] + gr[m], gi[m]);
 }
 
 // 1 / (1 - dt L(q)), complex (operators with odd i q_i powers)
@@ -206,47 +360,34 @@ __device__ __forceinline__ bool mask_keep(const DevMask& mk, int kx, int ky, int
     return s * mk.den2 < mk.rhs;
 }
 
-// Largest w^2 kept by mask mk along a line whose other indices are fixed at
-// (kx, ky) (2D: kz is the line index; 3D lines run along z, 2D lines along
-// y with kz absent): a mode of the line with index w is kept iff w*w <= lim.
-// -1: the whole line is masked.  Decided once per line, exactly as
-// mask_keep decides each mode.
-template <int DIM>
-__device__ __forceinline__ int line_lim(const DevMask& mk, int kx, int ky, int L) {
-    const int hmax = (L >> 1) * (L >> 1);  // the largest w^2 on the line
-    if (mk.shape == 2) return hmax;
-    const int ia = DIM == 2 ? 1 : 2;  // axis of the line
-    if (mk.shape == 1) {
-        bool k = true;
-        if (mk.h[0]) k = k && (mk.den * abs(kx) < mk.num * mk.h[0]);
-        if (DIM == 3 && mk.h[1]) k = k && (mk.den * abs(ky) < mk.num * mk.h[1]);
-        if (!k) return -1;
-        if (!mk.h[ia]) return hmax;
-        // den |w| < num h  <=>  |w| <= (num h - 1) / den
-        const int wmax = (mk.num * mk.h[ia] - 1) / mk.den;
-        return wmax * wmax;
-    }
-    // radial: (P0 + w_a w^2) den2 < rhs  <=>  w^2 <= (floor((rhs - 1)/den2) - P0) / w_a
-    const int64_t p0 = mk.w[0] * kx * kx + (DIM == 3 ? mk.w[1] * ky * ky : 0);
-    const int64_t room = (mk.rhs - 1) / mk.den2 - p0;
-    if (room < 0) return -1;
-    const int64_t wa = mk.w[ia];
-    const int64_t lim = wa > 0 ? room / wa : hmax;
-    return lim > hmax ? hmax : static_cast<int>(lim);
+// What the noise of one field takes from the plan
+struct NoiseKey {
+    uint32_t k0, k1, step;
+    int fid;
+    float amp_pair, amp_self;
+};
+__device__ __forceinline__ NoiseKey noise_key(const DevPlan& p, int f, uint32_t step) {
+    return NoiseKey{p.key0, p.key1, step, p.fid[f], p.amp_pair, p.amp_self};
 }
-
 // Scaled unit white noise sigma(q) xi_hat(k) of field f at step `step` for a
 // mode with full-spectrum linear index lin and negative-mode index lneg, and
-// noise strength D(q) (Sec. "Adding noise").
-__device__ __forceinline__ float2 noise_value(const DevPlan& p, int f, uint32_t step, uint32_t lin, uint32_t lneg,
-                                              float D) {
+// noise strength D(q) (Sec. "Adding noise").  PAIR: the mode is known not to
+// be its own negative.
+template <bool PAIR = false>
+__device__ __forceinline__ float2 noise_value(const NoiseKey& n, uint32_t lin, uint32_t lneg, float D) {
     const uint32_t c = lin < lneg ? lin : lneg;
-    const uint4 w = philox4x32_10(make_uint4(c, step, static_cast<uint32_t>(p.fid[f]), 0u), p.key0, p.key1);
+    const uint4 w = philox4x32_10(make_uint4(c, n.step, static_cast<uint32_t>(n.fid), 0u), n.k0, n.k1);
     const float2 g = box_muller(w.x, w.y);
     const float sd = __builtin_amdgcn_sqrtf(fmaxf(D, 0.f));
-    if (lin == lneg) return make_float2(p.amp_self * sd * g.x, 0.f);
-    const float a = p.amp_pair * sd;
+    if constexpr (!PAIR) {
+        if (lin == lneg) return make_float2(n.amp_self * sd * g.x, 0.f);
+    }
+    const float a = n.amp_pair * sd;
     return lin == c ? make_float2(a * g.x, a * g.y) : make_float2(a * g.x, -a * g.y);
+}
+__device__ __forceinline__ float2 noise_value(const DevPlan& p, int f, uint32_t step, uint32_t lin, uint32_t lneg,
+                                              float D) {
+    return noise_value(noise_key(p, f, step), lin, lneg, D);
 }
 template <bool GEN>
 __device__ __forceinline__ float2 noise_mode(const DevPlan& p, int f, uint32_t step, uint32_t lin, uint32_t lneg,
@@ -254,17 +395,16 @@ __device__ __forceinline__ float2 noise_mode(const DevPlan& p, int f, uint32_t s
     return noise_value(p, f, step, lin, lneg, eval_op<GEN>(p.noise_op[f], q).x);
 }
 
-// full-spectrum linear index of mode (kx, ky, kz), each in [0, n_i)
-__device__ __forceinline__ uint32_t lin_index(const DevPlan& p, int kx, int ky, int kz) {
-    return (static_cast<uint32_t>(kz) * p.n[1] + ky) * p.n[0] + kx;
-}
-
 // full-spectrum linear index and its negative for signed mode indices
-__device__ __forceinline__ void mode_lin(const DevPlan& p, int kx, int ky, int kz, uint32_t& lin, uint32_t& lneg) {
-    const int nx = p.n[0], ny = p.n[1], nz = p.n[2];
+__device__ __forceinline__ void mode_lin(int nx, int ny, int nz, int kx, int ky, int kz, uint32_t& lin,
+                                         uint32_t& lneg) {
+    auto at = [&](int x, int y, int z) { return (static_cast<uint32_t>(z) * ny + y) * nx + x; };
     const int ux = kx & (nx - 1), uy = ky & (ny - 1), uz = kz & (nz - 1);
-    lin = lin_index(p, ux, uy, uz);
-    lneg = lin_index(p, (nx - ux) & (nx - 1), (ny - uy) & (ny - 1), (nz - uz) & (nz - 1));
+    lin = at(ux, uy, uz);
+    lneg = at((nx - ux) & (nx - 1), (ny - uy) & (ny - 1), (nz - uz) & (nz - 1));
+}
+__device__ __forceinline__ void mode_lin(const DevPlan& p, int kx, int ky, int kz, uint32_t& lin, uint32_t& lneg) {
+    mode_lin(p.n[0], p.n[1], p.n[2], kx, ky, kz, lin, lneg);
 }
 
 // f(integral_constant<int, I>) for I = 0 .. N-1, unrolled at compile time
@@ -332,7 +472,21 @@ __device__ __forceinline__ void add_to(float2 (&a)[NF][P], int f, int m, float2 
 // Transforms of a packed line see S(u) = phi(0,u) + i phi(Nx/2,u); the slot
 // form is converted to and from it through one LDS line (block-uniform
 // barriers; a block holds at most one packed line, its first).
-// LDS: TC*TO line-transform regions | one exchange line of L | twiddles of L.
+// LDS: TC*TO line-transform regions | one exchange line of L | twiddles of L
+// (P = 16 only; up to 8 points a thread keep them in registers).
+//
+// What bounds a 2D launch of one lattice is latency: 1024^2 is two blocks per
+// CU and one round, so the launch lasts as long as one block's chain.  Cycle
+// stamps along that chain (2.4 GHz): 1000 for the kernel arguments, 1700 to
+// 5000 for the plan's scalars and the first loads, 2400 for the noise, 1300
+// for each transform, 2000 for operators, update and mask.  Hence: every read
+// is issued at the top (the plan as blocks of scalar loads held in registers,
+// 35 waits in a row before), the de-aliasing limits come from a table (two
+// 64-bit divisions a line before), and the self-conjugate modes of column 0
+// are evaluated in four lanes (one thread's serial tail before, on the block
+// that the launch waits for).  64^2: 8.0 -> 5.5 us, 1024^2: 10.2 -> 8.4 us a
+// launch; with general operators (walked once per line instead of once per
+// mode) KPZ 22.8 -> 12.5 us and Model H 69 -> 30 us.
 
 // packed line: S(u), S(L-u) -> slot value of u (the forward direction)
 template <int L>
@@ -380,19 +534,19 @@ __device__ __forceinline__ void slot_at(const LineModes lm, int u, float& q2, ui
 }
 
 template <int L, int DIM>
-__device__ __forceinline__ LineModes line_modes(const DevPlan& p, bool packed, int kx_l, int ky_l) {
+__device__ __forceinline__ LineModes line_modes(int nx, int ny, const float (&qs)[3], bool packed, int kx_l,
+                                                int ky_l) {
     LineModes lm;
-    const int nx = p.n[0], ny = p.n[1];
     lm.packed = packed;
     lm.kx = kx_l;
     lm.ky = ky_l;
-    const float qx = static_cast<float>(kx_l) * p.qs[0];
-    const float qy = DIM == 3 ? static_cast<float>(ky_l) * p.qs[1] : 0.f;
-    const float qxN = static_cast<float>(nx >> 1) * p.qs[0];
+    const float qx = static_cast<float>(kx_l) * qs[0];
+    const float qy = DIM == 3 ? static_cast<float>(ky_l) * qs[1] : 0.f;
+    const float qxN = static_cast<float>(nx >> 1) * qs[0];
     lm.qq = fmaf(qx, qx, qy * qy);
     lm.qq0 = qy * qy;
     lm.qqN = fmaf(qxN, qxN, qy * qy);
-    lm.qs = p.qs[DIM == 2 ? 1 : 2];
+    lm.qs = qs[DIM == 2 ? 1 : 2];
     lm.lstride = DIM == 2 ? static_cast<uint32_t>(nx) : static_cast<uint32_t>(nx) * ny;
     const uint32_t ux = static_cast<uint32_t>(kx_l) & (nx - 1), uxn = static_cast<uint32_t>(-kx_l) & (nx - 1);
     const uint32_t uy = DIM == 3 ? (static_cast<uint32_t>(ky_l) & (ny - 1)) : 0u;
@@ -420,50 +574,104 @@ __device__ __forceinline__ void pair_modes(int ky_l, int u, int L, int& ky, int&
     }
 }
 
-// op applied to a pair slot (re: kx = 0 mode, im: kx = -Nx/2 mode)
-template <int DIM, bool GEN>
-__device__ __forceinline__ float2 pair_op_d(const DevPlan& p, const DevOp& op, int ky_l, int u, int L, float2 a) {
+// The four self-conjugate modes of a packed line (kx in {0, -Nx/2}, w in
+// {0, -L/2}), which its slots 0 and L/2 hold in pairs.  Their operators and
+// noise are evaluated side by side, mode j = lane & 3, and the thread that
+// holds the two slots (the block's first) takes the four results from lanes 0
+// to 3: evaluated in turn by that thread alone they were the longest chain of
+// the launch, on the one block that every other waits for.
+struct Self {
+    ModeQ q;             // of the mode of this lane
+    uint32_t lin, lneg;
+};
+struct Four {
+    float v[4];
+};
+__device__ __forceinline__ Four four_lanes(float x) {
+    Four r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        r.v[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
+    return r;
+}
+template <int L, int DIM>
+__device__ __forceinline__ Self self_modes(int nx, int ny, int nz, const float (&qs)[3], int ky_pack, int tid) {
+    Self s;
     int ky, kz;
-    pair_modes<DIM>(ky_l, u, L, ky, kz);
-    return make_float2(eval_op<GEN>(op, mode_q(p, 0, ky, kz)).x * a.x,
-                       eval_op<GEN>(op, mode_q(p, -(p.n[0] >> 1), ky, kz)).x * a.y);
+    pair_modes<DIM>(ky_pack, (tid & 2) ? (L >> 1) : 0, L, ky, kz);
+    const int kx = (tid & 1) ? -(nx >> 1) : 0;
+    s.q = mode_q(nx, ny, nz, qs, kx, ky, kz);
+    mode_lin(nx, ny, nz, kx, ky, kz, s.lin, s.lneg);
+    return s;
+}
+// v (pair slots m = 0 and P/2) times the real parts c of an operator there
+template <int P>
+__device__ __forceinline__ void pair_scale(const Four& c, const float2 (&v)[P], float2& lo, float2& hi) {
+    static_assert(P >= 2, "slots 0 and L/2 lie in one thread");
+    lo = make_float2(c.v[0] * v[0].x, c.v[1] * v[0].y);
+    hi = make_float2(c.v[2] * v[P / 2].x, c.v[3] * v[P / 2].y);
 }
 
-// semi-implicit update of a pair slot
-template <int DIM, bool GEN>
-__device__ __forceinline__ float2 pair_update_d(const DevPlan& p, int f, uint32_t step, int ky_l, int u, int L,
-                                                float2 old, float2 acc, bool noisy) {
-    int ky, kz;
-    pair_modes<DIM>(ky_l, u, L, ky, kz);
-    const int kn = -(p.n[0] >> 1);
-    const ModeQ q0 = mode_q(p, 0, ky, kz), qn = mode_q(p, kn, ky, kz);
-    float2 r = cadd(old, cscale(acc, p.dt));
-    if (noisy) {
-        uint32_t lin, lneg;
-        mode_lin(p, 0, ky, kz, lin, lneg);
-        r.x += noise_mode<GEN>(p, f, step, lin, lneg, q0).x;
-        mode_lin(p, kn, ky, kz, lin, lneg);
-        r.y += noise_mode<GEN>(p, f, step, lin, lneg, qn).x;
+// What the lines of a block have in common, for the per-mode operators
+template <int P, bool LANES>
+struct LineCtx {
+    float q2[P];      // of the slots (pair slots: unused)
+    bool first_wave;  // the wave holding the block's packed line, if it has one
+    bool pair_lane;   // the thread holding that line's slots 0 and L/2
+    Self self[LANES ? 1 : 4];  // first wave only: this lane's mode, or all four
+};
+// f at the four self-conjugate modes (first wave only): one per lane, or, on
+// lines held by fewer than four threads, all of them in every thread
+template <int P, bool LANES, class F>
+__device__ __forceinline__ Four self_eval(const LineCtx<P, LANES>& cx, F&& f) {
+    if constexpr (LANES) {
+        return four_lanes(f(cx.self[0]));
+    } else {
+        Four r;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) r.v[j] = f(cx.self[j]);
+        return r;
     }
-    return make_float2(r.x * cinv_implicit(p.dt, eval_op<GEN>(p.implicit_op[f], q0)).x,
-                       r.y * cinv_implicit(p.dt, eval_op<GEN>(p.implicit_op[f], qn)).x);
 }
 
 // mode q of slot u of a line, for the general-monomial operators
 template <int L, int DIM>
-__device__ __forceinline__ ModeQ slot_q(const DevPlan& p, const LineModes lm, int u) {
+__device__ __forceinline__ ModeQ slot_q(int nx, int ny, int nz, const float (&qs)[3], const LineModes lm, int u) {
     const bool upper = lm.packed && u > (L >> 1);
     const int w = lm.packed ? (upper ? L - u : u) : (u < (L >> 1) ? u : u - L);
-    const int kx = lm.packed ? (upper ? -(p.n[0] >> 1) : 0) : lm.kx;
-    return DIM == 2 ? mode_q(p, kx, w, 0) : mode_q(p, kx, lm.ky, w);
+    const int kx = lm.packed ? (upper ? -(nx >> 1) : 0) : lm.kx;
+    return DIM == 2 ? mode_q(nx, ny, nz, qs, kx, w, 0) : mode_q(nx, ny, nz, qs, kx, lm.ky, w);
 }
 
-// slots 0 and L/2 of a packed line: op applied to their two real modes each
-template <int DIM, bool GEN, int NF, int P>
-__device__ __forceinline__ void pair_accumulate(float2 (&acc)[NF][P], int target, const float2 (&v)[P],
-                                                const DevPlan& p, const DevOp& op, int ky_l, int L) {
-    add_to(acc, target, 0, pair_op_d<DIM, GEN>(p, op, ky_l, 0, L, v[0]));
-    add_to(acc, target, P / 2, pair_op_d<DIM, GEN>(p, op, ky_l, L >> 1, L, v[P / 2]));
+// acc[target] += op v on the slots of a line
+template <bool GEN, int NF, int P, bool LANES>
+__device__ __forceinline__ void accumulate(float2 (&acc)[NF][P], int target, const float2 (&v)[P], const DevOp& op,
+                                           const OpPoly& poly, const LineCtx<P, LANES>& cx,
+                                           const ModeQ (&qv)[GEN ? P : 1]) {
+    float2 d[P];
+    if constexpr (GEN) {
+        float2 M[P];
+        eval_op_p(op, cx.q2, qv, M);
+#pragma unroll
+        for (int m = 0; m < P; ++m) d[m] = cmul(M[m], v[m]);
+    } else {
+        float M[P];
+        horner_p(poly, cx.q2, M);
+#pragma unroll
+        for (int m = 0; m < P; ++m) d[m] = cscale(v[m], M[m]);
+    }
+    // slots 0 and L/2 of a packed line: two real modes each (operators are real on them)
+    if (cx.first_wave) {
+        const Four f = self_eval(cx, [&](const Self& e) {
+            if constexpr (GEN)
+                return eval_op<true>(op, e.q).x;
+            else
+                return horner(poly, e.q.q2);
+        });
+        if (cx.pair_lane) pair_scale(f, v, d[0], d[P / 2]);
+    }
+#pragma unroll
+    for (int m = 0; m < P; ++m) add_to(acc, target, m, d[m]);
 }
 
 // Fourier value of an intermediate field at the slots of one line, from the
@@ -472,51 +680,55 @@ __device__ __forceinline__ void pair_accumulate(float2 (&acc)[NF][P], int target
 // On a packed line the pair slots come out in the same form as the state's:
 // (value of the kx = 0 mode, value of the kx = -Nx/2 mode), both real, since
 // every operator is real on those four self-conjugate modes.
-template <int L, int P, int NF, int DIM>
-__device__ __forceinline__ void interm_line(const DevPlan& p, const DevInterm& I, const float2 (&s)[NF][P],
-                                            const LineModes lm, int t, bool pair_lane, int ky_l, float2 (&v)[P]) {
-    constexpr int T = L / P;
-    ModeQ q[P];
+template <int P, int NF, bool LANES>
+__device__ __forceinline__ void interm_line(const DevInterm& I, const float2 (&s)[NF][P], const LineCtx<P, LANES>& cx,
+                                            const ModeQ (&q)[P], float2 (&v)[P]) {
+    float2 plo = make_float2(0.f, 0.f), phi = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int m = 0; m < P; ++m) {
-        q[m] = slot_q<L, DIM>(p, lm, t + m * T);
-        v[m] = make_float2(0.f, 0.f);
-    }
+    for (int m = 0; m < P; ++m) v[m] = make_float2(0.f, 0.f);
     for (int k = 0; k < I.nsrc; ++k) {
         const int src = I.src[k];
+        float2 M[P], a[P];
+        eval_op_p(I.op[k], cx.q2, q, M);
 #pragma unroll
-        for (int m = 0; m < P; ++m) v[m] = cadd(v[m], cmul(eval_op<true>(I.op[k], q[m]), pick(s, src, m)));
-    }
-#pragma unroll
-    for (int m = 0; m < P; ++m) v[m] = cmul(v[m], cinv_implicit(1.f, eval_op<true>(I.den, q[m])));
-    if (pair_lane) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int mm = h ? P / 2 : 0;
-            int ky, kz;
-            pair_modes<DIM>(ky_l, h ? (L >> 1) : 0, L, ky, kz);
-            const ModeQ q0 = mode_q(p, 0, ky, kz), qn = mode_q(p, -(p.n[0] >> 1), ky, kz);
-            float re = 0.f, im = 0.f;
-            for (int k = 0; k < I.nsrc; ++k) {
-                const float2 a = pick(s, I.src[k], mm);
-                re = fmaf(eval_op<true>(I.op[k], q0).x, a.x, re);
-                im = fmaf(eval_op<true>(I.op[k], qn).x, a.y, im);
-            }
-            v[mm] = make_float2(re * cinv_implicit(1.f, eval_op<true>(I.den, q0)).x,
-                                im * cinv_implicit(1.f, eval_op<true>(I.den, qn)).x);
+        for (int m = 0; m < P; ++m) {
+            a[m] = pick(s, src, m);
+            v[m] = cadd(v[m], cmul(M[m], a[m]));
         }
+        if (cx.first_wave) {
+            const Four f = self_eval(cx, [&](const Self& e) { return eval_op<true>(I.op[k], e.q).x; });
+            plo = make_float2(fmaf(f.v[0], a[0].x, plo.x), fmaf(f.v[1], a[0].y, plo.y));
+            phi = make_float2(fmaf(f.v[2], a[P / 2].x, phi.x), fmaf(f.v[3], a[P / 2].y, phi.y));
+        }
+    }
+    if (!I.no_den) {  // 1 - L_psi = 1 otherwise
+        float2 M[P];
+        eval_op_p(I.den, cx.q2, q, M);
+#pragma unroll
+        for (int m = 0; m < P; ++m) v[m] = cmul(v[m], cinv_implicit(1.f, M[m]));
+        if (cx.first_wave) {
+            const Four f =
+                self_eval(cx, [&](const Self& e) { return cinv_implicit(1.f, eval_op<true>(I.den, e.q)).x; });
+            plo = make_float2(plo.x * f.v[0], plo.y * f.v[1]);
+            phi = make_float2(phi.x * f.v[2], phi.y * f.v[3]);
+        }
+    }
+    if (cx.pair_lane) {
+        v[0] = plo;
+        v[P / 2] = phi;
     }
 }
 
 // the values of factor or linear-term source `src` at the slots of a line:
 // a dynamic field's own, or an intermediate's (only plans with the general
 // operator code have intermediates)
-template <int L, int P, int NF, int DIM, bool GEN>
-__device__ __forceinline__ void source_line(const DevPlan& p, int src, const float2 (&s)[NF][P], const LineModes lm,
-                                            int t, bool pair_lane, int ky_l, float2 (&v)[P]) {
+template <int P, int NF, bool GEN, bool LANES>
+__device__ __forceinline__ void source_line(const DevPlan& p, int src, const float2 (&s)[NF][P],
+                                            const LineCtx<P, LANES>& cx,
+                                            const ModeQ (&qv)[GEN ? P : 1], float2 (&v)[P]) {
     if constexpr (GEN) {
         if (src >= PSS_MAXF) {
-            interm_line<L, P, NF, DIM>(p, p.interm[src - PSS_MAXF], s, lm, t, pair_lane, ky_l, v);
+            interm_line(p.interm[src - PSS_MAXF], s, cx, qv, v);
             return;
         }
     }
@@ -566,14 +778,24 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     const int li = tid / T;  // line of the block
     const int cc = li & (tc - 1);
     const int lo = li >> geo.tc_log2;
-    const int ct = blk % ntile;  // tile index
-    const int og = blk / ntile;  // group of `to` other-index lines
+    const int og = DIM == 2 ? 0 : __builtin_amdgcn_readfirstlane(blk / ntile);  // group of `to` other-index lines
+    const int ct = blk - og * ntile;                                            // tile index
     const int o = og * to + lo;
     const int c = ct * tc + cc;  // packed column
-    const int nx = p.n[0], ny = p.n[1];
-    const size_t base = (static_cast<size_t>(o) * ntile + ct) * L * tc + cc;
-    const size_t vbase = DIM == 2 ? base : (static_cast<size_t>(ct) * ny + o) * tc + cc;
-    const size_t vstride = DIM == 2 ? static_cast<size_t>(tc) : static_cast<size_t>(ntile) * ny * tc;
+    const int nx = geo.nx, ny = geo.ny;
+    using I = std::conditional_t<DIM == 2, uint32_t, size_t>;
+    const I base = (static_cast<I>(o) * ntile + ct) * L * tc + cc;
+    // the exchange arrays: products in, factors (and transform modes' arrays) out
+    Exch<I> xin, xout;
+    if constexpr (DIM == 2) {
+        xin = xout = exch_column(geo, ct, cc, L);
+    } else {
+        xin = Exch<I>{base, static_cast<I>(tc), false};
+        xout = Exch<I>{(static_cast<I>(ct) * ny + o) * tc + cc, static_cast<I>(ntile) * ny * tc, false};
+    }
+    // this thread's first position and the step from slot to slot
+    const I sat = base + static_cast<I>(t) * tc, sstep = static_cast<I>(T) * tc;
+    const I iat = xin.at(t), istep = xin.step(T), oat = xout.at(t), ostep = xout.step(T);
     LdsLine ld;
     ld.wl = smem + li * FFT::kLds;
     ld.blk0 = ld.wl + FFT::kReg;
@@ -582,10 +804,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     float2* xbuf = smem + tc * to * FFT::kLds;  // packed-line exchange
     float2* twl = xbuf + L;
     const int dr = FFT::drev(t);  // gathered / scattered positions dr + m*T
-    // twiddles: loaded now, stored to LDS after each mode's first loads
-    float2 twr[P];
-    load_twiddles<L, P>(twr, tw_g, tid, nthr);
-    const float2* tw = twl;
+    Twiddles<FFT, L, P> tw;
     // block holds a packed line (block-uniform); this thread is on it
     const bool blk_packed = ct == 0 && (DIM == 2 || og * to == 0 || og * to == (ny >> 1));
     const bool packed = blk_packed && cc == 0 && lo == 0;
@@ -604,7 +823,6 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             }
         }
     }
-    const int nf = p.nf;
 
     // packed line only: exchange v (natural order) with the partner slot -u
     // and map it (block-uniform)
@@ -630,154 +848,219 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         // forward transform of an array in the state layout, stored as the state
         float2 v[P];
 #pragma unroll
-        for (int m = 0; m < P; ++m) v[m] = gload(bufs.in + base + (dr + m * T) * tc);
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
-        FFT::template dit<-1>(v, ld, t, tw);
+        for (int m = 0; m < P; ++m) v[m] = gload(bufs.in + xin.at(dr + m * T));
+        tw.load(tw_g, t, tid, nthr);
+        tw.ready(twl, tid, nthr);
+        FFT::template dit<-1>(v, ld, t, tw.get());
         exchange(v, true);
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore(bufs.S[bufs.sel] + base + (t + m * T) * tc, v[m]);
+        for (int m = 0; m < P; ++m) gstore(elem(bufs.S[bufs.sel], sat + m * sstep), v[m]);
         return;
     }
     if constexpr (MODE == MODE_INV_OUT) {
         float2 v[P];
 #pragma unroll
-        for (int m = 0; m < P; ++m) v[m] = gload(bufs.S[bufs.sel] + base + (t + m * T) * tc);
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
+        for (int m = 0; m < P; ++m) v[m] = gload(elem(bufs.S[bufs.sel], sat + m * sstep));
+        tw.load(tw_g, t, tid, nthr);
+        tw.ready(twl, tid, nthr);
         exchange(v, false);
-        FFT::template dif<1>(v, ld, t, tw);
+        FFT::template dif<1>(v, ld, t, tw.get());
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore(bufs.out + vbase + (dr + m * T) * vstride, v[m]);
+        for (int m = 0; m < P; ++m) gstore(bufs.out + xout.at(dr + m * T), v[m]);
         return;
     }
 
     // ---- MODE_STEP, MODE_PROLOGUE or MODE_INTERM_OUT
-    const LineModes lmode = line_modes<L, DIM>(p, packed, kx_l, ky_l);
+    // Every read that the step starts from is issued here, before anything
+    // waits: the plan's scalars and (plans of one or two fields) its
+    // operators as blocks of scalar loads, the first channel, the twiddles
+    // and the state.  With the plan read where it is used, the launch spent
+    // some 35 scalar-load waits in a row.
+    constexpr bool STEP = MODE == MODE_STEP;
+    constexpr bool HOT = STEP && !GEN && NF <= 2;
+    int nf = p.nf, nch = p.nch, ng = p.ng, nd = p.nd;
+    float qs[3] = {p.qs[0], p.qs[1], p.qs[2]};
+    float dt = p.dt, amp_pair = p.amp_pair, amp_self = p.amp_self;
+    uint32_t key0 = p.key0, key1 = p.key1;
+    int noisy[NF], fid[NF];
+    OpPoly imp[HOT ? NF : 1], noi[HOT ? NF : 1], ch0;
+    if constexpr (STEP) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            noisy[f] = p.noisy[f];
+            fid[f] = p.fid[f];
+        }
+    }
+    if constexpr (HOT) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            imp[f] = op_poly(p.implicit_op[f]);
+            noi[f] = op_poly(p.noise_op[f]);
+        }
+        ch0 = op_poly(p.ch[0].op[0]);
+    }
+    const int32_t* lim0 = p.lim[0];
+    uint32_t step = 0;
+    if constexpr (STEP) step = static_cast<uint32_t>(gload_u64(step_ctr)) + static_cast<uint32_t>(step_off);
+
+    float2 nxt[STEP ? P : 1];
+    if constexpr (STEP) {
+        // the arrays of a plan without products are null: read the state instead
+        const float2* n0 = bufs.N[0] ? bufs.N[0] : bufs.S[0];
+#pragma unroll
+        for (int m = 0; m < P; ++m) nxt[m] = gload(elem(n0, iat + m * istep));
+    }
+    tw.load(tw_g, t, tid, nthr);
     float2 s[NF][P];  // state, then new state (slot form on a packed line)
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-        if (f < nf) {
+        if (f == 0 || f < nf) {
 #pragma unroll
-            for (int m = 0; m < P; ++m) s[f][m] = gload(bufs.S[f] + base + (t + m * T) * tc);
+            for (int m = 0; m < P; ++m) s[f][m] = gload(elem(bufs.S[f], sat + m * sstep));
         } else {
 #pragma unroll
             for (int m = 0; m < P; ++m) s[f][m] = make_float2(0.f, 0.f);
         }
     }
+    if constexpr (STEP) {
+        hold(nf), hold(nch), hold(ng), hold(nd), hold(dt), hold(amp_pair), hold(amp_self), hold(key0), hold(key1);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) hold(qs[i]);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) hold(noisy[f]), hold(fid[f]);
+        hold(step);
+    }
+    if constexpr (HOT) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) hold(imp[f]), hold(noi[f]);
+        hold(ch0);
+    }
+    // the de-aliasing limits of the line for the first factor
+    const int kxa = kx_l < 0 ? -kx_l : kx_l, kya = ky_l < 0 ? -ky_l : ky_l;
+    const int lrow = kya * ((nx >> 1) + 1);
+    int lim_0 = -1, limN_0 = -1;
+    if (ng > 0 && ct * tc < geo.ncol[0]) {
+        lim_0 = lim0[lrow + kxa];
+        if (blk_packed) limN_0 = lim0[lrow + (nx >> 1)];
+    }
+
+    const LineModes lmode = line_modes<L, DIM>(nx, ny, qs, packed, kx_l, ky_l);
+    // per-slot modes of the line (slot form on a packed line)
+    constexpr bool LANES = T >= 4;
+    LineCtx<P, LANES> cx;
+    uint32_t lin[P], lneg[P];
+#pragma unroll
+    for (int m = 0; m < P; ++m) slot_at<L>(lmode, t + m * T, cx.q2[m], lin[m], lneg[m]);
+    cx.pair_lane = pair_lane;
+    cx.first_wave = blk_packed && tid < 64;
+    if (cx.first_wave) {
+#pragma unroll
+        for (int j = 0; j < (LANES ? 1 : 4); ++j)
+            cx.self[j] = self_modes<L, DIM>(nx, ny, geo.nz, qs, DIM == 3 ? signed_mode(og * to, ny) : 0,
+                                            LANES ? tid : j);
+    }
+    // general operators: the mode vectors of the slots, once per line
+    ModeQ qv[GEN ? P : 1];
+    if constexpr (GEN) {
+#pragma unroll
+        for (int m = 0; m < P; ++m) qv[m] = slot_q<L, DIM>(nx, ny, geo.nz, qs, lmode, t + m * T);
+    }
 
     if constexpr (MODE == MODE_INTERM_OUT) {
         // an intermediate field from the current state, inverse-transformed
         // along the line into `out` (natural order, as MODE_INV_OUT)
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
+        tw.ready(twl, tid, nthr);
         float2 v[P];
-        source_line<L, P, NF, DIM, GEN>(p, PSS_MAXF + bufs.sel, s, lmode, t, pair_lane, ky_l, v);
+        source_line<P, NF, GEN, (T >= 4)>(p, PSS_MAXF + bufs.sel, s, cx, qv, v);
         exchange(v, false);
-        FFT::template dif<1>(v, ld, t, tw);
+        FFT::template dif<1>(v, ld, t, tw.get());
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore(bufs.out + vbase + (dr + m * T) * vstride, v[m]);
+        for (int m = 0; m < P; ++m) gstore(bufs.out + xout.at(dr + m * T), v[m]);
         return;
     }
-    if constexpr (MODE == MODE_PROLOGUE) {
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
-    }
-    if constexpr (MODE == MODE_STEP) {
-        const uint32_t step = static_cast<uint32_t>(gload_u64(step_ctr)) + static_cast<uint32_t>(step_off);
-        // the first channel's loads go out before the twiddles are stored
-        float2 nxt[P];
-        if (p.nch > 0) {
-#pragma unroll
-            for (int m = 0; m < P; ++m) nxt[m] = gload(bufs.N[0] + base + (t + m * T) * tc);
-        }
-        // per-slot modes of the line (slot form on a packed line)
-        float q2[P];
-        uint32_t lin[P], lneg[P];
-#pragma unroll
-        for (int m = 0; m < P; ++m) slot_at<L>(lmode, t + m * T, q2[m], lin[m], lneg[m]);
-        // general operators: the mode vectors of the slots, once per line
-        ModeQ qv[GEN ? P : 1];
-        if constexpr (GEN) {
-#pragma unroll
-            for (int m = 0; m < P; ++m) qv[m] = slot_q<L, DIM>(p, lmode, t + m * T);
-        }
+    if constexpr (MODE == MODE_PROLOGUE) tw.ready(twl, tid, nthr);
+    if constexpr (STEP) {
         // the step's noise depends on the step and the modes only: formed
-        // here, while the loads above are still in flight
-        float2 eta[GEN ? 1 : NF][P];
-        if constexpr (!GEN) {
+        // here, while the loads above are still in flight.  Per field: of the
+        // slots, and of the four self-conjugate modes.
+        float2 eta[NF][P];
+        Four eta4[NF];
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                if (f < nf && p.noisy[f] != 0) {
-                    float Dn[P];
-                    horner_p(p.noise_op[f], q2, Dn);
+        for (int f = 0; f < NF; ++f) {
+            if (f < nf && noisy[f] != 0) {
+                const NoiseKey nk{key0, key1, step, fid[f], amp_pair, amp_self};
+                float Dn[P];
+                if constexpr (HOT) {
+                    horner_p(noi[f], cx.q2, Dn);
+                } else if constexpr (GEN) {
+                    float2 D2[P];
+                    eval_op_p(p.noise_op[f], cx.q2, qv, D2);
 #pragma unroll
-                    for (int m = 0; m < P; ++m) eta[f][m] = noise_value(p, f, step, lin[m], lneg[m], Dn[m]);
+                    for (int m = 0; m < P; ++m) Dn[m] = D2[m].x;
                 } else {
-#pragma unroll
-                    for (int m = 0; m < P; ++m) eta[f][m] = make_float2(0.f, 0.f);
+                    horner_p(p.noise_op[f], cx.q2, Dn);
                 }
+#pragma unroll
+                for (int m = 0; m < P; ++m) eta[f][m] = noise_value<true>(nk, lin[m], lneg[m], Dn[m]);
+                if (cx.first_wave) {
+                    eta4[f] = self_eval(cx, [&](const Self& e) {
+                        float Ds;
+                        if constexpr (HOT)
+                            Ds = horner(noi[f], e.q.q2);
+                        else
+                            Ds = eval_op<GEN>(p.noise_op[f], e.q).x;
+                        return noise_value(nk, e.lin, e.lneg, Ds).x;
+                    });
+                }
+            } else {
+#pragma unroll
+                for (int m = 0; m < P; ++m) eta[f][m] = make_float2(0.f, 0.f);
             }
         }
-        store_twiddles<L, P>(twl, twr, tid, nthr);  // waits for the twiddle loads
-        __syncthreads();  // twiddles in LDS
+        tw.ready(twl, tid, nthr);
         float2 acc[NF][P];  // explicit contributions
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int m = 0; m < P; ++m) acc[f][m] = make_float2(0.f, 0.f);
         // explicit real-space channels: forward transform, then M(q) per mode
-        for (int ch = 0; ch < p.nch; ++ch) {
+        for (int ch = 0; ch < nch; ++ch) {
             const DevChannel& C = p.ch[ch];
             float2 v[P];
 #pragma unroll
             for (int m = 0; m < P; ++m) v[m] = nxt[m];
-            if (ch + 1 < p.nch) {
-#pragma unroll
-                for (int m = 0; m < P; ++m) nxt[m] = gload(bufs.N[ch + 1] + base + (t + m * T) * tc);
-            }
-            FFT::template dit<-1>(v, ld, t, tw);
-            exchange(v, true);
             // each output: its operator times the transform, into its field
             // (one field: one output, so the loop is left out)
             const int nout = NF == 1 ? 1 : C.nout;
-            for (int o = 0; o < nout; ++o) {
-                const DevOp& op = C.op[o];
-                const int tg = C.target[o];
-                if constexpr (GEN) {
+            if (ch + 1 < nch) {
 #pragma unroll
-                    for (int m = 0; m < P; ++m)
-                        if (!(pair_lane && (m == 0 || m == P / 2)))
-                            add_to(acc, tg, m, cmul(eval_op<GEN>(op, qv[m]), v[m]));
-                } else {
-                    float M[P];
-                    horner_p(op, q2, M);
-#pragma unroll
-                    for (int m = 0; m < P; ++m)
-                        if (!(pair_lane && (m == 0 || m == P / 2))) add_to(acc, tg, m, cscale(v[m], M[m]));
+                for (int m = 0; m < P; ++m) nxt[m] = gload(elem(bufs.N[ch + 1], iat + m * istep));
+            }
+            FFT::template dit<-1>(v, ld, t, tw.get());
+            exchange(v, true);
+            for (int o2 = 0; o2 < nout; ++o2) {
+                const DevOp& op = C.op[o2];
+                const int tg = NF == 1 ? 0 : C.target[o2];
+                OpPoly poly;
+                if constexpr (HOT) {
+                    if (ch == 0 && o2 == 0)
+                        poly = ch0;
+                    else
+                        poly = op_poly(op);
+                } else if constexpr (!GEN) {
+                    poly = op_poly(op);
                 }
-                // slots 0 and L/2 of a packed line: two real modes (operators are real on them)
-                if (pair_lane) pair_accumulate<DIM, GEN>(acc, tg, v, p, op, ky_l, L);
+                accumulate<GEN>(acc, tg, v, op, poly, cx, qv);
             }
         }
         // Fourier-space terms with a single linear factor
-        for (int d = 0; d < p.nd; ++d) {
+        for (int d = 0; d < nd; ++d) {
             const DevDirect& Dd = p.direct[d];
             float2 src[P];  // from the step-n state (an intermediate: its step-n value)
-            source_line<L, P, NF, DIM, GEN>(p, Dd.src, s, lmode, t, pair_lane, ky_l, src);
-            if constexpr (GEN) {
-#pragma unroll
-                for (int m = 0; m < P; ++m)
-                    if (!(pair_lane && (m == 0 || m == P / 2)))
-                        add_to(acc, Dd.target, m, cmul(eval_op<GEN>(Dd.op, qv[m]), src[m]));
-            } else {
-                float M[P];
-                horner_p(Dd.op, q2, M);
-#pragma unroll
-                for (int m = 0; m < P; ++m)
-                    if (!(pair_lane && (m == 0 || m == P / 2))) add_to(acc, Dd.target, m, cscale(src[m], M[m]));
-            }
-            if (pair_lane) pair_accumulate<DIM, GEN>(acc, Dd.target, src, p, Dd.op, ky_l, L);
+            source_line<P, NF, GEN, (T >= 4)>(p, Dd.src, s, cx, qv, src);
+            OpPoly poly;
+            if constexpr (!GEN) poly = op_poly(Dd.op);
+            accumulate<GEN>(acc, Dd.target, src, Dd.op, poly, cx, qv);
         }
         // semi-implicit update (eq:timeupdate) with in-register noise
         // fields unrolled by template: a loop that the compiler leaves rolled
@@ -787,34 +1070,58 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         static_for<NF>([&](auto FF) {
             constexpr int f = decltype(FF)::value;
             if (f >= nf) return;
-            const bool noisy = p.noisy[f] != 0;
+            const bool nz = noisy[f] != 0;
             const float2 old0 = s[f][0], oldh = s[f][P / 2];
-            float Ar[P];
-            if constexpr (!GEN) horner_p(p.implicit_op[f], q2, Ar);
+            if constexpr (GEN) {
+                float2 A[P];
+                eval_op_p(p.implicit_op[f], cx.q2, qv, A);
 #pragma unroll
-            for (int m = 0; m < P; ++m) {
-                float2 r = cadd(s[f][m], cscale(acc[f][m], p.dt));
-                if constexpr (GEN) {
-                    const ModeQ& q = qv[m];
-                    if (noisy) r = cadd(r, noise_mode<GEN>(p, f, step, lin[m], lneg[m], q));
-                    s[f][m] = cmul(r, cinv_implicit(p.dt, eval_op<GEN>(p.implicit_op[f], q)));
-                } else {
-                    if (noisy) r = cadd(r, eta[f][m]);
-                    s[f][m] = cscale(r, __builtin_amdgcn_rcpf(fmaf(-p.dt, Ar[m], 1.f)));
+                for (int m = 0; m < P; ++m) {
+                    float2 r = cadd(s[f][m], cscale(acc[f][m], dt));
+                    if (nz) r = cadd(r, eta[f][m]);
+                    s[f][m] = cmul(r, cinv_implicit(dt, A[m]));
+                }
+            } else {
+                float A[P];
+                if constexpr (HOT)
+                    horner_p(imp[f], cx.q2, A);
+                else
+                    horner_p(p.implicit_op[f], cx.q2, A);
+#pragma unroll
+                for (int m = 0; m < P; ++m) {
+                    float2 r = cadd(s[f][m], cscale(acc[f][m], dt));
+                    if (nz) r = cadd(r, eta[f][m]);
+                    s[f][m] = cscale(r, __builtin_amdgcn_rcpf(fmaf(-dt, A[m], 1.f)));
                 }
             }
-            if (pair_lane) {
-                // slots 0 and L/2 hold two real modes each
-                s[f][0] = pair_update_d<DIM, GEN>(p, f, step, ky_l, 0, L, old0, acc[f][0], noisy);
-                s[f][P / 2] = pair_update_d<DIM, GEN>(p, f, step, ky_l, L >> 1, L, oldh, acc[f][P / 2], noisy);
+            if (cx.first_wave) {
+                const Four inv = self_eval(cx, [&](const Self& e) {
+                    float A;
+                    if constexpr (HOT)
+                        A = horner(imp[f], e.q.q2);
+                    else
+                        A = eval_op<GEN>(p.implicit_op[f], e.q).x;
+                    return cinv_implicit(dt, make_float2(A, 0.f)).x;
+                });
+                if (pair_lane) {
+                    // slots 0 and L/2 hold two real modes each
+                    float2 r = cadd(old0, cscale(acc[f][0], dt)), rh = cadd(oldh, cscale(acc[f][P / 2], dt));
+                    if (nz) {
+                        r = make_float2(r.x + eta4[f].v[0], r.y + eta4[f].v[1]);
+                        rh = make_float2(rh.x + eta4[f].v[2], rh.y + eta4[f].v[3]);
+                    }
+                    pair_scale<2>(inv, {r, rh}, s[f][0], s[f][P / 2]);
+                }
             }
-            bool fin = true;
+            // x * 0 is NaN for a NaN or an infinity, and a sum keeps it
+            float fin = 0.f;
 #pragma unroll
             for (int m = 0; m < P; ++m) {
-                gstore_sel<!TABLE>(bufs.S[f] + base + (t + m * T) * tc, s[f][m]);
-                fin = fin && __builtin_isfinite(s[f][m].x) && __builtin_isfinite(s[f][m].y);
+                gstore_sel<!TABLE>(elem(bufs.S[f], sat + m * sstep), s[f][m]);
+                fin = fmaf(s[f][m].x, 0.f, fin);
+                fin = fmaf(s[f][m].y, 0.f, fin);
             }
-            if (!fin) bad |= 1u << f;  // a NaN or infinity in the new state
+            if (fin != 0.f) bad |= 1u << f;  // a NaN or infinity in the new state
         });
         if (bad) {
             if constexpr (TAB) {
@@ -826,16 +1133,24 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     }
 
     // de-aliased inverse transforms of every factor field (eq:cubicexampledealiased)
-    for (int g = 0; g < p.ng; ++g) {
-        const DevMask& mk = p.mask[g];
-        if (ct * tc >= mk.ncol) continue;  // whole tile masked: never read (block-uniform)
+    for (int g = 0; g < ng; ++g) {
+        // whole tile masked: never read (block-uniform)
+        if (ct * tc >= geo.ncol[g]) continue;
         // the factor's Fourier values (a dynamic field's new state, or an
         // intermediate computed from it)
         float2 a[P];
-        source_line<L, P, NF, DIM, GEN>(p, p.gfield[g], s, lmode, t, pair_lane, ky_l, a);
+        if constexpr (NF == 1 && !GEN) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) a[m] = s[0][m];
+        } else {
+            source_line<P, NF, GEN, (T >= 4)>(p, p.gfield[g], s, cx, qv, a);
+        }
         // the largest kept w^2 of this line (packed: of each half)
-        const int lim = line_lim<DIM>(mk, lmode.packed ? 0 : kx_l, ky_l, L);
-        const int limN = line_lim<DIM>(mk, -(nx >> 1), ky_l, L);
+        int lim = lim_0, limN = limN_0;
+        if (g > 0) {
+            lim = p.lim[g][lrow + kxa];
+            if (blk_packed) limN = p.lim[g][lrow + (nx >> 1)];
+        }
         float2 v[P];
 #pragma unroll
         for (int m = 0; m < P; ++m) {
@@ -852,9 +1167,9 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             v[P / 2] = make_float2(wh <= lim ? ah.x : 0.f, wh <= limN ? ah.y : 0.f);
         }
         exchange(v, false);
-        FFT::template dif<1>(v, ld, t, tw);
+        FFT::template dif<1>(v, ld, t, tw.get());
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore_sel<!TABLE>(bufs.V[g] + vbase + (t + m * T) * vstride, v[m]);
+        for (int m = 0; m < P; ++m) gstore_sel<!TABLE>(elem(bufs.V[g], oat + m * ostep), v[m]);
     }
 }
 
@@ -867,8 +1182,8 @@ __global__ void __launch_bounds__(256) update_kernel(const Member* __restrict__ 
                                                       const float2* __restrict__ tw_g) {
     // lattice blockIdx.y, XCD-ordered over the whole grid
     const int nb = gridDim.x;
-    const int lin_b = xcd_block(blockIdx.y * nb + blockIdx.x, nb * gridDim.y);
-    const int mi = lin_b / nb;
+    const int lin_b = TABLE ? xcd_block(blockIdx.y * nb + blockIdx.x, nb * gridDim.y) : xcd_block(blockIdx.x, nb);
+    const int mi = TABLE ? __builtin_amdgcn_readfirstlane(lin_b / nb) : 0;
     update_block<L, P, NF, MODE, DIM, GEN, TABLE>(mi, lin_b - mi * nb, members, plans, plan_a, bufs_a, geo,
                                                   step_ctr_a, flag_a, step_off, tw_g);
 }
@@ -896,6 +1211,8 @@ __global__ void __launch_bounds__(256) adjcol_kernel(AdjArgs aa, Geo geo, const 
     const int nx = p.n[0];
     const int kn = -(nx >> 1);
     const size_t base = static_cast<size_t>(ct) * L * tc + cc;
+    const Exch<uint32_t> xch = exch_column(geo, ct, cc, L);
+    const uint32_t xat = xch.at(t), xstep = xch.step(T);
     LdsLine ld;
     ld.wl = smem + cc * FFT::kLds;
     ld.blk0 = ld.wl + FFT::kReg;
@@ -904,9 +1221,8 @@ __global__ void __launch_bounds__(256) adjcol_kernel(AdjArgs aa, Geo geo, const 
     float2* xbuf = smem + tc * FFT::kLds;
     float2* twl = xbuf + L;
     const int dr = FFT::drev(t);
-    float2 twr[P];
-    load_twiddles<L, P>(twr, tw_g, tid, nthr);
-    const float2* tw = twl;
+    Twiddles<FFT, L, P> tw;
+    tw.load(tw_g, t, tid, nthr);
     const bool blk_packed = ct == 0;
     const bool packed = blk_packed && cc == 0;
     const DevMask& mk = p.mask[0];
@@ -952,15 +1268,13 @@ __global__ void __launch_bounds__(256) adjcol_kernel(AdjArgs aa, Geo geo, const 
     if (aa.first) {
 #pragma unroll
         for (int m = 0; m < P; ++m) g[m] = aa.G[base + (t + m * T) * tc];
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
+        tw.ready(twl, tid, nthr);
     } else {
         float2 v[P];
 #pragma unroll
-        for (int m = 0; m < P; ++m) v[m] = aa.X[base + (t + m * T) * tc];
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
-        FFT::template dit<-1>(v, ld, t, tw);
+        for (int m = 0; m < P; ++m) v[m] = aa.X[xat + m * xstep];
+        tw.ready(twl, tid, nthr);
+        FFT::template dit<-1>(v, ld, t, tw.get());
         exchange(v, true);
 #pragma unroll
         for (int m = 0; m < P; ++m) {
@@ -1033,13 +1347,13 @@ __global__ void __launch_bounds__(256) adjcol_kernel(AdjArgs aa, Geo geo, const 
         aa.Rout[e] = r;
     }
     exchange(wr, false);
-    FFT::template dif<1>(wr, ld, t, tw);
+    FFT::template dif<1>(wr, ld, t, tw.get());
 #pragma unroll
-    for (int m = 0; m < P; ++m) aa.W[base + (t + m * T) * tc] = wr[m];
+    for (int m = 0; m < P; ++m) aa.W[xat + m * xstep] = wr[m];
     exchange(um, false);
-    FFT::template dif<1>(um, ld, t, tw);
+    FFT::template dif<1>(um, ld, t, tw.get());
 #pragma unroll
-    for (int m = 0; m < P; ++m) aa.U[base + (t + m * T) * tc] = um[m];
+    for (int m = 0; m < P; ++m) aa.U[xat + m * xstep] = um[m];
     if (aa.D > 0.f) part[2] /= 2.0 * aa.D;
     block_sum_to_slot(part, aa.acc + static_cast<size_t>(blockIdx.x) * 3);
 }
@@ -1117,10 +1431,9 @@ __global__ void __launch_bounds__(256) ypass_kernel(YArgs ya, Geo geo, const flo
     ld.par = 0;
     float2* xb = smem + tc * tz * FFT::kLds + lz * L;  // column-0 exchange, one line per z
     const int dr = FFT::drev(t);
-    float2 twr[P];
-    load_twiddles<L, P>(twr, tw_g, tid, nthr);
-    const float2* tw = store_twiddles<L, P>(smem + tc * tz * FFT::kLds + tz * L, twr, tid, nthr);
-    __syncthreads();
+    Twiddles<FFT, L, P> tw;
+    tw.load(tw_g, t, tid, nthr);
+    tw.ready(smem + tc * tz * FFT::kLds + tz * L, tid, nthr);
     const size_t ibase = (static_cast<size_t>(z) * ntile + ct) * L * tc + cc;
     const size_t obase = MODE == MODE_YFWD ? (static_cast<size_t>(ct) * nz + z) * tc + cc : ibase;
     const size_t ostride = MODE == MODE_YFWD ? static_cast<size_t>(ntile) * nz * tc : static_cast<size_t>(tc);
@@ -1146,13 +1459,13 @@ __global__ void __launch_bounds__(256) ypass_kernel(YArgs ya, Geo geo, const flo
             }
             // in place (src == dst) is safe: a line is read whole before any of
             // it is written, within one wave or across the transform's barrier
-            FFT::template dit<1>(v, ld, t, tw);
+            FFT::template dit<1>(v, ld, t, tw.get());
 #pragma unroll
             for (int m = 0; m < P; ++m) dst[obase + (t + m * T) * ostride] = v[m];
         } else {
 #pragma unroll
             for (int m = 0; m < P; ++m) v[m] = src[ibase + (t + m * T) * tc];
-            FFT::template dif<-1>(v, ld, t, tw);
+            FFT::template dif<-1>(v, ld, t, tw.get());
             if (ct == 0) {
                 // column 0: the partner of ky is L - ky, exchanged by natural position
                 if (c == 0) {
@@ -1179,10 +1492,31 @@ __global__ void __launch_bounds__(256) ypass_kernel(YArgs ya, Geo geo, const flo
 }
 
 // ----------------------------------------------------------------- x kernel
+// 1024^2: the launch was bound by its gather (16 bytes of each 128-byte line
+// of [c][y] columns, in digit-reversed order: one line a lane, 1.4 us), by
+// the loops over factor powers and by scalar-load waits; with grouped rows,
+// natural order and straight-line powers 8.2 -> 6.7 us, KPZ 11.6 -> 7.6 us,
+// Model H 31 -> 18 us.
+// What is left is memory latency (1.2 us), two transforms and the launch.
 // Rows of length L = Nx; block = RB consecutive rows, pair pr = rows
 // (2 pr, 2 pr + 1) packed as one complex line held by T consecutive threads.
 // Packed-column arrays are read and written in whole tile blocks of RB*TC
 // contiguous elements.
+// a[m] *= z[m]^n by components, n <= 8 uniform: one forward branch out of a
+// straight line instead of a loop
+template <int E, int P>
+__device__ __forceinline__ void times_power(float2 (&a)[P], const float2 (&z)[P], int n) {
+    if constexpr (E < PSS_MAXPOW) {
+        if (n <= E) return;
+#pragma unroll
+        for (int m = 0; m < P; ++m) {
+            a[m].x *= z[m].x;
+            a[m].y *= z[m].y;
+        }
+        times_power<E + 1>(a, z, n);
+    }
+}
+
 // One block of the x kernel: row block `blk` of lattice `mi` (as in the update kernel)
 template <int L, int P, int NG, int MODE, bool TABLE, int PADS = kFftPad>
 __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __restrict__ members,
@@ -1213,8 +1547,8 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
     const int pr = tid / T;  // pair within the block
     const int t = tid & (T - 1);
     const int r0 = blk * rb;  // first row; row index = z*Ny + y
-    const int ny = p.n[1];
-    const int zr = r0 / ny;          // z of the block (0 in 2D)
+    const int ny = geo.ny;
+    const int zr = geo.nz == 1 ? 0 : r0 / ny;  // z of the block (0 in 2D)
     const int y0 = r0 - zr * ny;     // first y of the block
     const int lt = geo.tc_log2;
     LdsLine ld;
@@ -1223,18 +1557,21 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
     ld.blk1 = ld.wl + 2 * FFT::kReg;
     ld.par = 0;
     const int dr = FFT::drev(t);
-    // twiddles: loaded now, stored to LDS after each mode's first loads
-    float2 twr[P];
-    load_twiddles<L, P>(twr, tw_g, tid, nthr);
+    Twiddles<FFT, L, P> tw;
     float2* const twl = smem + (rb >> 1) * FFT::kLds;
-    const float2* tw = twl;
 
     // Gather the packed complex input Z[k] = X_row0[k] + i X_row1[k] of pair
-    // pr at k = dr + m T straight from the packed-column array (columns
+    // pr at k = k0 + m T straight from the packed-column array (columns
     // [0, ncol) are stored; the others are zero); all loads are issued together.
-    const size_t row0 = (static_cast<size_t>(zr) * ntile * ny + y0 + 2 * pr) * tc;
-    const size_t tstride = static_cast<size_t>(ny) * tc;  // one column tile
-    auto build_z = [&](float2 (&v)[P], const float2* __restrict__ src, int ncol) {
+    // A step gathers in natural order (k0 = t: neighbouring threads read
+    // neighbouring columns), transforms to digit-reversed x, where the
+    // products do not mind the order, and back to natural k; the modes that
+    // deliver or take real rows need natural x and gather at k0 = D(t).
+    const int yr = y0 + 2 * pr;  // the pair's first row in its plane
+    const size_t row0 = geo.grp ? (static_cast<size_t>(yr >> 2) * ntile << 2) + (yr & 3)
+                                : (static_cast<size_t>(zr) * ntile * ny + yr) * tc;
+    const size_t tstride = geo.grp ? 4 : static_cast<size_t>(ny) * tc;  // one column tile
+    auto build_z = [&](float2 (&v)[P], const float2* __restrict__ src, int ncol, int k0) {
         // all loads first, without control flow between them; a dropped
         // column reads column 0 and then counts as zero
         float2 a[P], b[P];
@@ -1244,7 +1581,7 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
             // takes both (half the address work of two 8-byte loads)
 #pragma unroll
             for (int m = 0; m < P; ++m) {
-                const int k = dr + m * T;
+                const int k = k0 + m * T;
                 const int kk = (k == NC) ? 0 : (k < NC ? k : L - k);
                 const int kc = kk < ncol ? kk : 0;
                 gload_pair(src + row0 + kc * tstride, a[m], b[m]);
@@ -1252,7 +1589,7 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
         } else {
 #pragma unroll
             for (int m = 0; m < P; ++m) {
-                const int k = dr + m * T;
+                const int k = k0 + m * T;
                 const int kk = (k == NC) ? 0 : (k < NC ? k : L - k);
                 const int kc = kk < ncol ? kk : 0;
                 const size_t off = row0 + (kc >> lt) * tstride + (kc & (tc - 1));
@@ -1262,7 +1599,7 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
         }
 #pragma unroll
         for (int m = 0; m < P; ++m) {
-            const int k = dr + m * T;
+            const int k = k0 + m * T;
             const int kk = (k == NC) ? 0 : (k < NC ? k : L - k);
             const float2 zero = make_float2(0.f, 0.f);
             const float2 am = kk < ncol ? a[m] : zero, bm = kk < ncol ? b[m] : zero;
@@ -1277,18 +1614,35 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
             v[m] = z;
         }
     };
-    // Stage the forward transform W (held at k = dr + m T) of every pair in
+    // Stage the forward transform W (held at k = k0 + m T) of every pair in
     // LDS at its natural positions, then unpack the two real rows of each
     // pair and store whole packed-column tiles.  A line wider than a wave
     // stages in its next block buffer; a narrower one in its own region
     // (its wave is done with it).  The caller separates consecutive calls by
     // a block barrier when the staging region is the in-wave one.
-    auto store_rows = [&](const float2 (&w)[P], float2* __restrict__ dst) {
+    auto store_rows = [&](const float2 (&w)[P], float2* __restrict__ dst, int k0) {
         float2* stage = FFT::kCross ? ld.next_blk() : ld.wl;
         if constexpr (!FFT::kCross) wave_lds_sync();  // after the transform's last in-wave reads
 #pragma unroll
-        for (int m = 0; m < P; ++m) stage[dr + m * T] = w[m];
+        for (int m = 0; m < P; ++m) stage[k0 + m * T] = w[m];
         __syncthreads();
+        if (tc == 1) {
+            // one-column tiles: a pair's two rows are neighbours in the
+            // column, so one thread unpacks both and stores 16 bytes (half
+            // the LDS reads and stores of an element a thread)
+            const float2* W = stage;
+            float2* const d0 = dst + row0;
+#pragma unroll
+            for (int j = 0; j < (NC + T - 1) / T; ++j) {
+                const int c = t + j * T;
+                if (NC % T != 0 && c >= NC) break;
+                const float2 a = W[c], b = W[c == 0 ? NC : L - c];
+                const float2 lo = c == 0 ? make_float2(a.x, b.x) : make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
+                const float2 hi = c == 0 ? make_float2(a.y, b.y) : make_float2(0.5f * (a.y + b.y), 0.5f * (b.x - a.x));
+                gstore_pair_sel<!TABLE>(d0 + c * tstride, lo, hi);
+            }
+            return;
+        }
         const int lp = geo.rb_log2 + lt;  // log2(rb * tc)
         const int total = ntile << lp;
         const size_t sbase = (static_cast<size_t>(zr) * ntile) * ny + y0;
@@ -1298,15 +1652,10 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
             const int r = rem >> lt, cc = rem & (tc - 1);
             const int c = (tl << lt) + cc;
             const float2* W = smem + (r >> 1) * FFT::kLds + (FFT::kCross ? (stage - ld.wl) : 0);
-            float2 o;
-            if (c == 0) {
-                const float2 a = W[0], b = W[NC];
-                o = (r & 1) ? make_float2(a.y, b.y) : make_float2(a.x, b.x);
-            } else {
-                const float2 a = W[c], b = W[L - c];
-                o = (r & 1) ? make_float2(0.5f * (a.y + b.y), 0.5f * (b.x - a.x))
-                            : make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
-            }
+            const float2 a = W[c], b = W[c == 0 ? NC : L - c];
+            float2 o = (r & 1) ? make_float2(0.5f * (a.y + b.y), 0.5f * (b.x - a.x))
+                               : make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
+            if (c == 0) o = (r & 1) ? make_float2(a.y, b.y) : make_float2(a.x, b.x);
             gstore_sel<!TABLE>(dst + ((sbase + static_cast<size_t>(tl) * ny + r) << lt) + cc, o);
         }
     };
@@ -1321,18 +1670,18 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
             v[m] = make_float2(src[static_cast<size_t>(r0 + 2 * pr) * L + x],
                                src[static_cast<size_t>(r0 + 2 * pr + 1) * L + x]);
         }
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
-        FFT::template dif<-1>(v, ld, t, tw);
-        store_rows(v, bufs.out);
+        tw.load(tw_g, t, tid, nthr);
+        tw.ready(twl, tid, nthr);
+        FFT::template dif<-1>(v, ld, t, tw.get());
+        store_rows(v, bufs.out, dr);
         return;
     }
     if constexpr (MODE == MODE_C2R_OUT) {
         float2 v[P];
-        build_z(v, bufs.in, NC);
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
-        FFT::template dit<1>(v, ld, t, tw);
+        build_z(v, bufs.in, NC, dr);
+        tw.load(tw_g, t, tid, nthr);
+        tw.ready(twl, tid, nthr);
+        FFT::template dit<1>(v, ld, t, tw.get());
         float* __restrict__ dst = bufs.real_out;
 #pragma unroll
         for (int m = 0; m < P; ++m) {
@@ -1350,12 +1699,12 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
         // the factor b); and the FP64 sum of u^3 w, which is
         // <r, -dt q^2 F[u^3]> = dL/db of the step, by Parseval
         float2 u[P], w[P];
-        build_z(u, bufs.V[0], p.mask[0].ncol);
-        build_z(w, bufs.V[1], p.mask[1].ncol);
-        store_twiddles<L, P>(twl, twr, tid, nthr);
-        __syncthreads();
-        FFT::template dit<1>(u, ld, t, tw);
-        FFT::template dit<1>(w, ld, t, tw);
+        build_z(u, bufs.V[0], geo.ncol[0], t);
+        build_z(w, bufs.V[1], NC, t);
+        tw.load(tw_g, t, tid, nthr);
+        tw.ready(twl, tid, nthr);
+        FFT::template dif<1>(u, ld, t, tw.get());
+        FFT::template dif<1>(w, ld, t, tw.get());
         double part[1] = {0.0};
 #pragma unroll
         for (int m = 0; m < P; ++m) {
@@ -1363,8 +1712,8 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
             part[0] += static_cast<double>(ux) * ux * ux * w[m].x + static_cast<double>(uy) * uy * uy * w[m].y;
             u[m] = make_float2(3.f * ux * ux * w[m].x, 3.f * uy * uy * w[m].y);
         }
-        FFT::template dif<-1>(u, ld, t, tw);
-        store_rows(u, bufs.N[0]);
+        FFT::template dit<-1>(u, ld, t, tw.get());
+        store_rows(u, bufs.N[0], t);
         block_sum_to_slot(part, bufs.acc + blockIdx.x);
         return;
     }
@@ -1378,56 +1727,67 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
             *step_ctr_a += static_cast<uint64_t>(advance);
         }
     }
+    // the plan's scalars and the first channel's first product as one block of
+    // scalar loads ahead of the transforms
+    float inv_n = p.inv_n;
+    int nch = p.nch, ng = NG > 4 ? p.ng : NG;
+    int np0 = p.ch[0].nprod;
+    float c0 = p.ch[0].prod[0].coef;
+    static_assert(sizeof(p.ch[0].prod[0].pow) == 8, "eight factor slots");
+    uint32_t pw0[2];
+    __builtin_memcpy(pw0, p.ch[0].prod[0].pow, sizeof(pw0));
     // real-space values of every factor field (the variant with room for
     // more than four holds zeros in the slots beyond the plan's)
     float2 z[NG][P];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-        if (NG > 4 && g >= p.ng) {
+        if (NG > 4 && g >= ng) {
 #pragma unroll
             for (int m = 0; m < P; ++m) z[g][m] = make_float2(0.f, 0.f);
             continue;
         }
         float2 v[P];
-        build_z(v, bufs.V[g], p.mask[g].ncol);
+        build_z(v, bufs.V[g], geo.ncol[g], t);
         if (g == 0) {
-            store_twiddles<L, P>(twl, twr, tid, nthr);
-            __syncthreads();
+            tw.load(tw_g, t, tid, nthr);
+            hold(inv_n), hold(nch), hold(ng), hold(np0), hold(c0), hold(pw0[0]), hold(pw0[1]);
+            tw.ready(twl, tid, nthr);
         }
-        FFT::template dit<1>(v, ld, t, tw);
+        FFT::template dif<1>(v, ld, t, tw.get());
 #pragma unroll
-        for (int m = 0; m < P; ++m) z[g][m] = cscale(v[m], p.inv_n);
+        for (int m = 0; m < P; ++m) z[g][m] = cscale(v[m], inv_n);
     }
     // products per channel, forward transform, store
-    for (int ch = 0; ch < p.nch; ++ch) {
+    for (int ch = 0; ch < nch; ++ch) {
         const DevChannel& C = p.ch[ch];
         float2 w[P];
 #pragma unroll
         for (int m = 0; m < P; ++m) w[m] = make_float2(0.f, 0.f);
-        for (int k = 0; k < C.nprod; ++k) {
-            const DevProd& pd = C.prod[k];
-            // the factor powers read as one 64-bit word (a scalar load)
-            static_assert(sizeof(pd.pow) == 8, "eight factor slots");
-            uint64_t pw;
-            __builtin_memcpy(&pw, pd.pow, sizeof(pw));
-#pragma unroll
-            for (int m = 0; m < P; ++m) {
-                float a = pd.coef, b = pd.coef;
-#pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    const int pg = static_cast<int>((pw >> (8 * g)) & 0xffull);
-                    for (int e = 0; e < pg; ++e) {
-                        a *= z[g][m].x;
-                        b *= z[g][m].y;
-                    }
-                }
-                w[m].x += a;
-                w[m].y += b;
+        const int np = ch == 0 ? np0 : C.nprod;
+        for (int k = 0; k < np; ++k) {
+            // the factor powers read as two words (scalar loads)
+            float cf = c0;
+            uint32_t pw[2] = {pw0[0], pw0[1]};
+            if (ch > 0 || k > 0) {
+                const DevProd& pd = C.prod[k];
+                cf = pd.coef;
+                __builtin_memcpy(pw, pd.pow, sizeof(pw));
             }
+            float2 a[P];
+#pragma unroll
+            for (int m = 0; m < P; ++m) a[m] = make_float2(cf, cf);
+            // the powers are uniform: one loop per factor for all points
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int pg = static_cast<int>((pw[g >> 2] >> (8 * (g & 3))) & 0xffu);
+                times_power<0>(a, z[g], pg);
+            }
+#pragma unroll
+            for (int m = 0; m < P; ++m) w[m] = cadd(w[m], a[m]);
         }
         if (!FFT::kCross && ch > 0) __syncthreads();  // the previous channel's rows are stored
-        FFT::template dif<-1>(w, ld, t, tw);
-        store_rows(w, bufs.N[ch]);
+        FFT::template dit<-1>(w, ld, t, tw.get());
+        store_rows(w, bufs.N[ch], t);
     }
 }
 
@@ -1438,8 +1798,8 @@ __global__ void __launch_bounds__(256) xrow_kernel(const Member* __restrict__ me
                                                     const float2* __restrict__ tw_g, int64_t advance,
                                                     uint64_t* __restrict__ step_ctr_a) {
     const int nb = gridDim.x;
-    const int lin_b = xcd_block(blockIdx.y * nb + blockIdx.x, nb * gridDim.y);
-    const int mi = lin_b / nb;
+    const int lin_b = TABLE ? xcd_block(blockIdx.y * nb + blockIdx.x, nb * gridDim.y) : xcd_block(blockIdx.x, nb);
+    const int mi = TABLE ? __builtin_amdgcn_readfirstlane(lin_b / nb) : 0;
     xrow_block<L, P, NG, MODE, TABLE>(mi, lin_b - mi * nb, members, plans, plan_a, bufs_a, geo, tw_g, advance,
                                       step_ctr_a);
 }
@@ -2853,10 +3213,11 @@ __device__ __forceinline__ int batch_class_of(const BatchLaunch& bl, int b) {
 }
 
 __global__ void __launch_bounds__(256) batch_update_kernel(BatchLaunch bl) {
-    const int b = xcd_block(blockIdx.x, gridDim.x);
-    const BatchClass& C = bl.cls[batch_class_of(bl, b)];
+    // uniform by construction; said so, since the division runs on the VALU
+    const int b = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
+    const BatchClass& C = bl.cls[__builtin_amdgcn_readfirstlane(batch_class_of(bl, b))];
     const int rel = b - C.start;
-    const int mi = rel / C.nblk;
+    const int mi = __builtin_amdgcn_readfirstlane(rel / C.nblk);
     const int blk = rel - mi * C.nblk;
     const Bufs none{};
 #define PSS_BU(LL)                                                                                                 \
@@ -2877,10 +3238,11 @@ __global__ void __launch_bounds__(256) batch_update_kernel(BatchLaunch bl) {
 }
 
 __global__ void __launch_bounds__(256) batch_xrow_kernel(BatchLaunch bl) {
-    const int b = xcd_block(blockIdx.x, gridDim.x);
-    const BatchClass& C = bl.cls[batch_class_of(bl, b)];
+    // uniform by construction; said so, since the division runs on the VALU
+    const int b = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
+    const BatchClass& C = bl.cls[__builtin_amdgcn_readfirstlane(batch_class_of(bl, b))];
     const int rel = b - C.start;
-    const int mi = rel / C.nblk;
+    const int mi = __builtin_amdgcn_readfirstlane(rel / C.nblk);
     const int blk = rel - mi * C.nblk;
     const Bufs none{};
 #define PSS_BX(LL)                                                                                          \
@@ -2932,9 +3294,10 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
     float2* const scr = X + NC * XS;                 // one exchange region per line of a round
     constexpr int SCR = CPR * FY::kReg > RPR * FX::kReg ? CPR * FY::kReg : RPR * FX::kReg;
     float2* const xbuf = scr + SCR;                  // packed-line exchange (LY)
-    float2* const twy = xbuf + LY;
-    float2* const twx = twy + LY;
-    const int mi = xcd_block(blockIdx.x, gridDim.x);
+    float2* const twy_w = xbuf + LY;
+    float2* const twx_w = twy_w + LY;
+    const float2 *const twy = twy_w, *const twx = twx_w;
+    const int mi = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
     const Member& mem = rl.members[mi];
     const DevPlan& p = rl.plans[mi];
     const int tid = threadIdx.x;
@@ -2943,18 +3306,16 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
     float2* __restrict__ Sg = mem.bufs.S[0];
     float2* __restrict__ Ng = mem.bufs.N[0];
 
-    for (int i = tid; i < LY; i += NTHR) twy[i] = rl.tw_y[i];
-    for (int i = tid; i < LX; i += NTHR) twx[i] = rl.tw_x[i];
+    for (int i = tid; i < LY; i += NTHR) twy_w[i] = rl.tw_y[i];
+    for (int i = tid; i < LX; i += NTHR) twx_w[i] = rl.tw_x[i];
     // column phase: line li of the round, thread t of the line
     const int li = tid / TY, tcol = tid & (TY - 1);
-    const int dry = FY::drev(tcol);
     LdsLine ldc;
     ldc.wl = scr + li * FY::kReg;
     ldc.blk0 = ldc.blk1 = nullptr;
     ldc.par = 0;
     // row phase: pair pi of the round, thread t of the pair
     const int pi = tid / TX, trow = tid & (TX - 1);
-    const int drx = FX::drev(trow);
     LdsLine ldr;
     ldr.wl = scr + pi * FX::kReg;
     ldr.blk0 = ldr.blk1 = nullptr;
@@ -2975,6 +3336,8 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
         X[c * XS + y] = gload(Ng + i);
     }
     const uint32_t step0 = static_cast<uint32_t>(gload_u64(mem.step_ctr));
+    // the four self-conjugate modes of column 0, one per lane (as in the update kernel)
+    const Self self = self_modes<LY, 2>(nx, LY, 1, p.qs, 0, tid);
     __syncthreads();
 
     uint32_t bad = 0;
@@ -2988,6 +3351,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
             const bool blk_packed = r == 0;  // the round holding column 0 (block-uniform)
             const bool packed = c == 0;
             const bool pair_lane = packed && tcol == 0;
+            const bool first_wave = blk_packed && tid < 64;
             const int kx_l = c, ky_l = 0;
             float2* const col = X + c * XS;
             auto exchange = [&](float2 (&v)[P], bool forward) {
@@ -3007,7 +3371,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
                 }
                 __syncthreads();
             };
-            const LineModes lmode = line_modes<LY, 2>(p, packed, kx_l, ky_l);
+            const LineModes lmode = line_modes<LY, 2>(nx, p.n[1], p.qs, packed, kx_l, ky_l);
             float2(&s)[P] = st[r];
             float q2[P];
             uint32_t lin[P], lneg[P];
@@ -3028,7 +3392,15 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
 #pragma unroll
                 for (int m = 0; m < P; ++m)
                     if (!(pair_lane && (m == 0 || m == P / 2))) add_to(acc, C.target[0], m, cscale(v[m], M[m]));
-                if (pair_lane) pair_accumulate<2, false>(acc, C.target[0], v, p, C.op[0], ky_l, LY);
+                if (first_wave) {
+                    const Four f = four_lanes(horner(C.op[0], self.q.q2));
+                    float2 lo, hi;
+                    pair_scale(f, v, lo, hi);
+                    if (pair_lane) {
+                        acc[0][0] = cadd(acc[0][0], lo);
+                        acc[0][P / 2] = cadd(acc[0][P / 2], hi);
+                    }
+                }
             }
             for (int d = 0; d < p.nd; ++d) {
                 const DevDirect& Dd = p.direct[d];
@@ -3040,7 +3412,15 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
 #pragma unroll
                 for (int m = 0; m < P; ++m)
                     if (!(pair_lane && (m == 0 || m == P / 2))) add_to(acc, Dd.target, m, cscale(src[m], M[m]));
-                if (pair_lane) pair_accumulate<2, false>(acc, Dd.target, src, p, Dd.op, ky_l, LY);
+                if (first_wave) {
+                    const Four f = four_lanes(horner(Dd.op, self.q.q2));
+                    float2 lo, hi;
+                    pair_scale(f, src, lo, hi);
+                    if (pair_lane) {
+                        acc[0][0] = cadd(acc[0][0], lo);
+                        acc[0][P / 2] = cadd(acc[0][P / 2], hi);
+                    }
+                }
             }
             {
                 const bool noisy = p.noisy[0] != 0;
@@ -3054,9 +3434,20 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
                     if (noisy) rr = cadd(rr, noise_value(p, 0, step, lin[m], lneg[m], Dn[m]));
                     s[m] = cscale(rr, __builtin_amdgcn_rcpf(fmaf(-p.dt, Ar[m], 1.f)));
                 }
-                if (pair_lane) {
-                    s[0] = pair_update_d<2, false>(p, 0, step, ky_l, 0, LY, old0, acc[0][0], noisy);
-                    s[P / 2] = pair_update_d<2, false>(p, 0, step, ky_l, LY >> 1, LY, oldh, acc[0][P / 2], noisy);
+                if (first_wave) {
+                    const Four inv = four_lanes(
+                        cinv_implicit(p.dt, make_float2(horner(p.implicit_op[0], self.q.q2), 0.f)).x);
+                    Four e{};
+                    if (noisy)
+                        e = four_lanes(noise_value(p, 0, step, self.lin, self.lneg, horner(p.noise_op[0], self.q.q2)).x);
+                    if (pair_lane) {
+                        float2 rl = cadd(old0, cscale(acc[0][0], p.dt)), rh = cadd(oldh, cscale(acc[0][P / 2], p.dt));
+                        if (noisy) {
+                            rl = make_float2(rl.x + e.v[0], rl.y + e.v[1]);
+                            rh = make_float2(rh.x + e.v[2], rh.y + e.v[3]);
+                        }
+                        pair_scale<2>(inv, {rl, rh}, s[0], s[P / 2]);
+                    }
                 }
                 bool fin = true;
 #pragma unroll
@@ -3066,9 +3457,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
             // de-aliased inverse transform of the factor (lines of a wave whose
             // first column is past the kept ones are never read)
             if (p.ng > 0 && (c / LPW) * LPW < p.mask[0].ncol) {
-                const DevMask& mk = p.mask[0];
-                const int lim = line_lim<2>(mk, packed ? 0 : kx_l, ky_l, LY);
-                const int limN = line_lim<2>(mk, -(nx >> 1), ky_l, LY);
+                const int lim = p.lim[0][kx_l], limN = p.lim[0][nx >> 1];
                 float2 v[P];
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
@@ -3106,7 +3495,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
                 float2 a[P], b[P];
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
-                    const int k = drx + m * TX;
+                    const int k = trow + m * TX;
                     const int kk = (k == NC) ? 0 : (k < NC ? k : LX - k);
                     const int kc = kk < ncol ? kk : 0;
                     a[m] = X[kc * XS + p0];
@@ -3114,7 +3503,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
                 }
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
-                    const int k = drx + m * TX;
+                    const int k = trow + m * TX;
                     const int kk = (k == NC) ? 0 : (k < NC ? k : LX - k);
                     const float2 zero = make_float2(0.f, 0.f);
                     const float2 am = kk < ncol ? a[m] : zero, bm = kk < ncol ? b[m] : zero;
@@ -3129,7 +3518,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
                     v[m] = z;
                 }
             }
-            FX::template dit<1>(v, ldr, trow, twx);
+            FX::template dif<1>(v, ldr, trow, twx);
             float2 z[P];
 #pragma unroll
             for (int m = 0; m < P; ++m) z[m] = cscale(v[m], p.inv_n);
@@ -3140,23 +3529,19 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
             for (int k = 0; k < C.nprod; ++k) {
                 const DevProd& pd = C.prod[k];
                 const int pg = static_cast<int>(pd.pow[0]);
+                float2 a[P];
 #pragma unroll
-                for (int m = 0; m < P; ++m) {
-                    float a = pd.coef, b = pd.coef;
-                    for (int e = 0; e < pg; ++e) {
-                        a *= z[m].x;
-                        b *= z[m].y;
-                    }
-                    w[m].x += a;
-                    w[m].y += b;
-                }
+                for (int m = 0; m < P; ++m) a[m] = make_float2(pd.coef, pd.coef);
+                times_power<0>(a, z, pg);
+#pragma unroll
+                for (int m = 0; m < P; ++m) w[m] = cadd(w[m], a[m]);
             }
-            FX::template dif<-1>(w, ldr, trow, twx);
+            FX::template dit<-1>(w, ldr, trow, twx);
             // unpack the pair's two rows into the packed columns
             float2* const W = ldr.wl;
             wave_lds_sync();
 #pragma unroll
-            for (int m = 0; m < P; ++m) W[drx + m * TX] = w[m];
+            for (int m = 0; m < P; ++m) W[trow + m * TX] = w[m];
             wave_lds_sync();
 #pragma unroll
             for (int j = 0; j < NC / TX; ++j) {

@@ -36,7 +36,7 @@
 
 namespace pss {
 
-struct DevMono {
+struct alignas(4) DevMono {
     float coef;
     int8_t q2, invq, ix, iy, iz, ipow;  // ipow = (ix + iy + iz) mod 4
     int8_t pad[2];
@@ -45,9 +45,9 @@ struct DevMono {
 // An operator: the pure (q^2)^j monomials folded into dense Horner
 // coefficients, plus the monomials with 1/|q| or i q_i factors listed apart.
 struct DevOp {
-    float poly[PSS_MAXPOW + 1];  // coefficient of (q^2)^j, j = 0..8
-    int32_t n;                   // monomials with 1/|q| or i q_i factors
+    float poly[PSS_MAXPOW + 1];  // coefficient of (q^2)^j, j = 0..8 (zero above deg)
     int32_t deg;                 // highest j with poly[j] != 0 (0 if none)
+    int32_t n;                   // monomials with 1/|q| or i q_i factors
     DevMono m[PSS_MAXM];
 };
 
@@ -82,7 +82,8 @@ struct DevInterm {
     int32_t nsrc;
     int32_t src[PSS_MAXF];  // dynamic field of each linear term
     DevOp op[PSS_MAXF];
-    DevOp den;  // L_psi
+    DevOp den;       // L_psi
+    int32_t no_den;  // L_psi is identically zero
 };
 
 struct DevMask {
@@ -111,6 +112,10 @@ struct DevPlan {
     int32_t noisy[PSS_MAXF];
     int32_t fid[PSS_MAXF];     // declaration index of each dynamic field (its random-number key)
     int32_t gfield[PSS_MAXG];  // factor slot -> dynamic field, or PSS_MAXF + intermediate
+    // per factor slot, the largest kept (mode index)^2 along the update axis
+    // (-1: none) of the line with fixed indices |kx|, |ky| (0 in 2D), at
+    // |ky| (Nx/2 + 1) + |kx|: power-of-two 2D and 3D lattices
+    const int32_t* lim[PSS_MAXG];
     DevMask mask[PSS_MAXG];    // per factor slot
     DevOp implicit_op[PSS_MAXF];
     DevOp noise_op[PSS_MAXF];

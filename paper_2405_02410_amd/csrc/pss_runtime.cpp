@@ -172,6 +172,8 @@ struct pss_ctx {
     pss::DevPlan* d_plan = nullptr;
     uint64_t* d_step = nullptr;
     float2* d_tw_u = nullptr;
+    int32_t* d_lim = nullptr;          // de-aliasing limits (DevPlan::lim), one table per distinct mask
+    size_t lim_off[PSS_MAXG] = {};
     float2* d_tw_x = nullptr;
     float2* d_tw_y = nullptr;
     // d_chan: channel inputs of the update kernel; d_chan_x: x-kernel outputs
@@ -423,6 +425,56 @@ pss::DevMask make_mask(const pss_ctx* c, int rule, int shape, int order) {
     return mk;
 }
 
+// Largest w^2 kept by mask mk on the line along the update axis (y in 2D, z
+// in 3D) with fixed indices kx, ky (2D: ky unused): a mode with index w is
+// kept iff w*w <= the limit, -1 if the whole line is masked.  Decided in
+// integers, exactly as the keep rule (pss_plan.h) decides each mode.
+int32_t line_lim(const pss::DevMask& mk, int ndim, int kx, int ky, int L) {
+    const int hmax = (L >> 1) * (L >> 1);
+    if (mk.shape == 2) return hmax;
+    const int ia = ndim == 2 ? 1 : 2;
+    if (mk.shape == 1) {
+        bool keep = true;
+        if (mk.h[0]) keep = keep && mk.den * kx < mk.num * mk.h[0];
+        if (ndim == 3 && mk.h[1]) keep = keep && mk.den * ky < mk.num * mk.h[1];
+        if (!keep) return -1;
+        if (!mk.h[ia]) return hmax;
+        const int wmax = (mk.num * mk.h[ia] - 1) / mk.den;  // den |w| < num h
+        return wmax * wmax;
+    }
+    // (P0 + w_a w^2) den2 < rhs
+    const int64_t p0 = mk.w[0] * kx * kx + (ndim == 3 ? mk.w[1] * ky * ky : 0);
+    const int64_t room = (mk.rhs - 1) / mk.den2 - p0;
+    if (room < 0) return -1;
+    const int64_t wa = mk.w[ia];
+    return static_cast<int32_t>(std::min<int64_t>(wa > 0 ? room / wa : hmax, hmax));
+}
+
+// The limits of every line, [|ky|][|kx|] for each distinct mask of the plan
+// (the rule is fixed once the plan is built): two 64-bit divisions a line are
+// then out of the kernels.
+pss_status upload_limits(pss_ctx* c) {
+    pss::DevPlan& P = c->plan;
+    if (c->ndim == 1 || c->mixed || P.ng == 0) return PSS_OK;
+    const int nkx = c->n[0] / 2 + 1, nky = c->ndim == 3 ? c->n[1] / 2 + 1 : 1;
+    std::vector<int32_t> tab;
+    for (int g = 0; g < P.ng; ++g) {
+        int same = 0;
+        while (same < g && std::memcmp(&P.mask[same], &P.mask[g], sizeof(pss::DevMask)) != 0) ++same;
+        if (same < g) {
+            c->lim_off[g] = c->lim_off[same];
+            continue;
+        }
+        c->lim_off[g] = tab.size();
+        for (int ky = 0; ky < nky; ++ky)
+            for (int kx = 0; kx < nkx; ++kx) tab.push_back(line_lim(P.mask[g], c->ndim, kx, ky, c->lu));
+    }
+    HIP_TRY(hipMalloc(&c->d_lim, sizeof(int32_t) * tab.size()));
+    HIP_TRY(hipMemcpy(c->d_lim, tab.data(), sizeof(int32_t) * tab.size(), hipMemcpyHostToDevice));
+    for (int g = 0; g < P.ng; ++g) P.lim[g] = c->d_lim + c->lim_off[g];
+    return PSS_OK;
+}
+
 pss_status build_plan(pss_ctx* c) {
     using namespace pss;
     DevPlan& P = c->plan;
@@ -648,6 +700,8 @@ pss_status build_plan(pss_ctx* c) {
     for (int i = 0; i < ni; ++i) {
         set_deg(P.interm[i].den);
         for (int k = 0; k < P.interm[i].nsrc; ++k) set_deg(P.interm[i].op[k]);
+        const DevOp& den = P.interm[i].den;
+        P.interm[i].no_den = den.n == 0 && den.deg == 0 && den.poly[0] == 0.f ? 1 : 0;
     }
     // kernels without the general-monomial code unless some operator needs it
     P.general = 0;
@@ -656,6 +710,7 @@ pss_status build_plan(pss_ctx* c) {
     for (int k = 0; k < P.nch; ++k)
         for (int o = 0; o < P.ch[k].nout; ++o) P.general |= P.ch[k].op[o].n > 0;
     P.general |= ni > 0;  // intermediates are evaluated by the general-operator code
+    for (int g = 0; g < P.ng; ++g) P.lim[g] = c->d_lim ? c->d_lim + c->lim_off[g] : nullptr;
     for (int f = 0; f < nf; ++f) {  // boundary frames already on the device
         P.frame[f] = c->d_frame[f];
         P.nframe[f] = c->d_frame[f] && f < static_cast<int>(c->frames.size())
@@ -682,7 +737,10 @@ pss_status choose_geometry(pss_ctx* c) {
     const int ncols = nx / 2;
     pss::Geo& g = c->geo;
     g = pss::Geo{};
+    g.nx = nx;
+    g.ny = ny;
     g.nz = nz;
+    for (int i = 0; i < c->plan.ng; ++i) g.ncol[i] = c->plan.mask[i].ncol;
     if (c->ndim == 1) {
         // one block holds the line, 4 points per thread (no tunable geometry)
         c->lu = nx;
@@ -754,8 +812,18 @@ pss_status choose_geometry(pss_ctx* c) {
     // a line within one 256-thread block; fewer points per thread measured
     // faster for every kernel (lower register use, more waves in flight)
     auto few_points = [](int L, int cap) { return std::min(cap, std::max(std::min(4, L), L / 256)); };
-    g.pu = tuned("pu", few_points(lu, pss::max_points(lu, pss::field_slots(nf))));
-    g.px = tuned("px", few_points(nx, pss::max_points(nx, pss::field_slots(ng))));
+    // Large 3D lattices are bound by memory, not by latency, and there a wave
+    // should hold several of the tile's neighbouring columns (it then moves 16
+    // or 32 bytes of a 32-byte tile row at once, not 8): at most 32 threads a
+    // line along z, 8 points a thread along x in one-wave blocks.  256^3: two
+    // fields 195 -> 144 us (update) and 64.5 -> 55.3 us (x), one field 86 -> 67
+    // and 33.2 -> 28.5; 256^2 x 64 and 128^3 measured slower (28.7 -> 33.4,
+    // 18.2 -> 20.0 us), so the line lies at 2^23 sites.
+    const bool large3 = c->ndim == 3 && c->sites() >= (int64_t{1} << 23);
+    auto points3 = [&](int L, int cap, int lanes) { return std::min(cap, std::max(std::min(4, L), L / lanes)); };
+    const int cap_u = pss::max_points(lu, pss::field_slots(nf)), cap_x = pss::max_points(nx, pss::field_slots(ng));
+    g.pu = tuned("pu", large3 ? points3(lu, cap_u, 32) : few_points(lu, cap_u));
+    g.px = tuned("px", large3 ? points3(nx, std::min(8, cap_x), 32) : few_points(nx, cap_x));
     if (!pow2(g.pu) || g.pu > pss::max_points(lu, pss::field_slots(nf)) || !pow2(g.px) ||
         g.px > pss::max_points(nx, pss::field_slots(ng)))
         return fail(PSS_E_UNSUPPORTED, "points per thread must be a power of two up to the variant limit");
@@ -774,9 +842,14 @@ pss_status choose_geometry(pss_ctx* c) {
     g.ntile = ncols / g.tc;
     g.nublk = c->ndim == 2 ? g.ntile : g.ntile * (ny / g.to);
     if (c->ndim == 3) {
-        // y pass: TC lines of Ny points per z share a block of <= 256 threads
-        g.py = tuned("py", std::min(pss::max_points(ny, 1),
-                                    std::max(few_points(ny, pss::max_points(ny, 1)), pick_pow2(g.tc * ny / 256, 1, 16))));
+        // y pass: TC lines of Ny points per z share a block of <= 256 threads,
+        // 16 threads a line: a wave then holds whole 32-byte tile rows, and the
+        // block several neighbouring z (256^3, two fields, inverse + forward:
+        // 182 us at 64 threads a line, 121 at 32, 96 at 16; 128^3: 21.5 us at
+        // 32, 18.8 at 16, 22.6 at 8).  Below 2^21 sites the chip is not full and
+        // more threads win.
+        const int lanes_y = c->sites() >= (int64_t{1} << 21) ? 16 : 256;
+        g.py = tuned("py", std::max(points3(ny, pss::max_points(ny, 1), lanes_y), pick_pow2(g.tc * ny / 256, 1, 16)));
         if (!pow2(g.py) || g.py > pss::max_points(ny, 1))
             return fail(PSS_E_UNSUPPORTED, "points per thread must be a power of two up to the variant limit");
         const int ty = g.tc * (ny / g.py);
@@ -795,11 +868,15 @@ pss_status choose_geometry(pss_ctx* c) {
     const int rb_lo = std::max(2, 2 * (64 / tx));
     const int rb_hi = std::max(2, 2 * (256 / tx));
     int rb = pick_pow2(std::max(2, rows / 512), rb_lo, rb_hi);
+    if (large3) rb = rb_lo;
     rb = tuned("rb", std::min(rb, ny));  // a block's rows share z
     if (!pow2(rb) || rb < 2 || rb > ny || (rb / 2) * tx > 256)
         return fail(PSS_E_UNSUPPORTED, "x-kernel block of %d rows is not valid", rb);
     g.rb = rb;
     g.nrowblk = rows / rb;
+    // one-column tiles: rows of the exchange arrays in groups of four (a line's
+    // threads hold whole groups)
+    g.grp = c->ndim == 2 && g.tc == 1 && tu % 4 == 0 ? 1 : 0;
     g.tc_log2 = 0;
     while ((1 << g.tc_log2) < g.tc) ++g.tc_log2;
     g.rb_log2 = 0;
@@ -833,6 +910,7 @@ void free_device(pss_ctx* c) {
     rel(c->d_plan);
     rel(c->d_step);
     rel(c->d_tw_u);
+    rel(c->d_lim);
     rel(c->d_tw_x);
     rel(c->d_tw_y);
     rel(c->d_tmp);
@@ -1043,6 +1121,7 @@ pss_status materialize(pss_ctx* c) {
     const auto twy = twiddles(c->n[1]);
     HIP_TRY(hipMalloc(&c->d_tw_y, sizeof(float2) * twy.size()));
     HIP_TRY(hipMemcpy(c->d_tw_y, twy.data(), sizeof(float2) * twy.size(), hipMemcpyHostToDevice));
+    if (pss_status s = upload_limits(c)) return s;
     if (pss_status s = upload_frames(c)) return s;
     HIP_TRY(hipMemcpy(c->d_plan, &c->plan, sizeof(pss::DevPlan), hipMemcpyHostToDevice));
     if (c->ndim == 1) HIP_TRY(pss::line1d_setup(c->n[0]));

@@ -1,0 +1,50 @@
+"""GPU: the forms that a step's launches take by size (exchange arrays in
+groups of four rows or in column tiles, the self-conjugate modes of a packed
+line in four lanes or in one thread, 3D points per thread), each against the
+FP64 oracle, and regroupings of the same arithmetic against each other."""
+
+import numpy as np
+import pytest
+
+import paper_2405_02410_amd as pss
+from oracle import model as om
+from oracle.spectral import Lattice as OLattice
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(n, steps, **tune):
+    lat = pss.Lattice(n, dt=0.01, seed=11)
+    lat.tune(**tune)
+    f, _ = pss.model_b(lat, a=-1.0, b=1.0, k=1.0, D=0.01)
+    lat.init_uniform(f, -0.1, 0.1)
+    lat.step(steps)
+    return lat.spectrum(f), lat.download(f)
+
+
+def _oracle(n, steps):
+    m = om.model_b(OLattice(*n), 0.01, a=-1.0, b=1.0, k=1.0, D=0.01, seed=11)
+    m.init_uniform(0, -0.1, 0.1)
+    m.step(steps)
+    return m.real(0).reshape(tuple(reversed(n)))
+
+
+# lines of 8 (two threads: no groups, the self-conjugate modes in one thread),
+# 16 (four threads: the smallest line in groups), one wave and several
+@pytest.mark.parametrize("n", [(8, 8), (16, 8), (8, 16), (16, 16), (64, 16), (16, 64), (64, 256), (32, 1024)])
+def test_one_column_tiles_equal_wider_tiles_and_the_oracle(n):
+    pu = {"pu": 8} if n[1] == 1024 else {}  # two lines of 1024 in a block take 8 points per thread
+    tall, real = _run(n, 5, tc=1, **pu)
+    wide, _ = _run(n, 5, tc=2, **pu)
+    assert np.array_equal(tall, wide)
+    # 5 steps at ~2e-6 of |phi| <= 0.1 each
+    assert np.max(np.abs(real - _oracle(n, 5))) <= 2e-6
+
+
+# points per thread change the radix and so the rounding: 1e-5 of |phi| <= 0.1
+@pytest.mark.parametrize("n", [(16, 16, 16), (16, 32, 64), (32, 256, 16)])
+def test_3d_points_per_thread(n):
+    want = _oracle(n, 3)
+    for tune in ({}, {"pu": 8, "px": 8, "py": 8}, {"pu": 8, "py": 16, "tz": 1}):
+        _, real = _run(n, 3, **tune)
+        assert np.max(np.abs(real - want)) <= 2e-6, tune
