@@ -164,16 +164,28 @@ __device__ __forceinline__ void gstore_sel(float2* p, float2 v) {
         *q = __builtin_bit_cast(double, v);
     }
 }
-// p + e of an array below 4 GiB, as a scalar base and a 32-bit byte offset
-// (the load's own addressing mode), or with a 64-bit offset
-__device__ __forceinline__ const float2* elem(const float2* p, uint32_t e) {
-    return reinterpret_cast<const float2*>(reinterpret_cast<const char*>(p) + static_cast<uint32_t>(e * 8u));
+// Element e of an array, p uniform.  With a 32-bit index (arrays below 4 GiB)
+// the address is a scalar base and a 32-bit byte offset, the load's own
+// addressing mode; the base is made a global pointer before the offset is
+// added, or the sum would be carried as a 64-bit address per element.
+typedef __attribute__((address_space(1))) char pss_gchar;
+__device__ __forceinline__ float2 gload_at(const float2* p, uint32_t e) {
+    const pss_gchar* q = (const pss_gchar*)(p);
+    return __builtin_bit_cast(float2, *(const pss_gdouble*)(q + static_cast<uint32_t>(e * 8u)));
 }
-__device__ __forceinline__ float2* elem(float2* p, uint32_t e) {
-    return reinterpret_cast<float2*>(reinterpret_cast<char*>(p) + static_cast<uint32_t>(e * 8u));
+__device__ __forceinline__ float2 gload_at(const float2* p, size_t e) { return gload(p + e); }
+template <bool NT>
+__device__ __forceinline__ void gstore_at(float2* p, uint32_t e, float2 v) {
+    pss_gchar* b = (pss_gchar*)(p);
+    pss_gdouble* q = (pss_gdouble*)(b + static_cast<uint32_t>(e * 8u));
+    if constexpr (NT) {
+        __builtin_nontemporal_store(__builtin_bit_cast(double, v), q);
+    } else {
+        *q = __builtin_bit_cast(double, v);
+    }
 }
-__device__ __forceinline__ const float2* elem(const float2* p, size_t e) { return p + e; }
-__device__ __forceinline__ float2* elem(float2* p, size_t e) { return p + e; }
+template <bool NT>
+__device__ __forceinline__ void gstore_at(float2* p, size_t e, float2 v) { gstore_sel<NT>(p + e, v); }
 // two neighbouring float2 in one 16-byte load (p 16-byte aligned).  Loaded
 // as four floats: the same load typed as two doubles and split by bit casts
 // compiled here to overlapping destination registers for loads in flight,

@@ -30,11 +30,12 @@
 // (each group writes only its own Ls elements) and, for lines wider than a
 // wave, two buffers for the block exchanges, used alternately (LdsLine::par):
 // a buffer is written again only after the next block barrier, which every
-// thread reaches after it has read the older exchange.  Each region holds
-// kReg = L + L/2^PSS_FFT_PAD elements: element e of an exchange sits at
-// e + (e >> PSS_FFT_PAD), one pad slot after every 2^PSS_FFT_PAD elements,
-// so that the strided exchange patterns spread over the LDS banks (lines of
-// 4096 stay unpadded, see pss_fft_layout.h).
+// thread reaches after it has read the older exchange.  The longest lines
+// have one block buffer (fft_one_buffer), written after a barrier of its own.
+// Each region holds kReg = L + L/2^PSS_FFT_PAD elements: element e of an
+// exchange sits at e + (e >> PSS_FFT_PAD), one pad slot after every
+// 2^PSS_FFT_PAD elements, so that the strided exchange patterns spread over
+// the LDS banks.
 #pragma once
 
 #include "pss_device.h"
@@ -74,7 +75,16 @@ struct LineFFT {
     static constexpr int T = L / P;
     static constexpr bool kCross = T > 64;                  // the first exchange crosses waves
     static constexpr int kReg = fft_region(L, PADS);        // one exchange region
-    static constexpr int kLds = kCross ? 3 * kReg : kReg;  // LDS elements per line
+    static constexpr bool kOne = kCross && fft_one_buffer(L, P);  // one block buffer
+    static constexpr int kLds = fft_regions(L, P) * kReg;         // LDS elements per line
+    static __device__ __forceinline__ LdsLine lds_line(float2* base) {
+        LdsLine ld;
+        ld.wl = base;
+        ld.blk0 = base + kReg;
+        ld.blk1 = kOne ? ld.blk0 : base + 2 * kReg;
+        ld.par = 0;
+        return ld;
+    }
     static __device__ __forceinline__ int pad(int e) { return fft_padded(L, PADS) ? e + (e >> PADS) : e; }
 
     // stage s: sub-transform length, group size and radix
@@ -147,13 +157,29 @@ struct LineFFT {
                     for (int h = 0; h < PR; ++h)
 #pragma unroll
                         for (int k1 = 1; k1 < R; ++k1)
-                            w[tw_count(S) + h * (R - 1) + k1 - 1] = gload(elem(tw_g, static_cast<uint32_t>((g + h * G) * k1 * (L / Ls))));
+                            w[tw_count(S) + h * (R - 1) + k1 - 1] = gload_at(tw_g, static_cast<uint32_t>((g + h * G) * k1 * (L / Ls)));
                 }
                 load_stage<S - 1>(tw_g, t);
             }
         }
         // the stages that a forward (dit) transform runs first are loaded first
         __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t) { load_stage<kSt.n - 1>(tw_g, t); }
+    };
+    // the first stage's in registers, the later stages' from the table of the
+    // sub-transforms' length (entry i stands for w_L^(i R0))
+    struct Split {
+        static constexpr int R0 = kSt.R[0];
+        float2 w[tw_count(1) > 0 ? tw_count(1) : 1];
+        const float2* __restrict__ p;
+        __device__ __forceinline__ float2 at(int flat, int i) const { return flat < tw_count(1) ? w[flat] : p[i / R0]; }
+        __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t) {
+            constexpr int G = kSt.G[0];
+#pragma unroll
+            for (int h = 0; h < P / R0; ++h)
+#pragma unroll
+                for (int k1 = 1; k1 < R0; ++k1)
+                    w[h * (R0 - 1) + k1 - 1] = gload_at(tw_g, static_cast<uint32_t>((t + h * G) * k1));
+        }
     };
     // the same read from a table (in LDS) at each use
     struct Table {
@@ -198,6 +224,7 @@ struct LineFFT {
             float2* __restrict__ buf = cross ? ld.next_blk() : ld.wl;
             const int gb = (t - g) * P;  // the group's Ls elements
             if constexpr (!cross) wave_lds_sync();
+            if constexpr (cross && kOne) __syncthreads();
             float2* const wb = buf + pad(gb + g);
 #pragma unroll
             for (int h = 0; h < PR; ++h)
@@ -230,6 +257,7 @@ struct LineFFT {
             const int gb = (t - g) * P;
             const int k1 = g / Gn, gp = g & (Gn - 1);
             if constexpr (!cross) wave_lds_sync();
+            if constexpr (cross && kOne) __syncthreads();
             float2* const wb = buf + pad(gb + k1 * Lr + gp);
 #pragma unroll
             for (int j = 0; j < P; ++j) wb[pad(j * Gn)] = v[j];

@@ -13,24 +13,36 @@ namespace pss {
 // kernels, where the pad's address registers would cost occupancy)
 constexpr int kFftPad = PSS_FFT_PAD;
 
-// elements of one exchange region of a line of L points, padded by shift
-// `pads`; lines of 4096 keep the unpadded layout, so that such a line with
-// its packed-line exchange and twiddle table still fits in one workgroup's
-// 160 KiB
-constexpr bool fft_padded(int L, int pads) { return pads > 0 && L < 4096; }
+// elements of one exchange region of a line of L points, padded by shift `pads`
+constexpr bool fft_padded(int, int pads) { return pads > 0; }
 constexpr int fft_region(int L, int pads = kFftPad) { return fft_padded(L, pads) ? L + (L >> pads) : L; }
 
-// LDS elements of the line transforms of `lines` lines of L points held by
-// L/P threads each: one region per line, three when a line spans waves
-constexpr int fft_lds_elems(int L, int P, int lines, int pads = kFftPad) {
-    return lines * ((L / P > 64) ? 3 : 1) * fft_region(L, pads);
-}
+// Exchange regions of a line held by L/P threads: one within a wave; a line
+// of several waves adds two block buffers used in turn, or, from 2048 points
+// at 8 or more a thread, one that is guarded by a second barrier.  With three
+// regions a line of 4096 left room for one block of four waves per CU, with
+// two it is two blocks of eight.
+constexpr bool fft_one_buffer(int L, int P) { return L >= 2048 && P >= 8; }
+constexpr int fft_regions(int L, int P) { return L / P <= 64 ? 1 : (fft_one_buffer(L, P) ? 2 : 3); }
 
-// Where the twiddles of a line held P points a thread live: in registers up
-// to 8 points (at most 21 complex values, read once and used by every
-// transform of the kernel), in an LDS copy of the table for 16 (30 values
-// would halve the waves in flight).
-constexpr bool fft_reg_twiddles(int P) { return P <= 8; }
-constexpr int fft_tw_elems(int L, int P) { return fft_reg_twiddles(P) ? 0 : L; }
+// LDS elements of the line transforms of `lines` lines of L points held by
+// L/P threads each
+constexpr int fft_lds_elems(int L, int P, int lines, int pads = kFftPad) {
+    return lines * fft_regions(L, P) * fft_region(L, pads);
+}
+// the packed line's exchange: its own L elements, or the line's block buffer
+constexpr int fft_xbuf_elems(int L, int P) { return L / P > 64 && fft_one_buffer(L, P) ? 0 : L; }
+
+// Where the twiddles of a line held P points a thread live.  Up to 8 points:
+// in registers (at most 20 complex values, read once and used by every
+// transform of the kernel), except that lines of 2048 and more keep only the
+// first stage's there and the later stages' (a table of 512) in LDS (the
+// update kernel then takes 148 registers and not 180).  16 points: an LDS
+// copy of the table (30 values would halve the waves in flight).
+constexpr int kTwRegs = 0, kTwSplit = 1, kTwTable = 2;
+constexpr int fft_tw_form(int L, int P) { return P > 8 ? kTwTable : (L >= 2048 && P == 8 ? kTwSplit : kTwRegs); }
+constexpr int fft_tw_elems(int L, int P) {
+    return fft_tw_form(L, P) == kTwRegs ? 0 : (fft_tw_form(L, P) == kTwSplit ? 512 : L);
+}
 
 }  // namespace pss

@@ -299,16 +299,18 @@ hipError_t launch_philox(hipStream_t s, uint32_t c0, uint32_t c1, uint32_t c2, u
 
 // register-array count an instantiation is built for (1, 2 or 4 fields)
 inline int field_slots(int n) { return n <= 1 ? 1 : (n == 2 ? 2 : 4); }
+// threads of the largest block of a kernel of lines of L held with P points
+// per thread
+__host__ __device__ constexpr int line_block(int L, int P) { return L / P > 256 ? L / P : 256; }
 // LDS elements of the line transforms of `lines` lines of length L held with
-// P points per thread: one in-wave region per line, plus two block-exchange
-// buffers per line when a line spans more than one wave (pss_fft.h)
+// P points per thread (pss_fft_layout.h)
 inline size_t fft_lds(int L, int P, int lines, int pads = kFftPad) {
     return static_cast<size_t>(fft_lds_elems(L, P, lines, pads));
 }
 // dynamic LDS of the update kernel: TC*TO line transforms, one exchange line
 // and the twiddle table where it is staged, in that order
 inline size_t update_lds_bytes(int L, int P, int tc, int to, int pads = kFftPad) {
-    return sizeof(float2) * (fft_lds(L, P, tc * to, pads) + static_cast<size_t>(L + fft_tw_elems(L, P)));
+    return sizeof(float2) * (fft_lds(L, P, tc * to, pads) + static_cast<size_t>(fft_xbuf_elems(L, P) + fft_tw_elems(L, P)));
 }
 // dynamic LDS of the y pass: TC*TZ line transforms, one exchange line per z
 // and the twiddle table where it is staged, in that order

@@ -65,15 +65,38 @@ __device__ __forceinline__ const float2* store_twiddles(float2* dst, const float
 // the kernel's first data loads, ready() ends before the first transform (a
 // block barrier only where the table is staged in LDS), get() goes to
 // dif / dit.
-template <class FFT, int L, int P, bool REG = fft_reg_twiddles(P)>
-struct Twiddles {
+template <class FFT, int L, int P, int FORM = fft_tw_form(L, P)>
+struct Twiddles;
+template <class FFT, int L, int P>
+struct Twiddles<FFT, L, P, kTwRegs> {
     typename FFT::Regs r;
     __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t, int, int) { r.load(tw_g, t); }
     __device__ __forceinline__ void ready(float2*, int, int) {}
     __device__ __forceinline__ const typename FFT::Regs& get() const { return r; }
 };
 template <class FFT, int L, int P>
-struct Twiddles<FFT, L, P, false> {
+struct Twiddles<FFT, L, P, kTwSplit> {
+    static constexpr int N1 = fft_tw_elems(L, P), PER = (N1 + FFT::T - 1) / FFT::T;
+    static_assert(N1 == L / FFT::Split::R0, "the table is that of the second stage");
+    typename FFT::Split r;
+    float2 e[PER];
+    __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t, int tid, int nthr) {
+        r.load(tw_g, t);
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            e[k] = gload_at(tw_g, static_cast<uint32_t>(((tid + k * nthr) & (N1 - 1)) * FFT::Split::R0));
+    }
+    __device__ __forceinline__ void ready(float2* lds, int tid, int nthr) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (tid + k * nthr < N1) lds[tid + k * nthr] = e[k];
+        r.p = lds;
+        __syncthreads();
+    }
+    __device__ __forceinline__ const typename FFT::Split& get() const { return r; }
+};
+template <class FFT, int L, int P>
+struct Twiddles<FFT, L, P, kTwTable> {
     float2 w[P];
     typename FFT::Table tab;
     __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int, int tid, int nthr) {
@@ -487,6 +510,11 @@ __device__ __forceinline__ void add_to(float2 (&a)[NF][P], int f, int m, float2 
 // that the launch waits for).  64^2: 8.0 -> 5.5 us, 1024^2: 10.2 -> 8.4 us a
 // launch; with general operators (walked once per line instead of once per
 // mode) KPZ 22.8 -> 12.5 us and Model H 69 -> 30 us.
+//
+// Long lines (2048, 4096) run in many rounds and are bound by how many waves
+// hide the memory: see EARLY below and fft_one_buffer.  4096^2: 135 -> 85 us
+// (2.9 TB/s), the x kernel 93 -> 53.5 us; a cap of 128 registers for four
+// waves per SIMD spills (86.3 us), as it does in 3D (144 -> 273 us).
 
 // packed line: S(u), S(L-u) -> slot value of u (the forward direction)
 template <int L>
@@ -796,13 +824,11 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     // this thread's first position and the step from slot to slot
     const I sat = base + static_cast<I>(t) * tc, sstep = static_cast<I>(T) * tc;
     const I iat = xin.at(t), istep = xin.step(T), oat = xout.at(t), ostep = xout.step(T);
-    LdsLine ld;
-    ld.wl = smem + li * FFT::kLds;
-    ld.blk0 = ld.wl + FFT::kReg;
-    ld.blk1 = ld.wl + 2 * FFT::kReg;
-    ld.par = 0;
-    float2* xbuf = smem + tc * to * FFT::kLds;  // packed-line exchange
-    float2* twl = xbuf + L;
+    LdsLine ld = FFT::lds_line(smem + li * FFT::kLds);
+    // packed-line exchange (the block's first line where it shares that line's
+    // block buffer)
+    float2* xbuf = FFT::kOne ? smem + FFT::kReg : smem + tc * to * FFT::kLds;
+    float2* twl = smem + tc * to * FFT::kLds + fft_xbuf_elems(L, P);
     const int dr = FFT::drev(t);  // gathered / scattered positions dr + m*T
     Twiddles<FFT, L, P> tw;
     // block holds a packed line (block-uniform); this thread is on it
@@ -828,6 +854,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     // and map it (block-uniform)
     auto exchange = [&](float2 (&v)[P], bool forward) {
         if (!blk_packed) return;
+        if constexpr (FFT::kOne) __syncthreads();  // the block buffer's readers are done
         if (packed) {
 #pragma unroll
             for (int m = 0; m < P; ++m) xbuf[t + m * T] = v[m];
@@ -854,13 +881,13 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         FFT::template dit<-1>(v, ld, t, tw.get());
         exchange(v, true);
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore(elem(bufs.S[bufs.sel], sat + m * sstep), v[m]);
+        for (int m = 0; m < P; ++m) gstore_at<false>(bufs.S[bufs.sel], sat + m * sstep, v[m]);
         return;
     }
     if constexpr (MODE == MODE_INV_OUT) {
         float2 v[P];
 #pragma unroll
-        for (int m = 0; m < P; ++m) v[m] = gload(elem(bufs.S[bufs.sel], sat + m * sstep));
+        for (int m = 0; m < P; ++m) v[m] = gload_at(bufs.S[bufs.sel], sat + m * sstep);
         tw.load(tw_g, t, tid, nthr);
         tw.ready(twl, tid, nthr);
         exchange(v, false);
@@ -908,20 +935,28 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         // the arrays of a plan without products are null: read the state instead
         const float2* n0 = bufs.N[0] ? bufs.N[0] : bufs.S[0];
 #pragma unroll
-        for (int m = 0; m < P; ++m) nxt[m] = gload(elem(n0, iat + m * istep));
+        for (int m = 0; m < P; ++m) nxt[m] = gload_at(n0, iat + m * istep);
     }
     tw.load(tw_g, t, tid, nthr);
     float2 s[NF][P];  // state, then new state (slot form on a packed line)
+    auto load_state = [&]() {
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        if (f == 0 || f < nf) {
+        for (int f = 0; f < NF; ++f) {
+            if (f == 0 || f < nf) {
 #pragma unroll
-            for (int m = 0; m < P; ++m) s[f][m] = gload(elem(bufs.S[f], sat + m * sstep));
-        } else {
+                for (int m = 0; m < P; ++m) s[f][m] = gload_at(bufs.S[f], sat + m * sstep);
+            } else {
 #pragma unroll
-            for (int m = 0; m < P; ++m) s[f][m] = make_float2(0.f, 0.f);
+                for (int m = 0; m < P; ++m) s[f][m] = make_float2(0.f, 0.f);
+            }
         }
-    }
+    };
+    // Few points per thread: the launch is a round or two of blocks, and the
+    // loads, the noise and the next channel go ahead of what needs them.  With
+    // 8 and more points other blocks cover the waits, and what would be held
+    // across the transforms costs waves: each is taken where it is used.
+    constexpr bool EARLY = P < 8;
+    if constexpr (EARLY || !STEP) load_state();
     if constexpr (STEP) {
         hold(nf), hold(nch), hold(ng), hold(nd), hold(dt), hold(amp_pair), hold(amp_self), hold(key0), hold(key1);
 #pragma unroll
@@ -948,9 +983,11 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     // per-slot modes of the line (slot form on a packed line)
     constexpr bool LANES = T >= 4;
     LineCtx<P, LANES> cx;
-    uint32_t lin[P], lneg[P];
 #pragma unroll
-    for (int m = 0; m < P; ++m) slot_at<L>(lmode, t + m * T, cx.q2[m], lin[m], lneg[m]);
+    for (int m = 0; m < P; ++m) {
+        uint32_t lin, lneg;
+        slot_at<L>(lmode, t + m * T, cx.q2[m], lin, lneg);
+    }
     cx.pair_lane = pair_lane;
     cx.first_wave = blk_packed && tid < 64;
     if (cx.first_wave) {
@@ -980,13 +1017,10 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     }
     if constexpr (MODE == MODE_PROLOGUE) tw.ready(twl, tid, nthr);
     if constexpr (STEP) {
-        // the step's noise depends on the step and the modes only: formed
-        // here, while the loads above are still in flight.  Per field: of the
-        // slots, and of the four self-conjugate modes.
-        float2 eta[NF][P];
-        Four eta4[NF];
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
+        // The step's noise depends on the step and the modes only.  Per field:
+        // of the slots, and of the four self-conjugate modes.
+        auto noise_of = [&](auto FF, float2 (&e)[P], Four& e4) {
+            constexpr int f = decltype(FF)::value;
             if (f < nf && noisy[f] != 0) {
                 const NoiseKey nk{key0, key1, step, fid[f], amp_pair, amp_self};
                 float Dn[P];
@@ -1001,9 +1035,17 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                     horner_p(p.noise_op[f], cx.q2, Dn);
                 }
 #pragma unroll
-                for (int m = 0; m < P; ++m) eta[f][m] = noise_value<true>(nk, lin[m], lneg[m], Dn[m]);
+                for (int m = 0; m < P; ++m) {
+                    float q2m;
+                    uint32_t lin, lneg;
+                    slot_at<L>(lmode, t + m * T, q2m, lin, lneg);
+                    e[m] = noise_value<true>(nk, lin, lneg, Dn[m]);
+                    // two modes at a time: eight interleaved generators would
+                    // hold some fifty registers
+                    if (P >= 8 && (m & 1)) __builtin_amdgcn_sched_barrier(0);
+                }
                 if (cx.first_wave) {
-                    eta4[f] = self_eval(cx, [&](const Self& e) {
+                    e4 = self_eval(cx, [&](const Self& e) {
                         float Ds;
                         if constexpr (HOT)
                             Ds = horner(noi[f], e.q.q2);
@@ -1014,8 +1056,13 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                 }
             } else {
 #pragma unroll
-                for (int m = 0; m < P; ++m) eta[f][m] = make_float2(0.f, 0.f);
+                for (int m = 0; m < P; ++m) e[m] = make_float2(0.f, 0.f);
             }
+        };
+        float2 eta[EARLY ? NF : 1][P];
+        Four eta4[EARLY ? NF : 1];
+        if constexpr (EARLY) {
+            static_for<NF>([&](auto FF) { noise_of(FF, eta[decltype(FF)::value], eta4[decltype(FF)::value]); });
         }
         tw.ready(twl, tid, nthr);
         float2 acc[NF][P];  // explicit contributions
@@ -1032,10 +1079,13 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             // each output: its operator times the transform, into its field
             // (one field: one output, so the loop is left out)
             const int nout = NF == 1 ? 1 : C.nout;
-            if (ch + 1 < nch) {
+            auto load_next = [&]() {
+                if (ch + 1 < nch) {
 #pragma unroll
-                for (int m = 0; m < P; ++m) nxt[m] = gload(elem(bufs.N[ch + 1], iat + m * istep));
-            }
+                    for (int m = 0; m < P; ++m) nxt[m] = gload_at(bufs.N[ch + 1], iat + m * istep);
+                }
+            };
+            if constexpr (EARLY) load_next();
             FFT::template dit<-1>(v, ld, t, tw.get());
             exchange(v, true);
             for (int o2 = 0; o2 < nout; ++o2) {
@@ -1052,7 +1102,9 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                 }
                 accumulate<GEN>(acc, tg, v, op, poly, cx, qv);
             }
+            if constexpr (!EARLY) load_next();
         }
+        if constexpr (!EARLY) load_state();
         // Fourier-space terms with a single linear factor
         for (int d = 0; d < nd; ++d) {
             const DevDirect& Dd = p.direct[d];
@@ -1071,6 +1123,8 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             constexpr int f = decltype(FF)::value;
             if (f >= nf) return;
             const bool nz = noisy[f] != 0;
+            constexpr int fe = EARLY ? f : 0;
+            if constexpr (!EARLY) noise_of(FF, eta[0], eta4[0]);
             const float2 old0 = s[f][0], oldh = s[f][P / 2];
             if constexpr (GEN) {
                 float2 A[P];
@@ -1078,7 +1132,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
                     float2 r = cadd(s[f][m], cscale(acc[f][m], dt));
-                    if (nz) r = cadd(r, eta[f][m]);
+                    if (nz) r = cadd(r, eta[fe][m]);
                     s[f][m] = cmul(r, cinv_implicit(dt, A[m]));
                 }
             } else {
@@ -1090,7 +1144,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
                     float2 r = cadd(s[f][m], cscale(acc[f][m], dt));
-                    if (nz) r = cadd(r, eta[f][m]);
+                    if (nz) r = cadd(r, eta[fe][m]);
                     s[f][m] = cscale(r, __builtin_amdgcn_rcpf(fmaf(-dt, A[m], 1.f)));
                 }
             }
@@ -1107,8 +1161,8 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                     // slots 0 and L/2 hold two real modes each
                     float2 r = cadd(old0, cscale(acc[f][0], dt)), rh = cadd(oldh, cscale(acc[f][P / 2], dt));
                     if (nz) {
-                        r = make_float2(r.x + eta4[f].v[0], r.y + eta4[f].v[1]);
-                        rh = make_float2(rh.x + eta4[f].v[2], rh.y + eta4[f].v[3]);
+                        r = make_float2(r.x + eta4[fe].v[0], r.y + eta4[fe].v[1]);
+                        rh = make_float2(rh.x + eta4[fe].v[2], rh.y + eta4[fe].v[3]);
                     }
                     pair_scale<2>(inv, {r, rh}, s[f][0], s[f][P / 2]);
                 }
@@ -1117,7 +1171,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             float fin = 0.f;
 #pragma unroll
             for (int m = 0; m < P; ++m) {
-                gstore_sel<!TABLE>(elem(bufs.S[f], sat + m * sstep), s[f][m]);
+                gstore_at<!TABLE>(bufs.S[f], sat + m * sstep, s[f][m]);
                 fin = fmaf(s[f][m].x, 0.f, fin);
                 fin = fmaf(s[f][m].y, 0.f, fin);
             }
@@ -1169,12 +1223,12 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         exchange(v, false);
         FFT::template dif<1>(v, ld, t, tw.get());
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore_sel<!TABLE>(elem(bufs.V[g], oat + m * ostep), v[m]);
+        for (int m = 0; m < P; ++m) gstore_at<!TABLE>(bufs.V[g], oat + m * ostep, v[m]);
     }
 }
 
 template <int L, int P, int NF, int MODE, int DIM, bool GEN, bool TABLE>
-__global__ void __launch_bounds__(256) update_kernel(const Member* __restrict__ members,
+__global__ void __launch_bounds__(line_block(L, P)) update_kernel(const Member* __restrict__ members,
                                                       const DevPlan* __restrict__ plans,
                                                       const DevPlan* __restrict__ plan_a, Bufs bufs_a, Geo geo,
                                                       const uint64_t* __restrict__ step_ctr_a,
@@ -1196,7 +1250,7 @@ __global__ void __launch_bounds__(256) update_kernel(const Member* __restrict__ 
 // slots with weight 2 (a mode and its conjugate), and weight 1 for each real
 // component of the pair slots.
 template <int L, int P, int MODE>
-__global__ void __launch_bounds__(256) adjcol_kernel(AdjArgs aa, Geo geo, const float2* __restrict__ tw_g) {
+__global__ void __launch_bounds__(line_block(L, P)) adjcol_kernel(AdjArgs aa, Geo geo, const float2* __restrict__ tw_g) {
     using FFT = LineFFT<L, P>;
     constexpr int T = FFT::T;
     extern __shared__ float2 smem[];
@@ -1213,13 +1267,9 @@ __global__ void __launch_bounds__(256) adjcol_kernel(AdjArgs aa, Geo geo, const 
     const size_t base = static_cast<size_t>(ct) * L * tc + cc;
     const Exch<uint32_t> xch = exch_column(geo, ct, cc, L);
     const uint32_t xat = xch.at(t), xstep = xch.step(T);
-    LdsLine ld;
-    ld.wl = smem + cc * FFT::kLds;
-    ld.blk0 = ld.wl + FFT::kReg;
-    ld.blk1 = ld.wl + 2 * FFT::kReg;
-    ld.par = 0;
-    float2* xbuf = smem + tc * FFT::kLds;
-    float2* twl = xbuf + L;
+    LdsLine ld = FFT::lds_line(smem + cc * FFT::kLds);
+    float2* xbuf = FFT::kOne ? smem + FFT::kReg : smem + tc * FFT::kLds;
+    float2* twl = smem + tc * FFT::kLds + fft_xbuf_elems(L, P);
     const int dr = FFT::drev(t);
     Twiddles<FFT, L, P> tw;
     tw.load(tw_g, t, tid, nthr);
@@ -1229,6 +1279,7 @@ __global__ void __launch_bounds__(256) adjcol_kernel(AdjArgs aa, Geo geo, const 
 
     auto exchange = [&](float2 (&v)[P], bool forward) {  // as in the update kernel
         if (!blk_packed) return;
+        if constexpr (FFT::kOne) __syncthreads();  // the block buffer's readers are done
         if (packed) {
 #pragma unroll
             for (int m = 0; m < P; ++m) xbuf[t + m * T] = v[m];
@@ -1407,7 +1458,7 @@ __global__ void adjseed_kernel(const float2* __restrict__ phi, float2* __restric
 //   slots 0 and Ny/2       : Y unchanged     (packed, Hermitian along z)
 // and the inverse pass undoes it before transforming.
 template <int L, int P, int MODE>
-__global__ void __launch_bounds__(256) ypass_kernel(YArgs ya, Geo geo, const float2* __restrict__ tw_g) {
+__global__ void __launch_bounds__(line_block(L, P)) ypass_kernel(YArgs ya, Geo geo, const float2* __restrict__ tw_g) {
     using FFT = LineFFT<L, P>;
     constexpr int T = FFT::T;
     extern __shared__ float2 smem[];
@@ -1424,11 +1475,7 @@ __global__ void __launch_bounds__(256) ypass_kernel(YArgs ya, Geo geo, const flo
     const int ct = blk % ntile;
     const int z = (blk / ntile) * tz + lz;
     const int c = ct * tc + cc;
-    LdsLine ld;
-    ld.wl = smem + li * FFT::kLds;
-    ld.blk0 = ld.wl + FFT::kReg;
-    ld.blk1 = ld.wl + 2 * FFT::kReg;
-    ld.par = 0;
+    LdsLine ld = FFT::lds_line(smem + li * FFT::kLds);
     float2* xb = smem + tc * tz * FFT::kLds + lz * L;  // column-0 exchange, one line per z
     const int dr = FFT::drev(t);
     Twiddles<FFT, L, P> tw;
@@ -1551,11 +1598,7 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
     const int zr = geo.nz == 1 ? 0 : r0 / ny;  // z of the block (0 in 2D)
     const int y0 = r0 - zr * ny;     // first y of the block
     const int lt = geo.tc_log2;
-    LdsLine ld;
-    ld.wl = smem + pr * FFT::kLds;
-    ld.blk0 = ld.wl + FFT::kReg;
-    ld.blk1 = ld.wl + 2 * FFT::kReg;
-    ld.par = 0;
+    LdsLine ld = FFT::lds_line(smem + pr * FFT::kLds);
     const int dr = FFT::drev(t);
     Twiddles<FFT, L, P> tw;
     float2* const twl = smem + (rb >> 1) * FFT::kLds;
@@ -1623,6 +1666,7 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
     auto store_rows = [&](const float2 (&w)[P], float2* __restrict__ dst, int k0) {
         float2* stage = FFT::kCross ? ld.next_blk() : ld.wl;
         if constexpr (!FFT::kCross) wave_lds_sync();  // after the transform's last in-wave reads
+        if constexpr (FFT::kOne) __syncthreads();     // the block buffer's readers are done
 #pragma unroll
         for (int m = 0; m < P; ++m) stage[k0 + m * T] = w[m];
         __syncthreads();
@@ -1792,7 +1836,7 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
 }
 
 template <int L, int P, int NG, int MODE, bool TABLE>
-__global__ void __launch_bounds__(256) xrow_kernel(const Member* __restrict__ members,
+__global__ void __launch_bounds__(line_block(L, P)) xrow_kernel(const Member* __restrict__ members,
                                                     const DevPlan* __restrict__ plans,
                                                     const DevPlan* __restrict__ plan_a, Bufs bufs_a, Geo geo,
                                                     const float2* __restrict__ tw_g, int64_t advance,
@@ -2756,11 +2800,7 @@ __global__ void __launch_bounds__(N / 4 < 64 ? 64 : N / 4)
     extern __shared__ float2 smem[];
     const DevPlan& p = *plan;
     const int t = threadIdx.x;
-    LdsLine ld;
-    ld.wl = smem;
-    ld.blk0 = smem + FFT::kReg;
-    ld.blk1 = smem + 2 * FFT::kReg;
-    ld.par = 0;
+    LdsLine ld = FFT::lds_line(smem);
     float2* const twl = smem + FFT::kLds;
     float* const xst = reinterpret_cast<float*>(twl + N);  // real-space staging of the frames
     for (int i = t; i < N; i += T) twl[i] = tw_g[i];

@@ -48,3 +48,13 @@ def test_3d_points_per_thread(n):
     for tune in ({}, {"pu": 8, "px": 8, "py": 8}, {"pu": 8, "py": 16, "tz": 1}):
         _, real = _run(n, 3, **tune)
         assert np.max(np.abs(real - want)) <= 2e-6, tune
+
+
+# lines of 2048 and 4096: one guarded block buffer, split twiddles, blocks of
+# 512 threads, in either direction, and the forms that 16 points a thread keep
+@pytest.mark.parametrize("n", [(2048, 16), (16, 2048), (4096, 8), (8, 4096)])
+def test_long_lines(n):
+    want = _oracle(n, 5)
+    for tune in ({}, {"pu" if n[1] > n[0] else "px": 16}):
+        _, real = _run(n, 5, **tune)
+        assert np.max(np.abs(real - want)) <= 2e-6, tune
