@@ -135,6 +135,125 @@ struct DFT<16, DIR> {
     }
 };
 
+template <int DIR>
+struct DFT<3, DIR> {
+    static __device__ __forceinline__ void run(float2* a) {
+        constexpr float s60 = 0.86602540378443864676f;
+        const float2 t = cadd(a[1], a[2]), u = mul_dir_i<DIR>(cscale(csub(a[1], a[2]), s60));
+        const float2 m = make_float2(fmaf(-0.5f, t.x, a[0].x), fmaf(-0.5f, t.y, a[0].y));
+        a[0] = cadd(a[0], t);
+        a[1] = cadd(m, u);
+        a[2] = csub(m, u);
+    }
+};
+
+template <int DIR>
+struct DFT<5, DIR> {
+    static __device__ __forceinline__ void run(float2* a) {
+        // cos and sin of 72 and 144 degrees
+        constexpr float c1 = 0.30901699437494742410f, s1 = 0.95105651629515357212f;
+        constexpr float c2 = -0.80901699437494742410f, s2 = 0.58778525229247312917f;
+        const float2 p = cadd(a[1], a[4]), q = cadd(a[2], a[3]), d = csub(a[1], a[4]), e = csub(a[2], a[3]);
+        const float2 m1 = make_float2(fmaf(c2, q.x, fmaf(c1, p.x, a[0].x)), fmaf(c2, q.y, fmaf(c1, p.y, a[0].y)));
+        const float2 m2 = make_float2(fmaf(c1, q.x, fmaf(c2, p.x, a[0].x)), fmaf(c1, q.y, fmaf(c2, p.y, a[0].y)));
+        const float2 u1 = mul_dir_i<DIR>(make_float2(fmaf(s2, e.x, s1 * d.x), fmaf(s2, e.y, s1 * d.y)));
+        const float2 u2 = mul_dir_i<DIR>(make_float2(fmaf(-s1, e.x, s2 * d.x), fmaf(-s1, e.y, s2 * d.y)));
+        a[0] = cadd(a[0], cadd(p, q));
+        a[1] = cadd(m1, u1);
+        a[4] = csub(m1, u1);
+        a[2] = cadd(m2, u2);
+        a[3] = csub(m2, u2);
+    }
+};
+
+template <int DIR>
+struct DFT<9, DIR> {
+    // 3 x 3 split: X[k1 + 3 k2] = sum_n2 w3^(n2 k2) w9^(n2 k1) sum_n1 a[3 n1 + n2] w3^(n1 k1)
+    static __device__ __forceinline__ void run(float2* a) {
+        // cos and sin of 40, 80 and 160 degrees
+        constexpr float c[3] = {0.76604444311897803520f, 0.17364817766693034885f, -0.93969262078590838405f};
+        constexpr float s[3] = {0.64278760968653932632f, 0.98480775301220805937f, 0.34202014332566873304f};
+        float2 b[3][3];
+#pragma unroll
+        for (int n2 = 0; n2 < 3; ++n2) {
+            float2 t[3] = {a[n2], a[n2 + 3], a[n2 + 6]};
+            DFT<3, DIR>::run(t);
+#pragma unroll
+            for (int k1 = 0; k1 < 3; ++k1) b[n2][k1] = t[k1];
+        }
+        auto rot = [](float2 v, float cr, float sr) {
+            const float si = DIR > 0 ? sr : -sr;
+            return make_float2(v.x * cr - v.y * si, v.x * si + v.y * cr);
+        };
+        b[1][1] = rot(b[1][1], c[0], s[0]);
+        b[1][2] = rot(b[1][2], c[1], s[1]);
+        b[2][1] = rot(b[2][1], c[1], s[1]);
+        b[2][2] = rot(b[2][2], c[2], s[2]);
+#pragma unroll
+        for (int k1 = 0; k1 < 3; ++k1) {
+            float2 t[3] = {b[0][k1], b[1][k1], b[2][k1]};
+            DFT<3, DIR>::run(t);
+#pragma unroll
+            for (int k2 = 0; k2 < 3; ++k2) a[k1 + 3 * k2] = t[k2];
+        }
+    }
+};
+
+// Coprime R = A B by the prime-factor map (Van Loan, Sec. 4.1; Good 1958):
+// input n = (B n1 + A n2) mod R, output k = k1 mod A and k2 mod B, with no
+// twiddles between the two small transforms.
+template <int A, int B, int DIR>
+struct PfaDFT {
+    static constexpr int out(int k1, int k2) {
+        for (int k = 0; k < A * B; ++k)
+            if (k % A == k1 && k % B == k2) return k;
+        return 0;
+    }
+    template <int N2>
+    static __device__ __forceinline__ void first(const float2* a, float2 (&b)[B][A]) {
+        if constexpr (N2 < B) {
+            float2 t[A];
+#pragma unroll
+            for (int n1 = 0; n1 < A; ++n1) t[n1] = a[(B * n1 + A * N2) % (A * B)];
+            DFT<A, DIR>::run(t);
+#pragma unroll
+            for (int k1 = 0; k1 < A; ++k1) b[N2][k1] = t[k1];
+            first<N2 + 1>(a, b);
+        }
+    }
+    template <int K1, int K2>
+    static __device__ __forceinline__ void put(float2* a, const float2 (&t)[B]) {
+        if constexpr (K2 < B) {
+            a[out(K1, K2)] = t[K2];
+            put<K1, K2 + 1>(a, t);
+        }
+    }
+    template <int K1>
+    static __device__ __forceinline__ void second(float2* a, const float2 (&b)[B][A]) {
+        if constexpr (K1 < A) {
+            float2 t[B];
+#pragma unroll
+            for (int n2 = 0; n2 < B; ++n2) t[n2] = b[n2][K1];
+            DFT<B, DIR>::run(t);
+            put<K1, 0>(a, t);
+            second<K1 + 1>(a, b);
+        }
+    }
+    static __device__ __forceinline__ void run(float2* a) {
+        float2 b[B][A];
+        first<0>(a, b);
+        second<0>(a, b);
+    }
+};
+template <int DIR>
+struct DFT<6, DIR> : PfaDFT<2, 3, DIR> {};
+template <int DIR>
+struct DFT<10, DIR> : PfaDFT<2, 5, DIR> {};
+template <int DIR>
+struct DFT<12, DIR> : PfaDFT<4, 3, DIR> {};
+template <int DIR>
+struct DFT<15, DIR> : PfaDFT<3, 5, DIR> {};
+
 // ------------------------------------------------------------ global access
 // The step kernels read their array pointers from a table in device memory,
 // so the compiler sees generic pointers and would emit FLAT loads and stores

@@ -119,6 +119,7 @@ struct LaunchArgs {
     const DevPlan* plans;   // step modes: their nmem plans (device memory)
     int nmem;
     bool general;           // the plans need the general-monomial operator code
+    bool simple;            // one field, one channel and one factor, no other explicit terms, not general
     int step_off;
     int64_t advance;     // x kernel, step modes: add this to every member's step counter (0: none)
     const float2* tw_u;  // twiddles of the update-axis length
@@ -214,29 +215,78 @@ hipError_t line1d_setup(int N);
 
 // 1D lines of mixed-radix length N = 2^a 3^b 5^c, a >= 1, not a power of two
 // (launch_line1d sends them to their own kernel): the radices of the
-// self-sorting passes, 4 first, then 2, 3 and 5.  False if N does not factor
-// so or is not even.
+// self-sorting passes.  False if N does not factor so or is not even.
+constexpr int kMrPasses = 12;
 struct MrPlan {
     int n;
     int nst;
-    int radix[24];
+    int radix[kMrPasses];
+    float rper[kMrPasses], rs[kMrPasses];  // 1 / (butterflies of a line), 1 / s of each pass (FastDiv)
 };
-inline bool mr_plan(int N, MrPlan* mr) {
-    if (N < 2 || (N & 1)) return false;
-    mr->n = N;
-    mr->nst = 0;
-    int n = N;
-    while (n % 4 == 0 && n > 4) {
-        mr->radix[mr->nst++] = 4;
-        n /= 4;
+// Threads of a block of N line elements: at most kMrPerThread each (blocks of
+// up to 4096), within 64 .. 1024.  960^2: half or twice as many are slower.
+constexpr int kMrPerThread = 4;
+inline int mr_threads(int N) {
+    int t = 64;
+    while (t < 1024 && kMrPerThread * t < N) t <<= 1;
+    return t;
+}
+constexpr int kMrRadices[] = {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
+// Cycles of one pass of radix r: a trip through LDS and a barrier, the chain
+// of one thread's butterfly (about 5 cycles an instruction), once per round
+// of the block's threads, and the issue slots that all its waves take (two
+// blocks a CU).  Few passes of radices 8 to 12 win: 960 = 10 12 8.
+inline int mr_pass_cost(int N, int r) {
+    const int bf = N / r, t = mr_threads(N);
+    const int ops = r == 16 ? 170 : r == 15 ? 170 : r == 12 ? 120 : r == 10 ? 100 : r == 9 ? 100 : r == 8 ? 64
+                    : r == 6 ? 36 : r == 5 ? 36 : r == 4 ? 16 : r == 3 ? 16 : 4;
+    const int instr = 40 + 12 * r + ops;
+    return 300 + ((bf + t - 1) / t) * 5 * instr + bf * instr * 11 / 320;
+}
+// cheapest factorization of n (a divisor of N) into radices from kMrRadices[i0] on
+inline void mr_split(int N, int n, int i0, int cost, int* cur, int ncur, int* best, int* nbest, int* cbest) {
+    if (cost >= *cbest) return;
+    if (n == 1) {
+        for (int i = 0; i < ncur; ++i) best[i] = cur[i];
+        *nbest = ncur;
+        *cbest = cost;
+        return;
     }
-    for (int r : {4, 2, 3, 5})
-        while (n % r == 0) {
-            if (mr->nst >= 24) return false;
-            mr->radix[mr->nst++] = r;
-            n /= r;
-        }
-    return n == 1;
+    for (int i = i0; i < static_cast<int>(sizeof(kMrRadices) / sizeof(int)); ++i) {
+        const int r = kMrRadices[i];
+        if (n % r != 0) continue;
+        cur[ncur] = r;
+        mr_split(N, n / r, i, cost + mr_pass_cost(N, r), cur, ncur + 1, best, nbest, cbest);
+    }
+}
+inline bool mr_plan(int N, MrPlan* mr) {
+    if (N < 2 || (N & 1) || N > 4096) return false;
+    int n = N;
+    for (int r : {2, 3, 5})
+        while (n % r == 0) n /= r;
+    if (n != 1) return false;
+    mr->n = N;
+    int cur[kMrPasses], best[kMrPasses], nbest = 0, cbest = 1 << 30;  // 2^12 is the longest chain
+    mr_split(N, N, 0, 0, cur, 0, best, &nbest, &cbest);
+    mr->nst = nbest;
+    // the largest odd factor first: the first pass writes with the stride of
+    // its radix, which an odd one spreads over the LDS banks
+    auto odd_part = [](int v) {
+        while (v % 2 == 0) v /= 2;
+        return v;
+    };
+    int odd = 0;
+    for (int i = 1; i < nbest; ++i)
+        if (odd_part(best[i]) > odd_part(best[odd])) odd = i;
+    mr->radix[0] = best[odd];
+    for (int i = 0, k = 1; i < nbest; ++i)
+        if (i != odd) mr->radix[k++] = best[i];
+    for (int i = 0, s = 1; i < nbest; ++i) {
+        mr->rper[i] = 1.0f / static_cast<float>(N / mr->radix[i]);
+        mr->rs[i] = 1.0f / static_cast<float>(s);
+        s *= mr->radix[i];
+    }
+    return true;
 }
 // LDS of the mixed-radix 1D kernel: twiddle table, two transform buffers,
 // NF states and NF contribution arrays (complex), ng real factor lines
@@ -248,33 +298,38 @@ hipError_t launch_line1d_mr(int mode, int N, int nf, int ng, const LaunchArgs& a
 hipError_t line1d_mr_setup();
 
 // 2D and 3D lattices of mixed-radix sizes (even 2^a 3^b 5^c, not all powers
-// of two): full complex spectra, mode (kx, ky, kz) at (kz Ny + ky) Nx + kx.  Column launch
-// (geo.tc neighbouring lines per block): MODE_STEP (channels N[ch] in (y, kx) form -> update ->
-// factors V[g] in (y, kx) form), MODE_PROLOGUE (factors from the state),
-// MODE_FWD_STORE (in, (y, kx) -> state sel), MODE_INV_OUT (state sel -> out,
-// (y, kx)), MODE_INTERM_OUT (intermediate sel -> out).  Row launch (one block
-// per y): MODE_STEP (V -> products -> N; a.advance moves the counter on),
-// MODE_R2C_IN (real_in -> out), MODE_C2R_OUT (in -> real_out, normalised).
-// column launch: the twiddles of a line, then two transform buffers, NF
-// states and NF contribution arrays of tc lines each; the y pass: the
-// twiddles and two buffers of tc lines
+// of two): the state is a full complex spectrum, mode (kx, ky, kz) at
+// (kz Ny + ky) Nx + kx.  The arrays that pass between the launches of a step
+// (channels N, factors V) are transforms of real fields: they hold kx = 0 ..
+// Nx/2 only, rows r = z Ny + y in pairs, element (kx, r) at
+// ((r >> 1) NC + kx) 2 + (r & 1) with NC = Nx/2 + 1.
+//   launch_mr2_col: MODE_STEP (channels -> update -> factors), MODE_PROLOGUE
+//     (factors from the state); along y in 2D, z in 3D, geo.tc lines of
+//     neighbouring kx per block.  On full spectra: MODE_FWD_STORE (in -> state
+//     sel), MODE_INV_OUT (state sel -> out), MODE_INTERM_OUT (intermediate).
+//   launch_mr2_row: MODE_STEP (V -> products -> N, a row pair per block;
+//     a.advance moves the counter on), MODE_R2C_IN, MODE_C2R_OUT (full rows).
+//   launch_mr3_ypass: 3D, transforms along y (sign -1 forward, +1 inverse) of
+//     the arrays of ya, half spectra or (full) whole ones, geo.py lines of
+//     neighbouring kx per block.
+// LDS of the column launch: the twiddles of a line, then two transform
+// buffers, NF states and NF contribution arrays of tc lines each; the y pass:
+// the twiddles and two buffers of tc lines; the row launch: the twiddles, two
+// buffers and ng factors of `rows` real rows (2, or 1 where 2 do not fit).
 inline size_t mr2_col_lds_bytes(int L, int NF, int tc) {
     return sizeof(float2) * static_cast<size_t>(L) * (1 + static_cast<size_t>(tc) * (2 + 2 * static_cast<size_t>(NF)));
 }
 inline size_t mr3_ypass_lds_bytes(int Ny, int tc) {
     return sizeof(float2) * static_cast<size_t>(Ny) * (1 + 2 * static_cast<size_t>(tc));
 }
-inline size_t mr2_row_lds_bytes(int Nx, int ng) {
+inline size_t mr2_row_lds_bytes(int Nx, int ng, int rows) {
     return sizeof(float2) * static_cast<size_t>(Nx) * 3 +
-           sizeof(float) * static_cast<size_t>(Nx) * static_cast<size_t>(ng > 0 ? ng : 1);
+           sizeof(float) * static_cast<size_t>(Nx) * static_cast<size_t>(rows) * static_cast<size_t>(ng > 0 ? ng : 1);
 }
-// In 3D the column launch runs along z (geo.tc lines of neighbouring kx per
-// block), the row launch covers Ny Nz rows, and launch_mr3_ypass transforms
-// the arrays of ya along y (sign -1 forward, +1 inverse), geo.py lines of
-// neighbouring kx per block.
+inline int mr2_rows(int Nx, int ng) { return mr2_row_lds_bytes(Nx, ng, 2) <= 160 * 1024 ? 2 : 1; }
 hipError_t launch_mr2_col(int mode, int nf, const LaunchArgs& a);
 hipError_t launch_mr2_row(int mode, const LaunchArgs& a);
-hipError_t launch_mr3_ypass(int sign, const YArgs& ya, const LaunchArgs& a);
+hipError_t launch_mr3_ypass(int sign, const YArgs& ya, bool full, const LaunchArgs& a);
 hipError_t mr2_setup();
 hipError_t launch_xrow(int mode, int L, int ng, const LaunchArgs& a);
 hipError_t launch_ypass(int mode, int L, const YArgs& ya, const LaunchArgs& a);

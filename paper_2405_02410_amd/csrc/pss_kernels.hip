@@ -2068,36 +2068,13 @@ __global__ void shell_means_kernel(int nshell, const unsigned int* __restrict__ 
 // ------------------------------------------- 1D lines of mixed-radix length
 // Lines whose length N = 2^a 3^b 5^c (a >= 1) is not a power of two.  One
 // block per lattice keeps the spectra in LDS and transforms them with
-// self-sorting (Stockham) passes of radix 4, 2, 3 and 5 (Van Loan, Sec. 1.7):
+// self-sorting (Stockham) passes of radices up to 16 (Van Loan, Sec. 1.7):
 // a pass of radix r over the current length n = m r and s interleaved
 // transforms maps x to
 //   y[q + s (r p + j)] = w_n^(j p) sum_l x[q + s (p + l m)] w_r^(j l),
 // p < m, q < s, j < r, w_n = exp(-+2 pi i / n), and the next pass takes n = m,
 // s = s r, until the result stands in natural order.  The step is the one of
 // the power-of-two 1D kernel, mode by mode over the whole line.
-
-// (cos, sin)(2 pi k / r) for r in {2, 3, 4, 5}
-__device__ __forceinline__ float2 small_root(int r, int k) {
-    // the fifth roots: cos and sin of 72 and 144 degrees
-    constexpr float c1 = 0.309016994374947424f, s1 = 0.951056516295153572f;
-    constexpr float c2 = -0.809016994374947424f, s2 = 0.587785252292473129f;
-    constexpr float h3 = 0.866025403784438647f;  // sin(120 degrees)
-    switch (r) {
-        case 2: return k == 0 ? make_float2(1.f, 0.f) : make_float2(-1.f, 0.f);
-        case 3: return k == 0 ? make_float2(1.f, 0.f) : (k == 1 ? make_float2(-0.5f, h3) : make_float2(-0.5f, -h3));
-        case 4:
-            return k == 0 ? make_float2(1.f, 0.f)
-                          : (k == 1 ? make_float2(0.f, 1.f) : (k == 2 ? make_float2(-1.f, 0.f) : make_float2(0.f, -1.f)));
-        default:
-            switch (k) {
-                case 0: return make_float2(1.f, 0.f);
-                case 1: return make_float2(c1, s1);
-                case 2: return make_float2(c2, s2);
-                case 3: return make_float2(c2, -s2);
-                default: return make_float2(c1, -s1);
-            }
-    }
-}
 
 // floor(x / d) for 0 <= x < 2^21 and d >= 1, without an integer division:
 // (x + 1/2)/d lies at least 1/(2d) from an integer, and rounding 1/d and the
@@ -2107,65 +2084,80 @@ struct FastDiv {
     int d;
     float rd;
     __device__ __forceinline__ explicit FastDiv(int dv) : d(dv), rd(1.0f / static_cast<float>(dv)) {}
+    __device__ __forceinline__ FastDiv(int dv, float rdv) : d(dv), rd(rdv) {}
     __device__ __forceinline__ int quo(int x) const {
         return static_cast<int>((static_cast<float>(x) + 0.5f) * rd);
     }
 };
 
 // One self-sorting pass of radix R over nl lines of N values (line l at
-// x + l N), sign sg = -1 (forward) or +1 (inverse): the radix-R transforms of
+// x + l N), sign SG = -1 (forward) or +1 (inverse): the radix-R transforms of
 // the current length n = m R, then the twiddles w_n^(j p).  n s = N at every
-// pass, so j p s < N indexes the table directly.  Lines hold at most 2^21
-// values in all (they sit in LDS).
-template <int R>
+// pass, so j p s < N indexes the table directly (the last pass, m = 1, has
+// none).  Lines hold at most 2^21 values in all (they sit in LDS).
+template <int R, int SG>
 __device__ __forceinline__ void mr_pass(const float2* __restrict__ x, float2* __restrict__ y,
-                                        const float2* __restrict__ tw, int N, int m, int s, int nl, float sg) {
+                                        const float2* __restrict__ tw, int N, int m, int s, int nl, float rper,
+                                        float rs) {
     const int per = m * s;
-    const FastDiv fper(per), fs(s);
+    const FastDiv fper(per, rper), fs(s, rs);
     for (int idx = threadIdx.x; idx < nl * per; idx += blockDim.x) {
-        const int line = fper.quo(idx), rem = idx - line * per;
+        const int line = nl == 1 ? 0 : fper.quo(idx), rem = idx - line * per;
         const int p = fs.quo(rem), q = rem - p * s;
-        const float2* xl = x + static_cast<size_t>(line) * N;
-        float2* yl = y + static_cast<size_t>(line) * N;
+        const float2* xl = x + line * N + rem;  // q + s p
+        float2* yl = y + line * N + q + s * R * p;
         float2 a[R];
 #pragma unroll
-        for (int l = 0; l < R; ++l) a[l] = xl[q + s * (p + l * m)];
+        for (int l = 0; l < R; ++l) a[l] = xl[l * per];
+        DFT<R, SG>::run(a);
+        if (m > 1) {
+            const int ps = p * s;
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            float2 b = a[0];
-#pragma unroll
-            for (int l = 1; l < R; ++l) {
-                float2 w = small_root(R, (j * l) % R);
-                w.y *= sg;
-                b = cadd(b, cmul(a[l], w));
+            for (int j = 1; j < R; ++j) {
+                float2 w = tw[j * ps];  // exp(-2 pi i j p s / N) = w_n^(j p)
+                if (SG > 0) w.y = -w.y;
+                a[j] = cmul(a[j], w);
             }
-            if (j > 0) {
-                float2 w = tw[j * p * s];  // exp(-2 pi i j p s / N) = w_n^(j p)
-                if (sg > 0.f) w.y = -w.y;
-                b = cmul(b, w);
-            }
-            yl[q + s * (R * p + j)] = b;
         }
+#pragma unroll
+        for (int j = 0; j < R; ++j) yl[j * s] = a[j];
     }
 }
 
 // Transform of nl lines of N values in x (LDS; line l at x + l N) with sign
-// -1 (forward) or +1 (inverse, unnormalised); y is LDS scratch of the same
-// size.  Returns the buffer holding the result.  Every thread of the block
-// calls it; it ends with a barrier.
-__device__ float2* mr_transform(float2* x, float2* y, const float2* __restrict__ tw, const MrPlan& mr, int sign,
-                                int nl = 1) {
+// SG = -1 (forward) or +1 (inverse, unnormalised); y is LDS scratch of the
+// same size.  Returns the buffer holding the result.  Every thread of the
+// block calls it; it ends with a barrier.
+//
+// Each pass is a trip through LDS that every wave of the block waits for, so
+// the passes are few: radices up to 16 in registers (MrPlan), their index
+// arithmetic is kept off divisions, and the block has a thread for four
+// elements.  960^2 Model B, a step: 56 us with passes of radix 4, 3, 5 on full
+// spectra; 37 with half spectra and paired rows; 35 with the loads ahead of
+// the transforms; 30 with passes of 10, 12 and 8.  Now 21 us a column launch
+// (mostly strided access to the full state, 8 or 16 bytes of a line) and 11 us
+// a row launch.
+template <int SG>
+__device__ __forceinline__ float2* mr_transform(float2* x, float2* y, const float2* __restrict__ tw, const MrPlan& mr,
+                                                int nl = 1) {
     const int N = mr.n;
-    const float sg = static_cast<float>(sign);
     int n = N, s = 1;
     for (int st = 0; st < mr.nst; ++st) {
         const int r = mr.radix[st];
-        const int m = n / r;
+        const float rper = mr.rper[st], rs = mr.rs[st];
+        const int m = FastDiv(r, 1.0f / static_cast<float>(r)).quo(n);
         switch (r) {
-            case 4: mr_pass<4>(x, y, tw, N, m, s, nl, sg); break;
-            case 2: mr_pass<2>(x, y, tw, N, m, s, nl, sg); break;
-            case 3: mr_pass<3>(x, y, tw, N, m, s, nl, sg); break;
-            default: mr_pass<5>(x, y, tw, N, m, s, nl, sg); break;
+            case 2: mr_pass<2, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 3: mr_pass<3, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 4: mr_pass<4, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 5: mr_pass<5, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 6: mr_pass<6, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 8: mr_pass<8, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 9: mr_pass<9, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 10: mr_pass<10, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 12: mr_pass<12, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            case 15: mr_pass<15, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
+            default: mr_pass<16, SG>(x, y, tw, N, m, s, nl, rper, rs); break;
         }
         __syncthreads();
         float2* t = x;
@@ -2178,7 +2170,7 @@ __device__ float2* mr_transform(float2* x, float2* y, const float2* __restrict__
 }
 
 template <int NF, bool GEN, int MODE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
     line1d_mr_kernel(const DevPlan* __restrict__ plan, Bufs bufs, uint64_t* __restrict__ step_ctr,
                      uint32_t* __restrict__ flag, int nsteps, int advance, const float2* __restrict__ tw_g, MrPlan mr) {
     extern __shared__ float2 smem[];
@@ -2197,14 +2189,14 @@ __global__ void __launch_bounds__(256)
     if constexpr (MODE == MODE_FWD_STORE) {
         for (int i = t; i < N; i += T) A[i] = make_float2(bufs.real_in[i], 0.f);
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, mr, -1);
+        const float2* r = mr_transform<-1>(A, B, tw, mr);
         for (int k = t; k < N; k += T) gstore(bufs.S[bufs.sel] + k, r[k]);
         return;
     }
     if constexpr (MODE == MODE_INV_OUT) {
         for (int k = t; k < N; k += T) A[k] = gload(bufs.S[bufs.sel] + k);
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, mr, 1);
+        const float2* r = mr_transform<1>(A, B, tw, mr);
         for (int i = t; i < N; i += T) bufs.real_out[i] = r[i].x * p.inv_n;
         return;
     }
@@ -2230,7 +2222,7 @@ __global__ void __launch_bounds__(256)
     if constexpr (MODE == MODE_INTERM_OUT) {
         for (int k = t; k < N; k += T) A[k] = source(PSS_MAXF + bufs.sel, k, kq(k));
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, mr, 1);
+        const float2* r = mr_transform<1>(A, B, tw, mr);
         for (int i = t; i < N; i += T) bufs.real_out[i] = r[i].x * p.inv_n;
         return;
     }
@@ -2248,7 +2240,7 @@ __global__ void __launch_bounds__(256)
                 A[k] = mask_keep(mk, k < (N >> 1) ? k : k - N, 0, 0) ? source(p.gfield[g], k, kq(k))
                                                                      : make_float2(0.f, 0.f);
             __syncthreads();
-            const float2* r = mr_transform(A, B, tw, mr, 1);
+            const float2* r = mr_transform<1>(A, B, tw, mr);
             for (int i = t; i < N; i += T) u[g * N + i] = r[i].x * p.inv_n;
             __syncthreads();
         }
@@ -2266,7 +2258,7 @@ __global__ void __launch_bounds__(256)
                 A[i] = make_float2(w, 0.f);
             }
             __syncthreads();
-            const float2* r = mr_transform(A, B, tw, mr, -1);
+            const float2* r = mr_transform<-1>(A, B, tw, mr);
             for (int k = t; k < N; k += T) {
                 const ModeQ q = kq(k);
                 for (int o = 0; o < C.nout; ++o) {
@@ -2312,14 +2304,14 @@ __global__ void __launch_bounds__(256)
             if (p.nframe[f] == 0) continue;
             for (int k = t; k < N; k += T) A[k] = S[f * N + k];
             __syncthreads();
-            float2* r = mr_transform(A, B, tw, mr, 1);
+            float2* r = mr_transform<1>(A, B, tw, mr);
             float2* o = r == A ? B : A;
             for (int i = t; i < N; i += T) o[i] = make_float2(r[i].x * p.inv_n, 0.f);
             __syncthreads();
             const int2* __restrict__ fr = p.frame[f];
             for (int i = t; i < p.nframe[f]; i += T) o[fr[i].x] = make_float2(__int_as_float(fr[i].y), 0.f);
             __syncthreads();
-            const float2* z = mr_transform(o, r, tw, mr, -1);
+            const float2* z = mr_transform<-1>(o, r, tw, mr);
             for (int k = t; k < N; k += T) S[f * N + k] = z[k];
             __syncthreads();
         }
@@ -2338,7 +2330,7 @@ hipError_t launch_line1d_mr(int mode, int N, int nf, int ng, const LaunchArgs& a
     const int NF = nf <= 1 ? 1 : (nf == 2 ? 2 : 4);
     const size_t lds = line1d_mr_lds_bytes(mr.n, NF, ng);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const dim3 grid(1), block(256);
+    const dim3 grid(1), block(mr_threads(mr.n));
     uint64_t* ctr = const_cast<uint64_t*>(a.step_ctr);
     const bool gen = a.general || mode == MODE_INTERM_OUT;
 #define PSS_MR(NFV, G, M)                                                                                   \
@@ -2397,17 +2389,517 @@ hipError_t line1d_mr_setup() {
 // of a field is its full complex spectrum, mode (kx, ky, kz) at
 // (kz Ny + ky) Nx + kx (natural order on every axis); real space is the real
 // part of the inverse transform, as everywhere.  A step is launched as on the
-// power-of-two path: the column kernel (one block per line along the last
-// axis: forward transforms of the channels, the update, the de-aliased
-// factors' inverse transforms), in 3D a y pass, the row kernel (one block per
-// x row: inverse x transforms of the factors, the real-space products, their
-// forward x transforms), in 3D a y pass back; each line in LDS and
-// transformed with the self-sorting passes above.
+// power-of-two path: the column kernel (lines along the last axis: forward
+// transforms of the channels, the update, the de-aliased factors' inverse
+// transforms), in 3D a y pass, the row kernel (inverse x transforms of the
+// factors, the real-space products, their forward x transforms), in 3D a y
+// pass back; each line in LDS and transformed with the self-sorting passes
+// above.
+//
+// The products are real, so their transforms, and what real space takes from
+// the factors, are Hermitian: the step's arrays hold kx = 0 .. Nx/2 only
+// (layout in pss_kernels.h), one line transform serves the modes k and -k of
+// the full state (the contribution to -k is the conjugate, the factor at k is
+// the mean of phi(k) and conj phi(-k), which is what the real part keeps),
+// and two real rows share one complex x transform.
+
+// The addresses of a column block: tc neighbouring lines along the last axis,
+// kx0 .. kx0 + nl - 1 of the half spectrum at one ky (3D), line c at c L in LDS
+struct MrCols {
+    int Nx, L, N1, NC, kx0, nl, ko;
+    bool d3;
+    __device__ __forceinline__ MrCols(const Geo& geo, int Lv, int blk) {
+        Nx = geo.nx;
+        L = Lv;
+        N1 = geo.ny;
+        NC = (Nx >> 1) + 1;
+        d3 = geo.nz > 1;
+        const int nxb = (NC + geo.tc - 1) / geo.tc;
+        ko = d3 ? blk / nxb : 0;
+        kx0 = (blk - ko * nxb) * geo.tc;
+        nl = min(geo.tc, NC - kx0);
+    }
+    // element of a step array: line c, position w along it
+    __device__ __forceinline__ size_t half(int c, int w) const {
+        return d3 ? (static_cast<size_t>(ko >> 1) * NC + static_cast<size_t>(w) * (N1 >> 1) * NC + kx0 + c) * 2 + (ko & 1)
+                  : (static_cast<size_t>(w >> 1) * NC + kx0 + c) * 2 + (w & 1);
+    }
+    // element of the state (and linear mode index): mode k of (c, w), and -k
+    __device__ __forceinline__ size_t pos(int c, int w) const {
+        return (d3 ? static_cast<size_t>(w) * N1 + ko : static_cast<size_t>(w)) * Nx + kx0 + c;
+    }
+    __device__ __forceinline__ size_t neg(int c, int w) const {
+        const int kx = kx0 + c, wn = w ? L - w : 0;
+        return (d3 ? static_cast<size_t>(wn) * N1 + (ko ? N1 - ko : 0) : static_cast<size_t>(wn)) * Nx + (kx ? Nx - kx : 0);
+    }
+    // -k lies in another column
+    __device__ __forceinline__ bool paired(int c) const { return kx0 + c > 0 && 2 * (kx0 + c) < Nx; }
+    __device__ __forceinline__ int w_signed(int w) const { return w < (L >> 1) ? w : w - L; }
+    __device__ __forceinline__ ModeQ q(const Geo& geo, const float (&qs)[3], int c, int w) const {
+        const int kx = kx0 + c, kxs = kx < (Nx >> 1) ? kx : kx - Nx, kos = ko < (N1 >> 1) ? ko : ko - N1;
+        return d3 ? mode_q(Nx, N1, geo.nz, qs, kxs, kos, w_signed(w)) : mode_q(Nx, N1, 1, qs, kxs, w_signed(w), 0);
+    }
+};
+
+// Column launch of a plan with one field, one channel, one factor and no
+// other explicit terms (Model B): the state, its values at -k and the channel
+// are read together at the top and stay in registers (at most U elements a
+// thread), the operators are read once, and the new state goes straight into
+// the factor's transform.  The general kernel below pays six memory latencies
+// in a row; 96^2 is nothing but that.
+template <int MODE>
+__global__ void __launch_bounds__(1024)
+    mr2_step1_kernel(const DevPlan* __restrict__ plan, const float2* __restrict__ Nin, float2* __restrict__ S,
+                     float2* __restrict__ V, Geo geo, const uint64_t* __restrict__ step_ctr,
+                     uint32_t* __restrict__ flag, int step_off, const float2* __restrict__ tw_g, MrPlan my) {
+    constexpr bool STEP = MODE == MODE_STEP;
+    constexpr int U = kMrPerThread;
+    extern __shared__ float2 smem[];
+    const DevPlan& p = *plan;
+    float qs[3] = {p.qs[0], p.qs[1], p.qs[2]};
+    float dt = p.dt, amp_pair = p.amp_pair, amp_self = p.amp_self;
+    uint32_t key0 = p.key0, key1 = p.key1;
+    int noisy = p.noisy[0], fid = p.fid[0];
+    OpPoly imp = op_poly(p.implicit_op[0]), noi = op_poly(p.noise_op[0]), ch0 = op_poly(p.ch[0].op[0]);
+    const int32_t* lim_g = p.lim[0];
+    uint32_t step = 0;
+    if constexpr (STEP) step = static_cast<uint32_t>(gload_u64(step_ctr)) + static_cast<uint32_t>(step_off);
+
+    // XCD-ordered blocks: neighbouring columns share their cache lines in one L2
+    const MrCols mc(geo, my.n, xcd_block(blockIdx.x, gridDim.x));
+    const int L = mc.L, nl = mc.nl, n = nl * L;
+    const int t = threadIdx.x, T = blockDim.x;
+    float2* const tw = smem;
+    float2* const A = smem + L;
+    float2* const B = A + geo.tc * L;
+    const FastDiv fnl(nl);  // n < 2^21: the LDS holds the lines
+    // this thread's elements (line index fastest: a wave touches neighbouring
+    // kx), the last one again past the end
+    int cu[U], wu[U];
+    float2 v[U], s[U], sn[U], twv[U];
+    int lim[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = min(t + u * T, n - 1);
+        wu[u] = fnl.quo(i);
+        cu[u] = i - wu[u] * nl;
+        if constexpr (STEP) v[u] = gload(Nin + mc.half(cu[u], wu[u]));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) twv[u] = tw_g[min(t + u * T, L - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        s[u] = gload(S + mc.pos(cu[u], wu[u]));
+        sn[u] = gload(S + mc.neg(cu[u], wu[u]));
+    }
+    if constexpr (STEP) {
+        hold(dt), hold(amp_pair), hold(amp_self), hold(key0), hold(key1), hold(noisy), hold(fid), hold(step);
+        hold(imp), hold(noi), hold(ch0);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) hold(qs[i]);
+    const bool kept = mc.kx0 < geo.ncol[0];  // some column holds kept modes (block-uniform)
+    if (kept) {
+        const int kos = min(mc.ko, mc.N1 - mc.ko);
+#pragma unroll
+        for (int u = 0; u < U; ++u) lim[u] = lim_g[(mc.d3 ? kos * mc.NC : 0) + mc.kx0 + cu[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (t + u * T < L) tw[t + u * T] = twv[u];
+    float2* o = A;  // the factor's transform starts here
+    float2* o2 = B;
+    if constexpr (STEP) {
+        // the noise, while the loads above are in flight
+        float2 eta[U];
+        float q2[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) q2[u] = mc.q(geo, qs, cu[u], wu[u]).q2;
+        if (noisy) {
+            const NoiseKey nk{key0, key1, step, fid, amp_pair, amp_self};
+            float D[U];
+            horner_p(noi, q2, D);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                eta[u] = u * T < n ? noise_value(nk, static_cast<uint32_t>(mc.pos(cu[u], wu[u])),
+                                                 static_cast<uint32_t>(mc.neg(cu[u], wu[u])), D[u])
+                                   : make_float2(0.f, 0.f);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (t + u * T < n) A[cu[u] * L + wu[u]] = v[u];
+        __syncthreads();
+        const float2* r = mr_transform<-1>(A, B, tw, my, nl);
+        o = r == A ? B : A;
+        o2 = r == A ? A : B;
+        float M[U], Ai[U];
+        horner_p(ch0, q2, M);
+        horner_p(imp, q2, Ai);
+        float fin = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t + u * T >= n) break;
+            const float2 a = cscale(r[cu[u] * L + wu[u]], M[u]);
+            float2 x = cadd(s[u], cscale(a, dt)), xn = cadd(sn[u], cscale(cconj(a), dt));
+            if (noisy) {
+                x = cadd(x, eta[u]);
+                xn = cadd(xn, cconj(eta[u]));
+            }
+            const float inv = cinv_implicit(dt, make_float2(Ai[u], 0.f)).x;
+            x = cscale(x, inv);
+            xn = cscale(xn, inv);
+            gstore(S + mc.pos(cu[u], wu[u]), x);
+            fin = fmaf(x.x, 0.f, fmaf(x.y, 0.f, fin));
+            if (mc.paired(cu[u])) {
+                gstore(S + mc.neg(cu[u], wu[u]), xn);
+                fin = fmaf(xn.x, 0.f, fmaf(xn.y, 0.f, fin));
+            }
+            s[u] = x;
+            sn[u] = xn;
+        }
+        if (fin != 0.f) atomicOr(flag, 1u);  // a NaN or infinity in the new state
+    }
+    if (!kept) return;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (t + u * T >= n) break;
+        float2 x = s[u];
+        if (mc.paired(cu[u])) x = make_float2(0.5f * (x.x + sn[u].x), 0.5f * (x.y - sn[u].y));
+        const int w = mc.w_signed(wu[u]);
+        o[cu[u] * L + wu[u]] = w * w <= lim[u] ? x : make_float2(0.f, 0.f);
+    }
+    __syncthreads();
+    const float2* r = mr_transform<1>(o, o2, tw, my, nl);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (t + u * T < n) gstore(V + mc.half(cu[u], wu[u]), r[cu[u] * L + wu[u]]);
+}
 
 template <int NF, bool GEN, int MODE>
-__global__ void __launch_bounds__(256)
-    mr2_col_kernel(const DevPlan* __restrict__ plan, Bufs bufs, const uint64_t* __restrict__ step_ctr,
-                   uint32_t* __restrict__ flag, int step_off, const float2* __restrict__ tw_g, MrPlan my, int tc) {
+__global__ void __launch_bounds__(1024)
+    mr2_step_kernel(const DevPlan* __restrict__ plan, Bufs bufs, Geo geo, const uint64_t* __restrict__ step_ctr,
+                    uint32_t* __restrict__ flag, int step_off, const float2* __restrict__ tw_g, MrPlan my) {
+    constexpr bool STEP = MODE == MODE_STEP;
+    constexpr int U = 4;  // loads issued together per thread
+    extern __shared__ float2 smem[];
+    const DevPlan& p = *plan;
+    const MrCols mc(geo, my.n, xcd_block(blockIdx.x, gridDim.x));
+    const int L = mc.L, nl = mc.nl, tc = geo.tc;
+    const int t = threadIdx.x, T = blockDim.x;
+    const int n = nl * L;
+    float2* const tw = smem;
+    float2* const A = smem + L;
+    float2* const B = A + tc * L;
+    float2* const S = B + tc * L;          // [NF][nl][L]
+    float2* const acc = S + NF * tc * L;   // [NF][nl][L]
+    const FastDiv fnl(nl), fL(L);  // n < 2^21: the LDS holds the lines
+    auto hat = [&](int c, int w) { return mc.half(c, w); };
+    auto sat = [&](int c, int w) { return mc.pos(c, w); };
+    // copies between global memory (line index fastest, so that a wave touches
+    // neighbouring kx) and LDS (line c at c L)
+    auto gin = [&](const float2* __restrict__ src, auto at, float2* dst) {
+        for (int i0 = t; i0 < n; i0 += U * T) {
+            float2 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min(i0 + u * T, n - 1), w = fnl.quo(i);
+                v[u] = gload(src + at(i - w * nl, w));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * T, w = fnl.quo(i);
+                if (i < n) dst[(i - w * nl) * L + w] = v[u];
+            }
+        }
+    };
+    float qs[3] = {p.qs[0], p.qs[1], p.qs[2]};
+    auto kq = [&](int c, int w) { return mc.q(geo, qs, c, w); };
+    const int nf = p.nf, nch = p.nch;
+
+    if (STEP && nch > 0) gin(bufs.N[0], hat, A);
+    for (int f = 0; f < nf; ++f) gin(bufs.S[f], sat, S + f * n);
+    for (int i = t; i < L; i += T) tw[i] = tw_g[i];
+    if constexpr (STEP) {
+        for (int i = t; i < nf * n; i += T) acc[i] = make_float2(0.f, 0.f);
+    }
+    __syncthreads();
+
+    // Fourier value of source src at a mode whose fields are v: a dynamic
+    // field's own, or an intermediate's (the operators at -k are the
+    // conjugates of those at k, their coefficients being real)
+    auto value = [&](int src, const float2 (&v)[NF][1], const ModeQ& q, bool neg) -> float2 {
+        if constexpr (GEN) {
+            if (src >= PSS_MAXF) {
+                const DevInterm& I = p.interm[src - PSS_MAXF];
+                auto at = [&](float2 o) { return neg ? cconj(o) : o; };
+                float2 r = make_float2(0.f, 0.f);
+                for (int j = 0; j < I.nsrc; ++j)
+                    r = cadd(r, cmul(at(eval_op<true>(I.op[j], q)), pick(v, I.src[j], 0)));
+                return cmul(r, cinv_implicit(1.f, at(eval_op<true>(I.den, q))));
+            }
+        }
+        return pick(v, src, 0);
+    };
+
+    if constexpr (STEP) {
+        const uint32_t step = static_cast<uint32_t>(gload_u64(step_ctr)) + static_cast<uint32_t>(step_off);
+        // channels: forward transforms of the products, M(q) per mode
+        for (int ch = 0; ch < nch; ++ch) {
+            const DevChannel& C = p.ch[ch];
+            if (ch > 0) {
+                gin(bufs.N[ch], hat, A);
+                __syncthreads();
+            }
+            const float2* r = mr_transform<-1>(A, B, tw, my, nl);
+            for (int i = t; i < n; i += T) {
+                const int c = fL.quo(i), w = i - c * L;
+                const ModeQ q = kq(c, w);
+                for (int o = 0; o < C.nout; ++o) {
+                    float2& d = acc[C.target[o] * n + i];
+                    d = cadd(d, cmul(eval_op<GEN>(C.op[o], q), r[i]));
+                }
+            }
+            __syncthreads();
+        }
+        // linear explicit terms from the step-n state, then the semi-implicit
+        // update with the noise, of k and (paired columns) of -k; S keeps what
+        // the factors take of the new state.  Each element by one thread, the
+        // line index fastest (the state's stores).
+        uint32_t bad = 0;
+        for (int i0 = t; i0 < n; i0 += U * T) {
+            float2 sn[U][NF][1];  // the states at -k
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min(i0 + u * T, n - 1), w = fnl.quo(i);
+                const size_t e = mc.neg(i - w * nl, w);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) sn[u][f][0] = f < nf ? gload(bufs.S[f] + e) : make_float2(0.f, 0.f);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * T;
+                if (i >= n) break;
+                const int w = fnl.quo(i), c = i - w * nl, e = c * L + w;
+                const bool pr = mc.paired(c);
+                const ModeQ q = kq(c, w);
+                const uint32_t lin = static_cast<uint32_t>(sat(c, w)), lneg = static_cast<uint32_t>(mc.neg(c, w));
+                float2 sv[NF][1], a[NF][1], an[NF][1];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    sv[f][0] = f < nf ? S[f * n + e] : make_float2(0.f, 0.f);
+                    a[f][0] = f < nf ? acc[f * n + e] : make_float2(0.f, 0.f);
+                    an[f][0] = cconj(a[f][0]);
+                }
+                for (int d = 0; d < p.nd; ++d) {
+                    const DevDirect& Dd = p.direct[d];
+                    const float2 op = eval_op<GEN>(Dd.op, q);
+                    add_to(a, Dd.target, 0, cmul(op, value(Dd.src, sv, q, false)));
+                    add_to(an, Dd.target, 0, cmul(cconj(op), value(Dd.src, sn[u], q, true)));
+                }
+                static_for<NF>([&](auto FF) {
+                    constexpr int f = decltype(FF)::value;
+                    if (f >= nf) return;
+                    float2 r = cadd(sv[f][0], cscale(a[f][0], p.dt)), rn = cadd(sn[u][f][0], cscale(an[f][0], p.dt));
+                    if (p.noisy[f] != 0) {
+                        const float2 eta = noise_mode<GEN>(p, f, step, lin, lneg, q);
+                        r = cadd(r, eta);
+                        rn = cadd(rn, cconj(eta));
+                    }
+                    const float2 inv = cinv_implicit(p.dt, eval_op<GEN>(p.implicit_op[f], q));
+                    r = cmul(r, inv);
+                    gstore(bufs.S[f] + lin, r);
+                    bool fin = __builtin_isfinite(r.x) && __builtin_isfinite(r.y);
+                    if (pr) {
+                        rn = cmul(rn, cconj(inv));
+                        gstore(bufs.S[f] + lneg, rn);
+                        fin = fin && __builtin_isfinite(rn.x) && __builtin_isfinite(rn.y);
+                        r = make_float2(0.5f * (r.x + rn.x), 0.5f * (r.y - rn.y));
+                    }
+                    if (!fin) bad |= 1u << f;
+                    S[f * n + e] = r;
+                });
+            }
+        }
+        if (bad) atomicOr(flag, bad);
+        __syncthreads();
+    } else {
+        // S: what the factors take of the state
+        for (int i = t; i < n; i += T) {
+            const int w = fnl.quo(i), c = i - w * nl, e = c * L + w;
+            if (!mc.paired(c)) continue;
+            for (int f = 0; f < nf; ++f) {
+                const float2 a = S[f * n + e], b = gload(bufs.S[f] + mc.neg(c, w));
+                S[f * n + e] = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
+            }
+        }
+        __syncthreads();
+    }
+
+    // inverse transforms of the de-aliased factors
+    for (int g = 0; g < p.ng; ++g) {
+        if (mc.kx0 >= geo.ncol[g]) continue;  // every column masked: never read (block-uniform)
+        // the largest kept w^2 of each line
+        const int32_t* lim = p.lim[g] + (mc.d3 ? min(mc.ko, mc.N1 - mc.ko) * mc.NC : 0) + mc.kx0;
+        for (int i = t; i < n; i += T) {
+            const int c = fL.quo(i), w = i - c * L;
+            float2 v = make_float2(0.f, 0.f);
+            if (mc.w_signed(w) * mc.w_signed(w) <= lim[c]) {
+                float2 sv[NF][1];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) sv[f][0] = f < nf ? S[f * n + i] : make_float2(0.f, 0.f);
+                v = value(p.gfield[g], sv, kq(c, w), false);
+            }
+            A[i] = v;
+        }
+        __syncthreads();
+        const float2* r = mr_transform<1>(A, B, tw, my, nl);
+        for (int i = t; i < n; i += T) {
+            const int w = fnl.quo(i), c = i - w * nl;
+            gstore(bufs.V[g] + hat(c, w), r[c * L + w]);
+        }
+        if (g + 1 < p.ng) __syncthreads();
+    }
+}
+
+// Row launch of a step: ROWS = 2 rows per block (one where two do not fit the
+// LDS), as one complex line Z = X1 + i X2
+template <int ROWS, bool ONE>
+__global__ void __launch_bounds__(1024)
+    mr2_prod_kernel(const DevPlan* __restrict__ plan, Bufs bufs, Geo geo, const float2* __restrict__ tw_g, MrPlan mx,
+                    int64_t advance, uint64_t* __restrict__ step_ctr) {
+    constexpr int U = 2;
+    extern __shared__ float2 smem[];
+    const DevPlan& p = *plan;
+    const int Nx = mx.n, NH = Nx >> 1, NC = NH + 1;
+    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    // the block's pair of rows and, of one row, which it is
+    const size_t pair = static_cast<size_t>(ROWS == 2 ? blk : blk >> 1) * NC * 2;
+    const int odd = ROWS == 2 ? 0 : blk & 1;
+    const int t = threadIdx.x, T = blockDim.x;
+    float2* const tw = smem;
+    float2* const A = smem + Nx;
+    float2* const B = smem + 2 * Nx;
+    float* const u = reinterpret_cast<float*>(smem + 3 * Nx);  // [ng][Nx][ROWS]
+    int ng = p.ng, nch = p.nch, np0 = p.ch[0].nprod;
+    float inv_n = p.inv_n, c0 = p.ch[0].prod[0].coef;
+    int pw0 = p.ch[0].prod[0].pow[0];
+    // Z[c] and Z[Nx - c] from column c of both rows (columns from ncol on are
+    // zero); of columns 0 and Nx/2 real space takes the real parts
+    auto gather = [&](const float2* __restrict__ src, int ncol) {
+        for (int c0 = t; c0 < NC; c0 += U * T) {
+            float2 x[U], y[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int c = min(c0 + k * T, NC - 1), cl = c < ncol ? c : 0;
+                const float2* e = src + pair + static_cast<size_t>(cl) * 2;
+                if constexpr (ROWS == 2) {
+                    gload_pair(e, x[k], y[k]);
+                } else {
+                    x[k] = gload(e + odd);
+                    y[k] = make_float2(0.f, 0.f);
+                }
+                if (c >= ncol) x[k] = y[k] = make_float2(0.f, 0.f);
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int c = c0 + k * T;
+                if (c >= NC) break;
+                if (c == 0 || c == NH) {
+                    A[c] = make_float2(x[k].x, y[k].x);
+                } else {
+                    A[c] = make_float2(x[k].x - y[k].y, x[k].y + y[k].x);
+                    A[Nx - c] = make_float2(x[k].x + y[k].y, y[k].x - x[k].y);
+                }
+            }
+        }
+    };
+    // unpack the rows of a transform and store their columns 0 .. Nx/2
+    auto store = [&](const float2* r, float2* __restrict__ dst) {
+        for (int c = t; c < NC; c += T) {
+            const float2 a = r[c], b = r[c == 0 ? 0 : Nx - c];
+            float2* e = dst + pair + static_cast<size_t>(c) * 2;
+            const float2 x1 = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
+            if constexpr (ROWS == 2) {
+                gstore_pair_sel<false>(e, x1, make_float2(0.5f * (a.y + b.y), 0.5f * (b.x - a.x)));
+            } else {
+                gstore(e + odd, x1);
+            }
+        }
+    };
+    gather(bufs.V[0], geo.ncol[0]);
+    for (int i = t; i < Nx; i += T) tw[i] = tw_g[i];
+    hold(ng), hold(nch), hold(np0), hold(inv_n), hold(c0), hold(pw0);
+    if constexpr (ONE) {
+        // one factor and one channel: the products go from one transform's
+        // result straight into the other's input
+        __syncthreads();
+        const float2* r = mr_transform<1>(A, B, tw, mx);
+        float2* const o = r == A ? B : A;
+        float2* const o2 = r == A ? A : B;
+        for (int x = t; x < Nx; x += T) {
+            const float2 z[1] = {cscale(r[x], inv_n)};
+            float2 w = make_float2(0.f, 0.f);
+            for (int k = 0; k < np0; ++k) {
+                const float cf = k == 0 ? c0 : p.ch[0].prod[k].coef;
+                const int pw = k == 0 ? pw0 : p.ch[0].prod[k].pow[0];
+                float2 a[1] = {make_float2(cf, cf)};
+                times_power<0>(a, z, pw);
+                w = cadd(w, a[0]);
+            }
+            if (ROWS == 1) w.y = 0.f;
+            o[x] = w;
+        }
+        __syncthreads();
+        store(mr_transform<-1>(o, o2, tw, mx), bufs.N[0]);
+        if (advance != 0 && blk == 0 && t == 0) *step_ctr += static_cast<uint64_t>(advance);
+        return;
+    }
+    for (int g = 0; g < ng; ++g) {
+        if (g > 0) gather(bufs.V[g], geo.ncol[g]);
+        __syncthreads();
+        const float2* r = mr_transform<1>(A, B, tw, mx);
+        for (int x = t; x < Nx; x += T) {
+            const float2 v = r[x];
+            u[(g * Nx + x) * ROWS] = v.x * inv_n;
+            if constexpr (ROWS == 2) u[(g * Nx + x) * ROWS + 1] = v.y * inv_n;
+        }
+        __syncthreads();
+    }
+    for (int ch = 0; ch < nch; ++ch) {
+        const DevChannel& C = p.ch[ch];
+        for (int x = t; x < Nx; x += T) {
+            float w[2] = {0.f, 0.f};
+            for (int k = 0; k < C.nprod; ++k) {
+                const DevProd& pd = C.prod[k];
+                float a[2] = {pd.coef, pd.coef};
+                for (int g = 0; g < ng; ++g) {
+                    const int pw = pd.pow[g];
+                    if (pw == 0) continue;
+                    float z[ROWS];
+#pragma unroll
+                    for (int j = 0; j < ROWS; ++j) z[j] = u[(g * Nx + x) * ROWS + j];
+                    for (int e = 0; e < pw; ++e) {
+#pragma unroll
+                        for (int j = 0; j < ROWS; ++j) a[j] *= z[j];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < ROWS; ++j) w[j] += a[j];
+            }
+            A[x] = make_float2(w[0], w[1]);
+        }
+        __syncthreads();
+        const float2* r = mr_transform<-1>(A, B, tw, mx);
+        store(r, bufs.N[ch]);
+        if (ch + 1 < nch) __syncthreads();
+    }
+    if (advance != 0 && blk == 0 && t == 0) *step_ctr += static_cast<uint64_t>(advance);
+}
+
+// the transform modes of full spectra
+template <int NF, bool GEN, int MODE>
+__global__ void __launch_bounds__(1024)
+    mr2_col_kernel(const DevPlan* __restrict__ plan, Bufs bufs, const float2* __restrict__ tw_g, MrPlan my, int tc) {
     extern __shared__ float2 smem[];
     const DevPlan& p = *plan;
     // tc neighbouring lines along the last axis: y in 2D (block = kx0 ..
@@ -2431,7 +2923,6 @@ __global__ void __launch_bounds__(256)
     float2* const A = smem + L;
     float2* const B = A + n;
     float2* const S = B + n;          // [NF][tc][L]
-    float2* const acc = S + NF * n;   // [NF][tc][L]
     for (int i = t; i < L; i += T) tw[i] = tw_g[i];
     const FastDiv ftc(tc), fL(L);  // n < 2^21: the LDS holds the lines
     // global element of line c at position w; loads and stores run with the
@@ -2461,14 +2952,14 @@ __global__ void __launch_bounds__(256)
     if constexpr (MODE == MODE_FWD_STORE) {
         gin(bufs.in, A);
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, my, -1, tc);
+        const float2* r = mr_transform<-1>(A, B, tw, my, tc);
         gout(r, bufs.S[bufs.sel]);
         return;
     }
     if constexpr (MODE == MODE_INV_OUT) {
         gin(bufs.S[bufs.sel], A);
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, my, 1, tc);
+        const float2* r = mr_transform<1>(A, B, tw, my, tc);
         gout(r, bufs.out);
         return;
     }
@@ -2489,96 +2980,20 @@ __global__ void __launch_bounds__(256)
         return S[src * n + i];
     };
 
-    if constexpr (MODE == MODE_INTERM_OUT) {
-        for (int i = t; i < n; i += T) {
-            int c, w;
-            lw(i, c, w);
-            A[i] = source(PSS_MAXF + bufs.sel, i, kq(c, w));
-        }
-        __syncthreads();
-        const float2* r = mr_transform(A, B, tw, my, 1, tc);
-        gout(r, bufs.out);
-        return;
+    // MODE_INTERM_OUT
+    for (int i = t; i < n; i += T) {
+        int c, w;
+        lw(i, c, w);
+        A[i] = source(PSS_MAXF + bufs.sel, i, kq(c, w));
     }
-
-    if constexpr (MODE == MODE_STEP) {
-        const uint32_t step = static_cast<uint32_t>(gload_u64(step_ctr)) + static_cast<uint32_t>(step_off);
-        for (int i = t; i < nf * n; i += T) acc[i] = make_float2(0.f, 0.f);
-        // channels: forward transforms of the products, M(q) per mode
-        for (int ch = 0; ch < p.nch; ++ch) {
-            const DevChannel& C = p.ch[ch];
-            gin(bufs.N[ch], A);
-            __syncthreads();
-            const float2* r = mr_transform(A, B, tw, my, -1, tc);
-            for (int i = t; i < n; i += T) {
-                int c, w;
-                lw(i, c, w);
-                const ModeQ q = kq(c, w);
-                for (int o = 0; o < C.nout; ++o) {
-                    float2& d = acc[C.target[o] * n + i];
-                    d = cadd(d, cmul(eval_op<GEN>(C.op[o], q), r[i]));
-                }
-            }
-            __syncthreads();
-        }
-        // linear explicit terms, then the semi-implicit update with the noise
-        for (int i = t; i < n && p.nd > 0; i += T) {
-            int c, w;
-            lw(i, c, w);
-            const ModeQ q = kq(c, w);
-            for (int d = 0; d < p.nd; ++d) {
-                const DevDirect& Dd = p.direct[d];
-                float2& a = acc[Dd.target * n + i];
-                a = cadd(a, cmul(eval_op<GEN>(Dd.op, q), source(Dd.src, i, q)));
-            }
-        }
-        __syncthreads();
-        uint32_t bad = 0;
-        for (int i = t; i < n; i += T) {
-            int c, w;
-            lw(i, c, w);
-            const int kx = kx0 + c;
-            const ModeQ q = kq(c, w);
-            const uint32_t lin = static_cast<uint32_t>(at(c, w));
-            // the linear index of the mode -k (each index modulo its size)
-            const size_t wn = w ? L - w : 0;
-            const size_t neg_line = d3 ? wn * N1 + static_cast<size_t>(ko ? N1 - ko : 0) : wn;
-            const uint32_t lneg = static_cast<uint32_t>(neg_line * Nx + static_cast<size_t>(kx ? Nx - kx : 0));
-            for (int f = 0; f < nf; ++f) {
-                float2 r = cadd(S[f * n + i], cscale(acc[f * n + i], p.dt));
-                if (p.noisy[f] != 0) r = cadd(r, noise_mode<GEN>(p, f, step, lin, lneg, q));
-                r = cmul(r, cinv_implicit(p.dt, eval_op<GEN>(p.implicit_op[f], q)));
-                S[f * n + i] = r;
-                if (!(__builtin_isfinite(r.x) && __builtin_isfinite(r.y))) bad |= 1u << f;
-            }
-        }
-        if (bad) atomicOr(flag, bad);
-        __syncthreads();
-        for (int f = 0; f < nf; ++f) gout(S + f * n, bufs.S[f]);
+    __syncthreads();
+    const float2* r = mr_transform<1>(A, B, tw, my, tc);
+    gout(r, bufs.out);
     }
-
-    // MODE_STEP and MODE_PROLOGUE: inverse transforms of the de-aliased
-    // factors from the (new) state
-    for (int g = 0; g < p.ng; ++g) {
-        const DevMask& mk = p.mask[g];
-        for (int i = t; i < n; i += T) {
-            int c, w;
-            lw(i, c, w);
-            A[i] = (d3 ? mask_keep(mk, kxs(c), kos, ws(w)) : mask_keep(mk, kxs(c), ws(w), 0))
-                       ? source(p.gfield[g], i, kq(c, w))
-                       : make_float2(0.f, 0.f);
-        }
-        __syncthreads();
-        const float2* r = mr_transform(A, B, tw, my, 1, tc);
-        gout(r, bufs.V[g]);
-        __syncthreads();
-    }
-}
 
 template <int MODE>
-__global__ void __launch_bounds__(256)
-    mr2_row_kernel(const DevPlan* __restrict__ plan, Bufs bufs, const float2* __restrict__ tw_g, MrPlan mx,
-                   int64_t advance, uint64_t* __restrict__ step_ctr) {
+__global__ void __launch_bounds__(1024)
+    mr2_row_kernel(const DevPlan* __restrict__ plan, Bufs bufs, const float2* __restrict__ tw_g, MrPlan mx) {
     extern __shared__ float2 smem[];
     const DevPlan& p = *plan;
     const int Nx = mx.n;
@@ -2587,87 +3002,64 @@ __global__ void __launch_bounds__(256)
     float2* const tw = smem;
     float2* const A = smem + Nx;
     float2* const B = smem + 2 * Nx;
-    float* const u = reinterpret_cast<float*>(smem + 3 * Nx);  // [ng][Nx]
     for (int i = t; i < Nx; i += T) tw[i] = tw_g[i];
 
     if constexpr (MODE == MODE_R2C_IN) {
         for (int x = t; x < Nx; x += T) A[x] = make_float2(bufs.real_in[row + x], 0.f);
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, mx, -1);
+        const float2* r = mr_transform<-1>(A, B, tw, mx);
         for (int k = t; k < Nx; k += T) gstore(bufs.out + row + k, r[k]);
         return;
     }
     if constexpr (MODE == MODE_C2R_OUT) {
         for (int k = t; k < Nx; k += T) A[k] = gload(bufs.in + row + k);
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, mx, 1);
+        const float2* r = mr_transform<1>(A, B, tw, mx);
         for (int x = t; x < Nx; x += T) bufs.real_out[row + x] = r[x].x * p.inv_n;
         return;
     }
-    // MODE_STEP: factors to real space, products, forward x transforms
-    for (int g = 0; g < p.ng; ++g) {
-        for (int k = t; k < Nx; k += T) A[k] = gload(bufs.V[g] + row + k);
-        __syncthreads();
-        const float2* r = mr_transform(A, B, tw, mx, 1);
-        for (int x = t; x < Nx; x += T) u[g * Nx + x] = r[x].x * p.inv_n;
-        __syncthreads();
-    }
-    for (int ch = 0; ch < p.nch; ++ch) {
-        const DevChannel& C = p.ch[ch];
-        for (int x = t; x < Nx; x += T) {
-            float w = 0.f;
-            for (int k = 0; k < C.nprod; ++k) {
-                const DevProd& pd = C.prod[k];
-                float a = pd.coef;
-                for (int g = 0; g < p.ng; ++g)
-                    for (int e = 0; e < pd.pow[g]; ++e) a *= u[g * Nx + x];
-                w += a;
-            }
-            A[x] = make_float2(w, 0.f);
-        }
-        __syncthreads();
-        const float2* r = mr_transform(A, B, tw, mx, -1);
-        for (int k = t; k < Nx; k += T) gstore(bufs.N[ch] + row + k, r[k]);
-        __syncthreads();
-    }
-    if (advance != 0 && blockIdx.x == 0 && t == 0) *step_ctr += static_cast<uint64_t>(advance);
 }
 
 // 3D: transforms along y of the arrays of ya (in place allowed: a line is
-// read whole before it is written), one block per (kx, z) line
-__global__ void __launch_bounds__(256)
-    mr3_ypass_kernel(const DevPlan* __restrict__ plan, YArgs ya, const float2* __restrict__ tw_g, MrPlan my, int sign,
-                     int tc) {
+// read whole before it is written), tc lines of neighbouring kx at one z per
+// block; half spectra (only columns below ya.ncol are read later) or full ones
+template <int SG, bool FULL>
+__global__ void __launch_bounds__(1024)
+    mr3_ypass_kernel(YArgs ya, Geo geo, const float2* __restrict__ tw_g, MrPlan my, int tc) {
     extern __shared__ float2 smem[];
-    const DevPlan& p = *plan;
-    const int Nx = p.n[0], Ny = my.n;
-    const int nxb = Nx / tc;
+    const int Nx = geo.nx, Ny = my.n, NK = FULL ? Nx : (Nx >> 1) + 1;
+    const int nxb = (NK + tc - 1) / tc;
     const int blk = xcd_block(blockIdx.x, gridDim.x);  // as in the column kernel
-    const int kx0 = (blk % nxb) * tc, z = blk / nxb;
-    const size_t base = static_cast<size_t>(z) * Nx * Ny + kx0;
+    const int z = blk / nxb, kx0 = (blk - z * nxb) * tc;
+    const int nl = min(tc, NK - kx0);
     const int t = threadIdx.x, T = blockDim.x;
-    const int n = tc * Ny;
-    const FastDiv ftc(tc);
+    const int n = nl * Ny;
+    const FastDiv fnl(nl);
     float2* const tw = smem;
     float2* const A = smem + Ny;
-    float2* const B = A + n;
+    float2* const B = A + tc * Ny;
+    auto at = [&](int c, int y) {
+        return FULL ? (static_cast<size_t>(z) * Ny + y) * Nx + kx0 + c
+                    : ((static_cast<size_t>(z) * (Ny >> 1) + (y >> 1)) * NK + kx0 + c) * 2 + (y & 1);
+    };
     for (int i = t; i < Ny; i += T) tw[i] = tw_g[i];
     for (int a = 0; a < ya.n; ++a) {
+        if (!FULL && kx0 >= ya.ncol[a]) continue;  // block-uniform
         for (int i = t; i < n; i += T) {
-            const int y = ftc.quo(i), c = i - y * tc;
-            A[c * Ny + y] = gload(ya.src[a] + base + c + static_cast<size_t>(y) * Nx);
+            const int y = fnl.quo(i), c = i - y * nl;
+            A[c * Ny + y] = gload(ya.src[a] + at(c, y));
         }
         __syncthreads();
-        const float2* r = mr_transform(A, B, tw, my, sign, tc);
+        const float2* r = mr_transform<SG>(A, B, tw, my, nl);
         for (int i = t; i < n; i += T) {
-            const int y = ftc.quo(i), c = i - y * tc;
-            gstore(ya.dst[a] + base + c + static_cast<size_t>(y) * Nx, r[c * Ny + y]);
+            const int y = fnl.quo(i), c = i - y * nl;
+            gstore(ya.dst[a] + at(c, y), r[c * Ny + y]);
         }
         __syncthreads();
     }
 }
 
-hipError_t launch_mr3_ypass(int sign, const YArgs& ya, const LaunchArgs& a) {
+hipError_t launch_mr3_ypass(int sign, const YArgs& ya, bool full, const LaunchArgs& a) {
     MrPlan my{};
     if (!mr_plan(a.ny, &my) || a.dim != 3) return hipErrorInvalidValue;
     if (ya.n <= 0) return hipSuccess;
@@ -2675,8 +3067,21 @@ hipError_t launch_mr3_ypass(int sign, const YArgs& ya, const LaunchArgs& a) {
     if (tc < 1 || a.nx % tc != 0) return hipErrorInvalidValue;
     const size_t lds = mr3_ypass_lds_bytes(my.n, tc);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(mr3_ypass_kernel, dim3((a.nx / tc) * a.nz), dim3(256), lds, a.stream, a.plan, ya, a.tw_y, my,
-                       sign, tc);
+    const int nk = full ? a.nx : a.nx / 2 + 1;
+    const dim3 grid(((nk + tc - 1) / tc) * a.nz), block(mr_threads(tc * my.n));
+#define PSS_Y3(SG, F) hipLaunchKernelGGL((mr3_ypass_kernel<SG, F>), grid, block, lds, a.stream, ya, a.geo, a.tw_y, my, tc)
+    if (sign < 0) {
+        if (full)
+            PSS_Y3(-1, true);
+        else
+            PSS_Y3(-1, false);
+    } else {
+        if (full)
+            PSS_Y3(1, true);
+        else
+            PSS_Y3(1, false);
+    }
+#undef PSS_Y3
     return hipGetLastError();
 }
 
@@ -2688,14 +3093,23 @@ hipError_t launch_mr2_col(int mode, int nf, const LaunchArgs& a) {
     if (tc < 1 || a.nx % tc != 0) return hipErrorInvalidValue;
     const size_t lds = mr2_col_lds_bytes(my.n, NF, tc);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const dim3 grid((a.nx / tc) * (a.dim == 3 ? a.ny : 1)), block(256);
-    const bool gen = a.general || mode == MODE_INTERM_OUT;
-#define PSS_C2(NFV, G, M)                                                                                    \
-    hipLaunchKernelGGL((mr2_col_kernel<NFV, G, M>), grid, block, lds, a.stream, a.plan, a.bufs, a.step_ctr,  \
-                       a.flag, a.step_off, a.tw_u, my, tc)
+    const int other = a.dim == 3 ? a.ny : 1;
+    const dim3 full((a.nx / tc) * other), half(((a.nx / 2 + tc) / tc) * other), block(mr_threads(tc * my.n));
+    const bool gen = a.general;
+#define PSS_C2(NFV, G, M)                                                                                         \
+    hipLaunchKernelGGL((mr2_step_kernel<NFV, G, M>), half, block, lds, a.stream, a.plan, a.bufs, a.geo, a.step_ctr, \
+                       a.flag, a.step_off, a.tw_u, my)
+    // one element per thread and load slot: the lines of the block fit
+    const bool one = a.simple && tc * my.n <= kMrPerThread * static_cast<int>(block.x);
+#define PSS_C1(M)                                                                                              \
+    hipLaunchKernelGGL((mr2_step1_kernel<M>), half, block, lds1, a.stream, a.plan, a.bufs.N[0], a.bufs.S[0],   \
+                       a.bufs.V[0], a.geo, a.step_ctr, a.flag, a.step_off, a.tw_u, my)
+    const size_t lds1 = mr3_ypass_lds_bytes(my.n, tc);  // twiddles and two buffers
 #define PSS_C2F(M)                       \
     do {                                 \
-        if (NF == 1) {                   \
+        if (one) {                       \
+            PSS_C1(M);                   \
+        } else if (NF == 1) {            \
             if (gen)                     \
                 PSS_C2(1, true, M);      \
             else                         \
@@ -2712,14 +3126,25 @@ hipError_t launch_mr2_col(int mode, int nf, const LaunchArgs& a) {
                 PSS_C2(4, false, M);     \
         }                                \
     } while (0)
+#define PSS_CT(NFV, G, M) \
+    hipLaunchKernelGGL((mr2_col_kernel<NFV, G, M>), full, block, lds, a.stream, a.plan, a.bufs, a.tw_u, my, tc)
     switch (mode) {
         case MODE_STEP: PSS_C2F(MODE_STEP); break;
         case MODE_PROLOGUE: PSS_C2F(MODE_PROLOGUE); break;
-        case MODE_INTERM_OUT: PSS_C2F(MODE_INTERM_OUT); break;
-        case MODE_FWD_STORE: PSS_C2(1, false, MODE_FWD_STORE); break;
-        case MODE_INV_OUT: PSS_C2(1, false, MODE_INV_OUT); break;
+        case MODE_INTERM_OUT:
+            if (NF == 1)
+                PSS_CT(1, true, MODE_INTERM_OUT);
+            else if (NF == 2)
+                PSS_CT(2, true, MODE_INTERM_OUT);
+            else
+                PSS_CT(4, true, MODE_INTERM_OUT);
+            break;
+        case MODE_FWD_STORE: PSS_CT(1, false, MODE_FWD_STORE); break;
+        case MODE_INV_OUT: PSS_CT(1, false, MODE_INV_OUT); break;
         default: return hipErrorInvalidValue;
     }
+#undef PSS_CT
+#undef PSS_C1
 #undef PSS_C2F
 #undef PSS_C2
     return hipGetLastError();
@@ -2728,22 +3153,35 @@ hipError_t launch_mr2_col(int mode, int nf, const LaunchArgs& a) {
 hipError_t launch_mr2_row(int mode, const LaunchArgs& a) {
     MrPlan mx{};
     if (!mr_plan(a.nx, &mx)) return hipErrorInvalidValue;
-    const size_t lds = mr2_row_lds_bytes(mx.n, a.ng);
+    const int rows = a.ny * (a.dim == 3 ? a.nz : 1);
+    const int per = mode == MODE_STEP ? mr2_rows(mx.n, a.ng) : 1;
+    const size_t lds = mr2_row_lds_bytes(mx.n, mode == MODE_STEP ? a.ng : 1, per);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const dim3 grid(a.ny * (a.dim == 3 ? a.nz : 1)), block(256);
+    const dim3 grid(rows / per), block(mr_threads(mx.n));
     uint64_t* ctr = const_cast<uint64_t*>(a.step_ctr);
     switch (mode) {
         case MODE_STEP:
-            hipLaunchKernelGGL(mr2_row_kernel<MODE_STEP>, grid, block, lds, a.stream, a.plan, a.bufs, a.tw_x, mx,
-                               a.advance, ctr);
+#define PSS_PR(R, ONE)                                                                                         \
+    hipLaunchKernelGGL((mr2_prod_kernel<R, ONE>), grid, block, lds, a.stream, a.plan, a.bufs, a.geo, a.tw_x, mx, \
+                       a.advance, ctr)
+            if (per == 2) {
+                if (a.simple)
+                    PSS_PR(2, true);
+                else
+                    PSS_PR(2, false);
+            } else {
+                if (a.simple)
+                    PSS_PR(1, true);
+                else
+                    PSS_PR(1, false);
+            }
+#undef PSS_PR
             break;
         case MODE_R2C_IN:
-            hipLaunchKernelGGL(mr2_row_kernel<MODE_R2C_IN>, grid, block, lds, a.stream, a.plan, a.bufs, a.tw_x, mx,
-                               int64_t{0}, ctr);
+            hipLaunchKernelGGL(mr2_row_kernel<MODE_R2C_IN>, grid, block, lds, a.stream, a.plan, a.bufs, a.tw_x, mx);
             break;
         case MODE_C2R_OUT:
-            hipLaunchKernelGGL(mr2_row_kernel<MODE_C2R_OUT>, grid, block, lds, a.stream, a.plan, a.bufs, a.tw_x, mx,
-                               int64_t{0}, ctr);
+            hipLaunchKernelGGL(mr2_row_kernel<MODE_C2R_OUT>, grid, block, lds, a.stream, a.plan, a.bufs, a.tw_x, mx);
             break;
         default: return hipErrorInvalidValue;
     }
@@ -2752,29 +3190,36 @@ hipError_t launch_mr2_row(int mode, const LaunchArgs& a) {
 
 hipError_t mr2_setup() {
     const int lds = 160 * 1024;
-#define PSS_C2A(NFV, G, M)                                                                                     \
-    if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mr2_col_kernel<NFV, G, M>),          \
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds))                   \
+#define PSS_LDS(...)                                                                     \
+    if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&(__VA_ARGS__)), \
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds)) \
         return e;
-#define PSS_C2B(M) PSS_C2A(1, false, M) PSS_C2A(1, true, M) PSS_C2A(2, false, M) PSS_C2A(2, true, M) \
-    PSS_C2A(4, false, M) PSS_C2A(4, true, M)
+#define PSS_C2B(M)                                                                                     \
+    PSS_LDS(mr2_step_kernel<1, false, M>) PSS_LDS(mr2_step_kernel<1, true, M>)                         \
+    PSS_LDS(mr2_step_kernel<2, false, M>) PSS_LDS(mr2_step_kernel<2, true, M>)                         \
+    PSS_LDS(mr2_step_kernel<4, false, M>) PSS_LDS(mr2_step_kernel<4, true, M>)
     PSS_C2B(MODE_STEP)
     PSS_C2B(MODE_PROLOGUE)
-    PSS_C2B(MODE_INTERM_OUT)
-    PSS_C2A(1, false, MODE_FWD_STORE)
-    PSS_C2A(1, false, MODE_INV_OUT)
 #undef PSS_C2B
-#undef PSS_C2A
-#define PSS_R2A(M)                                                                                             \
-    if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mr2_row_kernel<M>),                  \
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds))                   \
-        return e;
-    PSS_R2A(MODE_STEP)
-    PSS_R2A(MODE_R2C_IN)
-    PSS_R2A(MODE_C2R_OUT)
-#undef PSS_R2A
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&mr3_ypass_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    PSS_LDS(mr2_col_kernel<1, true, MODE_INTERM_OUT>)
+    PSS_LDS(mr2_col_kernel<2, true, MODE_INTERM_OUT>)
+    PSS_LDS(mr2_col_kernel<4, true, MODE_INTERM_OUT>)
+    PSS_LDS(mr2_col_kernel<1, false, MODE_FWD_STORE>)
+    PSS_LDS(mr2_col_kernel<1, false, MODE_INV_OUT>)
+    PSS_LDS(mr2_prod_kernel<1, false>)
+    PSS_LDS(mr2_prod_kernel<2, false>)
+    PSS_LDS(mr2_prod_kernel<1, true>)
+    PSS_LDS(mr2_prod_kernel<2, true>)
+    PSS_LDS(mr2_step1_kernel<MODE_STEP>)
+    PSS_LDS(mr2_step1_kernel<MODE_PROLOGUE>)
+    PSS_LDS(mr2_row_kernel<MODE_R2C_IN>)
+    PSS_LDS(mr2_row_kernel<MODE_C2R_OUT>)
+    PSS_LDS(mr3_ypass_kernel<-1, false>)
+    PSS_LDS(mr3_ypass_kernel<-1, true>)
+    PSS_LDS(mr3_ypass_kernel<1, false>)
+    PSS_LDS(mr3_ypass_kernel<1, true>)
+#undef PSS_LDS
+    return hipSuccess;
 }
 #endif  // PSS_COMMON
 

@@ -114,7 +114,7 @@ struct DevPlan {
     int32_t gfield[PSS_MAXG];  // factor slot -> dynamic field, or PSS_MAXF + intermediate
     // per factor slot, the largest kept (mode index)^2 along the update axis
     // (-1: none) of the line with fixed indices |kx|, |ky| (0 in 2D), at
-    // |ky| (Nx/2 + 1) + |kx|: power-of-two 2D and 3D lattices
+    // |ky| (Nx/2 + 1) + |kx|: 2D and 3D lattices
     const int32_t* lim[PSS_MAXG];
     DevMask mask[PSS_MAXG];    // per factor slot
     DevOp implicit_op[PSS_MAXF];

@@ -455,7 +455,7 @@ int32_t line_lim(const pss::DevMask& mk, int ndim, int kx, int ky, int L) {
 // then out of the kernels.
 pss_status upload_limits(pss_ctx* c) {
     pss::DevPlan& P = c->plan;
-    if (c->ndim == 1 || c->mixed || P.ng == 0) return PSS_OK;
+    if (c->ndim == 1 || P.ng == 0) return PSS_OK;
     const int nkx = c->n[0] / 2 + 1, nky = c->ndim == 3 ? c->n[1] / 2 + 1 : 1;
     std::vector<int32_t> tab;
     for (int g = 0; g < P.ng; ++g) {
@@ -740,7 +740,10 @@ pss_status choose_geometry(pss_ctx* c) {
     g.nx = nx;
     g.ny = ny;
     g.nz = nz;
-    for (int i = 0; i < c->plan.ng; ++i) g.ncol[i] = c->plan.mask[i].ncol;
+    // columns kx < ncol hold kept modes (half spectra of mixed-radix lattices:
+    // kx = Nx/2 is a column of its own, kept only without de-aliasing)
+    for (int i = 0; i < c->plan.ng; ++i)
+        g.ncol[i] = c->mixed && c->plan.mask[i].shape == 2 ? nx / 2 + 1 : c->plan.mask[i].ncol;
     if (c->ndim == 1) {
         // one block holds the line, 4 points per thread (no tunable geometry)
         c->lu = nx;
@@ -766,17 +769,22 @@ pss_status choose_geometry(pss_ctx* c) {
         return PSS_OK;
     }
     if (c->mixed) {
-        // spectra in LDS, one block per x row; the column launch (and the 3D
-        // y pass) takes tc lines of neighbouring kx per block.  One line per
-        // block is the default: the blocks are XCD-ordered, so neighbouring
-        // columns share their cache lines in one L2, and the smaller LDS
-        // footprint keeps more blocks per CU (960^2 Model B: 54.2, 56.7 and
-        // 73.5 us per step at tc = 1, 2, 4)
+        // lines in LDS, a pair of x rows per block; the column launch (and the
+        // 3D y pass) takes tc (py) lines of neighbouring kx per block.  Two
+        // where that still leaves enough blocks: the lines of a block share the
+        // cache lines of their strided accesses (960^2 Model B: 32.3, 30.2 and
+        // 30.7 us per step at tc = 1, 2, 4; 1500^2 57.6, 56.5; 120^3 67.9, 59.1,
+        // 57.4, and 55.0 with py = 2), one on small lattices (96^2: 14.8, 15.2).
         c->lu = c->ndim == 3 ? nz : ny;
         const int NF = nf <= 1 ? 1 : (nf == 2 ? 2 : 4);
-        auto fits1 = [&](auto bytes) { return bytes(1) <= 160 * 1024 ? 1 : 0; };
-        g.tc = fits1([&](int tc) { return pss::mr2_col_lds_bytes(c->lu, NF, tc); });
-        g.py = c->ndim == 3 ? fits1([&](int tc) { return pss::mr3_ypass_lds_bytes(ny, tc); }) : 1;
+        const int64_t lines_u = static_cast<int64_t>(nx / 2 + 1) * (c->ndim == 3 ? ny : 1);
+        auto fits = [&](int64_t lines, int L, auto bytes) {
+            if (bytes(1) > 160 * 1024) return 0;
+            return lines >= 400 && 2 * L <= 4096 && bytes(2) <= 80 * 1024 ? 2 : 1;
+        };
+        g.tc = fits(lines_u, c->lu, [&](int tc) { return pss::mr2_col_lds_bytes(c->lu, NF, tc); });
+        g.py = c->ndim == 3 ? fits(static_cast<int64_t>(nx / 2 + 1) * nz, ny,
+                                   [&](int tc) { return pss::mr3_ypass_lds_bytes(ny, tc); }) : 1;
         // pss_tuning_set may force either (a divisor of Nx that fits)
         auto forced = [&](const char* key, int& v, auto bytes) {
             auto it = c->tune.find(key);
@@ -792,10 +800,10 @@ pss_status choose_geometry(pss_ctx* c) {
         g.to = 1;
         g.pu = g.px = 4;
         g.ntile = ncols;
-        g.nublk = (nx / std::max(g.tc, 1)) * (c->ndim == 3 ? ny : 1);
-        g.nrowblk = ny * nz;
-        g.rb = 2;
-        const size_t lr = pss::mr2_row_lds_bytes(nx, c->plan.ng);
+        g.nublk = ((nx / 2 + std::max(g.tc, 1)) / std::max(g.tc, 1)) * (c->ndim == 3 ? ny : 1);
+        g.rb = pss::mr2_rows(nx, c->plan.ng);
+        g.nrowblk = ny * nz / g.rb;
+        const size_t lr = pss::mr2_row_lds_bytes(nx, c->plan.ng, 1);
         if (g.tc == 0 || g.py == 0 || lr > 160 * 1024)
             return fail(PSS_E_UNSUPPORTED, "lattice needs more LDS than a workgroup has (%zu, %zu bytes)",
                         pss::mr2_col_lds_bytes(c->lu, NF, 1), lr);
@@ -966,6 +974,7 @@ pss::LaunchArgs args(pss_ctx* c, int step_off = 0) {
     a.plans = c->d_plan;
     a.nmem = 1;
     a.general = c->plan.general != 0;
+    a.simple = !a.general && c->plan.nf == 1 && c->plan.nch == 1 && c->plan.ng == 1 && c->plan.nd == 0;
     a.step_off = step_off;
     a.tw_u = c->d_tw_u;
     a.tw_x = c->d_tw_x;
@@ -1020,14 +1029,16 @@ hipError_t y_forward_channels(pss_ctx* c) {
 
 // 3D mixed-radix lattices: y transforms (sign -1 forward, +1 inverse) of n
 // arrays in place
-hipError_t mr_ypass(pss_ctx* c, int sign, float2* const* arrs, int n) {
+hipError_t mr_ypass(pss_ctx* c, int sign, float2* const* arrs, int n, bool full = false) {
     pss::YArgs ya{};
     ya.n = n;
     for (int i = 0; i < n; ++i) {
         ya.src[i] = arrs[i];
         ya.dst[i] = arrs[i];
+        // inverse passes take factors, whose masked columns are never read
+        ya.ncol[i] = sign > 0 && !full ? c->geo.ncol[i] : c->n[0] / 2 + 1;
     }
-    return pss::launch_mr3_ypass(sign, ya, args(c));
+    return pss::launch_mr3_ypass(sign, ya, full, args(c));
 }
 
 bool has_frames(const pss_ctx* c) {
@@ -1316,7 +1327,7 @@ pss_status forward_to_state(pss_ctx* c, int field) {
         a.bufs.real_in = c->d_real;
         a.bufs.out = c->d_tmp;
         HIP_TRY(pss::launch_mr2_row(pss::MODE_R2C_IN, a));
-        if (c->ndim == 3) HIP_TRY(mr_ypass(c, -1, &c->d_tmp, 1));
+        if (c->ndim == 3) HIP_TRY(mr_ypass(c, -1, &c->d_tmp, 1, true));
         a.bufs.in = c->d_tmp;
         a.bufs.sel = field;
         HIP_TRY(pss::launch_mr2_col(pss::MODE_FWD_STORE, 1, a));
@@ -1354,7 +1365,7 @@ pss_status state_to_real(pss_ctx* c, int field) {
         a.bufs.sel = field;
         a.bufs.out = c->d_tmp;
         HIP_TRY(pss::launch_mr2_col(pss::MODE_INV_OUT, 1, a));
-        if (c->ndim == 3) HIP_TRY(mr_ypass(c, 1, &c->d_tmp, 1));
+        if (c->ndim == 3) HIP_TRY(mr_ypass(c, 1, &c->d_tmp, 1, true));
         a.bufs.in = c->d_tmp;
         a.bufs.real_out = c->d_real;
         HIP_TRY(pss::launch_mr2_row(pss::MODE_C2R_OUT, a));
@@ -1391,7 +1402,7 @@ pss_status interm_to_real(pss_ctx* c, int i) {
         a.bufs.sel = i;
         a.bufs.out = c->d_tmp;
         HIP_TRY(pss::launch_mr2_col(pss::MODE_INTERM_OUT, static_cast<int>(c->fields.size()), a));
-        if (c->ndim == 3) HIP_TRY(mr_ypass(c, 1, &c->d_tmp, 1));
+        if (c->ndim == 3) HIP_TRY(mr_ypass(c, 1, &c->d_tmp, 1, true));
         a.bufs.in = c->d_tmp;
         a.bufs.real_out = c->d_real;
         HIP_TRY(pss::launch_mr2_row(pss::MODE_C2R_OUT, a));
@@ -2494,8 +2505,12 @@ pss_status pss_kernel_bytes(pss_ctx* c, int32_t which, double* bytes) {
         *bytes = 2 * arr * nf;
         return PSS_OK;
     }
-    if (c->mixed) {  // full arrays: channels in, state in/out, factors out; factors in, channels out
-        *bytes = which == 0 ? arr * (P.nch + 2 * nf + P.ng) : arr * (P.ng + P.nch);
+    if (c->mixed) {  // half spectra of the channels and the kept factor columns, the state in full
+        const double half = 8.0 * (c->n[0] / 2 + 1) * lines;
+        double fac = 0;
+        for (int g = 0; g < P.ng; ++g) fac += 8.0 * c->geo.ncol[g] * lines;
+        *bytes = which == 0 ? half * P.nch + 2 * arr * nf + fac : (which == 1 ? fac + half * P.nch
+                                                                : (which == 2 ? 2 * fac : 2 * half * P.nch));
         return PSS_OK;
     }
     switch (which) {

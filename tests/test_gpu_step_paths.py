@@ -58,3 +58,22 @@ def test_long_lines(n):
     for tune in ({}, {"pu" if n[1] > n[0] else "px": 16}):
         _, real = _run(n, 5, **tune)
         assert np.max(np.abs(real - want)) <= 2e-6, tune
+
+
+# mixed-radix steps on half spectra: odd line pairs, every radix of the passes
+# (2 3 4 5 6 8 9 10 12 15 16 among these sizes), blocks of one and two lines
+# with a ragged last block, and no de-aliasing (column Nx/2 is kept)
+@pytest.mark.parametrize("n", [(12, 10), (18, 50), (162, 20), (90, 96), (240, 30), (10, 2048), (1500, 12), (24, 10, 18),
+                               (16, 30, 12), (800, 12, 8)])
+@pytest.mark.parametrize("dealias", [pss.DEALIAS_TWO_THIRDS, pss.DEALIAS_NONE])
+def test_mixed_radix_steps(n, dealias):
+    lat = pss.Lattice(n, dt=0.01, seed=11, dealias=dealias)
+    f, _ = pss.model_b(lat, a=-1.0, b=1.0, k=1.0, D=0.01)
+    lat.init_uniform(f, -0.1, 0.1)
+    lat.step(5)
+    rule = {pss.DEALIAS_TWO_THIRDS: om.DEALIAS_TWO_THIRDS, pss.DEALIAS_NONE: om.DEALIAS_NONE}[dealias]
+    m = om.model_b(OLattice(*n), 0.01, a=-1.0, b=1.0, k=1.0, D=0.01, seed=11, dealias=rule)
+    m.init_uniform(0, -0.1, 0.1)
+    m.step(5)
+    got = lat.download(f)
+    assert np.max(np.abs(got - m.real(0).reshape(got.shape))) <= 2e-6
