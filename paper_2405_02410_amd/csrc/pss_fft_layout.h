@@ -13,6 +13,26 @@ namespace pss {
 // kernels, where the pad's address registers would cost occupancy)
 constexpr int kFftPad = PSS_FFT_PAD;
 
+// D(t): the first output index that thread t of L/P holds after a transform
+// of a line of L (LineFFT::drev, pss_fft.h), on the host
+inline int fft_drev(int L, int P, int t) {
+    int M = 1;
+    while (M * P <= L) M *= P;
+    int Ls = L, G = L / P, R = L / M > 1 ? L / M : P, d = 0, mul = 1;
+    while (Ls > R) {
+        const int Gn = G / R;
+        if (G > 1) {
+            d += mul * (t / Gn);
+            mul *= R;
+            t &= Gn - 1;
+        }
+        Ls /= R;
+        G /= R;
+        R = P;
+    }
+    return d;
+}
+
 // elements of one exchange region of a line of L points, padded by shift `pads`
 constexpr bool fft_padded(int, int pads) { return pads > 0; }
 constexpr int fft_region(int L, int pads = kFftPad) { return fft_padded(L, pads) ? L + (L >> pads) : L; }

@@ -23,6 +23,10 @@ enum {
     MODE_ADJCOL = 9,     // adjoint column kernel: one reverse step
     MODE_ADJFIN = 10,    // adjoint column kernel: g_0 from the last reverse step
     MODE_INTERM_OUT = 11,  // update kernel: inverse transform of intermediate `sel` into `out`
+    // boundary frames, 2D lattices of one field:
+    MODE_FRAME_STEP = 12,  // update kernel: one time step, the new state's inverse transform into `out` (not stored)
+    MODE_FRAME_ROW = 13,   // x kernel: `in` to real space, frame values (frame_rows), back into `out`
+    MODE_FRAME_FWD = 14,   // update kernel: forward transform of `in`, stored as the state, then MODE_PROLOGUE
 };
 
 // Device arrays used by a launch (all in the packed half-spectrum layout
@@ -35,6 +39,7 @@ struct Bufs {
     float2* out;
     const float* real_in;
     float* real_out;
+    const int32_t* frame_rows;  // MODE_FRAME_ROW: starts of the rows' entries [Ny + 1], padding, entries (x, value bits)
     double* acc;  // adjoint row pass: one FP64 slot per block of sum_x u^3 w
     int sel;
 };

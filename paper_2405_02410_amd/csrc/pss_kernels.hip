@@ -903,7 +903,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     // operators as blocks of scalar loads, the first channel, the twiddles
     // and the state.  With the plan read where it is used, the launch spent
     // some 35 scalar-load waits in a row.
-    constexpr bool STEP = MODE == MODE_STEP;
+    constexpr bool STEP = MODE == MODE_STEP || MODE == MODE_FRAME_STEP;
     constexpr bool HOT = STEP && !GEN && NF <= 2;
     int nf = p.nf, nch = p.nch, ng = p.ng, nd = p.nd;
     float qs[3] = {p.qs[0], p.qs[1], p.qs[2]};
@@ -956,7 +956,13 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     // 8 and more points other blocks cover the waits, and what would be held
     // across the transforms costs waves: each is taken where it is used.
     constexpr bool EARLY = P < 8;
-    if constexpr (EARLY || !STEP) load_state();
+    if constexpr (MODE == MODE_FRAME_FWD) {
+        // the state from real space: the frame was set there
+#pragma unroll
+        for (int m = 0; m < P; ++m) s[0][m] = gload_at(bufs.in, iat + m * istep);
+    } else if constexpr (EARLY || !STEP) {
+        load_state();
+    }
     if constexpr (STEP) {
         hold(nf), hold(nch), hold(ng), hold(nd), hold(dt), hold(amp_pair), hold(amp_self), hold(key0), hold(key1);
 #pragma unroll
@@ -1016,6 +1022,13 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         return;
     }
     if constexpr (MODE == MODE_PROLOGUE) tw.ready(twl, tid, nthr);
+    if constexpr (MODE == MODE_FRAME_FWD) {
+        tw.ready(twl, tid, nthr);
+        FFT::template dit<-1>(s[0], ld, t, tw.get());
+        exchange(s[0], true);
+#pragma unroll
+        for (int m = 0; m < P; ++m) gstore_at<true>(bufs.S[0], sat + m * sstep, s[0][m]);
+    }
     if constexpr (STEP) {
         // The step's noise depends on the step and the modes only.  Per field:
         // of the slots, and of the four self-conjugate modes.
@@ -1171,7 +1184,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             float fin = 0.f;
 #pragma unroll
             for (int m = 0; m < P; ++m) {
-                gstore_at<!TABLE>(bufs.S[f], sat + m * sstep, s[f][m]);
+                if constexpr (MODE == MODE_STEP) gstore_at<!TABLE>(bufs.S[f], sat + m * sstep, s[f][m]);
                 fin = fmaf(s[f][m].x, 0.f, fin);
                 fin = fmaf(s[f][m].y, 0.f, fin);
             }
@@ -1184,6 +1197,14 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                 atomicOr(flag_a, bad);
             }
         }
+    }
+
+    if constexpr (MODE == MODE_FRAME_STEP) {
+        exchange(s[0], false);
+        FFT::template dif<1>(s[0], ld, t, tw.get());
+#pragma unroll
+        for (int m = 0; m < P; ++m) gstore_at<true>(bufs.out, oat + m * ostep, s[0][m]);
+        return;
     }
 
     // de-aliased inverse transforms of every factor field (eq:cubicexampledealiased)
@@ -1733,6 +1754,45 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
             dst[static_cast<size_t>(r0 + 2 * pr) * L + x] = v[m].x * p.inv_n;
             dst[static_cast<size_t>(r0 + 2 * pr + 1) * L + x] = v[m].y * p.inv_n;
         }
+        return;
+    }
+
+    if constexpr (MODE == MODE_FRAME_ROW) {
+        // the state's rows to real space, the frame's values on its sites, and
+        // back: the row pair is staged in LDS at natural x, where the threads
+        // of the pair write the entries of its two rows
+        float2 v[P];
+        build_z(v, bufs.in, NC, t);
+        tw.load(tw_g, t, tid, nthr);
+        const int32_t* __restrict__ fr = bufs.frame_rows + yr;
+        const int e0 = fr[0], e1 = fr[1], e2 = fr[2];
+        float inv_n = p.inv_n;
+        hold(inv_n);
+        const int2* __restrict__ ent = reinterpret_cast<const int2*>(bufs.frame_rows + ny + 2);
+        tw.ready(twl, tid, nthr);
+        FFT::template dif<1>(v, ld, t, tw.get());
+        float2* stage = FFT::kCross ? ld.next_blk() : ld.wl;
+        auto sync = [&]() {
+            if constexpr (FFT::kCross) {
+                __syncthreads();
+            } else {
+                wave_lds_sync();
+            }
+        };
+        if constexpr (FFT::kOne || !FFT::kCross) sync();
+#pragma unroll
+        for (int m = 0; m < P; ++m) stage[dr + m * T] = cscale(v[m], inv_n);
+        sync();
+        for (int i = e0 + t; i < e2; i += T) {
+            const int2 e = ent[i];
+            float* w = reinterpret_cast<float*>(stage + e.x);
+            w[i < e1 ? 0 : 1] = __int_as_float(e.y);
+        }
+        sync();
+#pragma unroll
+        for (int m = 0; m < P; ++m) v[m] = stage[dr + m * T];
+        FFT::template dit<-1>(v, ld, t, tw.get());
+        store_rows(v, bufs.out, t);
         return;
     }
 
@@ -3493,6 +3553,27 @@ static hipError_t launch_update_d(int mode, const LaunchArgs& a) {
             hipLaunchKernelGGL((update_kernel<L, P, 1, MODE_INV_OUT, DIM, false, false>), grid, block, lds, a.stream,
                                a.members, a.plans, a.plan, a.bufs, a.geo, a.step_ctr, a.flag, a.step_off, a.tw_u);
             break;
+        case MODE_FRAME_STEP:
+        case MODE_FRAME_FWD:
+            if constexpr (NF == 1 && DIM == 2) {
+#define PSS_UF(M, G)                                                                                                \
+    hipLaunchKernelGGL((update_kernel<L, P, 1, M, DIM, G, false>), grid, block, lds, a.stream, a.members, a.plans,  \
+                       a.plan, a.bufs, a.geo, a.step_ctr, a.flag, a.step_off, a.tw_u)
+                if (mode == MODE_FRAME_STEP) {
+                    if (a.general)
+                        PSS_UF(MODE_FRAME_STEP, true);
+                    else
+                        PSS_UF(MODE_FRAME_STEP, false);
+                } else {
+                    if (a.general)
+                        PSS_UF(MODE_FRAME_FWD, true);
+                    else
+                        PSS_UF(MODE_FRAME_FWD, false);
+                }
+#undef PSS_UF
+                break;
+            }
+            return hipErrorInvalidValue;
         default:
             return hipErrorInvalidValue;
     }
@@ -3527,6 +3608,11 @@ static hipError_t launch_xrow_t(int mode, const LaunchArgs& a) {
             break;
         case MODE_C2R_OUT:
             hipLaunchKernelGGL((xrow_kernel<L, P, 1, MODE_C2R_OUT, false>), grid, block, lds, a.stream, a.members,
+                               a.plans, a.plan, a.bufs, a.geo, a.tw_x, int64_t{0}, ctr);
+            break;
+        case MODE_FRAME_ROW:
+            if (a.geo.nz != 1 || !a.bufs.frame_rows) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((xrow_kernel<L, P, 1, MODE_FRAME_ROW, false>), grid, block, lds, a.stream, a.members,
                                a.plans, a.plan, a.bufs, a.geo, a.tw_x, int64_t{0}, ctr);
             break;
         case MODE_ADJROW:

@@ -172,6 +172,7 @@ struct pss_ctx {
     pss::DevPlan* d_plan = nullptr;
     uint64_t* d_step = nullptr;
     float2* d_tw_u = nullptr;
+    float2* d_tables = nullptr;        // one allocation: twiddles of the axes, de-aliasing limits
     int32_t* d_lim = nullptr;          // de-aliasing limits (DevPlan::lim), one table per distinct mask
     size_t lim_off[PSS_MAXG] = {};
     float2* d_tw_x = nullptr;
@@ -185,6 +186,7 @@ struct pss_ctx {
     float2* d_tmp2 = nullptr;
     float* d_real = nullptr;
     int2* d_frame[PSS_MAXF] = {};  // device copies of the frames
+    int32_t* d_frame_rows = nullptr;  // fused frame steps: row starts, then (x, value bits) by row (upload_frames)
     unsigned long long* d_shell_acc = nullptr;  // shell accumulators (kShellWords per shell)
     // one-entry member tables of the step kernels (update kernel, x kernel)
     pss::Member* d_member_u = nullptr;
@@ -450,27 +452,46 @@ int32_t line_lim(const pss::DevMask& mk, int ndim, int kx, int ky, int L) {
     return static_cast<int32_t>(std::min<int64_t>(wa > 0 ? room / wa : hmax, hmax));
 }
 
-// The limits of every line, [|ky|][|kx|] for each distinct mask of the plan
-// (the rule is fixed once the plan is built): two 64-bit divisions a line are
-// then out of the kernels.
-pss_status upload_limits(pss_ctx* c) {
+// The constant tables of the launches in one allocation and one copy: the
+// twiddles of the three axes, and the limits of every line, [|ky|][|kx|] for
+// each distinct mask of the plan (the rule is fixed once the plan is built;
+// two 64-bit divisions a line are then out of the kernels).
+pss_status upload_tables(pss_ctx* c) {
     pss::DevPlan& P = c->plan;
-    if (c->ndim == 1 || P.ng == 0) return PSS_OK;
-    const int nkx = c->n[0] / 2 + 1, nky = c->ndim == 3 ? c->n[1] / 2 + 1 : 1;
-    std::vector<int32_t> tab;
-    for (int g = 0; g < P.ng; ++g) {
-        int same = 0;
-        while (same < g && std::memcmp(&P.mask[same], &P.mask[g], sizeof(pss::DevMask)) != 0) ++same;
-        if (same < g) {
-            c->lim_off[g] = c->lim_off[same];
-            continue;
+    std::vector<float2> tab = twiddles(c->n[0]);
+    auto append = [&](int L) {
+        const size_t at = tab.size();
+        const auto tw = twiddles(L);
+        tab.insert(tab.end(), tw.begin(), tw.end());
+        return at;
+    };
+    const size_t at_u = c->lu == c->n[0] ? 0 : append(c->lu);
+    const size_t at_y = c->n[1] == c->n[0] ? 0 : (c->n[1] == c->lu ? at_u : append(c->n[1]));
+    const size_t at_lim = tab.size();
+    std::vector<int32_t> lim;
+    if (c->ndim > 1) {
+        const int nkx = c->n[0] / 2 + 1, nky = c->ndim == 3 ? c->n[1] / 2 + 1 : 1;
+        for (int g = 0; g < P.ng; ++g) {
+            int same = 0;
+            while (same < g && std::memcmp(&P.mask[same], &P.mask[g], sizeof(pss::DevMask)) != 0) ++same;
+            if (same < g) {
+                c->lim_off[g] = c->lim_off[same];
+                continue;
+            }
+            c->lim_off[g] = lim.size();
+            for (int ky = 0; ky < nky; ++ky)
+                for (int kx = 0; kx < nkx; ++kx) lim.push_back(line_lim(P.mask[g], c->ndim, kx, ky, c->lu));
         }
-        c->lim_off[g] = tab.size();
-        for (int ky = 0; ky < nky; ++ky)
-            for (int kx = 0; kx < nkx; ++kx) tab.push_back(line_lim(P.mask[g], c->ndim, kx, ky, c->lu));
     }
-    HIP_TRY(hipMalloc(&c->d_lim, sizeof(int32_t) * tab.size()));
-    HIP_TRY(hipMemcpy(c->d_lim, tab.data(), sizeof(int32_t) * tab.size(), hipMemcpyHostToDevice));
+    static_assert(sizeof(float2) == 2 * sizeof(int32_t), "two limits per table element");
+    tab.resize(at_lim + (lim.size() + 1) / 2);
+    if (!lim.empty()) std::memcpy(&tab[at_lim], lim.data(), sizeof(int32_t) * lim.size());
+    HIP_TRY(hipMalloc(&c->d_tables, sizeof(float2) * tab.size()));
+    HIP_TRY(hipMemcpy(c->d_tables, tab.data(), sizeof(float2) * tab.size(), hipMemcpyHostToDevice));
+    c->d_tw_x = c->d_tables;
+    c->d_tw_u = c->d_tables + at_u;
+    c->d_tw_y = c->d_tables + at_y;
+    c->d_lim = reinterpret_cast<int32_t*>(c->d_tables + at_lim);
     for (int g = 0; g < P.ng; ++g) P.lim[g] = c->d_lim + c->lim_off[g];
     return PSS_OK;
 }
@@ -925,10 +946,9 @@ void free_device(pss_ctx* c) {
     for (auto*& p : c->d_v) rel(p);
     rel(c->d_plan);
     rel(c->d_step);
-    rel(c->d_tw_u);
-    rel(c->d_lim);
-    rel(c->d_tw_x);
-    rel(c->d_tw_y);
+    rel(c->d_tables);
+    c->d_tw_u = c->d_tw_x = c->d_tw_y = nullptr;  // parts of it
+    c->d_lim = nullptr;
     rel(c->d_tmp);
     rel(c->d_tmp2);
     rel(c->d_real);
@@ -936,6 +956,7 @@ void free_device(pss_ctx* c) {
     rel(c->d_member_u);
     rel(c->d_member_x);
     for (auto*& p : c->d_frame) rel(p);
+    rel(c->d_frame_rows);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     c->stream = nullptr;
     c->own_stream = false;
@@ -1047,6 +1068,10 @@ bool has_frames(const pss_ctx* c) {
     return false;
 }
 
+// 2D power-of-two lattices of one field take their framed steps in four
+// launches (enqueue_steps)
+bool fused_frames(const pss_ctx* c) { return c->ndim == 2 && !c->mixed && c->fields.size() == 1 && has_frames(c); }
+
 // copy every field's frame to the device and point the plan at it (the
 // caller uploads the plan)
 pss_status upload_frames(pss_ctx* c) {
@@ -1061,6 +1086,28 @@ pss_status upload_frames(pss_ctx* c) {
         HIP_TRY(hipMemcpy(c->d_frame[f], fr.data(), sizeof(int2) * fr.size(), hipMemcpyHostToDevice));
         c->plan.frame[f] = c->d_frame[f];
         c->plan.nframe[f] = static_cast<int32_t>(fr.size());
+    }
+    if (c->d_frame_rows) (void)hipFree(c->d_frame_rows);
+    c->d_frame_rows = nullptr;
+    if (fused_frames(c)) {
+        // the frame by rows of the exchange arrays, which hold along y position
+        // t + m T the row D(t) + m T: row starts [Ny + 1], then (x, value bits)
+        const int nx = c->n[0], ny = c->n[1], T = ny / c->geo.pu;
+        std::vector<int> pos(ny);
+        for (int q = 0; q < ny; ++q) pos[pss::fft_drev(ny, c->geo.pu, q % T) + q / T * T] = q;
+        const auto& fr = c->frames[0];
+        std::vector<int32_t> tab(ny + 2, 0);  // (one more, so that the entries are 8-byte aligned)
+        for (const int2& e : fr) ++tab[pos[e.x / nx] + 1];
+        for (int y = 0; y < ny; ++y) tab[y + 1] += tab[y];
+        std::vector<int32_t> fill(tab.begin(), tab.end());
+        tab.resize(ny + 2 + 2 * fr.size());
+        for (const int2& e : fr) {
+            const size_t at = static_cast<size_t>(ny + 2) + 2 * static_cast<size_t>(fill[pos[e.x / nx]]++);
+            tab[at] = e.x % nx;
+            tab[at + 1] = e.y;
+        }
+        HIP_TRY(hipMalloc(&c->d_frame_rows, sizeof(int32_t) * tab.size()));
+        HIP_TRY(hipMemcpy(c->d_frame_rows, tab.data(), sizeof(int32_t) * tab.size(), hipMemcpyHostToDevice));
     }
     return PSS_OK;
 }
@@ -1131,16 +1178,7 @@ pss_status materialize(pss_ctx* c) {
     // the step counter and, in the next word, the non-finite flag
     HIP_TRY(hipMalloc(&c->d_step, 2 * sizeof(uint64_t)));
     HIP_TRY(hipMemset(c->d_step, 0, 2 * sizeof(uint64_t)));
-    const auto twx = twiddles(c->n[0]);
-    const auto twu = twiddles(c->lu);
-    HIP_TRY(hipMalloc(&c->d_tw_x, sizeof(float2) * twx.size()));
-    HIP_TRY(hipMalloc(&c->d_tw_u, sizeof(float2) * twu.size()));
-    HIP_TRY(hipMemcpy(c->d_tw_x, twx.data(), sizeof(float2) * twx.size(), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->d_tw_u, twu.data(), sizeof(float2) * twu.size(), hipMemcpyHostToDevice));
-    const auto twy = twiddles(c->n[1]);
-    HIP_TRY(hipMalloc(&c->d_tw_y, sizeof(float2) * twy.size()));
-    HIP_TRY(hipMemcpy(c->d_tw_y, twy.data(), sizeof(float2) * twy.size(), hipMemcpyHostToDevice));
-    if (pss_status s = upload_limits(c)) return s;
+    if (pss_status s = upload_tables(c)) return s;
     if (pss_status s = upload_frames(c)) return s;
     HIP_TRY(hipMemcpy(c->d_plan, &c->plan, sizeof(pss::DevPlan), hipMemcpyHostToDevice));
     if (c->ndim == 1) HIP_TRY(pss::line1d_setup(c->n[0]));
@@ -1265,9 +1303,9 @@ pss_status enqueue_steps(pss_ctx* c, int64_t k) {
     // framed state (the prologue after the frames), so its steps run only the
     // update launch: the product launches of the unframed state would be
     // overwritten unread.
-    const bool framed = has_frames(c);
+    const bool framed = has_frames(c), fused = fused_frames(c);
     // in 2D the last x kernel of the sequence moves the step counter on
-    const bool x_advances = c->ndim == 2 && c->plan.nch > 0 && !framed;
+    const bool x_advances = c->ndim == 2 && c->plan.nch > 0 && (!framed || fused);
     for (int64_t i = 0; i < k; ++i) {
         pss::LaunchArgs a = args(c, static_cast<int>(i));
         const int64_t at = c->steps_taken + i;
@@ -1276,6 +1314,26 @@ pss_status enqueue_steps(pss_ctx* c, int64_t k) {
         HIP_TRY(launch);                                          \
         if (pss_status s_ = debug_check(c, name, at)) return s_;  \
     } while (0)
+        if (fused) {
+            // update and inverse y transform; x there, frame, x back; forward y
+            // transform into the state and the factors' inverse; products
+            a.bufs.out = c->d_tmp;
+            PSS_CHECKED(pss::launch_update(pss::MODE_FRAME_STEP, c->lu, nf, a), "update_kernel");
+            pss::LaunchArgs af = args(c);
+            af.bufs.in = c->d_tmp;
+            af.bufs.out = c->d_tmp2;
+            af.bufs.frame_rows = c->d_frame_rows;
+            PSS_CHECKED(pss::launch_xrow(pss::MODE_FRAME_ROW, c->n[0], 1, af), "xrow_kernel(frame)");
+            af.bufs.in = c->d_tmp2;
+            PSS_CHECKED(pss::launch_update(pss::MODE_FRAME_FWD, c->lu, nf, af), "update_kernel(frame)");
+            if (c->plan.nch > 0) {
+                pss::LaunchArgs ax = xargs(c);
+                ax.advance = (x_advances && i == k - 1) ? k : 0;
+                PSS_CHECKED(pss::launch_xrow(pss::MODE_STEP, c->n[0], c->plan.ng, ax), "xrow_kernel");
+            }
+            c->dirty = false;  // the products are those of the framed state
+            continue;
+        }
         if (c->mixed) {
             PSS_CHECKED(pss::launch_mr2_col(pss::MODE_STEP, nf, a), "mr2_col_kernel");
             if (c->plan.nch > 0 && !framed) {
