@@ -11,7 +11,7 @@ namespace pss {
 
 // kernel modes
 enum {
-    MODE_STEP = 0,       // one time step
+    MODE_STEP = 0,       // one time step (update kernel of one field: the new state into `out` if that is set)
     MODE_PROLOGUE = 1,   // update kernel: masked inverse of the current state only
     MODE_FWD_STORE = 2,  // update kernel: forward transform of `in`, stored as state `sel`
     MODE_INV_OUT = 3,    // update kernel: inverse transform of state `sel` into `out`

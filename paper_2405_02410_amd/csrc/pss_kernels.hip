@@ -114,9 +114,12 @@ struct Twiddles<FFT, L, P, kTwTable> {
 // thread 0 into this block's own slot[0..NV).  Launches with the same grid
 // add into the same slots in stream order, so the slots, and a fixed-order
 // sum over them, do not depend on how the blocks are scheduled.  Every thread
-// of the block calls it; the block is whole waves or a part of one.
+// of the block calls it; the block is whole waves or a part of one.  old: the
+// slot's values, which thread 0 read at the kernel's start (read here, they
+// would be a memory latency at its very end).
 template <int NV>
-__device__ __forceinline__ void block_sum_to_slot(double (&v)[NV], double* __restrict__ slot) {
+__device__ __forceinline__ void block_sum_to_slot(double (&v)[NV], const double (&old)[NV],
+                                                  double* __restrict__ slot) {
     __shared__ double red[64 * NV];
     const int nt = blockDim.x, tid = threadIdx.x;
     const bool waves = (nt & 63) == 0;
@@ -139,7 +142,7 @@ __device__ __forceinline__ void block_sum_to_slot(double (&v)[NV], double* __res
         for (int i = 0; i < NV; ++i) {
             double acc = 0.0;
             for (int w = 0; w < n; ++w) acc += red[w * NV + i];
-            slot[i] += acc;
+            slot[i] = old[i] + acc;
         }
     }
 }
@@ -1132,6 +1135,11 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         // (the general-operator bodies are large) indexes s and acc at run
         // time, which moves both arrays to scratch memory
         uint32_t bad = 0;
+        // the new state replaces the old one, or (one field) goes to `out`
+        float2* sout[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) sout[f] = bufs.S[f];
+        if constexpr (NF == 1 && MODE == MODE_STEP && !TABLE) sout[0] = bufs.out ? bufs.out : bufs.S[0];
         static_for<NF>([&](auto FF) {
             constexpr int f = decltype(FF)::value;
             if (f >= nf) return;
@@ -1184,7 +1192,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             float fin = 0.f;
 #pragma unroll
             for (int m = 0; m < P; ++m) {
-                if constexpr (MODE == MODE_STEP) gstore_at<!TABLE>(bufs.S[f], sat + m * sstep, s[f][m]);
+                if constexpr (MODE == MODE_STEP) gstore_at<!TABLE>(sout[f], sat + m * sstep, s[f][m]);
                 fin = fmaf(s[f][m].x, 0.f, fin);
                 fin = fmaf(s[f][m].y, 0.f, fin);
             }
@@ -1270,10 +1278,16 @@ __global__ void __launch_bounds__(line_block(L, P)) update_kernel(const Member* 
 // u = t + m*T.  Inner products over all modes become sums over the stored
 // slots with weight 2 (a mode and its conjugate), and weight 1 for each real
 // component of the pair slots.
+//
+// 256^2 is latency from end to end: as in the update kernel, every read is
+// issued at the top, the noise is formed meanwhile, the limits of the mask
+// come from the table and the self-conjugate modes are evaluated in four
+// lanes.  14.2 -> 8.2 us a launch.
 template <int L, int P, int MODE>
 __global__ void __launch_bounds__(line_block(L, P)) adjcol_kernel(AdjArgs aa, Geo geo, const float2* __restrict__ tw_g) {
     using FFT = LineFFT<L, P>;
     constexpr int T = FFT::T;
+    constexpr bool LANES = T >= 4;
     extern __shared__ float2 smem[];
     const DevPlan& p = *aa.plan;
     const int tc = geo.tc;
@@ -1283,20 +1297,53 @@ __global__ void __launch_bounds__(line_block(L, P)) adjcol_kernel(AdjArgs aa, Ge
     const int cc = tid / T;
     const int ct = xcd_block(blockIdx.x, gridDim.x);
     const int c = ct * tc + cc;
-    const int nx = p.n[0];
-    const int kn = -(nx >> 1);
-    const size_t base = static_cast<size_t>(ct) * L * tc + cc;
+    const int nx = geo.nx;
+    const uint32_t sat = static_cast<uint32_t>((ct * L + t) * tc + cc), sstep = static_cast<uint32_t>(T * tc);
     const Exch<uint32_t> xch = exch_column(geo, ct, cc, L);
     const uint32_t xat = xch.at(t), xstep = xch.step(T);
     LdsLine ld = FFT::lds_line(smem + cc * FFT::kLds);
     float2* xbuf = FFT::kOne ? smem + FFT::kReg : smem + tc * FFT::kLds;
     float2* twl = smem + tc * FFT::kLds + fft_xbuf_elems(L, P);
-    const int dr = FFT::drev(t);
-    Twiddles<FFT, L, P> tw;
-    tw.load(tw_g, t, tid, nthr);
     const bool blk_packed = ct == 0;
     const bool packed = blk_packed && cc == 0;
-    const DevMask& mk = p.mask[0];
+    const bool pair_lane = packed && t == 0, first_wave = blk_packed && tid < 64;
+    auto pair_slot = [&](int m) { return pair_lane && (m == 0 || m == P / 2); };
+
+    float qs[3] = {p.qs[0], p.qs[1], p.qs[2]};
+    float dt = p.dt, inv_n = p.inv_n, amp_pair = p.amp_pair, amp_self = p.amp_self;
+    uint32_t key0 = p.key0, key1 = p.key1;
+    int noisy = p.noisy[0], fid = p.fid[0];
+    OpPoly noi = op_poly(p.noise_op[0]);
+    const int32_t* lim_g = p.lim[0];
+    double* const slot = aa.acc + static_cast<size_t>(blockIdx.x) * 3;
+    double old[3] = {0.0, 0.0, 0.0};
+    if (MODE == MODE_ADJCOL && tid == 0) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) old[i] = slot[i];
+    }
+    float2 g[P], rin[P], f1[P], f0[P];
+    Twiddles<FFT, L, P> tw;
+    if (aa.first) {
+#pragma unroll
+        for (int m = 0; m < P; ++m) g[m] = gload_at(aa.G, sat + m * sstep);
+    } else {
+#pragma unroll
+        for (int m = 0; m < P; ++m) g[m] = gload_at(aa.X, xat + m * xstep);
+#pragma unroll
+        for (int m = 0; m < P; ++m) rin[m] = gload_at(aa.Rin, sat + m * sstep);
+    }
+    tw.load(tw_g, t, tid, nthr);
+    if constexpr (MODE == MODE_ADJCOL) {
+#pragma unroll
+        for (int m = 0; m < P; ++m) f1[m] = gload_at(aa.phi1, sat + m * sstep);
+#pragma unroll
+        for (int m = 0; m < P; ++m) f0[m] = gload_at(aa.phi0, sat + m * sstep);
+    }
+    hold(dt), hold(inv_n), hold(amp_pair), hold(amp_self), hold(key0), hold(key1), hold(noisy), hold(fid), hold(noi);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) hold(qs[i]);
+    const int lim = lim_g[c];
+    const int limN = blk_packed ? lim_g[nx >> 1] : -1;
 
     auto exchange = [&](float2 (&v)[P], bool forward) {  // as in the update kernel
         if (!blk_packed) return;
@@ -1316,118 +1363,139 @@ __global__ void __launch_bounds__(line_block(L, P)) adjcol_kernel(AdjArgs aa, Ge
         }
         __syncthreads();
     };
-    // modes of slot u: (kx, ky) of a plain slot, or pair = the two real modes
-    auto slot = [&](int u, int& kx, int& ky, bool& pair) {
-        pair = false;
-        if (!packed) {
-            kx = c;
-            ky = signed_mode(u, L);
-        } else if (u == 0 || u == (L >> 1)) {
-            pair = true;
-            kx = 0;
-            ky = u == 0 ? 0 : -(L >> 1);
-        } else if (u < (L >> 1)) {
-            kx = 0;
-            ky = u;
-        } else {
-            kx = kn;
-            ky = L - u;
-        }
-    };
-
-    // g_{n+1}
-    float2 g[P];
-    if (aa.first) {
-#pragma unroll
-        for (int m = 0; m < P; ++m) g[m] = aa.G[base + (t + m * T) * tc];
-        tw.ready(twl, tid, nthr);
-    } else {
-        float2 v[P];
-#pragma unroll
-        for (int m = 0; m < P; ++m) v[m] = aa.X[xat + m * xstep];
-        tw.ready(twl, tid, nthr);
-        FFT::template dit<-1>(v, ld, t, tw.get());
-        exchange(v, true);
+    // the de-aliased values of a line (slot form on the packed line)
+    auto masked = [&](float2 (&v)[P]) {
+        const float2 a0 = v[0], ah = v[P / 2];
 #pragma unroll
         for (int m = 0; m < P; ++m) {
-            int kx, ky;
-            bool pair;
-            slot(t + m * T, kx, ky, pair);
-            float2 y = cscale(v[m], p.inv_n * aa.b);
-            if (!pair) {
-                if (!mask_keep(mk, kx, ky, 0)) y = make_float2(0.f, 0.f);
-            } else {
-                if (!mask_keep(mk, 0, ky, 0)) y.x = 0.f;
-                if (!mask_keep(mk, kn, ky, 0)) y.y = 0.f;
-            }
-            g[m] = cadd(aa.Rin[base + (t + m * T) * tc], y);
+            const int u = t + m * T;
+            const bool upper = packed && u > (L >> 1);
+            const int w = packed ? (upper ? L - u : u) : (u < (L >> 1) ? u : u - L);
+            if (w * w > (upper ? limN : lim)) v[m] = make_float2(0.f, 0.f);
         }
+        if (pair_lane) {
+            const int wh = (L >> 1) * (L >> 1);
+            v[0] = make_float2(0 <= lim ? a0.x : 0.f, 0 <= limN ? a0.y : 0.f);
+            v[P / 2] = make_float2(wh <= lim ? ah.x : 0.f, wh <= limN ? ah.y : 0.f);
+        }
+    };
+    const LineModes lmode = line_modes<L, 2>(nx, L, qs, packed, c, 0);
+    Self self[LANES ? 1 : 4];
+    if (first_wave) {
+#pragma unroll
+        for (int j = 0; j < (LANES ? 1 : 4); ++j) self[j] = self_modes<L, 2>(nx, L, 1, qs, 0, LANES ? tid : j);
+    }
+    // the forward step's noise, while the loads above are in flight
+    float q2[P];
+    float2 eta[P];
+    float eta_s[LANES ? 1 : 4];
+    {
+        const NoiseKey nk{key0, key1, aa.step, fid, amp_pair, amp_self};
+        uint32_t lin[P], lneg[P];
+        float D[P];
+#pragma unroll
+        for (int m = 0; m < P; ++m) slot_at<L>(lmode, t + m * T, q2[m], lin[m], lneg[m]);
+        if (MODE == MODE_ADJCOL && noisy) {
+            horner_p(noi, q2, D);
+#pragma unroll
+            for (int m = 0; m < P; ++m) eta[m] = noise_value<true>(nk, lin[m], lneg[m], D[m]);
+            if (first_wave) {
+#pragma unroll
+                for (int j = 0; j < (LANES ? 1 : 4); ++j)
+                    eta_s[j] = noise_value(nk, self[j].lin, self[j].lneg, horner(noi, self[j].q.q2)).x;
+            }
+        }
+    }
+    tw.ready(twl, tid, nthr);
+
+    // g_{n+1}
+    if (!aa.first) {
+        FFT::template dit<-1>(g, ld, t, tw.get());
+        exchange(g, true);
+        masked(g);
+#pragma unroll
+        for (int m = 0; m < P; ++m) g[m] = cadd(rin[m], cscale(g[m], inv_n * aa.b));
     }
     if constexpr (MODE == MODE_ADJFIN) {
 #pragma unroll
-        for (int m = 0; m < P; ++m) aa.Rout[base + (t + m * T) * tc] = g[m];
+        for (int m = 0; m < P; ++m) gstore_at<false>(aa.Rout, sat + m * sstep, g[m]);
         return;
     }
 
     // r_n = g_{n+1} / A, the coefficient sums, -dt q^2 r_n and m phi_n
-    const float dt = p.dt;
-    const bool noisy = p.noisy[0] != 0;
     double part[3] = {0.0, 0.0, 0.0};  // d/da, d/dk, <r, eta>
-    float2 wr[P], um[P];
+    float2 wr[P];
 #pragma unroll
     for (int m = 0; m < P; ++m) {
-        const int u = t + m * T;
-        const size_t e = base + u * tc;
-        int kx, ky;
-        bool pair;
-        slot(u, kx, ky, pair);
-        const float2 f1 = aa.phi1[e], f0 = aa.phi0[e];
-        float2 r;
-        if (!pair) {
-            const ModeQ q = mode_q(p, kx, ky, 0);
-            r = cscale(g[m], 1.f / (1.f + dt * q.q2 * (aa.a + aa.k * q.q2)));
-            const double re1 = static_cast<double>(r.x) * f1.x + static_cast<double>(r.y) * f1.y;
-            part[0] -= 2.0 * dt * q.q2 * re1;
-            part[1] -= 2.0 * dt * static_cast<double>(q.q2) * q.q2 * re1;
-            if (noisy) {
-                uint32_t lin, lneg;
-                mode_lin(p, kx, ky, 0, lin, lneg);
-                const float2 eta = noise_mode<false>(p, 0, aa.step, lin, lneg, q);
-                part[2] += 2.0 * (static_cast<double>(r.x) * eta.x + static_cast<double>(r.y) * eta.y);
-            }
-            wr[m] = cscale(r, -dt * q.q2);
-            um[m] = mask_keep(mk, kx, ky, 0) ? f0 : make_float2(0.f, 0.f);
-        } else {
-            // two real modes: re part kx = 0, im part kx = -Nx/2
-            const ModeQ q0 = mode_q(p, 0, ky, 0), qn = mode_q(p, kn, ky, 0);
-            r = make_float2(g[m].x / (1.f + dt * q0.q2 * (aa.a + aa.k * q0.q2)),
-                            g[m].y / (1.f + dt * qn.q2 * (aa.a + aa.k * qn.q2)));
-            const double e0 = static_cast<double>(r.x) * f1.x, en = static_cast<double>(r.y) * f1.y;
-            part[0] -= dt * (q0.q2 * e0 + qn.q2 * en);
-            part[1] -= dt * (static_cast<double>(q0.q2) * q0.q2 * e0 + static_cast<double>(qn.q2) * qn.q2 * en);
-            if (noisy) {
-                uint32_t lin, lneg;
-                mode_lin(p, 0, ky, 0, lin, lneg);
-                const float eta0 = noise_mode<false>(p, 0, aa.step, lin, lneg, q0).x;
-                mode_lin(p, kn, ky, 0, lin, lneg);
-                const float etan = noise_mode<false>(p, 0, aa.step, lin, lneg, qn).x;
-                part[2] += static_cast<double>(r.x) * eta0 + static_cast<double>(r.y) * etan;
-            }
-            wr[m] = make_float2(-dt * q0.q2 * r.x, -dt * qn.q2 * r.y);
-            um[m] = make_float2(mask_keep(mk, 0, ky, 0) ? f0.x : 0.f, mask_keep(mk, kn, ky, 0) ? f0.y : 0.f);
+        const float2 r = cscale(g[m], 1.f / (1.f + dt * q2[m] * (aa.a + aa.k * q2[m])));
+        wr[m] = cscale(r, -dt * q2[m]);
+        if (!pair_slot(m)) {
+            const double re1 = static_cast<double>(r.x) * f1[m].x + static_cast<double>(r.y) * f1[m].y;
+            part[0] -= 2.0 * dt * q2[m] * re1;
+            part[1] -= 2.0 * dt * static_cast<double>(q2[m]) * q2[m] * re1;
+            if (noisy)
+                part[2] += 2.0 * (static_cast<double>(r.x) * eta[m].x + static_cast<double>(r.y) * eta[m].y);
+            g[m] = r;
         }
-        aa.Rout[e] = r;
     }
+    if (first_wave) {
+        // the pair slots: four real modes, one per lane (or all in one thread),
+        // from the values that the first thread holds
+        const float gp[4] = {g[0].x, g[0].y, g[P / 2].x, g[P / 2].y};
+        const float fp[4] = {f1[0].x, f1[0].y, f1[P / 2].x, f1[P / 2].y};
+        auto mode = [&](float q, float gv, float f1v, float es) {
+            const float r = gv / (1.f + dt * q * (aa.a + aa.k * q));
+            const double e = static_cast<double>(r) * f1v;
+            part[0] -= dt * static_cast<double>(q) * e;
+            part[1] -= dt * static_cast<double>(q) * q * e;
+            if (noisy) part[2] += static_cast<double>(r) * es;
+            return r;
+        };
+        Four r, q;
+        if constexpr (LANES) {
+            float gl = 0.f, fl = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(gp[j]), 0));
+                const float b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fp[j]), 0));
+                gl = (tid & 3) == j ? a : gl;
+                fl = (tid & 3) == j ? b : fl;
+            }
+            const double keep[3] = {part[0], part[1], part[2]};
+            const float rl = mode(self[0].q.q2, gl, fl, eta_s[0]);
+            if (tid >= 4) {  // lanes 0 to 3 add the four modes once
+#pragma unroll
+                for (int i = 0; i < 3; ++i) part[i] = keep[i];
+            }
+            r = four_lanes(rl);
+            q = four_lanes(self[0].q.q2);
+        } else if (pair_lane) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                q.v[j] = self[j].q.q2;
+                r.v[j] = mode(q.v[j], gp[j], fp[j], eta_s[j]);
+            }
+        }
+        if (pair_lane) {
+            g[0] = make_float2(r.v[0], r.v[1]);
+            g[P / 2] = make_float2(r.v[2], r.v[3]);
+            wr[0] = make_float2(-dt * q.v[0] * r.v[0], -dt * q.v[1] * r.v[1]);
+            wr[P / 2] = make_float2(-dt * q.v[2] * r.v[2], -dt * q.v[3] * r.v[3]);
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < P; ++m) gstore_at<false>(aa.Rout, sat + m * sstep, g[m]);
     exchange(wr, false);
     FFT::template dif<1>(wr, ld, t, tw.get());
 #pragma unroll
-    for (int m = 0; m < P; ++m) aa.W[xat + m * xstep] = wr[m];
-    exchange(um, false);
-    FFT::template dif<1>(um, ld, t, tw.get());
+    for (int m = 0; m < P; ++m) gstore_at<false>(aa.W, xat + m * xstep, wr[m]);
+    masked(f0);
+    exchange(f0, false);
+    FFT::template dif<1>(f0, ld, t, tw.get());
 #pragma unroll
-    for (int m = 0; m < P; ++m) aa.U[xat + m * xstep] = um[m];
+    for (int m = 0; m < P; ++m) gstore_at<false>(aa.U, xat + m * xstep, f0[m]);
     if (aa.D > 0.f) part[2] /= 2.0 * aa.D;
-    block_sum_to_slot(part, aa.acc + static_cast<size_t>(blockIdx.x) * 3);
+    block_sum_to_slot(part, old, slot);
 }
 
 #if defined(PSS_COMMON)
@@ -1802,6 +1870,8 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
         // 3 u^2 w -> forward x transform into N[0] (the column kernel applies
         // the factor b); and the FP64 sum of u^3 w, which is
         // <r, -dt q^2 F[u^3]> = dL/db of the step, by Parseval
+        double old[1] = {0.0};
+        if (tid == 0) old[0] = bufs.acc[blockIdx.x];
         float2 u[P], w[P];
         build_z(u, bufs.V[0], geo.ncol[0], t);
         build_z(w, bufs.V[1], NC, t);
@@ -1818,7 +1888,7 @@ __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __rest
         }
         FFT::template dit<-1>(u, ld, t, tw.get());
         store_rows(u, bufs.N[0], t);
-        block_sum_to_slot(part, bufs.acc + blockIdx.x);
+        block_sum_to_slot(part, old, bufs.acc + blockIdx.x);
         return;
     }
 

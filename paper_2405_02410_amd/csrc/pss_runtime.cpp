@@ -2846,7 +2846,7 @@ pss_status pss_adjoint_model_b_forward(pss_ctx* c, int64_t nsteps, int32_t ckpt_
     // workspace: checkpoints, one recomputed segment, adjoint arrays
     const size_t fb = tp->fb;
     tp->ck = static_cast<char*>(tape_alloc(tp, fb * static_cast<size_t>(tp->nck)));
-    tp->seg = static_cast<char*>(tape_alloc(tp, fb * static_cast<size_t>(tp->seglen + 1)));
+    tp->seg = static_cast<char*>(tape_alloc(tp, fb * static_cast<size_t>(tp->seglen)));
     tp->fT = static_cast<float2*>(tape_alloc(tp, fb));
     tp->G = static_cast<float2*>(tape_alloc(tp, fb));
     tp->R0 = static_cast<float2*>(tape_alloc(tp, fb));
@@ -2861,7 +2861,7 @@ pss_status pss_adjoint_model_b_forward(pss_ctx* c, int64_t nsteps, int32_t ckpt_
     tp->plan_raw = static_cast<pss::DevPlan*>(tape_alloc(tp, sizeof(pss::DevPlan)));
     if (tp->mem.size() != 13)
         return bail(fail(PSS_E_NOMEM, "adjoint workspace of %zu bytes does not fit",
-                         fb * static_cast<size_t>(tp->nck + tp->seglen + 8)));
+                         fb * static_cast<size_t>(tp->nck + tp->seglen + 7)));
 #define TAPE_HIP(expr)                                                                                      \
     do {                                                                                                    \
         hipError_t e_ = (expr);                                                                             \
@@ -2928,7 +2928,6 @@ pss_status pss_adjoint_model_b_backward(pss_tape* tp, double* grad, float* grad_
         return fail(PSS_E_STATE, "the lattice changed (coefficients, seed or state) after the forward run");
     if (pss_status s = begin_work(c)) return s;
     const int nx = c->n[0], ny = c->n[1];
-    const size_t fb = tp->fb;
 #define ADJ_HIP(expr)                                                                                \
     do {                                                                                             \
         hipError_t e_ = (expr);                                                                      \
@@ -2962,25 +2961,34 @@ pss_status pss_adjoint_model_b_backward(pss_tape* tp, double* grad, float* grad_
     ax.bufs.N[0] = tp->X;
     ax.bufs.acc = tp->acc + 3 * static_cast<size_t>(c->geo.nublk);
     const int64_t n0 = tp->n0, nsteps = tp->nsteps;
+    // state i of segment sgi: the checkpoint, then the recomputed ones
+    auto state_of = [&](int64_t sgi, int64_t i) {
+        return i == 0 ? tape_at(tp, tp->ck, sgi) : tape_at(tp, tp->seg, i - 1);
+    };
     for (int64_t sgi = tp->nck - 1; sgi >= 0; --sgi) {
         const int64_t start = sgi * tp->ckpt;
         const int64_t len = std::min<int64_t>(tp->ckpt, nsteps - start);
-        const uint64_t st = static_cast<uint64_t>(n0 + start);
-        ADJ_HIP(hipStreamSynchronize(c->stream));
-        ADJ_HIP(hipMemcpy(c->d_step, &st, sizeof(st), hipMemcpyHostToDevice));
-        ADJ_HIP(hipMemcpyAsync(c->d_state[0], tape_at(tp, tp->ck, sgi), fb, hipMemcpyDeviceToDevice, c->stream));
-        ADJ_HIP(hipMemcpyAsync(tape_at(tp, tp->seg, 0), tape_at(tp, tp->ck, sgi), fb, hipMemcpyDeviceToDevice,
-                               c->stream));
-        if (pss_status s = prologue(c)) return s;
+        // each state of the segment is written straight into its place; the
+        // step counter stays at the end of the run, the launches name their
+        // step relative to it
+        pss::LaunchArgs a0 = args(c);
+        const pss::LaunchArgs x0 = xargs(c);
+        a0.bufs.S[0] = tape_at(tp, tp->ck, sgi);
+        ADJ_HIP(pss::launch_update(pss::MODE_PROLOGUE, c->lu, 1, a0));
+        ADJ_HIP(pss::launch_xrow(pss::MODE_STEP, nx, 1, x0));
         for (int64_t i = 1; i <= len; ++i) {
-            if (pss_status s = enqueue_steps(c, 1)) return s;
-            ADJ_HIP(hipMemcpyAsync(tape_at(tp, tp->seg, i), c->d_state[0], fb, hipMemcpyDeviceToDevice, c->stream));
+            pss::LaunchArgs a = args(c, static_cast<int>(start + i - 1 - nsteps));
+            a.bufs.S[0] = state_of(sgi, i - 1);
+            a.bufs.out = state_of(sgi, i);
+            ADJ_HIP(pss::launch_update(pss::MODE_STEP, c->lu, 1, a));
+            if (i < len) ADJ_HIP(pss::launch_xrow(pss::MODE_STEP, nx, 1, x0));
+            if (pss_status s = debug_check(c, "recomputed step", n0 + start + i - 1)) return s;
         }
         for (int64_t i = len - 1; i >= 0; --i) {
             aa.Rin = Rcur;
             aa.Rout = Rnxt;
-            aa.phi1 = tape_at(tp, tp->seg, i + 1);
-            aa.phi0 = tape_at(tp, tp->seg, i);
+            aa.phi1 = state_of(sgi, i + 1);
+            aa.phi0 = state_of(sgi, i);
             aa.step = static_cast<uint32_t>(n0 + start + i);
             ADJ_HIP(pss::launch_adjcol(pss::MODE_ADJCOL, ny, aa, args(c)));
             ADJ_HIP(pss::launch_xrow(pss::MODE_ADJROW, nx, 2, ax));
@@ -3007,11 +3015,8 @@ pss_status pss_adjoint_model_b_backward(pss_tape* tp, double* grad, float* grad_
         ADJ_HIP(hipMemcpyAsync(grad_phi0, c->d_real, sizeof(float) * static_cast<size_t>(c->sites()),
                                on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream));
     }
-    // leave the lattice at the end of the forward run
-    const uint64_t fin = static_cast<uint64_t>(n0 + nsteps);
+    // the lattice's state and counter are still those of the end of the forward run
     ADJ_HIP(hipStreamSynchronize(c->stream));
-    ADJ_HIP(hipMemcpy(c->d_step, &fin, sizeof(fin), hipMemcpyHostToDevice));
-    ADJ_HIP(hipMemcpy(c->d_state[0], tp->fT, fb, hipMemcpyDeviceToDevice));
 #undef ADJ_HIP
     c->steps_taken = n0 + nsteps;
     c->dirty = true;

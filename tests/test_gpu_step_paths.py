@@ -77,3 +77,19 @@ def test_mixed_radix_steps(n, dealias):
     m.step(5)
     got = lat.download(f)
     assert np.max(np.abs(got - m.real(0).reshape(got.shape))) <= 2e-6
+
+
+# the adjoint's column launches: lines of two and four threads, one wave and
+# several, tiles of one and more columns, segments of one step, of several and
+# a shorter last one; the bar is that of the adjoint's own tests (1e-3)
+@pytest.mark.parametrize("n,ckpt", [((16, 8), 1), ((8, 16), 4), ((16, 256), 5), ((16, 1024), 11), ((256, 32), 20)])
+def test_adjoint_line_forms(n, ckpt):
+    from tests.test_gpu_adjoint import _check, _gpu, _oracle as adjoint_oracle
+
+    S_star, Lo, go, gphio = adjoint_oracle(n, 11, seed=5)
+    lat = _gpu(n, seed=5)
+    L, g, gphi = lat.adjoint_model_b(11, S_star, ckpt_every=ckpt)
+    _check(L, g, gphi, Lo, go, gphio)
+    twin = _gpu(n, seed=5)
+    twin.step(11)
+    assert lat.step_index == 11 and np.array_equal(lat.spectrum(0), twin.spectrum(0))
