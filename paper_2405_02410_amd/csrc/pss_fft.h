@@ -148,7 +148,7 @@ struct LineFFT {
         float2 w[kTw > 0 ? kTw : 1];
         __device__ __forceinline__ float2 at(int flat, int) const { return w[flat]; }
         template <int S>
-        __device__ __forceinline__ void load_stage(const float2* __restrict__ tw_g, int t) {
+        __device__ __forceinline__ void load_stage(const float2* __restrict__ tw_g, int t, int every) {
             if constexpr (S >= 0) {
                 constexpr int Ls = kSt.Ls[S], G = kSt.G[S], R = kSt.R[S], PR = P / R;
                 if constexpr (Ls > R) {
@@ -157,13 +157,16 @@ struct LineFFT {
                     for (int h = 0; h < PR; ++h)
 #pragma unroll
                         for (int k1 = 1; k1 < R; ++k1)
-                            w[tw_count(S) + h * (R - 1) + k1 - 1] = gload_at(tw_g, static_cast<uint32_t>((g + h * G) * k1 * (L / Ls)));
+                            w[tw_count(S) + h * (R - 1) + k1 - 1] = gload_at(tw_g, static_cast<uint32_t>((g + h * G) * k1 * (L / Ls) * every));
                 }
-                load_stage<S - 1>(tw_g, t);
+                load_stage<S - 1>(tw_g, t, every);
             }
         }
-        // the stages that a forward (dit) transform runs first are loaded first
-        __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t) { load_stage<kSt.n - 1>(tw_g, t); }
+        // the stages that a forward (dit) transform runs first are loaded first;
+        // the table is that of a line of L * every points
+        __device__ __forceinline__ void load(const float2* __restrict__ tw_g, int t, int every = 1) {
+            load_stage<kSt.n - 1>(tw_g, t, every);
+        }
     };
     // the first stage's in registers, the later stages' from the table of the
     // sub-transforms' length (entry i stands for w_L^(i R0))

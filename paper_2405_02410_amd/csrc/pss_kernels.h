@@ -125,6 +125,7 @@ struct LaunchArgs {
     int nmem;
     bool general;           // the plans need the general-monomial operator code
     bool simple;            // one field, one channel and one factor, no other explicit terms, not general
+    bool framed;            // a field has boundary frames
     int step_off;
     int64_t advance;     // x kernel, step modes: add this to every member's step counter (0: none)
     const float2* tw_u;  // twiddles of the update-axis length
@@ -214,6 +215,14 @@ hipError_t launch_line1d(int mode, int N, int nf, const LaunchArgs& a);
 inline size_t line1d_lds_bytes(int N) {
     return sizeof(float2) * (static_cast<size_t>(fft_lds_elems(N, 4, 1)) + static_cast<size_t>(N)) +
            sizeof(float) * static_cast<size_t>(N);
+}
+// 1D lines of one field and one channel (line1d_half_kernel): points of the
+// half-length transforms a thread, threads, LDS (the transform's regions and
+// the pairs' exchange line)
+constexpr int kLineHalfPoints = 4;
+constexpr int line_half_threads(int N) { return N / 2 / kLineHalfPoints; }
+inline size_t line_half_lds_bytes(int N) {
+    return sizeof(float2) * static_cast<size_t>(fft_lds_elems(N / 2, kLineHalfPoints, 1) + N / 4);
 }
 // allow the 1D kernels of length N their LDS (above the default dynamic limit)
 hipError_t line1d_setup(int N);

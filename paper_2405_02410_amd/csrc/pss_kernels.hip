@@ -3572,6 +3572,204 @@ __global__ void __launch_bounds__(N / 4 < 64 ? 64 : N / 4)
     if (advance && t == 0) *step_ctr += static_cast<uint64_t>(nsteps);
 }
 
+// The same for a line of one field whose only explicit term is one channel of
+// products of that field, with operators in powers of q^2 (Model B, Model A):
+// the state is kept as the N/2 + 1 modes k >= 0 of a real field, and both
+// transforms are the complex ones of H = N/2 points on z[n] = x[2n] + i
+// x[2n+1] (Van Loan, Sec. 4.3).  Against the kernel above that halves the
+// noise (one Philox draw per mode and step, the largest part of its work),
+// the update and the transforms.
+//
+// A thread keeps P of the H points, k = t + m T, in both transforms (natural
+// order of modes, digit-reversed order of sites, which only meet pointwise
+// products) and P/2 pairs of modes (k, H - k), k = t + m T < H/2, in between:
+// the split into even and odd samples takes both of a pair, so the upper half
+// of the points goes through an LDS line of H/2 on the way in and out, in
+// which a thread reads and writes the same places.  Slot k = 0 holds modes 0
+// and N/2 (both real) and, as its partner, H/2.
+//
+// One block on one CU is a serial chain: everything that a step does not
+// change (operators, noise strengths, twiddles, the mask) is held in
+// registers over the launch's steps, and lines up to 512 are one wave, with
+// no barrier at all.  Four points a thread: 4096 (two waves a SIMD, 7800 of
+// the 10000 cycles of a step issue vector instructions) took 4.2 us a step
+// where 8 points took 4.4 and the kernel above 10.8; 1024: 2.4, 2.8 and 5.0; 64:
+// 1.7 with 4 points, 4.4 with the kernel above.
+template <int N>
+__global__ void __launch_bounds__(line_half_threads(N) < 64 ? 64 : line_half_threads(N))
+    line1d_half_kernel(const DevPlan* __restrict__ plan, Bufs bufs, uint64_t* __restrict__ step_ctr,
+                       uint32_t* __restrict__ flag, int nsteps, int advance, const float2* __restrict__ tw_g) {
+    constexpr int H = N / 2, P = kLineHalfPoints, PP = P / 2;
+    using FFT = LineFFT<H, P>;
+    constexpr int T = FFT::T;
+    constexpr int NB = T < 64 ? T : 64;  // steps whose N/2 noise is drawn at once
+    extern __shared__ float2 smem[];
+    const DevPlan& p = *plan;
+    const int t = threadIdx.x;
+    LdsLine ld = FFT::lds_line(smem);
+    float2* const xb = smem + FFT::kLds;
+
+    const float dt = p.dt, inv_n = p.inv_n;
+    const OpPoly imp = op_poly(p.implicit_op[0]), opc = op_poly(p.ch[0].op[0]), noi = op_poly(p.noise_op[0]);
+    const bool noisy = p.noisy[0] != 0;
+    const uint32_t key0 = p.key0, key1 = p.key1, fid = static_cast<uint32_t>(p.fid[0]);
+    const int nprod = p.ch[0].nprod;
+    const float coef0 = p.ch[0].prod[0].coef;
+    const int pow0 = p.ch[0].prod[0].pow[0];
+    const uint32_t step0 = static_cast<uint32_t>(gload_u64(step_ctr));
+    const bool zero = t == 0;  // this thread's pair 0 is (0 and N/2, H/2)
+
+    float2 a[PP], b[PP], wk[PP];
+#pragma unroll
+    for (int m = 0; m < PP; ++m) {
+        const int k = t + m * T;
+        const bool z = zero && m == 0;
+        a[m] = gload(bufs.S[0] + k);
+        b[m] = gload(bufs.S[0] + (z ? H / 2 : H - k));
+        wk[m] = gload(tw_g + k);
+    }
+    if (zero) a[0].y = gload(bufs.S[0] + H).x;
+    typename FFT::Regs tw;
+    tw.load(tw_g, t, 2);
+
+    // what the steps share: of the pair's modes, 1 / (1 - dt L), dt M / 2 (the
+    // half of the split), the noise amplitude and the mask
+    const DevMask mk = p.mask[0];
+    auto q2_of = [&](int k) { return mode_q(p, k < (N >> 1) ? k : k - N, 0, 0).q2; };
+    auto keep_of = [&](int k) { return mask_keep(mk, k < (N >> 1) ? k : k - N, 0, 0) ? 1.f : 0.f; };
+    // rounded as in the other kernels: the factor's error repeats in every step
+    auto implicit = [&](float q) { return cinv_implicit(dt, make_float2(horner(imp, q), 0.f)).x; };
+    float ia[PP], ib[PP], ma[PP], mb[PP], na[PP], nb[PP], ka[PP], kb[PP];
+#pragma unroll
+    for (int m = 0; m < PP; ++m) {
+        const int k = t + m * T, kp = zero && m == 0 ? H / 2 : H - k;
+        const float qa = q2_of(k), qb = q2_of(kp);
+        ia[m] = implicit(qa);
+        ib[m] = implicit(qb);
+        ma[m] = 0.5f * dt * horner(opc, qa);
+        mb[m] = 0.5f * dt * horner(opc, qb);
+        na[m] = p.amp_pair * __builtin_amdgcn_sqrtf(fmaxf(horner(noi, qa), 0.f));
+        nb[m] = p.amp_pair * __builtin_amdgcn_sqrtf(fmaxf(horner(noi, qb), 0.f));
+        ka[m] = keep_of(k);
+        kb[m] = keep_of(kp);
+    }
+    // modes 0 and N/2 of slot 0
+    const float qn = q2_of(H);
+    const float n0 = p.amp_self * __builtin_amdgcn_sqrtf(fmaxf(horner(noi, q2_of(0)), 0.f));
+    const float nn = p.amp_self * __builtin_amdgcn_sqrtf(fmaxf(horner(noi, qn), 0.f));
+    const float in = implicit(qn), mn = 0.5f * dt * horner(opc, qn), kn = keep_of(H);
+
+    auto draw = [&](uint32_t mode, uint32_t step) {
+        const uint4 w = philox4x32_10(make_uint4(mode, step, fid, 0u), key0, key1);
+        return box_muller(w.x, w.y);
+    };
+    // twice F[products] of the masked state at this thread's pairs
+    float2 fa[PP], fb[PP];
+    auto products = [&]() {
+        float2 z[P];
+#pragma unroll
+        for (int m = 0; m < PP; ++m) {
+            const float2 A = make_float2(a[m].x * ka[m], a[m].y * ka[m]), B = make_float2(b[m].x * kb[m], b[m].y * kb[m]);
+            const float2 e = make_float2(A.x + B.x, A.y - B.y);                             // A + conj B
+            const float2 o = cmul(make_float2(A.x - B.x, A.y + B.y), cconj(wk[m]));         // (A - conj B) / w
+            float2 zl = make_float2(e.x - o.y, e.y + o.x), zh = make_float2(e.x + o.y, o.x - e.y);
+            if (m == 0 && zero) {
+                const float yn = a[0].y * kn;
+                zl = make_float2(A.x + yn, A.x - yn);
+                zh = make_float2(2.f * B.x, -2.f * B.y);
+            }
+            z[m] = zl;
+            // k = 0: H/2, this thread's own first upper point
+            xb[(H / 2 - t - m * T) & (H / 2 - 1)] = zh;
+        }
+        if constexpr (T > 64) __syncthreads(); else wave_lds_sync();
+#pragma unroll
+        for (int m = PP; m < P; ++m) z[m] = xb[t + (m - PP) * T];
+        FFT::template dif<1>(z, ld, t, tw);
+        // the products, even sites in .x and odd sites in .y
+        float2 w[P];
+#pragma unroll
+        for (int m = 0; m < P; ++m) {
+            z[m] = cscale(z[m], inv_n);
+            w[m] = make_float2(coef0, coef0);
+        }
+        times_power<0>(w, z, pow0);
+        for (int k = 1; k < nprod; ++k) {
+            const DevProd& pd = p.ch[0].prod[k];
+            float2 c[P];
+#pragma unroll
+            for (int m = 0; m < P; ++m) c[m] = make_float2(pd.coef, pd.coef);
+            times_power<0>(c, z, pd.pow[0]);
+#pragma unroll
+            for (int m = 0; m < P; ++m) w[m] = cadd(w[m], c[m]);
+        }
+        FFT::template dit<-1>(w, ld, t, tw);
+#pragma unroll
+        for (int m = PP; m < P; ++m) xb[t + (m - PP) * T] = w[m];
+        if constexpr (T > 64) __syncthreads(); else wave_lds_sync();
+#pragma unroll
+        for (int m = 0; m < PP; ++m) {
+            const float2 zl = w[m], zh = xb[(H / 2 - t - m * T) & (H / 2 - 1)];
+            const float2 e = make_float2(zl.x + zh.x, zl.y - zh.y);                 // 2 E = Z + conj Z'
+            const float2 o = cmul(make_float2(zl.y + zh.y, zh.x - zl.x), wk[m]);    // 2 w O = -i w (Z - conj Z')
+            fa[m] = cadd(e, o);
+            fb[m] = make_float2(e.x - o.x, o.y - e.y);
+            if (m == 0 && zero) {
+                fa[0] = make_float2(2.f * (zl.x + zl.y), 2.f * (zl.x - zl.y));
+                fb[0] = make_float2(2.f * zh.x, -2.f * zh.y);
+            }
+        }
+    };
+
+    float gn = 0.f;  // lane j: the normal of mode N/2 at step (sn & -NB) + j
+    bool bad = false;
+    for (int sn = 0; sn < nsteps; ++sn) {
+        const uint32_t step = step0 + static_cast<uint32_t>(sn);
+        products();
+        if (noisy && (sn & (NB - 1)) == 0 && t < 64) gn = draw(H, step + static_cast<uint32_t>(t & (NB - 1))).x;
+        const float gh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(gn), sn & (NB - 1)));
+#pragma unroll
+        for (int m = 0; m < PP; ++m) {
+            const int k = t + m * T, kp = zero && m == 0 ? H / 2 : H - k;
+            float2 ra = make_float2(fmaf(ma[m], fa[m].x, a[m].x), fmaf(ma[m], fa[m].y, a[m].y));
+            float2 rb = make_float2(fmaf(mb[m], fb[m].x, b[m].x), fmaf(mb[m], fb[m].y, b[m].y));
+            float ny = na[m], iy = ia[m];
+            if (m == 0 && zero) {
+                ra.y = fmaf(mn, fa[0].y, a[0].y);
+                iy = in;
+            }
+            if (noisy) {
+                float2 ga = draw(static_cast<uint32_t>(k), step);
+                const float2 gb = draw(static_cast<uint32_t>(kp), step);
+                float nx = na[m];
+                if (m == 0 && zero) {
+                    nx = n0;
+                    ny = nn;
+                    ga.y = gh;
+                }
+                ra = make_float2(fmaf(nx, ga.x, ra.x), fmaf(ny, ga.y, ra.y));
+                rb = make_float2(fmaf(nb[m], gb.x, rb.x), fmaf(nb[m], gb.y, rb.y));
+            }
+            a[m] = make_float2(ra.x * ia[m], ra.y * iy);
+            b[m] = cscale(rb, ib[m]);
+            bad |= !(__builtin_isfinite(a[m].x) && __builtin_isfinite(a[m].y) && __builtin_isfinite(b[m].x) &&
+                     __builtin_isfinite(b[m].y));
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < PP; ++m) {
+        const int k = t + m * T, kp = zero && m == 0 ? H / 2 : H - k;
+        const bool z = zero && m == 0;
+        gstore(bufs.S[0] + k, z ? make_float2(a[m].x, 0.f) : a[m]);
+        gstore(bufs.S[0] + (z ? H : N - k), z ? make_float2(a[m].y, 0.f) : cconj(a[m]));
+        gstore(bufs.S[0] + kp, b[m]);
+        gstore(bufs.S[0] + N - kp, cconj(b[m]));
+    }
+    if (bad) atomicOr(flag, 1u);
+    __syncthreads();  // every thread has read the counter
+    if (advance && t == 0) *step_ctr += static_cast<uint64_t>(nsteps);
+}
+
 // This file is compiled once per line length with -DPSS_LINE_LEN=<L> (the
 // kernels of that length) and once with -DPSS_COMMON (utilities and the
 // length dispatch), so the instantiations build in parallel.
@@ -3727,6 +3925,13 @@ static hipError_t launch_line1d_t(int mode, const LaunchArgs& a) {
     const dim3 grid(1), block(N / 4);
     const size_t lds = line1d_lds_bytes(N);
     uint64_t* ctr = const_cast<uint64_t*>(a.step_ctr);
+    if constexpr (NF == 1 && !GEN) {
+        if (mode == MODE_STEP && a.simple && !a.framed) {
+            hipLaunchKernelGGL((line1d_half_kernel<N>), grid, dim3(line_half_threads(N)), line_half_lds_bytes(N), a.stream,
+                               a.plan, a.bufs, ctr, a.flag, a.nsteps, a.advance != 0 ? 1 : 0, a.tw_x);
+            return hipGetLastError();
+        }
+    }
 #define PSS_L1(M)                                                                                                 \
     hipLaunchKernelGGL((line1d_kernel<N, NF, GEN, M>), grid, block, lds, a.stream, a.plan, a.bufs, ctr, a.flag, \
                        a.nsteps, a.advance != 0 ? 1 : 0, a.tw_x)

@@ -980,6 +980,8 @@ pss_status debug_check(pss_ctx* c, const char* kernel, int64_t step) {
                 kernel, static_cast<long long>(step));
 }
 
+bool has_frames(const pss_ctx* c);
+
 pss::LaunchArgs args(pss_ctx* c, int step_off = 0) {
     pss::LaunchArgs a{};
     a.stream = c->stream;
@@ -995,6 +997,7 @@ pss::LaunchArgs args(pss_ctx* c, int step_off = 0) {
     a.nmem = 1;
     a.general = c->plan.general != 0;
     a.simple = !a.general && c->plan.nf == 1 && c->plan.nch == 1 && c->plan.ng == 1 && c->plan.nd == 0;
+    a.framed = has_frames(c);
     a.step_off = step_off;
     a.tw_u = c->d_tw_u;
     a.tw_x = c->d_tw_x;

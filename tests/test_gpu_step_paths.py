@@ -93,3 +93,40 @@ def test_adjoint_line_forms(n, ckpt):
     twin = _gpu(n, seed=5)
     twin.step(11)
     assert lat.step_index == 11 and np.array_equal(lat.spectrum(0), twin.spectrum(0))
+
+
+# lines stepped on half spectra: every length's threads and waves, both ends of
+# the spectrum kept (no de-aliasing), two products in one channel, more steps
+# than the mode N/2 draws at once (64), and the same in two chunks
+@pytest.mark.parametrize("n", [8, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("dealias", [pss.DEALIAS_TWO_THIRDS, pss.DEALIAS_NONE])
+def test_half_spectrum_lines(n, dealias):
+    def make(chunks):
+        lat = pss.Lattice((n,), dt=0.01, seed=11, dealias=dealias)
+        f = lat.field("phi")
+        lat.term(f, [pss.Mono(1.0, q2=1), pss.Mono(-1.0, q2=2)], [(f, 1)], implicit=True)
+        lat.term(f, [pss.Mono(-1.0, q2=1)], [(f, 3)])
+        lat.term(f, [pss.Mono(-1.0, q2=1)], [(f, 2)])
+        lat.noise(f, [pss.Mono(0.01, q2=1), pss.Mono(0.01)])
+        lat.init_uniform(f, -0.1, 0.1)
+        for k in chunks:
+            lat.step(k)
+        return lat.spectrum(f), lat.download(f)
+
+    rule = {pss.DEALIAS_TWO_THIRDS: om.DEALIAS_TWO_THIRDS, pss.DEALIAS_NONE: om.DEALIAS_NONE}[dealias]
+    m = om.Model(OLattice(n), 0.01, seed=11, dealias=rule)
+    f = m.add_field("phi")
+    m.add_term(f, [om.Mono(1.0, q2=1), om.Mono(-1.0, q2=2)], [(f, 1)], implicit=True)
+    m.add_term(f, [om.Mono(-1.0, q2=1)], [(f, 3)])
+    m.add_term(f, [om.Mono(-1.0, q2=1)], [(f, 2)])
+    m.set_noise(f, [om.Mono(0.01, q2=1), om.Mono(0.01)])
+    m.init_uniform(f, -0.1, 0.1)
+    m.step(70)
+    sp, real = make([70])
+    # as the other 1D parity runs: 1e-4 of max(1, |phi|) after some 100 steps
+    want = m.real(f)[0, 0]
+    assert np.max(np.abs(real - want)) <= 1e-4 * max(1.0, np.max(np.abs(want)))
+    ws = m.state[f][0, 0, : n // 2 + 1]
+    assert np.max(np.abs(sp - ws)) <= 1e-4 * np.max(np.abs(ws))
+    sp2, _ = make([33, 37])
+    assert np.array_equal(sp, sp2)
