@@ -194,6 +194,7 @@ struct pss_ctx {
     pss::Member* d_member_x = nullptr;
     int batches = 0;        // live batches holding this context
     int tapes = 0;          // live adjoint tapes recorded on this context
+    bool quiet = false;     // its own stream holds no work: a call waited for it, none came after
     uint64_t state_gen = 0; // bumped by every change of the state (steps, uploads, loads)
     uint64_t enq_gen = 0;   // bumped whenever the context enqueues work on its own stream
     hipEvent_t after_batch = nullptr;  // the context's own work must wait for this batch event
@@ -1253,6 +1254,7 @@ pss_status begin_work(pss_ctx* c) {
         c->after_batch = nullptr;
     }
     ++c->enq_gen;
+    c->quiet = false;
     return PSS_OK;
 }
 
@@ -1268,8 +1270,13 @@ pss_status batch_order_before(pss_batch* b, const std::vector<int>& which) {
         if (c->stream == b->stream) continue;
         if (c->after_batch && c->after_batch != b->ev) HIP_TRY(hipStreamWaitEvent(b->stream, c->after_batch, 0));
         if (c->enq_gen != b->seen[i]) {
-            HIP_TRY(hipEventRecord(b->ev, c->stream));
-            HIP_TRY(hipStreamWaitEvent(b->stream, b->ev, 0));
+            // a member whose last call waited for its own stream has nothing to
+            // wait for (336 members, each downloaded between batch calls of 100
+            // steps: an event and a wait for each were 4 of the call's 13.8 ms)
+            if (!c->quiet) {
+                HIP_TRY(hipEventRecord(b->ev, c->stream));
+                HIP_TRY(hipStreamWaitEvent(b->stream, b->ev, 0));
+            }
             b->seen[i] = c->enq_gen;
         }
     }
@@ -1293,7 +1300,7 @@ pss_status clear_nonfinite(pss_ctx* c) {
     return PSS_OK;
 }
 
-pss_status state_to_real(pss_ctx* c, int field);
+pss_status state_to_real(pss_ctx* c, int field, float* dst = nullptr);
 pss_status forward_to_state(pss_ctx* c, int field);
 
 pss_status enqueue_steps(pss_ctx* c, int64_t k) {
@@ -1416,12 +1423,13 @@ pss_status forward_to_state(pss_ctx* c, int field) {
     return PSS_OK;
 }
 
-// Fourier state of `field` -> real-space array on the device (d_real)
-pss_status state_to_real(pss_ctx* c, int field) {
+// Fourier state of `field` -> real-space array `dst` on the device (d_real if null)
+pss_status state_to_real(pss_ctx* c, int field, float* dst) {
+    if (!dst) dst = c->d_real;
     pss::LaunchArgs a = args(c);
     if (c->ndim == 1) {
         a.bufs.sel = field;
-        a.bufs.real_out = c->d_real;
+        a.bufs.real_out = dst;
         HIP_TRY(pss::launch_line1d(pss::MODE_INV_OUT, c->n[0], 1, a));
         return PSS_OK;
     }
@@ -1431,7 +1439,7 @@ pss_status state_to_real(pss_ctx* c, int field) {
         HIP_TRY(pss::launch_mr2_col(pss::MODE_INV_OUT, 1, a));
         if (c->ndim == 3) HIP_TRY(mr_ypass(c, 1, &c->d_tmp, 1, true));
         a.bufs.in = c->d_tmp;
-        a.bufs.real_out = c->d_real;
+        a.bufs.real_out = dst;
         HIP_TRY(pss::launch_mr2_row(pss::MODE_C2R_OUT, a));
         return PSS_OK;
     }
@@ -1447,18 +1455,18 @@ pss_status state_to_real(pss_ctx* c, int field) {
         HIP_TRY(pss::launch_ypass(pss::MODE_YINV, c->n[1], ya, a));
     }
     a.bufs.in = c->d_tmp;
-    a.bufs.real_out = c->d_real;
+    a.bufs.real_out = dst;
     HIP_TRY(pss::launch_xrow(pss::MODE_C2R_OUT, c->n[0], 1, a));
     return PSS_OK;
 }
 
 // intermediate field i, computed from the current state -> real-space array
-// on the device (d_real)
-pss_status interm_to_real(pss_ctx* c, int i) {
+// `dst` on the device
+pss_status interm_to_real(pss_ctx* c, int i, float* dst) {
     pss::LaunchArgs a = args(c);
     if (c->ndim == 1) {
         a.bufs.sel = i;
-        a.bufs.real_out = c->d_real;
+        a.bufs.real_out = dst;
         HIP_TRY(pss::launch_line1d(pss::MODE_INTERM_OUT, c->n[0], static_cast<int>(c->fields.size()), a));
         return PSS_OK;
     }
@@ -1468,7 +1476,7 @@ pss_status interm_to_real(pss_ctx* c, int i) {
         HIP_TRY(pss::launch_mr2_col(pss::MODE_INTERM_OUT, static_cast<int>(c->fields.size()), a));
         if (c->ndim == 3) HIP_TRY(mr_ypass(c, 1, &c->d_tmp, 1, true));
         a.bufs.in = c->d_tmp;
-        a.bufs.real_out = c->d_real;
+        a.bufs.real_out = dst;
         HIP_TRY(pss::launch_mr2_row(pss::MODE_C2R_OUT, a));
         return PSS_OK;
     }
@@ -1484,7 +1492,7 @@ pss_status interm_to_real(pss_ctx* c, int i) {
         HIP_TRY(pss::launch_ypass(pss::MODE_YINV, c->n[1], ya, a));
     }
     a.bufs.in = c->d_tmp;
-    a.bufs.real_out = c->d_real;
+    a.bufs.real_out = dst;
     HIP_TRY(pss::launch_xrow(pss::MODE_C2R_OUT, c->n[0], 1, a));
     return PSS_OK;
 }
@@ -2170,6 +2178,7 @@ pss_status pss_stream_set(pss_ctx* c, void* stream) {
                     c->batches);
     if (c->tapes > 0) return fail(PSS_E_STATE, "an adjoint tape holds this lattice; destroy it first");
     if (c->planned && c->stream) HIP_TRY(hipStreamSynchronize(c->stream));
+    c->quiet = false;
     if (c->own_stream && c->stream) {
         (void)hipStreamDestroy(c->stream);
         c->own_stream = false;
@@ -2256,22 +2265,51 @@ pss_status pss_field_init_uniform(pss_ctx* c, int32_t field, double lo, double h
     return clear_nonfinite(c);
 }
 
+// Whether a kernel of this context may write `bytes` at p in place of a copy:
+// one allocation of this device's memory, as the copy would have checked.
+// 128^2: a download into device memory takes 19 us where it took 24.
+static bool device_array(const pss_ctx* c, const void* p, size_t bytes) {
+    hipPointerAttribute_t at{}, own{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || hipPointerGetAttributes(&own, c->d_work) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t off = static_cast<size_t>(static_cast<const char*>(p) - static_cast<const char*>(base));
+    return at.type == hipMemoryTypeDevice && at.device == own.device && reinterpret_cast<uintptr_t>(p) % sizeof(float) == 0 &&
+           off <= size && bytes <= size - off;
+}
+
 pss_status pss_field_download(pss_ctx* c, int32_t field, float* real, int32_t on_device) {
     if (pss_status s = check_ctx(c)) return s;
     if (!real) return fail(PSS_E_INVAL, "null array");
     if (pss_status s = materialize(c)) return s;
     const int code = field_code(c, field);
     if (code < 0) return fail(PSS_E_INVAL, "bad field");
+    // batch work that has ended needs no wait on the stream (a packet for
+    // each member in turn, 1 us of a download)
+    if (c->after_batch) {
+        if (hipEventQuery(c->after_batch) == hipSuccess)
+            c->after_batch = nullptr;
+        else
+            (void)hipGetLastError();  // not ready
+    }
     if (pss_status s_bw = begin_work(c)) return s_bw;
+    const size_t bytes = sizeof(float) * static_cast<size_t>(c->sites());
+    const bool direct = on_device && device_array(c, real, bytes);
+    float* const dst = direct ? real : c->d_real;
     if (is_interm(code)) {
-        if (pss_status s = interm_to_real(c, code - PSS_MAXF)) return s;
-    } else if (pss_status s = state_to_real(c, code)) {
+        if (pss_status s = interm_to_real(c, code - PSS_MAXF, dst)) return s;
+    } else if (pss_status s = state_to_real(c, code, dst)) {
         return s;
     }
-    const size_t bytes = sizeof(float) * static_cast<size_t>(c->sites());
-    HIP_TRY(hipMemcpyAsync(real, c->d_real, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                           c->stream));
+    if (!direct)
+        HIP_TRY(hipMemcpyAsync(real, c->d_real, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                               c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    c->quiet = c->own_stream;
     return PSS_OK;
 }
 

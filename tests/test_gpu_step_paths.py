@@ -130,3 +130,61 @@ def test_half_spectrum_lines(n, dealias):
     assert np.max(np.abs(sp - ws)) <= 1e-4 * np.max(np.abs(ws))
     sp2, _ = make([33, 37])
     assert np.array_equal(sp, sp2)
+
+
+# a batch after its members' own work: downloaded (nothing left on the member's
+# stream) and stepped alone (work left on it), one on a caller's stream
+def test_batch_orders_itself_after_downloads_and_steps():
+    import torch
+
+    def members():
+        lats = []
+        for i, n in enumerate([64, 64, 128, 256]):
+            lat = pss.Lattice((n, n), dt=0.01, seed=20 + i)
+            f, _ = pss.model_b(lat, D=0.01)
+            lat.init_uniform(f, -0.1, 0.1)
+            lats.append((lat, f))
+        return lats
+
+    lats, alone = members(), members()
+    stream = torch.cuda.Stream()
+    lats[1][0].stream(stream.cuda_stream)
+    batch = pss.Batch([lat for lat, _ in lats])
+    outs = [torch.empty(lat.shape, device="cuda") for lat, _ in lats]
+    for k in range(3):
+        batch.step(7)
+        for (lat, f), out in zip(lats, outs):
+            lat.download(f, out)
+        for (lat, _), out in zip(lats[::2], outs):
+            lat.step(120)
+        batch.step(5)
+        lats[1][0].download(lats[1][1], outs[1])
+    for i, (lat, f) in enumerate(alone):
+        for k in range(3):
+            lat.step(7)
+            if i % 2 == 0:
+                lat.step(120)
+            lat.step(5)
+    for (lat, f), (one, g) in zip(lats, alone):
+        assert np.array_equal(lat.spectrum(f), one.spectrum(g))
+
+
+# downloads into device memory written in place of a copy: a whole tensor, a
+# part of one at any offset, and host tensors, which are copied to
+@pytest.mark.parametrize("n", [(16,), (60,), (32, 16), (24, 20), (16, 8, 8)])
+def test_downloads_into_tensors(n):
+    import torch
+
+    lat = pss.Lattice(n, dt=0.01, seed=3)
+    f, _ = pss.model_b(lat, D=0.01)
+    lat.init_uniform(f, -0.1, 0.1)
+    lat.step(3)
+    want = lat.download(f)
+    for dev in ("cuda", "cpu"):
+        for off in (0, 1, 3, 64):
+            big = torch.full((want.size + 100,), 7.0, device=dev)
+            torch.cuda.synchronize()
+            lat.download(f, big[off:off + want.size])
+            got = big.cpu().numpy()
+            assert np.array_equal(got[off:off + want.size].reshape(want.shape), want)
+            assert np.all(got[:off] == 7.0) and np.all(got[off + want.size:] == 7.0)
