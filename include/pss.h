@@ -458,7 +458,11 @@ pss_status pss_kernels_per_step(pss_ctx *ctx, int32_t *count);
  * host or device memory per on_device) = dL/dphi_0(x) for the real initial
  * field.  The lattice is left at step n0 + nsteps with the forward final
  * state.  Device workspace: (ceil(nsteps/ckpt_every) + min(ckpt_every,
- * nsteps) + 8) arrays of Nx*Ny*4 bytes, allocated for the call. */
+ * nsteps) + 8) arrays of Nx*Ny*4 bytes (and 2 KiB each), allocated for the
+ * call; a run whose nsteps + 1 states fit in 256 MiB keeps them all instead of
+ * checkpoints, if that much is free, and recomputes nothing (set
+ * PSS_TAPE_WHOLE=0 in the environment to keep to the checkpoints).  The
+ * results are the same bits either way. */
 pss_status pss_adjoint_model_b(pss_ctx *ctx, int64_t nsteps, int32_t ckpt_every, const double *S_target,
                                int32_t n_shells, double *loss, double *grad, float *grad_phi0, int32_t on_device);
 

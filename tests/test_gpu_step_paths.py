@@ -188,3 +188,28 @@ def test_downloads_into_tensors(n):
             got = big.cpu().numpy()
             assert np.array_equal(got[off:off + want.size].reshape(want.shape), want)
             assert np.all(got[:off] == 7.0) and np.all(got[off + want.size:] == 7.0)
+
+
+# the adjoint with every state kept and with checkpoints: the same bits, the
+# same lattice afterwards (segments of one step, several, a shorter last one)
+@pytest.mark.parametrize("n,steps,ckpt", [((16, 8), 1, 1), ((64, 32), 23, 5), ((32, 1024), 9, 9), ((64, 64), 70, 1)])
+def test_adjoint_with_and_without_recomputation(monkeypatch, n, steps, ckpt):
+    from tests.test_gpu_adjoint import _gpu
+
+    S = np.full(min(n) // 2 - 1, 0.01)
+    got = []
+    for whole in ("0", "1"):
+        monkeypatch.setenv("PSS_TAPE_WHOLE", whole)
+        lat = _gpu(n, seed=5)
+        lat.step(2)
+        L, g, gphi = lat.adjoint_model_b(steps, S, ckpt_every=ckpt)
+        at = lat.step_index, lat.spectrum(0)
+        lat.step(3)
+        got.append((L, g, gphi, *at, lat.spectrum(0)))
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
+    twin = _gpu(n, seed=5)
+    twin.step(steps + 2)
+    assert np.array_equal(twin.spectrum(0), got[0][4])
+    twin.step(3)
+    assert np.array_equal(twin.spectrum(0), got[0][5])
