@@ -69,12 +69,12 @@ struct LdsLine {
     }
 };
 
-template <int L, int P, int PADS = kFftPad>
+template <int L, int P>
 struct LineFFT {
     static_assert((L & (L - 1)) == 0 && (P & (P - 1)) == 0 && P <= 16 && P <= L, "bad line shape");
     static constexpr int T = L / P;
     static constexpr bool kCross = T > 64;                  // the first exchange crosses waves
-    static constexpr int kReg = fft_region(L, PADS);        // one exchange region
+    static constexpr int kReg = fft_region(L);        // one exchange region
     static constexpr bool kOne = kCross && fft_one_buffer(L, P);  // one block buffer
     static constexpr int kLds = fft_regions(L, P) * kReg;         // LDS elements per line
     static __device__ __forceinline__ LdsLine lds_line(float2* base) {
@@ -85,7 +85,7 @@ struct LineFFT {
         ld.par = 0;
         return ld;
     }
-    static __device__ __forceinline__ int pad(int e) { return fft_padded(L, PADS) ? e + (e >> PADS) : e; }
+    static __device__ __forceinline__ int pad(int e) { return e + (e >> kFftPad); }
 
     // stage s: sub-transform length, group size and radix
     struct Stages {

@@ -9,8 +9,8 @@
 
 namespace pss {
 
-// pad shift of the per-lattice kernels; 0 means no padding (the fused batch
-// kernels, where the pad's address registers would cost occupancy)
+// pad shift (a step of 256 lattices of 128^2 held in LDS: 20.0 us with one pad
+// element in 8, 20.6 with one in 16, 20.9 in 32, 22.4 without)
 constexpr int kFftPad = PSS_FFT_PAD;
 
 // D(t): the first output index that thread t of L/P holds after a transform
@@ -33,9 +33,8 @@ inline int fft_drev(int L, int P, int t) {
     return d;
 }
 
-// elements of one exchange region of a line of L points, padded by shift `pads`
-constexpr bool fft_padded(int, int pads) { return pads > 0; }
-constexpr int fft_region(int L, int pads = kFftPad) { return fft_padded(L, pads) ? L + (L >> pads) : L; }
+// elements of one exchange region of a line of L points
+constexpr int fft_region(int L) { return L + (L >> kFftPad); }
 
 // Exchange regions of a line held by L/P threads: one within a wave; a line
 // of several waves adds two block buffers used in turn, or, from 2048 points
@@ -47,8 +46,8 @@ constexpr int fft_regions(int L, int P) { return L / P <= 64 ? 1 : (fft_one_buff
 
 // LDS elements of the line transforms of `lines` lines of L points held by
 // L/P threads each
-constexpr int fft_lds_elems(int L, int P, int lines, int pads = kFftPad) {
-    return lines * fft_regions(L, P) * fft_region(L, pads);
+constexpr int fft_lds_elems(int L, int P, int lines) {
+    return lines * fft_regions(L, P) * fft_region(L);
 }
 // the packed line's exchange: its own L elements, or the line's block buffer
 constexpr int fft_xbuf_elems(int L, int P) { return L / P > 64 && fft_one_buffer(L, P) ? 0 : L; }

@@ -185,12 +185,12 @@ struct ResidentLaunch {
 __host__ __device__ constexpr int resident_threads(int lx, int ly) {
     return (lx / 2) * (ly / 4) < 1024 ? (lx / 2) * (ly / 4) : 1024;
 }
-// LDS: padded channel/factor array, line scratch, packed-line exchange, twiddles
+// LDS: padded channel/factor array, line scratch, packed-line exchange
 inline size_t resident_lds_bytes(int lx, int ly) {
     const int nthr = resident_threads(lx, ly);
     const size_t scr_y = static_cast<size_t>(nthr / (ly / 4)) * fft_region(ly);
     const size_t scr_x = static_cast<size_t>(nthr / (lx / 4)) * fft_region(lx);
-    return sizeof(float2) * (static_cast<size_t>(lx / 2) * (ly + 1) + (scr_y > scr_x ? scr_y : scr_x) + 2 * ly + lx);
+    return sizeof(float2) * (static_cast<size_t>(lx / 2) * (ly + 1) + (scr_y > scr_x ? scr_y : scr_x) + ly);
 }
 inline bool resident_shape(int lx, int ly) { return (lx == 64 || lx == 128) && (ly == 64 || ly == 128); }
 hipError_t resident_setup();
@@ -373,13 +373,13 @@ inline int field_slots(int n) { return n <= 1 ? 1 : (n == 2 ? 2 : 4); }
 __host__ __device__ constexpr int line_block(int L, int P) { return L / P > 256 ? L / P : 256; }
 // LDS elements of the line transforms of `lines` lines of length L held with
 // P points per thread (pss_fft_layout.h)
-inline size_t fft_lds(int L, int P, int lines, int pads = kFftPad) {
-    return static_cast<size_t>(fft_lds_elems(L, P, lines, pads));
+inline size_t fft_lds(int L, int P, int lines) {
+    return static_cast<size_t>(fft_lds_elems(L, P, lines));
 }
 // dynamic LDS of the update kernel: TC*TO line transforms, one exchange line
 // and the twiddle table where it is staged, in that order
-inline size_t update_lds_bytes(int L, int P, int tc, int to, int pads = kFftPad) {
-    return sizeof(float2) * (fft_lds(L, P, tc * to, pads) + static_cast<size_t>(fft_xbuf_elems(L, P) + fft_tw_elems(L, P)));
+inline size_t update_lds_bytes(int L, int P, int tc, int to) {
+    return sizeof(float2) * (fft_lds(L, P, tc * to) + static_cast<size_t>(fft_xbuf_elems(L, P) + fft_tw_elems(L, P)));
 }
 // dynamic LDS of the y pass: TC*TZ line transforms, one exchange line per z
 // and the twiddle table where it is staged, in that order

@@ -265,6 +265,13 @@ __device__ __forceinline__ void hold(OpPoly& o) {
     hold(o.deg);
 }
 
+// what is computed from x after this is computed here, not ahead of a loop or
+// a transform (where its registers would be held)
+template <class I>
+__device__ __forceinline__ void fresh(I& x) {
+    asm volatile("" : "+v"(x));
+}
+
 // sum_j c[j] (q^2)^j for P modes.  The coefficients above the degree are
 // zeros, so starting at a fixed power gives c[deg] exactly when it is reached
 // and the value does not depend on which of the three lengths is taken.
@@ -428,9 +435,6 @@ __device__ __forceinline__ void mode_lin(int nx, int ny, int nz, int kx, int ky,
     const int ux = kx & (nx - 1), uy = ky & (ny - 1), uz = kz & (nz - 1);
     lin = at(ux, uy, uz);
     lneg = at((nx - ux) & (nx - 1), (ny - uy) & (ny - 1), (nz - uz) & (nz - 1));
-}
-__device__ __forceinline__ void mode_lin(const DevPlan& p, int kx, int ky, int kz, uint32_t& lin, uint32_t& lneg) {
-    mode_lin(p.n[0], p.n[1], p.n[2], kx, ky, kz, lin, lneg);
 }
 
 // f(integral_constant<int, I>) for I = 0 .. N-1, unrolled at compile time
@@ -773,13 +777,13 @@ __device__ __forceinline__ void source_line(const DevPlan& p, int src, const flo
 // arguments, so the plan reads stay scalar loads).  A launch of one lattice
 // (and the transform modes) takes buffers, counter and flag from the
 // arguments: its data loads then wait for no table load.
-template <int L, int P, int NF, int MODE, int DIM, bool GEN, bool TABLE, int PADS = kFftPad>
+template <int L, int P, int NF, int MODE, int DIM, bool GEN, bool TABLE>
 __device__ __forceinline__ void update_block(int mi, int blk, const Member* __restrict__ members,
                                              const DevPlan* __restrict__ plans, const DevPlan* __restrict__ plan_a,
                                              const Bufs& bufs_a, const Geo& geo,
                                              const uint64_t* __restrict__ step_ctr_a, uint32_t* __restrict__ flag_a,
                                              int step_off, const float2* __restrict__ tw_g) {
-    using FFT = LineFFT<L, P, PADS>;
+    using FFT = LineFFT<L, P>;
     constexpr int T = FFT::T;
     extern __shared__ float2 smem[];
     constexpr bool TAB = (MODE == MODE_STEP || MODE == MODE_PROLOGUE) && TABLE;
@@ -956,9 +960,18 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     };
     // Few points per thread: the launch is a round or two of blocks, and the
     // loads, the noise and the next channel go ahead of what needs them.  With
-    // 8 and more points other blocks cover the waits, and what would be held
-    // across the transforms costs waves: each is taken where it is used.
-    constexpr bool EARLY = P < 8;
+    // 8 and more points, and in batches, other blocks cover the waits, and what
+    // would be held across the transforms costs waves: each is taken where it
+    // is used.
+    constexpr bool EARLY = P < 8 && !TABLE;
+    // 2D lines of 2048 and 4096 and batches also hold nothing across a
+    // transform that can be formed after it (addresses, q^2) and draw the noise
+    // into the state.  4096: 148 -> 123 registers, two blocks of eight waves
+    // per CU instead of one, 91 -> 74 us a launch.  Batches of lines up to
+    // 1024: 129 -> 109, four waves a SIMD (64 lattices of 256^2 and 16 of
+    // 512^2: 42.8 -> 41.9 us a launch).  In 3D, whose launches are bound by memory, the
+    // fourth wave cost more than it hid (256^3: 57 -> 65 us).
+    constexpr bool LEAN = STEP && !EARLY && !GEN && DIM == 2;
     if constexpr (MODE == MODE_FRAME_FWD) {
         // the state from real space: the frame was set there
 #pragma unroll
@@ -992,11 +1005,16 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     // per-slot modes of the line (slot form on a packed line)
     constexpr bool LANES = T >= 4;
     LineCtx<P, LANES> cx;
+    auto set_q2 = [&]() {
+        int tq = t;
+        if constexpr (LEAN) fresh(tq);
 #pragma unroll
-    for (int m = 0; m < P; ++m) {
-        uint32_t lin, lneg;
-        slot_at<L>(lmode, t + m * T, cx.q2[m], lin, lneg);
-    }
+        for (int m = 0; m < P; ++m) {
+            uint32_t lin, lneg;
+            slot_at<L>(lmode, tq + m * T, cx.q2[m], lin, lneg);
+        }
+    };
+    if constexpr (!LEAN) set_q2();
     cx.pair_lane = pair_lane;
     cx.first_wave = blk_packed && tid < 64;
     if (cx.first_wave) {
@@ -1035,9 +1053,9 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
     if constexpr (STEP) {
         // The step's noise depends on the step and the modes only.  Per field:
         // of the slots, and of the four self-conjugate modes.
-        auto noise_of = [&](auto FF, float2 (&e)[P], Four& e4) {
+        auto noise_modes = [&](auto FF, auto&& use, Four& e4) {
             constexpr int f = decltype(FF)::value;
-            if (f < nf && noisy[f] != 0) {
+            {
                 const NoiseKey nk{key0, key1, step, fid[f], amp_pair, amp_self};
                 float Dn[P];
                 if constexpr (HOT) {
@@ -1055,10 +1073,10 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                     float q2m;
                     uint32_t lin, lneg;
                     slot_at<L>(lmode, t + m * T, q2m, lin, lneg);
-                    e[m] = noise_value<true>(nk, lin, lneg, Dn[m]);
+                    use(m, noise_value<true>(nk, lin, lneg, Dn[m]));
                     // two modes at a time: eight interleaved generators would
                     // hold some fifty registers
-                    if (P >= 8 && (m & 1)) __builtin_amdgcn_sched_barrier(0);
+                    if ((P >= 8 || LEAN) && (m & 1)) __builtin_amdgcn_sched_barrier(0);
                 }
                 if (cx.first_wave) {
                     e4 = self_eval(cx, [&](const Self& e) {
@@ -1070,6 +1088,12 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                         return noise_value(nk, e.lin, e.lneg, Ds).x;
                     });
                 }
+            }
+        };
+        auto noise_of = [&](auto FF, float2 (&e)[P], Four& e4) {
+            constexpr int f = decltype(FF)::value;
+            if (f < nf && noisy[f] != 0) {
+                noise_modes(FF, [&](int m, float2 v) { e[m] = v; }, e4);
             } else {
 #pragma unroll
                 for (int m = 0; m < P; ++m) e[m] = make_float2(0.f, 0.f);
@@ -1097,13 +1121,16 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             const int nout = NF == 1 ? 1 : C.nout;
             auto load_next = [&]() {
                 if (ch + 1 < nch) {
+                    auto at = iat;
+                    if constexpr (LEAN) fresh(at);
 #pragma unroll
-                    for (int m = 0; m < P; ++m) nxt[m] = gload_at(bufs.N[ch + 1], iat + m * istep);
+                    for (int m = 0; m < P; ++m) nxt[m] = gload_at(bufs.N[ch + 1], at + m * istep);
                 }
             };
             if constexpr (EARLY) load_next();
             FFT::template dit<-1>(v, ld, t, tw.get());
             exchange(v, true);
+            if constexpr (LEAN) set_q2();
             for (int o2 = 0; o2 < nout; ++o2) {
                 const DevOp& op = C.op[o2];
                 const int tg = NF == 1 ? 0 : C.target[o2];
@@ -1121,6 +1148,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             if constexpr (!EARLY) load_next();
         }
         if constexpr (!EARLY) load_state();
+        if constexpr (LEAN) set_q2();
         // Fourier-space terms with a single linear factor
         for (int d = 0; d < nd; ++d) {
             const DevDirect& Dd = p.direct[d];
@@ -1145,15 +1173,24 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
             if (f >= nf) return;
             const bool nz = noisy[f] != 0;
             constexpr int fe = EARLY ? f : 0;
-            if constexpr (!EARLY) noise_of(FF, eta[0], eta4[0]);
+            if constexpr (!EARLY && !LEAN) noise_of(FF, eta[0], eta4[0]);
+            if constexpr (LEAN) {
+                // two arrays instead of three while the noise is drawn
+#pragma unroll
+                for (int m = 0; m < P; ++m) s[f][m] = cadd(s[f][m], cscale(acc[f][m], dt));
+            }
             const float2 old0 = s[f][0], oldh = s[f][P / 2];
+            auto with_acc = [&](float2 v, int m) { return LEAN ? v : cadd(v, cscale(acc[f][m], dt)); };
+            if constexpr (LEAN) {
+                if (nz) noise_modes(FF, [&](int m, float2 e) { s[f][m] = cadd(s[f][m], e); }, eta4[0]);
+            }
             if constexpr (GEN) {
                 float2 A[P];
                 eval_op_p(p.implicit_op[f], cx.q2, qv, A);
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
-                    float2 r = cadd(s[f][m], cscale(acc[f][m], dt));
-                    if (nz) r = cadd(r, eta[fe][m]);
+                    float2 r = with_acc(s[f][m], m);
+                    if (!LEAN && nz) r = cadd(r, eta[fe][m]);
                     s[f][m] = cmul(r, cinv_implicit(dt, A[m]));
                 }
             } else {
@@ -1164,8 +1201,8 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                     horner_p(p.implicit_op[f], cx.q2, A);
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
-                    float2 r = cadd(s[f][m], cscale(acc[f][m], dt));
-                    if (nz) r = cadd(r, eta[fe][m]);
+                    float2 r = with_acc(s[f][m], m);
+                    if (!LEAN && nz) r = cadd(r, eta[fe][m]);
                     s[f][m] = cscale(r, __builtin_amdgcn_rcpf(fmaf(-dt, A[m], 1.f)));
                 }
             }
@@ -1180,7 +1217,7 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
                 });
                 if (pair_lane) {
                     // slots 0 and L/2 hold two real modes each
-                    float2 r = cadd(old0, cscale(acc[f][0], dt)), rh = cadd(oldh, cscale(acc[f][P / 2], dt));
+                    float2 r = with_acc(old0, 0), rh = with_acc(oldh, P / 2);
                     if (nz) {
                         r = make_float2(r.x + eta4[fe].v[0], r.y + eta4[fe].v[1]);
                         rh = make_float2(rh.x + eta4[fe].v[2], rh.y + eta4[fe].v[3]);
@@ -1251,8 +1288,10 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         }
         exchange(v, false);
         FFT::template dif<1>(v, ld, t, tw.get());
+        auto at = oat;
+        if constexpr (LEAN) fresh(at);
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore_at<!TABLE>(bufs.V[g], oat + m * ostep, v[m]);
+        for (int m = 0; m < P; ++m) gstore_at<!TABLE>(bufs.V[g], at + m * ostep, v[m]);
     }
 }
 
@@ -1654,12 +1693,12 @@ __device__ __forceinline__ void times_power(float2 (&a)[P], const float2 (&z)[P]
 }
 
 // One block of the x kernel: row block `blk` of lattice `mi` (as in the update kernel)
-template <int L, int P, int NG, int MODE, bool TABLE, int PADS = kFftPad>
+template <int L, int P, int NG, int MODE, bool TABLE>
 __device__ __forceinline__ void xrow_block(int mi, int blk, const Member* __restrict__ members,
                                            const DevPlan* __restrict__ plans, const DevPlan* __restrict__ plan_a,
                                            const Bufs& bufs_a, const Geo& geo, const float2* __restrict__ tw_g,
                                            int64_t advance, uint64_t* __restrict__ step_ctr_a) {
-    using FFT = LineFFT<L, P, PADS>;
+    using FFT = LineFFT<L, P>;
     constexpr int T = FFT::T;
     constexpr int NC = L / 2;  // packed columns
     extern __shared__ float2 smem[];
@@ -4047,10 +4086,7 @@ hipError_t PSS_CAT(launch_xrow_L, PSS_LINE_LEN)(int mode, int ng, const LaunchAr
 // ------------------------------------------------------ fused batch launches
 // One launch per phase for a whole batch: block b (XCD-ordered) finds its
 // class in the work list, then its member and tile, and runs the block body
-// built for that class's line length.  The update launch uses unpadded
-// transform exchanges: the pad's address arithmetic would raise the register
-// count of a kernel that holds every line length's body, and with it cut the
-// waves per SIMD from 4 to 3 (padding moves data only, never the results).
+// built for that class's line length.
 __device__ __forceinline__ int batch_class_of(const BatchLaunch& bl, int b) {
     int k = 0;
     for (int i = 1; i < bl.ncls; ++i)
@@ -4068,7 +4104,7 @@ __global__ void __launch_bounds__(256) batch_update_kernel(BatchLaunch bl) {
     const Bufs none{};
 #define PSS_BU(LL)                                                                                                 \
     case LL:                                                                                                       \
-        update_block<LL, 4, 1, MODE_STEP, 2, false, true, 0>(mi, blk, C.members, C.plans, nullptr, none, C.geo,       \
+        update_block<LL, 4, 1, MODE_STEP, 2, false, true>(mi, blk, C.members, C.plans, nullptr, none, C.geo,       \
                                                              nullptr,                                                 \
                                                           nullptr, bl.step_off, C.tw);                             \
         break;
@@ -4121,6 +4157,14 @@ __global__ void __launch_bounds__(256) batch_xrow_kernel(BatchLaunch bl) {
 // exchanged arrays (the x phase works on positions as rows).  The launch
 // loads the state and the channel array, runs rl.nsteps steps, stores both
 // back and moves the member's step counter on.
+//
+// What bounds it: one block of 16 waves a CU, so 128 registers a thread, 70 %
+// of whose cycles issue vector instructions at 128^2.  The plan's values stay
+// in scalar registers and the twiddles in vector registers over the steps
+// (they were read from memory and from LDS in each), and addresses and q^2 are
+// formed where they are used: hoisted out of the loop over steps they spilled.
+// 256 lattices, a step: 128^2 23.2 -> 20.0 us, 64 x 128 12.5 -> 10.8, 64^2 9.4
+// -> 6.6.
 template <int LX, int LY>
 __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(ResidentLaunch rl) {
     constexpr int P = 4;
@@ -4140,9 +4184,6 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
     float2* const scr = X + NC * XS;                 // one exchange region per line of a round
     constexpr int SCR = CPR * FY::kReg > RPR * FX::kReg ? CPR * FY::kReg : RPR * FX::kReg;
     float2* const xbuf = scr + SCR;                  // packed-line exchange (LY)
-    float2* const twy_w = xbuf + LY;
-    float2* const twx_w = twy_w + LY;
-    const float2 *const twy = twy_w, *const twx = twx_w;
     const int mi = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
     const Member& mem = rl.members[mi];
     const DevPlan& p = rl.plans[mi];
@@ -4152,8 +4193,6 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
     float2* __restrict__ Sg = mem.bufs.S[0];
     float2* __restrict__ Ng = mem.bufs.N[0];
 
-    for (int i = tid; i < LY; i += NTHR) twy_w[i] = rl.tw_y[i];
-    for (int i = tid; i < LX; i += NTHR) twx_w[i] = rl.tw_x[i];
     // column phase: line li of the round, thread t of the line
     const int li = tid / TY, tcol = tid & (TY - 1);
     LdsLine ldc;
@@ -4167,6 +4206,17 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
     ldr.blk0 = ldr.blk1 = nullptr;
     ldr.par = 0;
 
+    // twiddles: 6 or 8 values, the same for both directions of a square lattice
+    typename FY::Regs twy;
+    typename FX::Regs twx_own;
+    twy.load(rl.tw_y, tcol);
+    if constexpr (LX != LY) twx_own.load(rl.tw_x, trow);
+    const auto& twx = [&]() -> const auto& {
+        if constexpr (LX == LY)
+            return twy;
+        else
+            return twx_own;
+    }();
     // the state of this thread's column slots, and the channel array
     float2 st[CR][P];
 #pragma unroll
@@ -4182,18 +4232,30 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
         X[c * XS + y] = gload(Ng + i);
     }
     const uint32_t step0 = static_cast<uint32_t>(gload_u64(mem.step_ctr));
+    // the plan's values, once for all steps
+    float dt = p.dt, qs[3] = {p.qs[0], p.qs[1], p.qs[2]}, inv_n = p.inv_n, amp_pair = p.amp_pair, amp_self = p.amp_self;
+    uint32_t key0 = p.key0, key1 = p.key1;
+    int noisy = p.noisy[0], fid = p.fid[0], nch = p.nch, nd = p.nd, ng = p.ng, ncol = p.mask[0].ncol, ny = p.n[1];
+    OpPoly imp = op_poly(p.implicit_op[0]), noi = op_poly(p.noise_op[0]), ch0 = op_poly(p.ch[0].op[0]);
+    hold(dt), hold(inv_n), hold(amp_pair), hold(amp_self), hold(key0), hold(key1), hold(noisy), hold(fid), hold(nch);
+    hold(nd), hold(ng), hold(ncol), hold(ny), hold(imp), hold(noi), hold(ch0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) hold(qs[i]);
     // the four self-conjugate modes of column 0, one per lane (as in the update kernel)
-    const Self self = self_modes<LY, 2>(nx, LY, 1, p.qs, 0, tid);
+    const Self self = self_modes<LY, 2>(nx, LY, 1, qs, 0, tid);
     __syncthreads();
 
     uint32_t bad = 0;
     for (int sn = 0; sn < rl.nsteps; ++sn) {
         const uint32_t step = step0 + static_cast<uint32_t>(sn);
+        const NoiseKey nk{key0, key1, step, fid, amp_pair, amp_self};
         // ---- column phase: forward y transform of the channel, update,
         // de-aliased inverse y transform of the factor
 #pragma unroll
         for (int r = 0; r < CR; ++r) {
-            const int c = r * CPR + li;
+            int lif = li;
+            fresh(lif);
+            const int c = r * CPR + lif;
             const bool blk_packed = r == 0;  // the round holding column 0 (block-uniform)
             const bool packed = c == 0;
             const bool pair_lane = packed && tcol == 0;
@@ -4217,77 +4279,77 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
                 }
                 __syncthreads();
             };
-            const LineModes lmode = line_modes<LY, 2>(nx, p.n[1], p.qs, packed, kx_l, ky_l);
+            const LineModes lmode = line_modes<LY, 2>(nx, ny, qs, packed, kx_l, ky_l);
             float2(&s)[P] = st[r];
-            float q2[P];
-            uint32_t lin[P], lneg[P];
+            // one round after the other, and within it one thing after the
+            // other: interleaved, they spilled
+            __builtin_amdgcn_sched_barrier(0);
+            auto slot_q2 = [&](float (&q2)[P]) {
+                int tq = tcol;
+                fresh(tq);
 #pragma unroll
-            for (int m = 0; m < P; ++m) slot_at<LY>(lmode, tcol + m * TY, q2[m], lin[m], lneg[m]);
-            float2 acc[1][P];
+                for (int m = 0; m < P; ++m) {
+                    uint32_t lin, lneg;
+                    slot_at<LY>(lmode, tq + m * TY, q2[m], lin, lneg);
+                }
+            };
+            float2 acc[P];
 #pragma unroll
-            for (int m = 0; m < P; ++m) acc[0][m] = make_float2(0.f, 0.f);
-            if (p.nch > 0) {
-                const DevChannel& C = p.ch[0];
+            for (int m = 0; m < P; ++m) acc[m] = make_float2(0.f, 0.f);
+            auto add_term = [&](const OpPoly& op, const float2 (&v)[P]) {
+                float q2[P], M[P];
+                slot_q2(q2);
+                horner_p(op, q2, M);
+                Four f{};
+                if (first_wave) f = four_lanes(horner(op, self.q.q2));
+#pragma unroll
+                for (int m = 0; m < P; ++m)
+                    if (!(pair_lane && (m == 0 || m == P / 2))) acc[m] = cadd(acc[m], cscale(v[m], M[m]));
+                if (pair_lane) {
+                    float2 lo, hi;
+                    pair_scale(f, v, lo, hi);
+                    acc[0] = cadd(acc[0], lo);
+                    acc[P / 2] = cadd(acc[P / 2], hi);
+                }
+            };
+            if (nch > 0) {
                 float2 v[P];
 #pragma unroll
                 for (int m = 0; m < P; ++m) v[m] = col[tcol + m * TY];
                 FY::template dit<-1>(v, ldc, tcol, twy);
                 exchange(v, true);
-                float M[P];
-                horner_p(C.op[0], q2, M);
-#pragma unroll
-                for (int m = 0; m < P; ++m)
-                    if (!(pair_lane && (m == 0 || m == P / 2))) add_to(acc, C.target[0], m, cscale(v[m], M[m]));
-                if (first_wave) {
-                    const Four f = four_lanes(horner(C.op[0], self.q.q2));
-                    float2 lo, hi;
-                    pair_scale(f, v, lo, hi);
-                    if (pair_lane) {
-                        acc[0][0] = cadd(acc[0][0], lo);
-                        acc[0][P / 2] = cadd(acc[0][P / 2], hi);
-                    }
-                }
+                add_term(ch0, v);
             }
-            for (int d = 0; d < p.nd; ++d) {
-                const DevDirect& Dd = p.direct[d];
-                float2 src[P];
-#pragma unroll
-                for (int m = 0; m < P; ++m) src[m] = s[m];
-                float M[P];
-                horner_p(Dd.op, q2, M);
-#pragma unroll
-                for (int m = 0; m < P; ++m)
-                    if (!(pair_lane && (m == 0 || m == P / 2))) add_to(acc, Dd.target, m, cscale(src[m], M[m]));
-                if (first_wave) {
-                    const Four f = four_lanes(horner(Dd.op, self.q.q2));
-                    float2 lo, hi;
-                    pair_scale(f, src, lo, hi);
-                    if (pair_lane) {
-                        acc[0][0] = cadd(acc[0][0], lo);
-                        acc[0][P / 2] = cadd(acc[0][P / 2], hi);
-                    }
-                }
-            }
+            for (int d = 0; d < nd; ++d) add_term(op_poly(p.direct[d].op), s);
             {
-                const bool noisy = p.noisy[0] != 0;
-                const float2 old0 = s[0], oldh = s[P / 2];
-                float Ar[P], Dn[P];
-                horner_p(p.implicit_op[0], q2, Ar);
-                if (noisy) horner_p(p.noise_op[0], q2, Dn);
 #pragma unroll
-                for (int m = 0; m < P; ++m) {
-                    float2 rr = cadd(s[m], cscale(acc[0][m], p.dt));
-                    if (noisy) rr = cadd(rr, noise_value(p, 0, step, lin[m], lneg[m], Dn[m]));
-                    s[m] = cscale(rr, __builtin_amdgcn_rcpf(fmaf(-p.dt, Ar[m], 1.f)));
+                for (int m = 0; m < P; ++m) s[m] = cadd(s[m], cscale(acc[m], dt));
+                const float2 old0 = s[0], oldh = s[P / 2];
+                __builtin_amdgcn_sched_barrier(0);
+                float q2[P], A[P];
+                slot_q2(q2);
+                if (noisy) {
+                    int tq = tcol;
+                    fresh(tq);
+                    horner_p(noi, q2, A);
+#pragma unroll
+                    for (int m = 0; m < P; ++m) {
+                        float q2m;
+                        uint32_t lin, lneg;
+                        slot_at<LY>(lmode, tq + m * TY, q2m, lin, lneg);
+                        s[m] = cadd(s[m], noise_value<true>(nk, lin, lneg, A[m]));
+                        if (m & 1) __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
+                horner_p(imp, q2, A);
+#pragma unroll
+                for (int m = 0; m < P; ++m) s[m] = cscale(s[m], __builtin_amdgcn_rcpf(fmaf(-dt, A[m], 1.f)));
                 if (first_wave) {
-                    const Four inv = four_lanes(
-                        cinv_implicit(p.dt, make_float2(horner(p.implicit_op[0], self.q.q2), 0.f)).x);
+                    const Four inv = four_lanes(cinv_implicit(dt, make_float2(horner(imp, self.q.q2), 0.f)).x);
                     Four e{};
-                    if (noisy)
-                        e = four_lanes(noise_value(p, 0, step, self.lin, self.lneg, horner(p.noise_op[0], self.q.q2)).x);
+                    if (noisy) e = four_lanes(noise_value(nk, self.lin, self.lneg, horner(noi, self.q.q2)).x);
                     if (pair_lane) {
-                        float2 rl = cadd(old0, cscale(acc[0][0], p.dt)), rh = cadd(oldh, cscale(acc[0][P / 2], p.dt));
+                        float2 rl = old0, rh = oldh;
                         if (noisy) {
                             rl = make_float2(rl.x + e.v[0], rl.y + e.v[1]);
                             rh = make_float2(rh.x + e.v[2], rh.y + e.v[3]);
@@ -4302,7 +4364,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
             }
             // de-aliased inverse transform of the factor (lines of a wave whose
             // first column is past the kept ones are never read)
-            if (p.ng > 0 && (c / LPW) * LPW < p.mask[0].ncol) {
+            if (ng > 0 && (c / LPW) * LPW < ncol) {
                 const int lim = p.lim[0][kx_l], limN = p.lim[0][nx >> 1];
                 float2 v[P];
 #pragma unroll
@@ -4333,15 +4395,18 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
         // values, the products, forward x transform into the channel values
 #pragma unroll
         for (int r = 0; r < CR; ++r) {
-            const int p0 = 2 * (r * RPR + pi);  // first position of the pair
-            if (p.nch == 0) break;
-            const int ncol = p.mask[0].ncol;
+            int pf = pi, tf = trow;
+            fresh(pf);
+            fresh(tf);
+            const int p0 = 2 * (r * RPR + pf);  // first position of the pair
+            if (nch == 0) break;
+            __builtin_amdgcn_sched_barrier(0);
             float2 v[P];
             {
                 float2 a[P], b[P];
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
-                    const int k = trow + m * TX;
+                    const int k = tf + m * TX;
                     const int kk = (k == NC) ? 0 : (k < NC ? k : LX - k);
                     const int kc = kk < ncol ? kk : 0;
                     a[m] = X[kc * XS + p0];
@@ -4349,7 +4414,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
                 }
 #pragma unroll
                 for (int m = 0; m < P; ++m) {
-                    const int k = trow + m * TX;
+                    const int k = tf + m * TX;
                     const int kk = (k == NC) ? 0 : (k < NC ? k : LX - k);
                     const float2 zero = make_float2(0.f, 0.f);
                     const float2 am = kk < ncol ? a[m] : zero, bm = kk < ncol ? b[m] : zero;
@@ -4367,7 +4432,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
             FX::template dif<1>(v, ldr, trow, twx);
             float2 z[P];
 #pragma unroll
-            for (int m = 0; m < P; ++m) z[m] = cscale(v[m], p.inv_n);
+            for (int m = 0; m < P; ++m) z[m] = cscale(v[m], inv_n);
             const DevChannel& C = p.ch[0];
             float2 w[P];
 #pragma unroll
@@ -4391,7 +4456,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
             wave_lds_sync();
 #pragma unroll
             for (int j = 0; j < NC / TX; ++j) {
-                const int c = trow + j * TX;
+                const int c = tf + j * TX;
 #pragma unroll
                 for (int rr = 0; rr < 2; ++rr) {
                     float2 o;

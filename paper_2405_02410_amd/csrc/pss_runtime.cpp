@@ -1642,8 +1642,7 @@ void batch_plan_fused(pss_batch* b) {
             C.tw = r->d_tw_u;
             C.geo = r->geo;
             b->fu.total += nmem * C.nblk;
-            // the fused update kernel's transforms are unpadded (its register budget)
-            b->fu_lds = std::max(b->fu_lds, pss::update_lds_bytes(r->lu, 4, r->geo.tc, 1, 0));
+            b->fu_lds = std::max(b->fu_lds, pss::update_lds_bytes(r->lu, 4, r->geo.tc, 1));
             b->in_fu[k] = 1;
         }
         const int nx = r->n[0], ny = r->n[1];
