@@ -302,6 +302,19 @@ struct LineFFT {
     static __device__ __forceinline__ void dit(float2 (&v)[P], LdsLine& ld, int t, const TW& tw) {
         dit_stage<DIR, 0>(v, ld, t, tw);
     }
+    // the points D(t) + m T in v for the points t + m T, through LDS (lines of
+    // several waves; called by the whole block)
+    static __device__ __forceinline__ void to_natural(float2 (&v)[P], LdsLine& ld, int t) {
+        static_assert(kCross, "lines of several waves");
+        float2* const buf = ld.next_blk();
+        const int d = drev(t);
+        if constexpr (kOne) __syncthreads();
+#pragma unroll
+        for (int m = 0; m < P; ++m) buf[pad(d + m * T)] = v[m];
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < P; ++m) v[m] = buf[pad(t + m * T)];
+    }
     // with the table in LDS
     template <int DIR>
     static __device__ __forceinline__ void dif(float2 (&v)[P], LdsLine& ld, int t, const float2* tw) {

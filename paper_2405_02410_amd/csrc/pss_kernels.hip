@@ -899,8 +899,17 @@ __device__ __forceinline__ void update_block(int mi, int blk, const Member* __re
         tw.ready(twl, tid, nthr);
         exchange(v, false);
         FFT::template dif<1>(v, ld, t, tw.get());
+        if constexpr (FFT::kCross) {
+            // a wave of a longer line would write 8 bytes of 64 places far
+            // apart: put in order first (4096^2: 56 -> 40 us a launch; the rows
+            // of C2R_OUT, gathered 16 bytes a place, gained nothing by it)
+            FFT::to_natural(v, ld, t);
 #pragma unroll
-        for (int m = 0; m < P; ++m) gstore(bufs.out + xout.at(dr + m * T), v[m]);
+            for (int m = 0; m < P; ++m) gstore(bufs.out + xout.at(t + m * T), v[m]);
+        } else {
+#pragma unroll
+            for (int m = 0; m < P; ++m) gstore(bufs.out + xout.at(dr + m * T), v[m]);
+        }
         return;
     }
 
