@@ -603,7 +603,7 @@ def main():
         return
     if args.workload == "mixed":
         x = mixed_radix(args, pss, torch)
-        cfg = {"workload": "2D Model B 960x960 FP32 (960 = 2^6 3 5: full spectra, radix-4/2/3/5 passes), a=-1 "
+        cfg = {"workload": "2D Model B 960x960 FP32 (960 = 2^6 3 5), a=-1 "
                            "b=1 k=1, conserved noise D=0.01 q^2, dt=0.01, 2/3 radial de-aliasing",
                "lattice": x["lattice"], "parallelism": "single GPU"}
         print(json.dumps(line(cfg, x["value"], x["steps"], min(args.warmup, 20), x["ms_per_step"],
