@@ -4235,11 +4235,18 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
 #pragma unroll
         for (int m = 0; m < P; ++m) st[r][m] = gload(Sg + base + static_cast<size_t>(tcol + m * TY) * tc);
     }
-    for (int i = tid; i < NC * LY; i += NTHR) {
+    // place in X of element i of the channel array, which lies as the step
+    // kernels' exchange arrays do (Exch): column tiles, or groups of four rows
+    const bool grp = rl.geo.grp != 0;
+    auto place = [&](int i) {
+        if (grp) {
+            const int g = i >> 2;
+            return (g & (NC - 1)) * XS + 4 * (g / NC) + (i & 3);
+        }
         const int ct = i / (LY * tc), rem = i - ct * (LY * tc);
-        const int y = rem >> lt, c = (ct << lt) + (rem & (tc - 1));
-        X[c * XS + y] = gload(Ng + i);
-    }
+        return ((ct << lt) + (rem & (tc - 1))) * XS + (rem >> lt);
+    };
+    for (int i = tid; i < NC * LY; i += NTHR) X[place(i)] = gload(Ng + i);
     const uint32_t step0 = static_cast<uint32_t>(gload_u64(mem.step_ctr));
     // the plan's values, once for all steps
     float dt = p.dt, qs[3] = {p.qs[0], p.qs[1], p.qs[2]}, inv_n = p.inv_n, amp_pair = p.amp_pair, amp_self = p.amp_self;
@@ -4492,11 +4499,7 @@ __global__ void __launch_bounds__(resident_threads(LX, LY)) resident_kernel(Resi
 #pragma unroll
         for (int m = 0; m < P; ++m) gstore(Sg + base + static_cast<size_t>(tcol + m * TY) * tc, st[r][m]);
     }
-    for (int i = tid; i < NC * LY; i += NTHR) {
-        const int ct = i / (LY * tc), rem = i - ct * (LY * tc);
-        const int y = rem >> lt, c = (ct << lt) + (rem & (tc - 1));
-        gstore(Ng + i, X[c * XS + y]);
-    }
+    for (int i = tid; i < NC * LY; i += NTHR) gstore(Ng + i, X[place(i)]);
     if (bad) atomicOr(mem.flag, bad);
     if (rl.advance && tid == 0) *mem.step_ctr += static_cast<uint64_t>(rl.nsteps);
 }

@@ -325,3 +325,34 @@ def test_batch_of_multi_field_models_is_bitwise_the_single_path():
         for f in ids:
             assert np.array_equal(m.spectrum(f), r.spectrum(f))
     batch.close()
+
+
+@pytest.mark.parametrize("n", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("tc", [1, 2])
+def test_resident_launch_at_other_tile_widths(n, tc):
+    """The LDS-resident kernel takes the product array as the step kernels
+    leave it, at every tile width (one column: rows in groups of four), and
+    leaves it so: members stepped alone before and after the batch."""
+    def make():
+        lats = []
+        for i in range(3):
+            lat = pss.Lattice(n, dt=0.01, seed=60 + i)
+            lat.tune(tc=tc)
+            f, _ = pss.model_b(lat, D=0.01)
+            lat.init_uniform(f, -0.1, 0.1)
+            lats.append(lat)
+        return lats
+    mem, twins = make(), make()
+    batch = pss.Batch(mem)
+    assert batch.launches()[2] == 1
+    mem[0].step(3)
+    for k in (1, 60):
+        batch.step(k)
+    mem[0].step(4)
+    mem[1].step(2)
+    batch.step(5)
+    for lat, tw, k in zip(mem, twins, (73, 68, 66)):
+        tw.step(k)
+        assert lat.step_index == k
+        assert np.array_equal(lat.spectrum(0), tw.spectrum(0))
+    batch.close()
