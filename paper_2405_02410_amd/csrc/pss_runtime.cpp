@@ -1536,7 +1536,11 @@ pss_status graph_for(pss_ctx* c, int64_t k, hipGraphExec_t* out) {
     }
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+    // framed steps end with the products of their state; recording them runs
+    // nothing, so products that are out of date stay so
+    const bool stale = c->dirty;
     pss_status st = enqueue_steps(c, k);
+    c->dirty = stale;
     hipError_t e = hipStreamEndCapture(c->stream, &g);
     if (st) {
         if (g) (void)hipGraphDestroy(g);

@@ -38,3 +38,36 @@ def test_fused_frame_steps(n, tune):
     got = lat.download(f)
     # 4 steps of four transforms each, ~5e-7 of the framed |phi| <= 0.2 apiece
     assert np.max(np.abs(got - m.real(0).reshape(got.shape))) <= 4e-6
+
+
+# the step graphs built before any step is taken (prepare) change nothing: the
+# first step still forms the products of the uploaded state, on every route of
+# a framed step
+@pytest.mark.parametrize("n", [(64, 32), (1024, 16), (16, 16, 16), (96, 64), (24, 12, 16), (64,), (60,)])
+@pytest.mark.parametrize("fields", [1, 2])
+def test_framed_steps_after_prepare(n, fields):
+    nx = n[0]
+    sites = np.array([i for i in range(int(np.prod(n))) if i % nx < 2])
+    rng = np.random.default_rng(3)
+    first, second = (rng.uniform(-0.1, 0.1, tuple(reversed(n))).astype(np.float32) for _ in range(2))
+
+    def run(prepare):
+        lat = pss.Lattice(n, dt=0.01, seed=5)
+        f, _ = pss.model_b(lat, D=0.01)
+        if fields == 2:
+            g = lat.field("psi")
+            lat.term(g, [pss.Mono(-1.0, q2=1)], [(g, 1)], implicit=True)
+            lat.term(g, [pss.Mono(-0.3)], [(f, 1), (g, 1)])
+            lat.upload(g, second)
+        lat.frame(f, sites, np.full(sites.size, 0.2, dtype=np.float32))
+        out = []
+        for x, k in ((first, 1), (second, 3), (first, 52)):
+            lat.upload(f, x)
+            if prepare:
+                lat.prepare(k)
+            lat.step(k)
+            out.append(lat.spectrum(f))
+        return out
+
+    for a, b in zip(run(True), run(False)):
+        assert np.array_equal(a, b)
