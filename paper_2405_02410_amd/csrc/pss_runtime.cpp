@@ -1922,6 +1922,10 @@ struct SaveHeader {
     int64_t step;
 };
 
+// columns per tile of the state's layout (1 for full spectra, which have no
+// tiles; there geo.tc only groups the lines of a launch)
+int32_t state_tc(const pss_ctx* c) { return c->mixed ? 1 : c->geo.tc; }
+
 }  // namespace
 
 extern "C" {
@@ -2498,7 +2502,7 @@ pss_status pss_state_save(pss_ctx* c, void* dst, size_t bytes) {
     h.ndim = c->ndim;
     h.nf = static_cast<int32_t>(c->fields.size());
     for (int i = 0; i < 3; ++i) h.n[i] = c->n[i];
-    h.tc = c->geo.tc;
+    h.tc = state_tc(c);
     h.step = c->steps_taken;
     std::memcpy(dst, &h, sizeof(h));
     char* p = static_cast<char*>(dst) + sizeof(h);
@@ -2518,7 +2522,7 @@ pss_status pss_state_load(pss_ctx* c, const void* src, size_t bytes) {
     SaveHeader h;
     std::memcpy(&h, src, sizeof(h));
     if (std::memcmp(h.magic, "PSSSTAT1", 8) != 0 || h.ndim != c->ndim || h.nf != static_cast<int>(c->fields.size()) ||
-        h.n[0] != c->n[0] || h.n[1] != c->n[1] || h.n[2] != c->n[2] || h.tc != c->geo.tc)
+        h.n[0] != c->n[0] || h.n[1] != c->n[1] || h.n[2] != c->n[2] || (h.tc != state_tc(c) && !c->mixed))
         return fail(PSS_E_INVAL, "state buffer does not match this lattice");
     const char* p = static_cast<const char*>(src) + sizeof(h);
     const size_t fb = sizeof(float2) * static_cast<size_t>(c->packed());

@@ -138,3 +138,31 @@ def test_lines_per_block_are_bitwise_and_checked():
     with pytest.raises(PssError) as e:
         lat.init_uniform(0, -0.1, 0.1)
     assert e.value.name == "PSS_E_UNSUPPORTED"
+
+
+# "tc" only groups the lines of a launch here, it is no part of the state: a
+# saved state loads at any value, and a default lattice saves what it always did
+def test_saved_states_load_at_any_number_of_lines_per_block():
+    n = (864, 16)
+
+    def make(tc):
+        lat = pss.Lattice(n, dt=0.01, seed=8)
+        f, _ = pss.model_b(lat, D=0.02)
+        if tc:
+            lat.tune(tc=tc)
+        lat.init_uniform(f, -0.2, 0.2)
+        return lat
+
+    default = make(None)
+    default.step(3)
+    blob = default.save()
+    assert int(np.frombuffer(blob[28:32], dtype=np.int32)[0]) == 1  # header: magic, ndim, nf, n[3], tc
+    default.step(4)
+    for tc in (1, 2, 4):
+        lat = make(tc)
+        lat.load(blob)
+        lat.step(4)
+        assert np.array_equal(lat.spectrum(0), default.spectrum(0)), tc
+        other = make(None)
+        other.load(lat.save())
+        assert other.step_index == 7 and np.array_equal(other.spectrum(0), default.spectrum(0)), tc
