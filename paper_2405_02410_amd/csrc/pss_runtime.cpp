@@ -2402,6 +2402,7 @@ pss_status pss_step(pss_ctx* c, int64_t nsteps) {
         // the same kernels, enqueued one by one and checked after each
         for (int64_t i = 0; i < nsteps; ++i) {
             if (pss_status s = enqueue_steps(c, 1)) {
+                c->dirty = true;  // the step's products may not have been formed
                 ++c->state_gen;
                 return s;
             }
@@ -2992,18 +2993,38 @@ pss_status pss_adjoint_model_b_forward(pss_ctx* c, int64_t nsteps, int32_t ckpt_
     tp->n0 = c->steps_taken;
     if (tp->whole) {
         if (c->dirty) TAPE_TRY(prologue(c));
-        TAPE_HIP(hipMemcpyAsync(tape_state(tp, 0, 0), c->d_state[0], fb, hipMemcpyDeviceToDevice, c->stream));
-        pss::LaunchArgs ax = xargs(c);
-        for (int64_t i = 0; i < nsteps; ++i) {
-            pss::LaunchArgs a = args(c, static_cast<int>(i));
-            a.bufs.S[0] = tape_state(tp, 0, i);
-            a.bufs.out = tape_state(tp, 0, i + 1);
-            TAPE_HIP(pss::launch_update(pss::MODE_STEP, c->lu, 1, a));
-            ax.advance = i == nsteps - 1 ? nsteps : 0;
-            TAPE_HIP(pss::launch_xrow(pss::MODE_STEP, nx, 1, ax));
-            TAPE_TRY(debug_check(c, "recorded step", tp->n0 + i));
+        // until the run has ended the products belong to a state of the tape
+        c->dirty = true;
+        int64_t i = 0, done = 0;  // the step at hand, steps whose new state is enqueued
+        auto record = [&]() -> pss_status {
+            HIP_TRY(hipMemcpyAsync(tape_state(tp, 0, 0), c->d_state[0], fb, hipMemcpyDeviceToDevice, c->stream));
+            pss::LaunchArgs ax = xargs(c);
+            for (; i < nsteps; ++i) {
+                pss::LaunchArgs a = args(c, static_cast<int>(i));
+                a.bufs.S[0] = tape_state(tp, 0, i);
+                a.bufs.out = tape_state(tp, 0, i + 1);
+                HIP_TRY(pss::launch_update(pss::MODE_STEP, c->lu, 1, a));
+                done = i + 1;
+                if (pss_status s = debug_check(c, "update_kernel", tp->n0 + i)) return s;
+                ax.advance = i == nsteps - 1 ? nsteps : 0;
+                HIP_TRY(pss::launch_xrow(pss::MODE_STEP, nx, 1, ax));
+                if (pss_status s = debug_check(c, "xrow_kernel", tp->n0 + i)) return s;
+            }
+            HIP_TRY(hipMemcpyAsync(c->d_state[0], tp->fT, fb, hipMemcpyDeviceToDevice, c->stream));
+            return PSS_OK;
+        };
+        if (pss_status s = record()) {
+            // the lattice ends as steps that fail there leave it: the state of
+            // the step that failed, the counter at that step
+            const uint64_t at = static_cast<uint64_t>(tp->n0 + i);
+            (void)hipStreamSynchronize(c->stream);
+            if (done > 0) (void)hipMemcpy(c->d_state[0], tape_state(tp, 0, done), fb, hipMemcpyDeviceToDevice);
+            (void)hipMemcpy(c->d_step, &at, sizeof(at), hipMemcpyHostToDevice);
+            c->steps_taken = static_cast<int64_t>(at);
+            ++c->state_gen;
+            return bail(s);
         }
-        TAPE_HIP(hipMemcpyAsync(c->d_state[0], tp->fT, fb, hipMemcpyDeviceToDevice, c->stream));
+        c->dirty = false;
         c->steps_taken += nsteps;
         ++c->state_gen;
     }
@@ -3055,6 +3076,7 @@ pss_status pss_adjoint_model_b_backward(pss_tape* tp, double* grad, float* grad_
             return fail(PSS_E_HIP, "%s: %s (%s:%d)", #expr, hipGetErrorString(e_), __FILE__, __LINE__); \
     } while (0)
     tp->done = true;
+    c->dirty = true;  // the sweep forms other products
     ADJ_HIP(pss::launch_adjseed(c->stream, tp->fT, tp->G, tp->coef, tp->ns, nx, ny, c->geo.tc));
     ADJ_HIP(hipMemsetAsync(tp->acc, 0, tp->nacc * sizeof(double), c->stream));
 
@@ -3138,7 +3160,6 @@ pss_status pss_adjoint_model_b_backward(pss_tape* tp, double* grad, float* grad_
     ADJ_HIP(hipStreamSynchronize(c->stream));
 #undef ADJ_HIP
     c->steps_taken = n0 + nsteps;
-    c->dirty = true;
     ++c->state_gen;
     // the per-block slots in block order: dL/da, dL/dk, dL/dD from the
     // column blocks, dL/db from the row blocks

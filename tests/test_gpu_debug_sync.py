@@ -133,3 +133,35 @@ def test_tuning_cache_file_across_processes(tmp_path):
     second = _child(path)
     assert second == first
     assert len(path.read_text().splitlines()) == 3
+
+
+# a recorded run that ends in a non-finite state leaves the lattice where the
+# same steps taken by pss_step leave it, whichever form the tape has
+def test_debug_mode_adjoint_that_blows_up_leaves_the_lattice_as_its_steps_do(monkeypatch):
+    monkeypatch.setenv("PSS_DEBUG_SYNC", "1")
+
+    def end(run):
+        lat = pss.Lattice((64, 32), dt=0.01, seed=4)
+        f, _ = pss.model_b(lat, b=-1e6, D=0.01)  # |phi| 0.1, 4e1, 2e9, 1e33, then above FP32
+        lat.init_uniform(f, -0.1, 0.1)
+        with pytest.raises(PssError) as e:
+            run(lat)
+        assert e.value.name == "PSS_E_NONFINITE" and "update_kernel" in str(e.value), str(e.value)
+        at, sp = lat.step_index, lat.spectrum(f)
+        # the lattice goes on from there
+        x = np.full((32, 64), 0.01, dtype=np.float32)
+        x[3, 5] = 0.02
+        lat.set_coef(1, 0, -1.0)
+        lat.upload(f, x)
+        lat.step(2)
+        return at, sp, lat.step_index, lat.spectrum(f)
+
+    S = np.full(15, 0.01)
+    at, sp, then, after = end(lambda lat: lat.step(10))
+    assert 1 <= at < 10 and then == at + 2
+    for whole in ("1", "0"):
+        monkeypatch.setenv("PSS_TAPE_WHOLE", whole)
+        a2, sp2, then2, after2 = end(lambda lat: lat.adjoint_forward(10, S, 4))
+        assert (a2, then2) == (at, then)
+        assert np.array_equal(sp2, sp, equal_nan=True)
+        assert np.array_equal(after2, after)
