@@ -884,15 +884,13 @@ pss_status choose_geometry(pss_ctx* c) {
     const bool large3 = c->ndim == 3 && c->sites() >= (int64_t{1} << 23);
     auto points3 = [&](int L, int cap, int lanes) { return std::min(cap, std::max(std::min(4, L), L / lanes)); };
     const int cap_u = pss::max_points(lu, pss::field_slots(nf)), cap_x = pss::max_points(nx, pss::field_slots(ng));
-    g.pu = tuned("pu", large3 ? points3(lu, cap_u, 32) : few_points(lu, cap_u));
-    g.px = tuned("px", large3 ? points3(nx, std::min(8, cap_x), 32) : few_points(nx, cap_x));
     // 2D lines of 4096 of one field: 8 points a thread in blocks of 512 threads
     // rather than 16 in blocks of 256 (twice the waves in flight; 4096^2:
     // update 135 -> 85 us, x 93 -> 53.5 us)
-    const bool wide_u = c->ndim == 2 && lu == 4096 && nf == 1 && !c->tune.count("pu");
-    const bool wide_x = c->ndim == 2 && nx == 4096 && ng == 1 && !c->tune.count("px");
-    if (wide_u) g.pu = 8;
-    if (wide_x) g.px = 8;
+    const bool long_u = c->ndim == 2 && lu == 4096 && nf == 1, long_x = c->ndim == 2 && nx == 4096 && ng == 1;
+    g.pu = tuned("pu", large3 ? points3(lu, cap_u, 32) : (long_u ? 8 : few_points(lu, cap_u)));
+    g.px = tuned("px", large3 ? points3(nx, std::min(8, cap_x), 32) : (long_x ? 8 : few_points(nx, cap_x)));
+    const bool wide_u = long_u && g.pu == 8, wide_x = long_x && g.px == 8;
     if (!pow2(g.pu) || g.pu > pss::max_points(lu, pss::field_slots(nf)) || !pow2(g.px) ||
         g.px > pss::max_points(nx, pss::field_slots(ng)))
         return fail(PSS_E_UNSUPPORTED, "points per thread must be a power of two up to the variant limit");

@@ -62,3 +62,22 @@ def test_autotune_keeps_forced_keys_and_caches():
     with pytest.raises(pss.PssError) as e:
         b.autotune()
     assert e.value.name == "PSS_E_STATE"
+
+
+# the geometry that a lattice reports can be asked for, and is then the same
+@pytest.mark.parametrize("n", [(4096, 8), (8, 4096), (4096, 4096), (2048, 8), (64, 64), (16, 32, 64)])
+def test_reported_geometry_can_be_forced(n):
+    a, fa = _model_b(n)
+    want = a.geometry()
+    b, fb = _model_b(n)
+    b.tune(**want)
+    assert b.geometry() == want
+    a.init_uniform(fa, -0.1, 0.1)
+    b.init_uniform(fb, -0.1, 0.1)
+    a.step(3)
+    b.step(3)
+    assert np.array_equal(a.spectrum(fa), b.spectrum(fb))
+    for key in ("pu", "px"):  # one alone
+        c, _ = _model_b(n)
+        c.tune(**{key: want[key]})
+        assert c.geometry() == want
