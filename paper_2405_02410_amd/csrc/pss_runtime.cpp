@@ -2737,6 +2737,7 @@ pss_status pss_autotune(pss_ctx* c, int32_t reps, double* us_per_step) {
         key += ",";
     }
     for (const auto& kv : c->tune) key += kv.first + "=" + std::to_string(kv.second);  // forced keys stay
+    key += "/k2";  // the kernels it was timed on: a choice made on earlier ones is not theirs
     for (char& ch : key)
         if (std::isspace(static_cast<unsigned char>(ch))) ch = '_';
     // PSS_TUNE_CACHE names a text file that keeps the choices across

@@ -165,3 +165,16 @@ def test_debug_mode_adjoint_that_blows_up_leaves_the_lattice_as_its_steps_do(mon
         assert (a2, then2) == (at, then)
         assert np.array_equal(sp2, sp, equal_nan=True)
         assert np.array_equal(after2, after)
+
+
+# a choice that was timed on earlier kernels (a key without their mark) is not
+# taken over: the lattice is timed anew and the new choice appended
+def test_tuning_cache_of_earlier_kernels_is_not_taken(tmp_path):
+    path = tmp_path / "tune.txt"
+    _child(path)
+    key, us, *kv = path.read_text().split()
+    assert key.endswith("/k2")
+    path.write_text(" ".join([key[: -len("/k2")], "0.001", "tc=1", "pu=16"]) + "\n")
+    got = _child(path)
+    assert got["us"] > 0.001
+    assert len(path.read_text().splitlines()) == 2
