@@ -221,7 +221,11 @@ struct pss_ctx {
 struct pss_batch {
     struct Class {
         std::vector<int> idx;          // members of the class
-        pss_ctx* rep = nullptr;        // first member: geometry and twiddles
+        pss_ctx* rep = nullptr;        // first member: twiddles
+        // Launch geometry.  Members may differ in their de-aliasing: ncol is
+        // the largest of theirs, and the update kernel writes zeros (no mode
+        // is within the limits there) to the columns that a member masks.
+        pss::Geo geo{};
         pss::Member* d_u = nullptr;    // member tables of the update and x kernels
         pss::Member* d_x = nullptr;
         pss::DevPlan* d_plans = nullptr;  // copies of the members' plans
@@ -1556,11 +1560,15 @@ pss_status graph_for(pss_ctx* c, int64_t k, hipGraphExec_t* out) {
 
 constexpr int64_t kGraphSteps = 50;
 
+// (launch geometry without the columns kept: Class::geo)
 bool same_class(const pss_ctx* a, const pss_ctx* b) {
+    pss::Geo ga = a->geo, gb = b->geo;
+    std::memset(ga.ncol, 0, sizeof(ga.ncol));
+    std::memset(gb.ncol, 0, sizeof(gb.ncol));
     return a->n[0] == b->n[0] && a->n[1] == b->n[1] && a->fields.size() == b->fields.size() &&
            a->interms.size() == b->interms.size() &&
            a->plan.ng == b->plan.ng && a->plan.nch == b->plan.nch && a->plan.general == b->plan.general &&
-           std::memcmp(&a->geo, &b->geo, sizeof(pss::Geo)) == 0;
+           std::memcmp(&ga, &gb, sizeof(pss::Geo)) == 0;
 }
 
 void free_batch(pss_batch* b) {
@@ -1628,7 +1636,7 @@ void batch_plan_fused(pss_batch* b) {
             rl.plans = cl.d_plans;
             rl.tw_x = r->d_tw_x;
             rl.tw_y = r->d_tw_u;
-            rl.geo = r->geo;
+            rl.geo = cl.geo;
             b->res.push_back(rl);
             b->in_res[k] = 1;
             continue;
@@ -1642,7 +1650,7 @@ void batch_plan_fused(pss_batch* b) {
             C.members = cl.d_u;
             C.plans = cl.d_plans;
             C.tw = r->d_tw_u;
-            C.geo = r->geo;
+            C.geo = cl.geo;
             b->fu.total += nmem * C.nblk;
             b->fu_lds = std::max(b->fu_lds, pss::update_lds_bytes(r->lu, 4, r->geo.tc, 1));
             b->in_fu[k] = 1;
@@ -1658,7 +1666,7 @@ void batch_plan_fused(pss_batch* b) {
             C.members = cl.d_x;
             C.plans = cl.d_plans;
             C.tw = r->d_tw_x;
-            C.geo = r->geo;
+            C.geo = cl.geo;
             C.geo.rb = rbf;
             C.geo.rb_log2 = 0;
             while ((1 << C.geo.rb_log2) < rbf) ++C.geo.rb_log2;
@@ -1707,6 +1715,7 @@ pss_status batch_enqueue(pss_batch* b, int64_t k) {
             a.stream = b->stream;
             a.members = cl.d_u;
             a.plans = cl.d_plans;
+            a.geo = cl.geo;
             a.nmem = static_cast<int>(cl.idx.size());
             HIP_TRY(pss::launch_update(pss::MODE_STEP, r->lu, static_cast<int>(r->fields.size()), a));
         }
@@ -1723,6 +1732,7 @@ pss_status batch_enqueue(pss_batch* b, int64_t k) {
             ax.stream = b->stream;
             ax.members = cl.d_x;
             ax.plans = cl.d_plans;
+            ax.geo = cl.geo;
             ax.nmem = static_cast<int>(cl.idx.size());
             ax.advance = adv;
             HIP_TRY(pss::launch_xrow(pss::MODE_STEP, r->n[0], r->plan.ng, ax));
@@ -3220,9 +3230,11 @@ pss_status pss_batch_create(pss_batch** out, pss_ctx* const* lattices, int32_t n
         if (it == b->cls.end()) {
             b->cls.emplace_back();
             b->cls.back().rep = lattices[i];
+            b->cls.back().geo = lattices[i]->geo;
             it = b->cls.end() - 1;
         }
         it->idx.push_back(i);
+        for (int g = 0; g < PSS_MAXG; ++g) it->geo.ncol[g] = std::max(it->geo.ncol[g], lattices[i]->geo.ncol[g]);
     }
     auto bail = [&](pss_status s) {
         free_batch(b);
@@ -3351,6 +3363,7 @@ pss_status pss_batch_time_kernel(pss_batch* b, int32_t cls, int32_t which, int32
     a.stream = b->stream;
     a.members = which == 0 ? cl.d_u : cl.d_x;
     a.plans = cl.d_plans;
+    a.geo = cl.geo;
     a.nmem = static_cast<int>(cl.idx.size());
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));

@@ -213,3 +213,31 @@ def test_adjoint_with_and_without_recomputation(monkeypatch, n, steps, ckpt):
     assert np.array_equal(twin.spectrum(0), got[0][4])
     twin.step(3)
     assert np.array_equal(twin.spectrum(0), got[0][5])
+
+
+# lattices that differ in their de-aliasing alone share a class and its
+# launches, each with its own kept columns: in LDS, fused, and launched by class
+@pytest.mark.parametrize("n,model,launches", [((64, 64), "b", (0, 0, 1)), ((256, 128), "b", (2, 1, 0)),
+                                              ((32, 16), "b", (2, 0, 0)), ((128, 64), "kpz", (2, 0, 0))])
+def test_batch_of_lattices_that_differ_in_their_dealiasing(n, model, launches):
+    def make():
+        out = []
+        for i, (rule, shape) in enumerate([(pss.DEALIAS_TWO_THIRDS, pss.SHAPE_RADIAL), (pss.DEALIAS_NONE, pss.SHAPE_RADIAL),
+                                           (pss.DEALIAS_PAPER_ORDER, pss.SHAPE_PER_AXIS), (pss.DEALIAS_NONE, pss.SHAPE_RADIAL)]):
+            lat = pss.Lattice(n, dt=0.01, seed=30 + i, dealias=rule, shape=shape)
+            f = pss.model_b(lat, D=0.01)[0] if model == "b" else pss.kpz(lat, D=0.01)[0]
+            lat.init_uniform(f, -0.5, 0.5)
+            out.append((lat, f))
+        return out
+
+    mem, alone = make(), make()
+    batch = pss.Batch([lat for lat, _ in mem])
+    assert batch.classes() == (1, [0, 0, 0, 0])
+    assert batch.launches() == launches
+    batch.step(40)
+    mem[1][0].step(3)
+    batch.step(7)
+    for i, ((lat, f), (one, g)) in enumerate(zip(mem, alone)):
+        one.step(50 if i == 1 else 47)
+        assert np.array_equal(lat.spectrum(f), one.spectrum(g)), i
+    batch.close()
