@@ -258,7 +258,8 @@ pss_status pss_stream_set(pss_ctx *ctx, void *hip_stream);
  * x and y kernels: 4, 8 or 16).  On a lattice with a size that is not a
  * power of two (2D, 3D) only "tc" (lines per column-kernel block) and "py"
  * (3D: lines per y-pass block) apply, each a divisor of Nx up to 64 whose
- * block fits the LDS.  value <= 0 restores the default.  Invalid
+ * block fits the LDS.  "ckpt" = 1 (no geometry, accepted at any time) keeps
+ * the adjoint's tapes to their checkpoints.  value <= 0 restores the default.  Invalid
  * combinations are reported as PSS_E_UNSUPPORTED when the plan is built. */
 pss_status pss_tuning_set(pss_ctx *ctx, const char *key, int64_t value);
 
@@ -443,11 +444,13 @@ pss_status pss_kernels_per_step(pss_ctx *ctx, int32_t *count);
  *
  * From the current state phi_0 at step n0 the call runs nsteps forward steps
  * (noise keyed by steps n0 .. n0+nsteps-1, as pss_step would), keeping a
- * checkpoint of the state every ckpt_every steps.  It evaluates
+ * checkpoint of the state every ckpt_every steps (or, in a short run, every
+ * state: see the workspace below).  It evaluates
  *   L = sum_{j=1}^{n_shells} (S_j - S_target[j-1])^2,
  * S_j the shell averages of pss_structure_factor at the final step
  * (n_shells = min(Nx, Ny)/2 - 1), and sweeps back through the steps,
- * recomputing each segment from its checkpoint, with the adjoint recursion
+ * recomputing each segment from its checkpoint (nothing, where every state was
+ * kept), with the adjoint recursion
  *   r = g_{n+1} / A,   g_n = r + b m F[3 u_n^2 N F^-1[-dt q^2 r]] / N,
  *   u_n = F^-1[m phi_n],   A = 1 + dt q^2 (a + k q^2),
  * where m is the de-aliasing mask and the noise of each step is regenerated
@@ -457,19 +460,22 @@ pss_status pss_kernels_per_step(pss_ctx *ctx, int32_t *count);
  * dL/dD = 0 when D = 0); grad_phi0 (may be NULL; else Nx*Ny floats,
  * host or device memory per on_device) = dL/dphi_0(x) for the real initial
  * field.  The lattice is left at step n0 + nsteps with the forward final
- * state.  Device workspace: (ceil(nsteps/ckpt_every) + min(ckpt_every,
- * nsteps) + 8) arrays of Nx*Ny*4 bytes (and 2 KiB each), allocated for the
- * call; a run whose nsteps + 1 states fit in 256 MiB keeps them all instead of
- * checkpoints, if that much is free, and recomputes nothing (set
- * PSS_TAPE_WHOLE=0 in the environment to keep to the checkpoints).  The
- * results are the same bits either way. */
+ * state.  Device workspace, allocated for the call: (ceil(nsteps/ckpt_every) +
+ * min(ckpt_every, nsteps) + 8) arrays of Nx*Ny*4 bytes (and 2 KiB each).  A run
+ * whose nsteps + 1 states fit in 256 MiB keeps them all instead of
+ * checkpoints and recomputes nothing, as long as sixteen times its workspace
+ * is free on the card and all live tapes of the process together take at most
+ * 1 GiB above the figure just given; pss_tuning_set(ctx, "ckpt", 1) keeps this
+ * lattice's tapes to that figure (at any time; PSS_TAPE_WHOLE=0 in the
+ * environment keeps every lattice's).  The results are the same bits either
+ * way. */
 pss_status pss_adjoint_model_b(pss_ctx *ctx, int64_t nsteps, int32_t ckpt_every, const double *S_target,
                                int32_t n_shells, double *loss, double *grad, float *grad_phi0, int32_t on_device);
 
 /* The same gradient in two phases, for callers that need the loss before
  * deciding on the gradient (an autograd forward followed, or not, by a
- * backward).  pss_adjoint_model_b_forward runs the checkpointed forward run
- * and returns the loss and a tape that owns the checkpoints and the reverse
+ * backward).  pss_adjoint_model_b_forward runs the recorded forward run
+ * and returns the loss and a tape that owns the states kept and the reverse
  * workspace (the device memory listed above; PSS_E_NOMEM if it does not fit).
  * pss_adjoint_model_b_backward runs the reverse sweep once and writes grad and
  * grad_phi0 as pss_adjoint_model_b does; it fails with PSS_E_STATE if the

@@ -288,7 +288,8 @@ class Lattice:
         _check(lib().pss_stream_set(self._h, ctypes.c_void_p(int(hip_stream) if hip_stream else 0)))
 
     def tune(self, **kw):
-        """Force launch-geometry values (tc, to, tz, rb, pu, px, py) before the plan is built."""
+        """Force launch-geometry values (tc, to, tz, rb, pu, px, py) before the plan is built;
+        ckpt=1, at any time, keeps the adjoint's tapes to their checkpoints."""
         for k, v in kw.items():
             _check(lib().pss_tuning_set(self._h, k.encode(), int(v)))
 
@@ -429,7 +430,9 @@ class Lattice:
     def adjoint_model_b(self, nsteps, S_target, ckpt_every=45, grad_phi0=True):
         """(loss, dL/d(a, b, k, D), dL/dphi_0 or None) of the structure-factor
         loss after nsteps Model B steps from the current state (pss_adjoint_model_b).
-        Leaves the lattice at the end of the forward run."""
+        Leaves the lattice at the end of the forward run.  A checkpoint every
+        ckpt_every steps; a run whose states fit in 256 MiB keeps them all
+        instead (within 1 GiB over all live tapes), unless tune(ckpt=1)."""
         S = np.ascontiguousarray(S_target, dtype=np.float64)
         loss = ctypes.c_double()
         grad = (ctypes.c_double * 4)()
@@ -441,8 +444,9 @@ class Lattice:
         return loss.value, np.array(list(grad)), out
 
     def adjoint_forward(self, nsteps, S_target, ckpt_every=45):
-        """Checkpointed forward phase of the Model B adjoint
-        (pss_adjoint_model_b_forward): (loss, Tape)."""
+        """Recorded forward phase of the Model B adjoint
+        (pss_adjoint_model_b_forward): (loss, Tape).  Checkpoints or every
+        state, as adjoint_model_b."""
         S = np.ascontiguousarray(S_target, dtype=np.float64)
         loss = ctypes.c_double()
         h = ctypes.c_void_p()

@@ -6,8 +6,9 @@ and theta = (a, b, k, D) (torch, 4 values) returns the structure-factor loss
 L(phi0, theta) after nsteps steps as a 0-d float64 tensor.
 
 The forward call runs only the forward trajectory.  When an input needs a
-gradient it records the checkpoints on the way (pss_adjoint_model_b_forward,
-a checkpoint every ckpt_every steps, the noise fixed by its Philox counters);
+gradient it records states on the way (pss_adjoint_model_b_forward, the noise
+fixed by its Philox counters): a checkpoint every ckpt_every steps, or every
+state where they fit in 256 MiB (.lat.tune(ckpt=1) keeps to the checkpoints).
 backward() then runs the reverse sweep (pss_adjoint_model_b_backward) and
 writes dL/dphi0 straight into a device tensor.  When no input needs a
 gradient the forward is the plain run (pss_step) and the loss comes from the

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cctype>
 #include <cmath>
 #include <complex>
@@ -194,6 +195,7 @@ struct pss_ctx {
     pss::Member* d_member_x = nullptr;
     int batches = 0;        // live batches holding this context
     int tapes = 0;          // live adjoint tapes recorded on this context
+    bool tape_ckpt = false; // tapes keep to their checkpoints (tuning key "ckpt")
     bool quiet = false;     // its own stream holds no work: a call waited for it, none came after
     uint64_t state_gen = 0; // bumped by every change of the state (steps, uploads, loads)
     uint64_t enq_gen = 0;   // bumped whenever the context enqueues work on its own stream
@@ -263,6 +265,7 @@ struct pss_tape {
     size_t fb = 0;      // bytes of one packed spectrum
     size_t stride = 0;  // from one spectrum of the tape to the next
     bool whole = false; // the forward run kept every state: one segment, nothing to recompute
+    size_t extra = 0;   // bytes above what the checkpoints would have taken
     double a = 0, b = 0, k = 0, D = 0, loss = 0;
     uint64_t plan_gen = 0, state_gen = 0;
     bool done = false;  // the reverse sweep has run
@@ -277,6 +280,9 @@ struct pss_tape {
 };
 
 namespace {
+
+// pss_tape::extra of every live tape of the process
+std::atomic<size_t> g_tape_extra{0};
 
 int field_code(const pss_ctx* c, int32_t id) {
     return id >= 0 && id < static_cast<int32_t>(c->ids.size()) ? c->ids[id] : -1;
@@ -300,6 +306,8 @@ void tape_free(pss_tape* tp) {
     if (tp->ctx && tp->ctx->stream) (void)hipStreamSynchronize(tp->ctx->stream);
     if (tp->mem) (void)hipFree(tp->mem);
     tp->mem = nullptr;
+    g_tape_extra -= tp->extra;
+    tp->extra = 0;
 }
 
 float2* tape_at(const pss_tape* tp, char* base, int64_t i) {
@@ -2242,6 +2250,10 @@ pss_status pss_stream_set(pss_ctx* c, void* stream) {
 
 pss_status pss_tuning_set(pss_ctx* c, const char* key, int64_t value) {
     if (pss_status s = check_ctx(c)) return s;
+    if (key && std::strcmp(key, "ckpt") == 0) {  // of the adjoint's tapes, at any time
+        c->tape_ckpt = value > 0;
+        return PSS_OK;
+    }
     if (c->planned) return fail(PSS_E_STATE, "the launch geometry is fixed once the plan is built");
     static const char* keys[] = {"tc", "to", "tz", "rb", "pu", "px", "py"};
     if (!key) return fail(PSS_E_INVAL, "null key");
@@ -2260,6 +2272,10 @@ pss_status pss_tuning_set(pss_ctx* c, const char* key, int64_t value) {
 pss_status pss_tuning_get(pss_ctx* c, const char* key, int64_t* value) {
     if (pss_status s = check_ctx(c)) return s;
     if (!key || !value) return fail(PSS_E_INVAL, "null argument");
+    if (std::strcmp(key, "ckpt") == 0) {
+        *value = c->tape_ckpt ? 1 : 0;
+        return PSS_OK;
+    }
     if (pss_status s = materialize(c)) return s;
     const pss::Geo& g = c->geo;
     const std::pair<const char*, int> vals[] = {{"tc", g.tc}, {"to", g.to}, {"tz", g.tz}, {"rb", g.rb},
@@ -2934,32 +2950,47 @@ pss_status pss_adjoint_model_b_forward(pss_ctx* c, int64_t nsteps, int32_t ckpt_
     // whose states all fit in 256 MiB (a thousandth of the card) keeps them:
     // it is one segment, recorded by the forward run, and the sweep does not
     // recompute it.  256^2, 400 steps, a checkpoint every 20: forward and
-    // backward 14.2 -> 11.1 ms.
-    constexpr size_t kWhole = size_t{256} << 20;
+    // backward 14.2 -> 11.1 ms.  ckpt_every bounds the memory all the same:
+    // what the live tapes of the process take above their checkpoints stays
+    // within 1 GiB, a tape takes it only from a card with sixteen times its
+    // size free, and the lattice can be told not to.
+    constexpr size_t kWhole = size_t{256} << 20, kExtraAll = size_t{1} << 30;
     const char* env = std::getenv("PSS_TAPE_WHOLE");
     const size_t fb = tp->fb;
     tp->stride = (fb + 255) / 256 * 256 + 2048;
     tp->nacc = 3 * static_cast<size_t>(c->geo.nublk) + static_cast<size_t>(c->geo.nrowblk);
-    tp->whole = !(env && std::strcmp(env, "0") == 0) && static_cast<size_t>(nsteps) + 1 <= kWhole / tp->stride;
-    size_t narr = 0;
-    for (;;) {
-        if (tp->whole) {
-            tp->nck = 1;
-            tp->ckpt = static_cast<int32_t>(nsteps);
-            tp->seglen = nsteps;
-        } else {
-            tp->nck = (nsteps + ckpt_every - 1) / ckpt_every;
-            tp->ckpt = ckpt_every;
-            tp->seglen = std::min<int64_t>(ckpt_every, nsteps);
+    const size_t rest = tp->nacc * sizeof(double) + sizeof(float) * ns + 2 * sizeof(pss::DevPlan) + 4 * 256;
+    const int64_t nck = (nsteps + ckpt_every - 1) / ckpt_every, seglen = std::min<int64_t>(ckpt_every, nsteps);
+    const size_t ckpt_bytes = tp->stride * static_cast<size_t>(nck + seglen + 7) + rest;
+    tp->whole = !(env && std::strcmp(env, "0") == 0) && !c->tape_ckpt &&
+                static_cast<size_t>(nsteps) + 1 <= kWhole / tp->stride;
+    if (tp->whole) {
+        const size_t bytes = tp->stride * static_cast<size_t>(nsteps + 7) + rest;
+        const size_t extra = bytes > ckpt_bytes ? bytes - ckpt_bytes : 0;
+        size_t free_bytes = 0, total = 0;
+        if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) (void)hipGetLastError();
+        tp->whole = extra == 0 || free_bytes / 16 >= bytes;
+        if (tp->whole && extra > 0) {
+            tp->extra = extra;  // returned by tape_free
+            tp->whole = g_tape_extra.fetch_add(extra) + extra <= kExtraAll;
         }
-        narr = static_cast<size_t>(tp->nck + tp->seglen) + (tp->whole ? 6 : 7);
-        const size_t rest = tp->nacc * sizeof(double) + sizeof(float) * ns + 2 * sizeof(pss::DevPlan) + 4 * 256;
-        if (hipMalloc(&tp->mem, tp->stride * narr + rest) == hipSuccess) break;
+        if (tp->whole && hipMalloc(&tp->mem, bytes) != hipSuccess) {
+            tp->mem = nullptr;
+            (void)hipGetLastError();
+            tp->whole = false;
+        }
+        if (!tp->whole) {
+            g_tape_extra -= tp->extra;
+            tp->extra = 0;
+        }
+    }
+    tp->nck = tp->whole ? 1 : nck;
+    tp->ckpt = tp->whole ? static_cast<int32_t>(nsteps) : ckpt_every;
+    tp->seglen = tp->whole ? nsteps : seglen;
+    if (!tp->whole && hipMalloc(&tp->mem, ckpt_bytes) != hipSuccess) {
         tp->mem = nullptr;
         (void)hipGetLastError();
-        if (!tp->whole)
-            return bail(fail(PSS_E_NOMEM, "adjoint workspace of %zu bytes does not fit", tp->stride * narr + rest));
-        tp->whole = false;
+        return bail(fail(PSS_E_NOMEM, "adjoint workspace of %zu bytes does not fit", ckpt_bytes));
     }
     char* at = tp->mem;
     auto take = [&](size_t bytes) {

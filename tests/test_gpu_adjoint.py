@@ -232,3 +232,47 @@ def test_adjoint_workload_256_against_the_stored_oracle(nsteps):
         assert abs(L - run["loss"]) <= 1e-2 * abs(run["loss"]), (L, run["loss"])
         assert np.all(np.abs(g - go) <= 1e-2 * scale), (g, go)
         assert dphi <= 1e-2
+
+
+def test_ckpt_every_bounds_the_memory_of_live_tapes():
+    """Tapes that keep every state take at most 256 MiB each and 1 GiB above
+    their checkpoints together; a lattice told so keeps to the workspace that
+    its checkpoints need; the gradients are the same bits."""
+    import torch
+
+    n, nsteps, ckpt = (256, 256), 400, 20
+    S = np.full(127, 0.01)
+    arrays = nsteps // ckpt + ckpt + 8
+    need = arrays * (4 * n[0] * n[1] + 2048) + (2 << 20)  # the slots of the sums, and the allocator's granule
+    mib = 1 << 20
+
+    def used(lats):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        out = [lat.adjoint_forward(nsteps, S, ckpt) for lat in lats]
+        return before - torch.cuda.mem_get_info()[0], out
+
+    lats = [_gpu(n, seed=3) for _ in range(9)]
+    for lat in lats:
+        lat.structure_factor(0)  # its accumulators are allocated on first use
+    lats[1].tune(ckpt=1)
+    one, ((_, t0),) = used(lats[:1])
+    assert one <= 256 * mib + need
+    kept, ((_, t1),) = used(lats[1:2])
+    assert kept <= need
+    g0, g1 = t0.backward(), t1.backward()
+    assert np.array_equal(g0, g1)
+    t0.close()
+    t1.close()
+    total, tapes = used(lats[2:])
+    assert total <= 1024 * mib + 7 * need
+    for _, t in tapes:
+        assert np.array_equal(t.backward(), g0)
+        t.close()
+    # what they took is free again
+    again, ((_, t),) = used(lats[3:4])
+    assert again == one
+    t.close()
+    lats[1].tune(ckpt=0)
+    one1, ((_, t),) = used(lats[1:2])
+    assert one1 == one
