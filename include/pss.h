@@ -169,7 +169,10 @@ pss_status pss_term_count(pss_ctx *ctx, int32_t *count);
 
 /* Change the coefficient of monomial `mono` of term `term_id`.  Allowed at
  * any time; takes effect at the next step (stream-ordered).  Re-checks
- * stability: PSS_E_UNSTABLE leaves the old value in place. */
+ * stability: PSS_E_UNSTABLE leaves the old value in place.  Products that enter
+ * the equations of two fields in proportion are formed once; a value that ends
+ * the proportion makes the lattice take another array, which it cannot while a
+ * batch holds it (PSS_E_STATE, the old value stays). */
 pss_status pss_term_set_coef(pss_ctx *ctx, int32_t term_id, int32_t mono, double coef);
 
 /* Add noise to a field (Sec. "Adding noise"): D(q) is a sum of monomials in

@@ -181,6 +181,7 @@ struct pss_ctx {
     // d_chan: channel inputs of the update kernel; d_chan_x: x-kernel outputs
     // (the same arrays in 2D; in 3D the forward y pass maps one to the other)
     std::vector<float2*> d_state, d_chan, d_chan_x, d_v;
+    std::vector<float2*> d_chan_own;  // allocations of channels that a later coefficient asked for
     void* bound[PSS_MAXF] = {};       // caller-owned state memory per dynamic field (pss_field_bind)
     size_t bound_bytes[PSS_MAXF] = {};
     float2* d_tmp = nullptr;
@@ -983,7 +984,9 @@ void free_device(pss_ctx* c) {
             rel(c->d_state[f]);
     }
     rel(c->d_work);
-    c->d_chan.clear();  // parts of it
+    for (auto*& p : c->d_chan_own) rel(p);
+    c->d_chan_own.clear();
+    c->d_chan.clear();  // parts of d_work, or in d_chan_own
     c->d_chan_x.clear();
     c->d_v.clear();
     c->d_tmp = c->d_tmp2 = nullptr;
@@ -1160,6 +1163,46 @@ pss_status upload_plan(pss_ctx* c) {
     HIP_TRY(hipStreamSynchronize(c->stream));
     HIP_TRY(hipMemcpy(c->d_plan, &c->plan, sizeof(pss::DevPlan), hipMemcpyHostToDevice));
     ++c->plan_gen;
+    return PSS_OK;
+}
+
+pss::Member member_u(pss_ctx* c);
+pss::Member member_x(pss_ctx* c);
+
+// After the plan of a planned lattice was built anew: channels that form the
+// same products share one (build_plan), which their coefficients decide, so a
+// coefficient can part them.  The lattice then gets the arrays it lacks, and
+// step graphs for the other count.
+pss_status fit_channels(pss_ctx* c, int nch_before) {
+    const size_t nch = static_cast<size_t>(c->plan.nch);
+    if (c->plan.nch == nch_before) return PSS_OK;
+    if (nch > c->d_chan.size() && c->batches > 0)
+        return fail(PSS_E_STATE, "the coefficient parts products that two fields shared, which takes an array that "
+                                 "the %d batch(es) holding this lattice do not know; destroy them first", c->batches);
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
+    c->graphs.clear();
+    if (nch <= c->d_chan.size()) return PSS_OK;
+    const size_t bytes = sizeof(float2) * static_cast<size_t>(c->packed());
+    const bool relay = c->ndim == 3 && !c->mixed;  // as in materialize
+    auto grow = [&](float2** out) -> pss_status {
+        HIP_TRY(hipMalloc(out, bytes));
+        c->d_chan_own.push_back(*out);
+        HIP_TRY(hipMemset(*out, c->debug_sync ? 0xFF : 0, bytes));
+        return PSS_OK;
+    };
+    while (c->d_chan.size() < nch) {
+        float2 *in = nullptr, *out = nullptr;
+        if (pss_status s = grow(&in)) return s;
+        if (relay)
+            if (pss_status s = grow(&out)) return s;
+        c->d_chan.push_back(in);
+        c->d_chan_x.push_back(relay ? out : in);
+    }
+    const pss::Member mu = member_u(c), mx = member_x(c);
+    HIP_TRY(hipMemcpy(c->d_member_u, &mu, sizeof(mu), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(c->d_member_x, &mx, sizeof(mx), hipMemcpyHostToDevice));
+    HIP_TRY(hipDeviceSynchronize());
     return PSS_OK;
 }
 
@@ -2134,10 +2177,12 @@ pss_status pss_term_set_coef(pss_ctx* c, int32_t term_id, int32_t mono, double c
     // recompile the coefficients (the structure is unchanged), and rebuild the
     // channel arrays of the next step from the current state
     const pss::DevPlan keep = c->plan;
-    if (pss_status s = build_plan(c)) {
+    pss_status st = build_plan(c);
+    if (!st) st = fit_channels(c, keep.nch);
+    if (st) {
         t.op[mono].coef = old;
         c->plan = keep;
-        return s;
+        return st;
     }
     c->dirty = true;
     return upload_plan(c);

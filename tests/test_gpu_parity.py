@@ -459,3 +459,57 @@ def test_nonfinite_member_is_reported_by_the_batch():
     with pytest.raises(pss.PssError):  # the state stays non-finite
         b.sync()
     b.close()
+
+
+# channels that two fields share while their coefficients are in proportion and
+# that part when one changes: as a lattice built with the new coefficients
+@pytest.mark.parametrize("n", [(32, 64), (16, 32, 16), (24, 20), (24, 16, 12), (64,)])
+def test_coefficients_that_split_and_join_shared_channels(n):
+    def make(c, d):
+        lat = pss.Lattice(n, dt=0.01, seed=9)
+        f, g = lat.field("phi"), lat.field("psi")
+        for h in (f, g):
+            lat.term(h, [Mono(-0.5), Mono(-1.0, q2=1)], [(h, 1)], implicit=True)
+        t0 = lat.term(f, [Mono(c)], [(f, 1), (g, 1)])
+        t1 = lat.term(g, [Mono(d)], [(f, 1), (g, 1)])
+        lat.noise(f, [Mono(0.01)])
+        for h in (f, g):
+            lat.init_uniform(h, -0.5, 0.5)
+        return lat, (t0, t1)
+
+    lat, (t0, t1) = make(0.3, -0.6)
+    lat.step(3)
+    for c, d in ((0.0, -0.6), (0.2, -0.6), (0.0, 0.1)):
+        lat.set_coef(t0, 0, c)
+        lat.set_coef(t1, 0, d)
+        blob = lat.save()
+        lat.step(4)
+        twin, _ = make(c, d)
+        twin.load(blob)
+        twin.step(4)
+        for f in (0, 1):
+            assert np.array_equal(lat.spectrum(f), twin.spectrum(f)), (c, d, f)
+
+
+def test_a_batch_refuses_coefficients_that_need_another_channel():
+    def make():
+        lat = pss.Lattice((32, 32), dt=0.01, seed=9)
+        f, g = lat.field("phi"), lat.field("psi")
+        t = [lat.term(h, [Mono(0.3)], [(f, 1), (g, 1)]) for h in (f, g)]
+        for h in (f, g):
+            lat.init_uniform(h, -0.5, 0.5)
+        return lat, t
+
+    (a, t), (b, _), (alone, _) = make(), make(), make()
+    batch = pss.Batch([a, b])
+    batch.step(2)
+    with pytest.raises(pss.PssError) as e:
+        a.set_coef(t[0], 0, 0.0)
+    assert e.value.name == "PSS_E_STATE"
+    batch.step(3)
+    alone.step(5)
+    assert np.array_equal(a.spectrum(0), alone.spectrum(0)) and np.array_equal(b.spectrum(1), alone.spectrum(1))
+    batch.close()
+    a.set_coef(t[0], 0, 0.0)
+    a.step(1)
+    a.sync()
