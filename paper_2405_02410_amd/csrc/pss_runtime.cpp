@@ -3005,7 +3005,10 @@ pss_status pss_adjoint_model_b_forward(pss_ctx* c, int64_t nsteps, int32_t ckpt_
     tp->stride = (fb + 255) / 256 * 256 + 2048;
     tp->nacc = 3 * static_cast<size_t>(c->geo.nublk) + static_cast<size_t>(c->geo.nrowblk);
     const size_t rest = tp->nacc * sizeof(double) + sizeof(float) * ns + 2 * sizeof(pss::DevPlan) + 4 * 256;
-    const int64_t nck = (nsteps + ckpt_every - 1) / ckpt_every, seglen = std::min<int64_t>(ckpt_every, nsteps);
+    const int64_t nck = nsteps / ckpt_every + (nsteps % ckpt_every != 0), seglen = std::min<int64_t>(ckpt_every, nsteps);
+    // (the size below must not wrap around)
+    const double asked = (static_cast<double>(nck) + static_cast<double>(seglen) + 8) * static_cast<double>(tp->stride);
+    if (asked > 1e18) return bail(fail(PSS_E_NOMEM, "adjoint workspace of %g bytes does not fit", asked));
     const size_t ckpt_bytes = tp->stride * static_cast<size_t>(nck + seglen + 7) + rest;
     tp->whole = !(env && std::strcmp(env, "0") == 0) && !c->tape_ckpt &&
                 static_cast<size_t>(nsteps) + 1 <= kWhole / tp->stride;

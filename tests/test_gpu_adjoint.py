@@ -276,3 +276,14 @@ def test_ckpt_every_bounds_the_memory_of_live_tapes():
     lats[1].tune(ckpt=0)
     one1, ((_, t),) = used(lats[1:2])
     assert one1 == one
+
+
+def test_a_workspace_beyond_any_address_is_refused():
+    lat = _gpu((16, 8), seed=3)
+    before = lat.spectrum(0)
+    for nsteps, ckpt in ((2**62, 1), (2**63 - 1, 1), (2**61, 2)):
+        with pytest.raises(pss.PssError) as e:
+            lat.adjoint_forward(nsteps, np.full(3, 0.01), ckpt)
+        assert e.value.name == "PSS_E_NOMEM"
+    assert lat.step_index == 0 and np.array_equal(lat.spectrum(0), before)
+    assert lat.adjoint_forward(3, np.full(3, 0.01), 2)[0] >= 0
