@@ -100,8 +100,9 @@ typedef struct {
  * device plan is built on the first upload, init or step.  A 1D lattice (the
  * line of the examples in Sec. "Callback functions" and "De-aliasing") is
  * stepped by one block that holds the whole line; its state is the full
- * complex spectrum of the line (pss_state_size), and it takes part in neither
- * batches nor the adjoint (PSS_E_UNSUPPORTED there).  A size may also be an
+ * complex spectrum of the line (pss_state_size), of which a step may keep only
+ * what the field, the real part of its inverse transform, keeps; and it takes
+ * part in neither batches nor the adjoint (PSS_E_UNSUPPORTED there).  A size may also be an
  * even 2^a 3^b 5^c (Sec. "Benchmarking": sizes other than powers of two are
  * allowed, at a lower speed).  Such lattices run on a generic path: the
  * state of a field is its full complex spectrum (mode (kx, ky, kz) at

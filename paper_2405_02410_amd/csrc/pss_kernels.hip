@@ -3670,10 +3670,14 @@ __global__ void __launch_bounds__(line_half_threads(N) < 64 ? 64 : line_half_thr
     float2 a[PP], b[PP], wk[PP];
 #pragma unroll
     for (int m = 0; m < PP; ++m) {
-        const int k = t + m * T;
-        const bool z = zero && m == 0;
-        a[m] = gload(bufs.S[0] + k);
-        b[m] = gload(bufs.S[0] + (z ? H / 2 : H - k));
+        const int k = t + m * T, kp = zero && m == 0 ? H / 2 : H - k;
+        // Real space is the real part, whose mode k is the mean of phi(k) and
+        // conj phi(-k): the modes themselves in a state that steps and uploads
+        // leave, but not in any that a caller loads or writes
+        const float2 ak = gload(bufs.S[0] + k), an = gload(bufs.S[0] + ((N - k) & (N - 1)));
+        const float2 bk = gload(bufs.S[0] + kp), bn = gload(bufs.S[0] + N - kp);
+        a[m] = make_float2(0.5f * (ak.x + an.x), 0.5f * (ak.y - an.y));
+        b[m] = make_float2(0.5f * (bk.x + bn.x), 0.5f * (bk.y - bn.y));
         wk[m] = gload(tw_g + k);
     }
     if (zero) a[0].y = gload(bufs.S[0] + H).x;

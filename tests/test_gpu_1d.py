@@ -157,3 +157,24 @@ def test_nonfinite_flag_and_refusals_1d():
     with pytest.raises(PssError) as e:
         pss.Batch([lat, other])
     assert e.value.name == "PSS_E_UNSUPPORTED"
+
+
+@pytest.mark.parametrize("n", [8, 64, 512, 2048])
+def test_a_loaded_spectrum_counts_by_its_real_field(n):
+    """Real space is the real part of the inverse transform.  A loaded spectrum
+    without the symmetry of a real field steps as the one of that real part."""
+    rng = np.random.default_rng(n)
+    lat, twin = (_model_b_pair(n, 1.0, seed=3)[0] for _ in range(2))
+    blob = lat.save()
+    head = len(blob) - 8 * n
+    S = (n * 0.02 * rng.standard_normal((n, 2)) / np.sqrt(n)).astype(np.float32)
+    mirror = S[(-np.arange(n)) % n] * np.array([1.0, -1.0], dtype=np.float32)
+    H = np.float32(0.5) * (S + mirror)
+    lat.load(blob[:head] + S.tobytes())
+    twin.load(blob[:head] + H.tobytes())
+    # two transforms of |phi| <= 0.1 or so at 1e-6 each
+    assert _close(lat.download(0), twin.download(0), 1e-6)
+    for k in (1, 20):
+        lat.step(k)
+        twin.step(k)
+        assert _close(lat.download(0), twin.download(0), 2e-6)
