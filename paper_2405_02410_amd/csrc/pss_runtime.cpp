@@ -1351,8 +1351,11 @@ pss_status batch_order_before(pss_batch* b, const std::vector<int>& which) {
             if (pss_status s = begin_work(c)) return s;
             if (pss_status s = prologue(c)) return s;
         }
+        if (c->after_batch && c->after_batch != b->ev) {  // another batch's steps
+            HIP_TRY(hipStreamWaitEvent(b->stream, c->after_batch, 0));
+            if (c->stream == b->stream) c->after_batch = nullptr;
+        }
         if (c->stream == b->stream) continue;
-        if (c->after_batch && c->after_batch != b->ev) HIP_TRY(hipStreamWaitEvent(b->stream, c->after_batch, 0));
         if (c->enq_gen != b->seen[i]) {
             // a member whose last call waited for its own stream has nothing to
             // wait for (336 members, each downloaded between batch calls of 100
@@ -1372,7 +1375,12 @@ pss_status batch_order_after(pss_batch* b, const std::vector<int>& which) {
     HIP_TRY(hipEventRecord(b->ev, b->stream));
     for (int i : which) {
         pss_ctx* c = b->mem[i];
-        if (c->stream != b->stream) c->after_batch = b->ev;
+        if (c->stream != b->stream) {
+            c->after_batch = b->ev;
+        } else {  // new work on the member's own stream, for other batches that hold it
+            ++c->enq_gen;
+            c->quiet = false;
+        }
     }
     return PSS_OK;
 }

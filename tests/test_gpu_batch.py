@@ -356,3 +356,43 @@ def test_resident_launch_at_other_tile_widths(n, tc):
         assert lat.step_index == k
         assert np.array_equal(lat.spectrum(0), tw.spectrum(0))
     batch.close()
+
+
+def test_batches_that_share_members_take_turns():
+    """Two batches with members in common, each running on the stream of a
+    member of the other: their steps, the members' own and downloads in between
+    act in the order of the calls."""
+    import torch
+
+    def make():
+        return [_model_b((n, n), 70 + i) for i, n in enumerate((512, 256, 512, 128))]
+    mem, alone = make(), make()
+    first = pss.Batch([mem[0], mem[1], mem[2]])   # on the stream of mem[0]
+    second = pss.Batch([mem[1], mem[0], mem[3]])  # on the stream of mem[1]
+    out = torch.empty(mem[0].shape, device="cuda")
+    taken = [0, 0, 0, 0]
+
+    def took(who, k):
+        for i in who:
+            taken[i] += k
+
+    for turn in range(4):
+        if turn != 1:
+            mem[0].download(0, out)  # nothing left on its stream
+        first.step(40)
+        took((0, 1, 2), 40)
+        second.step(30)
+        took((1, 0, 3), 30)
+        first.step(7)
+        took((0, 1, 2), 7)
+        if turn % 2:
+            mem[1].step(5)
+            took((1,), 5)
+        second.step(20)
+        took((1, 0, 3), 20)
+    for lat, one, k in zip(mem, alone, taken):
+        one.step(k)
+        assert lat.step_index == k
+        assert np.array_equal(lat.spectrum(0), one.spectrum(0)), lat.n
+    first.close()
+    second.close()

@@ -241,3 +241,16 @@ def test_batch_of_lattices_that_differ_in_their_dealiasing(n, model, launches):
         one.step(50 if i == 1 else 47)
         assert np.array_equal(lat.spectrum(f), one.spectrum(g)), i
     batch.close()
+
+
+# the adjoint over lines of 4096 (blocks of 512 threads in its two launches)
+@pytest.mark.parametrize("n", [(4096, 8), (8, 4096)])
+def test_adjoint_of_the_longest_lines(n):
+    from tests.test_gpu_adjoint import _check, _gpu, _oracle as adjoint_oracle
+
+    S_star, Lo, go, gphio = adjoint_oracle(n, 6, seed=5)
+    for ckpt in (0, 1):
+        lat = _gpu(n, seed=5)
+        lat.tune(ckpt=ckpt)
+        L, g, gphi = lat.adjoint_model_b(6, S_star, ckpt_every=4)
+        _check(L, g, gphi, Lo, go, gphio)
