@@ -1160,6 +1160,8 @@ pss_status upload_frames(pss_ctx* c) {
 }
 
 pss_status upload_plan(pss_ctx* c) {
+    // enqueued batch steps copy the plan that is there now on the batch's stream
+    if (c->after_batch) HIP_TRY(hipEventSynchronize(c->after_batch));
     HIP_TRY(hipStreamSynchronize(c->stream));
     HIP_TRY(hipMemcpy(c->d_plan, &c->plan, sizeof(pss::DevPlan), hipMemcpyHostToDevice));
     ++c->plan_gen;

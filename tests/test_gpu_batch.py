@@ -396,3 +396,30 @@ def test_batches_that_share_members_take_turns():
         assert np.array_equal(lat.spectrum(0), one.spectrum(0)), lat.n
     first.close()
     second.close()
+
+
+def test_coefficients_changed_between_enqueued_batch_steps():
+    """Coefficients, noise and seed of a member reach the steps enqueued after
+    the call and no earlier ones, however far behind the device is."""
+    def make():
+        return [_model_b((512, 512), 80 + i) for i in range(3)]
+    mem, alone = make(), make()
+    batch = pss.Batch(mem)
+    b, c = (-2.0, -0.5, -1.5), (0.02, 0.03, 0.01)
+    batch.step(300)
+    for i in range(3):
+        mem[1].set_coef(1, 0, b[i])
+        mem[2].noise(0, [Mono(c[i], q2=1)])
+        mem[2].seed(100 + i)
+        batch.step(4)
+    for lat in alone:
+        lat.step(300)
+    for i in range(3):
+        alone[1].set_coef(1, 0, b[i])
+        alone[2].noise(0, [Mono(c[i], q2=1)])
+        alone[2].seed(100 + i)
+        for lat in alone:
+            lat.step(4)
+    for i, (lat, one) in enumerate(zip(mem, alone)):
+        assert np.array_equal(lat.spectrum(0), one.spectrum(0)), i
+    batch.close()
