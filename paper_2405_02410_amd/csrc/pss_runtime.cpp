@@ -890,7 +890,8 @@ pss_status choose_geometry(pss_ctx* c) {
     // Large 3D lattices are bound by memory, not by latency, and there a wave
     // should hold several of the tile's neighbouring columns (it then moves 16
     // or 32 bytes of a 32-byte tile row at once, not 8): at most 32 threads a
-    // line along z, 8 points a thread along x in one-wave blocks.  256^3: two
+    // line along z, 8 points a thread along x in one-wave blocks (16 where a
+    // row of 4096 needs them for a block of 256).  256^3: two
     // fields 195 -> 144 us (update) and 64.5 -> 55.3 us (x), one field 86 -> 67
     // and 33.2 -> 28.5; 256^2 x 64 and 128^3 measured slower (28.7 -> 33.4,
     // 18.2 -> 20.0 us), so the line lies at 2^23 sites.
@@ -902,7 +903,8 @@ pss_status choose_geometry(pss_ctx* c) {
     // update 135 -> 85 us, x 93 -> 53.5 us)
     const bool long_u = c->ndim == 2 && lu == 4096 && nf == 1, long_x = c->ndim == 2 && nx == 4096 && ng == 1;
     g.pu = tuned("pu", large3 ? points3(lu, cap_u, 32) : (long_u ? 8 : few_points(lu, cap_u)));
-    g.px = tuned("px", large3 ? points3(nx, std::min(8, cap_x), 32) : (long_x ? 8 : few_points(nx, cap_x)));
+    g.px = tuned("px", large3 ? std::max(points3(nx, std::min(8, cap_x), 32), few_points(nx, cap_x))
+                              : (long_x ? 8 : few_points(nx, cap_x)));
     const bool wide_u = long_u && g.pu == 8, wide_x = long_x && g.px == 8;
     if (!pow2(g.pu) || g.pu > pss::max_points(lu, pss::field_slots(nf)) || !pow2(g.px) ||
         g.px > pss::max_points(nx, pss::field_slots(ng)))
