@@ -245,6 +245,18 @@ inline int mr_threads(int N) {
     while (t < 1024 && kMrPerThread * t < N) t <<= 1;
     return t;
 }
+// The same where the work per element outweighs the passes (1D lines, steps with
+// operators per mode or several channels) and the launch is too small to fill
+// the chip: a thread for each element, up to 256.  A step with mr_threads alone
+// and so: 250 sites, Model B 9.9 and 6.4 us, KPZ 13.8 and 7.5; KPZ 240^2 36.0
+// and 25.3, 960 x 120 38.1 and 29.3; Model H 240^2 116 and 76.  From 1024 blocks
+// on other blocks fill the waits and more threads cost waves: KPZ 96^3 (2400
+// blocks) 73.2 and 77.3.
+inline int mr_block_threads(int N, unsigned blocks) {
+    int t = mr_threads(N);
+    while (blocks <= 1024 && t < 256 && t < N) t <<= 1;
+    return t;
+}
 constexpr int kMrRadices[] = {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
 // Cycles of one pass of radix r: a trip through LDS and a barrier, the chain
 // of one thread's butterfly (about 5 cycles an instruction), once per round

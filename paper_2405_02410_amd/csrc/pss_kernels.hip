@@ -2508,7 +2508,7 @@ hipError_t launch_line1d_mr(int mode, int N, int nf, int ng, const LaunchArgs& a
     const int NF = nf <= 1 ? 1 : (nf == 2 ? 2 : 4);
     const size_t lds = line1d_mr_lds_bytes(mr.n, NF, ng);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const dim3 grid(1), block(mr_threads(mr.n));
+    const dim3 grid(1), block(mr_block_threads(mr.n, 1));
     uint64_t* ctr = const_cast<uint64_t*>(a.step_ctr);
     const bool gen = a.general || mode == MODE_INTERM_OUT;
 #define PSS_MR(NFV, G, M)                                                                                   \
@@ -3273,9 +3273,10 @@ hipError_t launch_mr2_col(int mode, int nf, const LaunchArgs& a) {
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     const int other = a.dim == 3 ? a.ny : 1;
     const dim3 full((a.nx / tc) * other), half(((a.nx / 2 + tc) / tc) * other), block(mr_threads(tc * my.n));
+    const dim3 wide(mr_block_threads(tc * my.n, half.x));
     const bool gen = a.general;
 #define PSS_C2(NFV, G, M)                                                                                         \
-    hipLaunchKernelGGL((mr2_step_kernel<NFV, G, M>), half, block, lds, a.stream, a.plan, a.bufs, a.geo, a.step_ctr, \
+    hipLaunchKernelGGL((mr2_step_kernel<NFV, G, M>), half, wide, lds, a.stream, a.plan, a.bufs, a.geo, a.step_ctr, \
                        a.flag, a.step_off, a.tw_u, my)
     // one element per thread and load slot: the lines of the block fit
     const bool one = a.simple && tc * my.n <= kMrPerThread * static_cast<int>(block.x);
@@ -3335,7 +3336,8 @@ hipError_t launch_mr2_row(int mode, const LaunchArgs& a) {
     const int per = mode == MODE_STEP ? mr2_rows(mx.n, a.ng) : 1;
     const size_t lds = mr2_row_lds_bytes(mx.n, mode == MODE_STEP ? a.ng : 1, per);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const dim3 grid(rows / per), block(mr_threads(mx.n));
+    const dim3 grid(rows / per);
+    const dim3 block(mode == MODE_STEP && !a.simple ? mr_block_threads(mx.n, grid.x) : mr_threads(mx.n));
     uint64_t* ctr = const_cast<uint64_t*>(a.step_ctr);
     switch (mode) {
         case MODE_STEP:
