@@ -188,7 +188,7 @@ struct pss_ctx {
     char* d_work = nullptr;  // one allocation: channels, factors, transform scratch, real space
     float2* d_tmp2 = nullptr;
     float* d_real = nullptr;
-    int2* d_frame[PSS_MAXF] = {};  // device copies of the frames
+    int2* d_frame[PSS_MAXF] = {};  // device copies of the frames (but of fused frame steps)
     int32_t* d_frame_rows = nullptr;  // fused frame steps: row starts, then (x, value bits) by row (upload_frames)
     unsigned long long* d_shell_acc = nullptr;  // shell accumulators (kShellWords per shell)
     // one-entry member tables of the step kernels (update kernel, x kernel)
@@ -1130,6 +1130,7 @@ pss_status upload_frames(pss_ctx* c) {
         c->plan.frame[f] = nullptr;
         c->plan.nframe[f] = 0;
         if (f >= static_cast<int>(c->frames.size()) || c->frames[f].empty()) continue;
+        if (fused_frames(c)) continue;  // takes the table by rows below instead
         const auto& fr = c->frames[f];
         HIP_TRY(hipMalloc(&c->d_frame[f], sizeof(int2) * fr.size()));
         HIP_TRY(hipMemcpy(c->d_frame[f], fr.data(), sizeof(int2) * fr.size(), hipMemcpyHostToDevice));
