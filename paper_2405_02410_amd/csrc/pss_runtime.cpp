@@ -1247,9 +1247,10 @@ pss_status materialize(pss_ctx* c) {
     const bool relay = c->ndim == 3 && !c->mixed;  // the x kernel's channels pass through the y pass
     // Arrays of a power of two bytes laid end to end keep every kernel's reads
     // and writes on the same memory channels in step; an offset of its own for
-    // each spreads them.  1024^2, a step: Model B 17.4 us without, 16.8 with
-    // 2 KiB between the arrays and 4 KiB before them (12 offsets by 6 starts
-    // tried: 16.8 .. 17.5), KPZ 23.7 -> 21.7, Model H 51.7 -> 50.4.
+    // each spreads them.  1024^2, a step: KPZ 23.7 us without, 21.7 with 2 KiB
+    // between the arrays and 4 KiB before them, Model H 51.7 -> 50.4; Model B,
+    // with two arrays, 17.4 -> 16.8, no more than builds of equal kernels differ
+    // (12 offsets by 6 starts tried: 16.8 .. 17.5).
     constexpr size_t kBetween = 2048, kBefore = 4096;
     const size_t step_bytes = (bytes + 255) / 256 * 256 + kBetween;
     const size_t narr = c->d_chan.size() * (relay ? 2 : 1) + c->d_v.size() + 3;
